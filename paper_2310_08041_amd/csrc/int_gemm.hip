@@ -50,6 +50,7 @@ struct GemmArgs {
     // A launch of the FP6 or the byte-operand kernel may cover the output features o_first .. O - 1 only (the call is
     // then two launches with different tiles, each with its own O); never together with acc_dump, whose rows are O long.
     int32_t o_first;
+    int32_t lds_epilogue; // 1: K allows finish_from_lds and nobody asked for the raw accumulators
 };
 
 template <int BITS>
@@ -714,6 +715,157 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void int_gemm_w4a4_kerne
     }
 }
 
+// ---- epilogue of the kernels that leave room for its constants in LDS (EPI_BYTES behind the ring).  A wave that
+// fetches them from global memory after its last K-tile waits for memory with nothing left to multiply, and the
+// bracket written out term by term is three 24-bit multiply-adds per output; both count where K is short.
+// With a' = a - 128 for 8-bit codes (else a), the same for w, and primed zero-points and sums to match,
+//   bracket = sum (a' - bx')(w' - bw') = acc - bx' * cs' - bw' * (rs - K bx),     rs - K bx = sum (a - bx),
+// two multiply-adds.  Taken when every zero-point of the tile lies among the codes, 0 <= beta <= qmax (a row or column
+// that spans zero): then |rs - K bx| and |cs'| <= qmax K < 2^23 and the bracket is below qmax_a qmax_w K < 2^31, so
+// 24-bit multiply-adds with wrapping 32-bit sums are exact.  Stores are 16 bytes per lane, 64 bytes of 16 rows each:
+// with 8 bytes per lane (32 of 16 rows) the same tiles leave at 3.65 instead of 4.9 TB/s, which a short K does not hide
+// (4096 x 5120 -> 27648: 318 -> 286 us; 2048 x 4096 -> 8192: 42.5 -> 39.2; odd widths, 777 x 5000 -> 4999 fp32: 41 -> 36).  On the FP6 path the same in floats: acc holds 1/64 of the
+// accumulator, bx * cs / 64 and bw * (rs - K bx) / 64 are multiples of 1/64 below 225 K / 64 and every partial sum of
+// the three terms, in the order they are added, is below 225 K / 64 < 2^24 / 64, hence exact; 64 goes into ax.
+template <int TM, int TN>
+constexpr int EPI_BYTES = TM * 16 + 3 * TN * 4 + 8 * 4;
+
+// 16-byte stores at whatever alignment Y's rows have (any width and stride): one instruction, dword- or half-word-aligned
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int v4u_any __attribute__((ext_vector_type(4), aligned(2)));
+
+// Called by all 512 lanes before the first K-tile; a barrier must follow before finish_from_lds.
+template <int ABITS, int WBITS, int TM, int TN, bool FP>
+__device__ __forceinline__ void stage_epilogue(const GemmArgs &g, uint8_t *epi, int n0, int o0, int tid)
+{
+    static_assert(TM + TN <= LTHREADS, "a lane stages one token or one feature");
+    constexpr int QA = (1 << ABITS) - 1, QW = (1 << WBITS) - 1, SA = ABITS == 8 ? 128 : 0, SW = WBITS == 8 ? 128 : 0;
+    uint32_t *tok = reinterpret_cast<uint32_t *>(epi), *feat = reinterpret_cast<uint32_t *>(epi + TM * 16);
+    bool ok = g.lds_epilogue != 0;
+    if (tid < TM) {
+        const int n = min(n0 + tid, g.N - 1);
+        const int32_t bx = g.bx[n], rs = g.rs[n];
+        const float ax = g.ax[n];
+        ok = ok && bx >= 0 && bx <= QA && (!FP || ax < 1e30f);
+        const int32_t rsk = rs - g.K * bx;
+        v4i v{SA - bx, rsk, 0, 0};
+        if constexpr (FP) v = v4i{__builtin_bit_cast(int, -(float)bx), __builtin_bit_cast(int, (float)rsk * (1.0f / 64.0f)), 0, 0};
+        v[2] = __builtin_bit_cast(int, FP ? ax * 64.0f : ax);
+        *reinterpret_cast<v4i *>(tok + 4 * tid) = v;
+    } else if (tid < TM + TN) {
+        const int f = tid - TM, o = min(o0 + f, g.O - 1);
+        const int32_t bw = g.bw[o], cs = g.cs[o] - SW * g.K;
+        ok = ok && bw >= 0 && bw <= QW;
+        feat[f] = FP ? __float_as_uint((float)cs * (1.0f / 64.0f)) : (uint32_t)cs;
+        feat[TN + f] = FP ? __float_as_uint(-(float)bw) : (uint32_t)(SW - bw);
+        feat[2 * TN + f] = __float_as_uint(g.aw[o]);
+    }
+    const bool all = __all(ok);
+    if ((tid & 63) == 0) reinterpret_cast<int32_t *>(epi + TM * 16 + 3 * TN * 4)[tid >> 6] = all;
+}
+
+// One wave tile from the constants in LDS; false: not taken (the caller falls back to finish_wave_tile).
+// nl, ol: the wave's first token and feature inside the workgroup's tile.
+template <typename YT, int TM, int TN, int NI, int NJ, typename ACC>
+__device__ __forceinline__ bool finish_from_lds(const GemmArgs &g, const ACC (&acc)[NI][NJ], const uint8_t *epi, int n0, int o0,
+                                                int nl, int ol, int lane)
+{
+    constexpr bool FP = std::is_same<ACC, v4f>::value;
+    const v4i *flags = reinterpret_cast<const v4i *>(epi + TM * 16 + 3 * TN * 4);
+    const v4i f0 = flags[0], f1 = flags[1];
+    if (!__builtin_amdgcn_readfirstlane(f0[0] & f0[1] & f0[2] & f0[3] & f1[0] & f1[1] & f1[2] & f1[3])) return false;
+    typedef typename std::conditional<FP, v4f, v4i>::type V;
+    const uint8_t *feat = epi + TM * 16;
+    const int oq = 4 * (lane >> 4);
+    V cs[NJ], nbw[NJ];
+    v4f aw[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        cs[j] = *reinterpret_cast<const V *>(feat + 4 * (ol + 16 * j + oq));
+        nbw[j] = *reinterpret_cast<const V *>(feat + 4 * (TN + ol + 16 * j + oq));
+        aw[j] = *reinterpret_cast<const v4f *>(feat + 4 * (2 * TN + ol + 16 * j + oq));
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int nt = nl + 16 * i + (lane & 15), n = n0 + nt;
+        const V c = *reinterpret_cast<const V *>(epi + 16 * nt);
+        const auto third = c[2]; // a value of its own: the compiler's bit cast of a vector's element takes the first one
+        const float ax = __builtin_bit_cast(float, third);
+        const bool row = n < g.N;
+        const int64_t at = (int64_t)n * g.ldy + o0 + ol + oq;
+        auto value = [&](int j, int r) {
+            float v;
+            if constexpr (FP) {
+                v = __builtin_fmaf(c[0], cs[j][r], acc[i][j][r]);
+                v = __builtin_fmaf(c[1], nbw[j][r], v);
+            } else {
+                int32_t s = acc[i][j][r] + __mul24(c[0], cs[j][r]);
+                s += __mul24(c[1], nbw[j][r]);
+                v = (float)s;
+            }
+            return (v * ax) * aw[j][r];
+        };
+        if constexpr (sizeof(YT) == 4) {
+            const int64_t at = (int64_t)n * g.ldy + o0 + ol + oq;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const v4f out{value(j, 0), value(j, 1), value(j, 2), value(j, 3)};
+                float *const yp = reinterpret_cast<float *>(g.y) + at + 16 * j;
+                const int left = row ? g.O - (o0 + ol + 16 * j + oq) : 0;
+                if (left >= 4) {
+                    *reinterpret_cast<v4f_any *>(yp) = out;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (e < left) yp[e] = out[e];
+                }
+            }
+        } else {
+            // a lane's four features of tile j and of tile j + 1 are 8 bytes each; rows of 16 lanes trade them so that
+            // every lane stores 8 neighbouring features of one tile
+            const int q = lane >> 4, half = 16 * (q & 1) + 8 * (q >> 1);
+            const int64_t at = (int64_t)n * g.ldy + o0 + ol + half;
+#pragma unroll
+            for (int j = 0; j < NJ; j += 2) {
+                const auto lo = __builtin_amdgcn_permlane16_swap(f32x2_to_bf16x2_rne(value(j, 0), value(j, 1)),
+                                                                 f32x2_to_bf16x2_rne(value(j + 1, 0), value(j + 1, 1)), false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(f32x2_to_bf16x2_rne(value(j, 2), value(j, 3)),
+                                                                 f32x2_to_bf16x2_rne(value(j + 1, 2), value(j + 1, 3)), false, false);
+                const uint32_t out[4] = {lo[0], hi[0], lo[1], hi[1]};
+                uint16_t *const yp = reinterpret_cast<uint16_t *>(g.y) + at + 16 * j;
+                const int left = row ? g.O - (o0 + ol + 16 * j + half) : 0;
+                if (left >= 8) {
+                    *reinterpret_cast<v4u_any *>(yp) = v4u{out[0], out[1], out[2], out[3]};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 7; ++e)
+                        if (e < left) yp[e] = (uint16_t)(out[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+    }
+    return true;
+}
+
+// Which tile of Y a workgroup of a large product takes.  Workgroups go to the eight XCDs in turn by their number, and
+// an XCD's workgroups share its L2: tiles are handed out so that each XCD walks a run of neighbouring tiles, down
+// bands of up to eight tiles of tokens and then along the features, and its 32 resident workgroups share
+// 8 + 4 operand streams whatever the grid's width is (4096 x 5120 -> 27648, 108 tiles wide: up to 30 streams in row
+// order, 335 us; 318 so).  Large tiles only: 128 x 128 tiles, two workgroups per CU, lost by it (777 x 5000 -> 4999 with
+// 8-bit activations 41.5 -> 45.3 us, 2048 x 4096 -> 4096 30.8 -> 32.1).
+struct TileAt {
+    int n, o;
+};
+__device__ __forceinline__ TileAt tile_at(int nb, int ob)
+{
+    const uint32_t b = blockIdx.y * gridDim.x + blockIdx.x, total = (uint32_t)nb * (uint32_t)ob, xcd = b & 7u;
+    const uint32_t t = xcd * (total >> 3) + min(xcd, total & 7u) + (b >> 3);
+    const uint32_t bands = ((uint32_t)nb + 7u) >> 3, height = ((uint32_t)nb + bands - 1u) / bands;
+    const uint32_t band = t / (height * (uint32_t)ob), r = t - band * height * (uint32_t)ob, first = band * height;
+    const uint32_t h = min(height, (uint32_t)nb - first), o = r / h;
+    return TileAt{__builtin_amdgcn_readfirstlane((int)(first + r - o * h)), __builtin_amdgcn_readfirstlane((int)o)};
+}
+
 // ---- 4-bit codes on both sides on the FP6 matrix cores.
 // gfx950 multiplies 6-bit floating-point operands (E2M3: sign, 2 exponent bits, 3 mantissa bits, no
 // infinities or NaNs) at twice the rate of int8, 128 values of K per operation.  The 6-bit pattern
@@ -769,7 +921,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     static_assert(STAGE % (8 * 1024) == 0, "a stage is a whole number of 1 KB loads per wave");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
-    const int n0 = blockIdx.y * TM, o0 = g.o_first + blockIdx.x * TN;
+    const TileAt at = MI < 8 ? TileAt{(int)blockIdx.y, (int)blockIdx.x} : tile_at((int)gridDim.y, (int)gridDim.x);
+    const int n0 = at.n * TM, o0 = g.o_first + at.o * TN;
     const int all_kt = g.Kpad / T6_KT;
     const int a_blocks = (g.N + 15) / 16, w_blocks = (g.O + 15) / 16;
 
@@ -810,6 +963,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     // this workgroup's K-tiles (fetches past them, up to the last K-tile of the row, go to stages nobody reads)
     const int kt_first = SPLIT ? (int)((int64_t)all_kt * blockIdx.z / gridDim.z) : 0;
     const int kt_end = SPLIT ? (int)((int64_t)all_kt * (blockIdx.z + 1) / gridDim.z) : all_kt;
+    uint8_t *const epi = lds + T6_STAGES * STAGE; // the epilogue's constants, behind the ring
+    if constexpr (!SPLIT) stage_epilogue<4, 4, TM, TN, true>(g, epi, n0, o0, tid);
     fetch(kt_first, 0);
     fetch(kt_first + 1, 1);
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
@@ -911,6 +1066,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
             }
         }
     } else {
+        if (finish_from_lds<YT, TM, TN>(g, acc, epi, n0, o0, wm * 16 * MI, wn * 16 * NJ, lane)) return;
         finish_wave_tile<4, 4, YT, MI, NJ>(g, acc, n0 + wm * 16 * MI, o0 + wn * 16 * NJ, lane); // 64 acc: the integer accumulators, exactly
     }
 }
@@ -972,7 +1128,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     static_assert(STAGE % (8 * 1024) == 0 && NLOAD <= MI, "a stage is a whole number of 1 KB loads per wave, one per group");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
-    const int n0 = blockIdx.y * TM, o0 = g.o_first + blockIdx.x * TN;
+    const TileAt at = MI < 8 ? TileAt{(int)blockIdx.y, (int)blockIdx.x} : tile_at((int)gridDim.y, (int)gridDim.x);
+    const int n0 = at.n * TM, o0 = g.o_first + at.o * TN;
     const int all_kt = (g.K + T8_KT - 1) / T8_KT;
     const int a_blocks = (g.N + 15) / 16, w_blocks = (g.O + 15) / 16;
 
@@ -1010,6 +1167,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     // this workgroup's K-tiles (fetches past them, up to the last K-tile of the row, go to stages nobody reads)
     const int kt_first = SPLIT ? (int)((int64_t)all_kt * blockIdx.z / gridDim.z) : 0;
     const int kt_end = SPLIT ? (int)((int64_t)all_kt * (blockIdx.z + 1) / gridDim.z) : all_kt;
+    uint8_t *const epi = lds + T8_STAGES * STAGE; // the epilogue's constants, behind the ring
+    if constexpr (!SPLIT) stage_epilogue<ABITS, WBITS, TM, TN, false>(g, epi, n0, o0, tid);
     fetch(kt_first, 0);
     fetch(kt_first + 1, 1);
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
@@ -1095,6 +1254,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
         }
     } else {
         // places past K are zero bytes on both sides, so only the K real places carry the two offsets of 128
+        if (finish_from_lds<YT, TM, TN>(g, acc, epi, n0, o0, wm * 16 * MI, wn * 16 * NJ, lane)) return;
         finish_wave_tile<ABITS, WBITS, YT, MI, NJ>(g, acc, n0 + wm * 16 * MI, o0 + wn * 16 * NJ, lane, g.K);
     }
 }
@@ -1384,7 +1544,7 @@ int32_t launch_fp6(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
-        constexpr size_t lds = (size_t)T6_STAGES * 16 * T6_BLOCK;
+        constexpr size_t lds = (size_t)T6_STAGES * 16 * T6_BLOCK + EPI_BYTES<128, 128>;
         if (ga.splits > 1) {
             const int32_t sp = launch_kernel(gemm_w4a4_fp6_kernel<float, 4, 2, true>, grid, dim3(LTHREADS), lds, ga, stream);
             if (sp != QLLM_OK) return sp;
@@ -1397,7 +1557,7 @@ int32_t launch_fp6(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     };
     auto launch_big = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + LBN - 1) / LBN), (unsigned)((ga.N + LBM - 1) / LBM));
-        constexpr size_t lds = (size_t)T6_STAGES * 32 * T6_BLOCK;
+        constexpr size_t lds = (size_t)T6_STAGES * 32 * T6_BLOCK + EPI_BYTES<256, 256>;
         if (y_dtype == QLLM_F32) return launch_kernel(gemm_w4a4_fp6_kernel<float, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
         return launch_kernel(gemm_w4a4_fp6_kernel<uint16_t, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
     };
@@ -1457,7 +1617,7 @@ int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
-        constexpr size_t lds = (size_t)T8_STAGES * 16 * T8_BLOCK;
+        constexpr size_t lds = (size_t)T8_STAGES * 16 * T8_BLOCK + EPI_BYTES<128, 128>;
         if (ga.splits > 1) {
             const int32_t sp = launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, true>, grid, dim3(LTHREADS), lds, ga, stream);
             if (sp != QLLM_OK) return sp;
@@ -1471,7 +1631,7 @@ int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     };
     auto launch_big = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + LBN - 1) / LBN), (unsigned)((ga.N + LBM - 1) / LBM));
-        constexpr size_t lds = (size_t)T8_STAGES * 32 * T8_BLOCK;
+        constexpr size_t lds = (size_t)T8_STAGES * 32 * T8_BLOCK + EPI_BYTES<256, 256>;
         if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
         return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
     };
@@ -1671,6 +1831,10 @@ extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, 
         }
     }
     g.small_zero = small_zero_bound(w->K, a_bits, wb);
+    // finish_from_lds: sums that fit 24 bits (see there), no raw accumulators
+    const int64_t q_most = qa > qw ? qa : qw;
+    g.lds_epilogue = !acc_dump && q_most * w->K < (1 << 23) &&
+                     (a_bits != 4 || wb != 4 || 225 * w->K < (1 << 24));
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     if (a_bits == 4) return launch<4, 4>(g, y_dtype, stream);
     if (a_bits == 6) return launch<6, 6>(g, y_dtype, stream);

@@ -461,6 +461,32 @@ def test_gemm_two_launch_tile_plan(oracle, b, a_bits, w_bits):
     assert np.array_equal(got, oracle.widen_bf16(oracle.round_to_bf16(exact.astype(np.float32))))
 
 
+@pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 8), (8, 4)])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K,O,inside", [(300, 200, 2056, True), (300, 200, 2056, False), (513, 264, 1029, True), (259, 32768, 522, True),
+                                          (2305, 128, 2304, True)])
+def test_gemm_epilogue_from_lds(oracle, b, a_bits, w_bits, y_dtype, N, K, O, inside):
+    """The epilogue that takes its constants from LDS and stores 16 bytes per lane against the general one (which any call
+    with acc_dump runs): the same bits, with zero-points at both ends of the code range (the widest sums it is taken
+    for), with one token whose zero-point lies outside it (its tiles fall back), with odd widths and unaligned rows, with
+    partial tiles on both edges, and for a number of tiles that is no multiple of the eight XCDs; and against the oracle.  The largest K has every code at its maximum."""
+    rng = np.random.default_rng(N + K + O + a_bits)
+    a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
+    qa, qw = 2 ** a_bits - 1, 2 ** w_bits - 1
+    if K == 32768:
+        a[:], w[:] = qa, qw
+    bx[:], bw[:] = rng.choice([0, qa // 2, qa], N), rng.choice([0, qw // 2, qw], O)
+    if not inside:
+        bx[N // 2] = -3
+    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=False)
+    y1, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True)
+    assert __import__("torch").equal(y, y1)
+    rows, cols = np.unique(np.r_[0, N // 2, N - 1, rng.integers(0, N, 13)]), np.unique(np.r_[0, O - 1, rng.integers(0, O, 29)])
+    rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
+    ref = oracle.epilogue(oracle.int_gemm(a[rows], w[cols]), K, ax[rows], bx[rows], rs[rows], aw[cols], bw[cols], cs[cols])
+    check_y(oracle, y[rows][:, cols].contiguous(), ref, y_dtype)
+
+
 def test_gemm_extreme_codes(oracle, b):
     """All codes at their maximum: the largest accumulators the shapes allow."""
     for bits, K in [(4, 28672), (6, 8192), (8, 28672)]:
