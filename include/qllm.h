@@ -249,7 +249,7 @@ int32_t qllm_theta_grid_host(const float *chan_absmax, int64_t C, int32_t P, flo
  * layer's output against the full-precision layer (the paper scores a whole attention block through Eq. (6);
  * a single linear layer has no softmax to go through, so the error is taken at the layer's own output).
  * DEVICE pointers.
- *   qllm_linear_f64   out[n, o] = sum_c y[n, c] W[c, o], products and sums in double, c ascending.
+ *   qllm_linear_f64   out[n, o] = sum_c y[n, c] W[c, o], products and sums in double, c ascending in fours.
  *                     y [N, ldy] fp32, W [C, ldw] fp32, out [N, ldo] double.
  *   qllm_sq_error     *result (one device double) = sum over n, o of (got[n, o] - ref[n, o])^2 in double, in a
  *                     fixed order.  got [N, ldg] fp32 or bf16, ref [N, ldr] double; workspace of

@@ -1021,6 +1021,39 @@ def test_reference_output_and_squared_error_kernels(b):
         assert np.isclose(loss.cpu().numpy()[0], (e * e).sum(), rtol=1e-13) and loss.cpu().numpy()[0] > 0
 
 
+@pytest.mark.parametrize("N,C,O,pad", [(1025, 67, 2050, 0), (1025, 68, 2052, 0), (1024, 100, 2048, 3), (33, 1, 31, 1), (1, 129, 1, 0)])
+def test_reference_output_tiles(b, N, C, O, pad):
+    """Both tile sizes of qllm_linear_f64 (enough 128 x 64 tiles for every CU, or 32 x 32 ones) at ragged edges, with rows
+    that allow 16-byte loads and rows that do not: exact on integers, nothing written outside the output's columns."""
+    import torch
+    rng = np.random.default_rng(N + C + O)
+    y = rng.integers(-8, 9, (N, C + pad)).astype(np.float32)
+    W = rng.integers(-8, 9, (C, O + pad)).astype(np.float32)
+    out = torch.full((N, O + 2), -1.0, dtype=torch.float64, device="cuda")
+    b.qllm_linear_f64(torch.from_numpy(y).cuda()[:, :C], torch.from_numpy(W).cuda()[:, :O], out[:, :O])
+    got = out.cpu().numpy()
+    assert np.array_equal(got[:, :O], y[:, :C].astype(np.float64) @ W[:, :O].astype(np.float64))
+    assert np.all(got[:, O:] == -1.0)
+
+
+@pytest.mark.parametrize("N,C,norm", [(3, 8200, "rms"), (700, 9001, "layer"), (1100, 516, "rms"), (513, 12, "none")])
+def test_channel_absmax_many_rows(oracle, b, N, C, norm):
+    """More rows than workgroups, rows of more than 8192 channels, ragged rows: the statistic starts from what the
+    caller left in it, and the dump holds the first rows of y."""
+    import torch
+    rng = np.random.default_rng(N + C)
+    x, gamma = rng.standard_normal((N, C)).astype(np.float32), rng.uniform(0.5, 1.5, C).astype(np.float32)
+    beta = rng.standard_normal(C).astype(np.float32) if norm == "layer" else None
+    y = oracle.norm(x, NORM_ID[norm], gamma, beta, 1e-5)
+    before = np.where(np.arange(C) % 3 == 0, np.float32(1e3), np.float32(0))
+    absmax = torch.from_numpy(before.copy()).cuda()
+    dump = torch.full((N - 1, C), float("nan"), device="cuda")
+    b.qllm_norm_channel_absmax(torch.from_numpy(x).cuda(), NORM_ID[norm], torch.from_numpy(gamma).cuda(),
+                               None if beta is None else torch.from_numpy(beta).cuda(), 1e-5, absmax, dump)
+    assert np.array_equal(absmax.cpu().numpy(), np.maximum(before, np.abs(y).max(0)))
+    assert np.array_equal(dump.cpu().numpy(), y[:N - 1])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits", [4, 6])
 def test_theta_grid_search_matches_the_oracle(oracle, b, bits):
