@@ -734,34 +734,51 @@ constexpr int EPI_BYTES = TM * 16 + 3 * TN * 4 + 8 * 4;
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int v4u_any __attribute__((ext_vector_type(4), aligned(2)));
 
-// Called by all 512 lanes before the first K-tile; a barrier must follow before finish_from_lds.
-template <int ABITS, int WBITS, int TM, int TN, bool FP>
-__device__ __forceinline__ void stage_epilogue(const GemmArgs &g, uint8_t *epi, int n0, int o0, int tid)
+// The constants on their way to LDS, one token's or one feature's per lane (at least TM + TN lanes, 4 or 8 waves).
+struct EpiRegs {
+    int32_t zero, sum;
+    float scale;
+};
+template <int TM, int TN>
+__device__ __forceinline__ EpiRegs load_epilogue(const GemmArgs &g, int n0, int o0, int tid)
 {
-    static_assert(TM + TN <= LTHREADS, "a lane stages one token or one feature");
+    EpiRegs e{0, 0, 0.0f};
+    if (tid < TM) {
+        const int n = min(n0 + tid, g.N - 1);
+        e.zero = g.bx[n]; e.sum = g.rs[n]; e.scale = g.ax[n];
+    } else if (tid < TM + TN) {
+        const int o = min(o0 + tid - TM, g.O - 1);
+        e.zero = g.bw[o]; e.sum = g.cs[o]; e.scale = g.aw[o];
+    }
+    return e;
+}
+
+// A barrier must follow before finish_from_lds.
+template <int ABITS, int WBITS, int TM, int TN, bool FP, int WAVES>
+__device__ __forceinline__ void store_epilogue(const GemmArgs &g, const EpiRegs &e, uint8_t *epi, int tid)
+{
     constexpr int QA = (1 << ABITS) - 1, QW = (1 << WBITS) - 1, SA = ABITS == 8 ? 128 : 0, SW = WBITS == 8 ? 128 : 0;
     uint32_t *tok = reinterpret_cast<uint32_t *>(epi), *feat = reinterpret_cast<uint32_t *>(epi + TM * 16);
     bool ok = g.lds_epilogue != 0;
     if (tid < TM) {
-        const int n = min(n0 + tid, g.N - 1);
-        const int32_t bx = g.bx[n], rs = g.rs[n];
-        const float ax = g.ax[n];
-        ok = ok && bx >= 0 && bx <= QA && (!FP || ax < 1e30f);
-        const int32_t rsk = rs - g.K * bx;
-        v4i v{SA - bx, rsk, 0, 0};
-        if constexpr (FP) v = v4i{__builtin_bit_cast(int, -(float)bx), __builtin_bit_cast(int, (float)rsk * (1.0f / 64.0f)), 0, 0};
-        v[2] = __builtin_bit_cast(int, FP ? ax * 64.0f : ax);
+        ok = ok && e.zero >= 0 && e.zero <= QA && (!FP || e.scale < 1e30f);
+        const int32_t rsk = e.sum - g.K * e.zero;
+        v4i v{SA - e.zero, rsk, 0, 0};
+        if constexpr (FP) v = v4i{__builtin_bit_cast(int, -(float)e.zero), __builtin_bit_cast(int, (float)rsk * (1.0f / 64.0f)), 0, 0};
+        v[2] = __builtin_bit_cast(int, FP ? e.scale * 64.0f : e.scale);
         *reinterpret_cast<v4i *>(tok + 4 * tid) = v;
     } else if (tid < TM + TN) {
-        const int f = tid - TM, o = min(o0 + f, g.O - 1);
-        const int32_t bw = g.bw[o], cs = g.cs[o] - SW * g.K;
-        ok = ok && bw >= 0 && bw <= QW;
+        const int f = tid - TM;
+        const int32_t cs = e.sum - SW * g.K;
+        ok = ok && e.zero >= 0 && e.zero <= QW;
         feat[f] = FP ? __float_as_uint((float)cs * (1.0f / 64.0f)) : (uint32_t)cs;
-        feat[TN + f] = FP ? __float_as_uint(-(float)bw) : (uint32_t)(SW - bw);
-        feat[2 * TN + f] = __float_as_uint(g.aw[o]);
+        feat[TN + f] = FP ? __float_as_uint(-(float)e.zero) : (uint32_t)(SW - e.zero);
+        feat[2 * TN + f] = __float_as_uint(e.scale);
     }
     const bool all = __all(ok);
-    if ((tid & 63) == 0) reinterpret_cast<int32_t *>(epi + TM * 16 + 3 * TN * 4)[tid >> 6] = all;
+    if ((tid & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < 8; k += WAVES) reinterpret_cast<int32_t *>(epi + TM * 16 + 3 * TN * 4)[k + (tid >> 6)] = all; // eight flags
 }
 
 // One wave tile from the constants in LDS; false: not taken (the caller falls back to finish_wave_tile).
@@ -964,7 +981,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     const int kt_first = SPLIT ? (int)((int64_t)all_kt * blockIdx.z / gridDim.z) : 0;
     const int kt_end = SPLIT ? (int)((int64_t)all_kt * (blockIdx.z + 1) / gridDim.z) : all_kt;
     uint8_t *const epi = lds + T6_STAGES * STAGE; // the epilogue's constants, behind the ring
-    if constexpr (!SPLIT) stage_epilogue<4, 4, TM, TN, true>(g, epi, n0, o0, tid);
+    if constexpr (!SPLIT) store_epilogue<4, 4, TM, TN, true, 8>(g, load_epilogue<TM, TN>(g, n0, o0, tid), epi, tid);
     fetch(kt_first, 0);
     fetch(kt_first + 1, 1);
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
@@ -1115,11 +1132,15 @@ __global__ __launch_bounds__(256) void tiles6_kernel(const uint8_t *codes, int64
 // kernels that expand packed codes at refill time spend most of their issue slots on that).
 // Tiling, ring, group plan and loop rotation are those of gemm_w4a4_fp6_kernel; one K-tile here is 64 codes,
 // which takes the int8 matrix cores as long as 128 codes take the FP6 ones.
-constexpr int T8_BLOCK = 1024, T8_KT = 64, T8_STAGES = 3;
+constexpr int T8_BLOCK = 1024, T8_KT = 64;
+
 
 // SPLIT: K is dealt out to gridDim.z workgroups per tile of Y (so few tiles that most CUs would idle); each writes
 // its raw accumulators to g.partial and splitk_finish_kernel adds them up and does the epilogue.
-template <int ABITS, int WBITS, typename YT, int MI, int NJ, bool SPLIT = false>
+// STAGES of the ring: three; four for the small tile where there is at most one workgroup per CU, which then waits for
+// memory (200 tokens, 13824 -> 5120 6 / 6 with K split in three: 32.7 -> 27.2 us; six change nothing more).  With two
+// workgroups per CU the fourth costs (2171 x 8832 -> 3712: 135 -> 144), for the large tile it changes nothing.
+template <int ABITS, int WBITS, typename YT, int MI, int NJ, int STAGES, bool SPLIT = false>
 __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(const GemmArgs g)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -1155,8 +1176,10 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
 #pragma unroll
         for (int t = 0; t < NLOAD; ++t) fetch_one(kt, stage, t);
     };
-    constexpr int WAIT_LANDED = NLOAD | (7 << 4) | (15 << 8);       // s_waitcnt vmcnt(NLOAD): all but the newest fetch
-    constexpr int WAIT_LANDED_LGKM0 = NLOAD | (7 << 4) | (0 << 8);  // ... and lgkmcnt(0)
+    constexpr int IN_FLIGHT = (STAGES - 2) * NLOAD; // loads of the K-tiles after the next one
+    constexpr int WAIT_LANDED = IN_FLIGHT | (7 << 4) | (15 << 8);       // s_waitcnt vmcnt(IN_FLIGHT): the next K-tile has landed
+    constexpr int WAIT_LANDED_LGKM0 = IN_FLIGHT | (7 << 4) | (0 << 8);  // ... and lgkmcnt(0)
+    static_assert(IN_FLIGHT < 16, "the low four bits of vmcnt");
 
     v4i acc[MI][NJ];
 #pragma unroll
@@ -1167,10 +1190,11 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     // this workgroup's K-tiles (fetches past them, up to the last K-tile of the row, go to stages nobody reads)
     const int kt_first = SPLIT ? (int)((int64_t)all_kt * blockIdx.z / gridDim.z) : 0;
     const int kt_end = SPLIT ? (int)((int64_t)all_kt * (blockIdx.z + 1) / gridDim.z) : all_kt;
-    uint8_t *const epi = lds + T8_STAGES * STAGE; // the epilogue's constants, behind the ring
-    if constexpr (!SPLIT) stage_epilogue<ABITS, WBITS, TM, TN, false>(g, epi, n0, o0, tid);
+    uint8_t *const epi = lds + STAGES * STAGE; // the epilogue's constants, behind the ring
+    if constexpr (!SPLIT) store_epilogue<ABITS, WBITS, TM, TN, false, 8>(g, load_epilogue<TM, TN>(g, n0, o0, tid), epi, tid);
     fetch(kt_first, 0);
-    fetch(kt_first + 1, 1);
+#pragma unroll
+    for (int s = 1; s < STAGES - 1; ++s) fetch(kt_first + s, s);
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
     __syncthreads();
 
@@ -1183,7 +1207,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     for (int j = 0; j < NJ; ++j) wr[0][j] = wr[1][j] = v4i{0, 0, 0, 0};
 
     const int a_blk0 = wm * MI, w_blk0 = TM / 16 + wn * NJ; // the wave's first token-side and feature-side block of a stage
-    int stage = 0, fetch_stage = 2;
+    int stage = 0, fetch_stage = STAGES - 1;
     auto k_tile = [&](auto parity, int kt) {
         constexpr int P = decltype(parity)::value;
         const uint8_t *cur = lds + stage * STAGE;
@@ -1194,7 +1218,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
         for (int u = 0; u < MI; ++u) {
             const bool old = u < AHEAD;
             const int i = old ? MI - AHEAD + u : u - AHEAD;
-            if (u < NLOAD) fetch_one(kt + 2, fetch_stage, u); // one load per group, not all at once
+            if (u < NLOAD) fetch_one(kt + STAGES - 1, fetch_stage, u); // one load per group, not all at once
             if (PER_STEP * u < MI) {
 #pragma unroll
                 for (int h = 0; h < PER_STEP; ++h)
@@ -1212,7 +1236,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         fetch_stage = stage;
-        stage = stage == T8_STAGES - 1 ? 0 : stage + 1;
+        stage = stage == STAGES - 1 ? 0 : stage + 1;
     };
     int kt = kt_first;
     for (; kt + 1 < kt_end; kt += 2) {
@@ -1322,67 +1346,117 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const GemmArgs g)
     if (g.acc_dump) g.acc_dump[idx] = raw;
 }
 
-// ---- few tokens (decode): the weights are read once from HBM and that is the whole cost.  A
-// workgroup owns 32 output features (two matrix-core row tiles) and all N <= 16 NT tokens (NT 1 or 2);
-// its 8 waves split K: wave w takes the 256-code steps w, w + 8, ... and works on its own, without
-// barriers, until the partial tiles are added up at the end.
+// ---- few tokens (decode, small batches): the weights are read once from HBM and that is the whole cost.  A
+// workgroup owns 16 RT output features and 16 NT tokens; its WAVES waves split K:
+// each takes a run of steps of STEP codes and works on its own, without barriers, until the partial tiles are added up
+// at the end.
 //   * Global loads are laid out for the memory pipeline, not for the matrix cores: consecutive lanes
-//     take consecutive 16-byte pieces of a row's 256 codes, so one load instruction touches whole
-//     cache lines (a lane per matrix-core operand row would touch three to four times as many lines,
+//     take consecutive 16-byte pieces of a row's STEP codes, so one load instruction touches whole
+//     (half) cache lines (a lane per matrix-core operand row would touch three to four times as many lines,
 //     and the address unit, one line per cycle, would be the limit).  Two steps' loads are in flight.
-//   * The pieces pass through a wave-private strip of LDS, still packed, and come back as the 64 codes
-//     256 s + 64 c .. + 63 of row r for lane (r, c), are expanded in registers and feed four
-//     matrix-core operations, the m-th on codes 16 m .. 16 m + 15 of every lane's 64: which 64 codes
+//   * The pieces pass through a wave-private strip of LDS, still packed, and come back as a quarter of the step's
+//     codes of row r, the c-th, for lane (r, c), are expanded in registers and feed STEP / 64 matrix-core
+//     operations, the m-th on codes 16 m .. 16 m + 15 of every lane's quarter: which 64 codes
 //     of the step one operation sums is free as long as both operands agree.
-constexpr int SK_THREADS = 512, SK_WAVES = 8, SK_RT = 2, SK_STEP = 256;
+template <int BITS, int STEP>
+constexpr int SK_ROW = STEP * BITS / 8 + 16; // bytes of LDS per row and step: the packed codes and a pad against bank conflicts
 
-template <int BITS>
-constexpr int SK_ROW = SK_STEP * BITS / 8 + 16; // bytes of LDS per row and step: the packed codes and a pad against bank conflicts
+template <int ABITS, int WBITS, int NT, int RT, int STEP>
+constexpr int SK_STRIP = 16 * RT * SK_ROW<WBITS, STEP> + 16 * NT * SK_ROW<ABITS, STEP>; // LDS bytes per wave
 
-template <int ABITS, int WBITS, int NT>
-constexpr int SK_STRIP = 16 * SK_RT * SK_ROW<WBITS> + 16 * NT * SK_ROW<ABITS>; // LDS bytes per wave
-
-template <int ABITS, int WBITS, typename YT, int NT>
-__global__ __launch_bounds__(SK_THREADS) void int_gemm_skinny_kernel(const GemmArgs g)
+template <int ABITS, int WBITS, int NT, int RT, int WAVES, int STEP>
+constexpr size_t skinny_lds()
 {
-    // [SK_WAVES] strips; afterwards reused as [SK_WAVES][NT * SK_RT][64] v4i for the final sum
+    const size_t strips = (size_t)WAVES * SK_STRIP<ABITS, WBITS, NT, RT, STEP>;
+    const size_t red = (size_t)WAVES * NT * RT * 64 * sizeof(v4i);
+    return (strips > red ? strips : red) + EPI_BYTES<16 * NT, 16 * RT>;
+}
+
+// CODES codes of one row (packed, in DW dwords) -> one byte per code; the orders of expand_unit
+template <int BITS, int CODES, bool PERM>
+__device__ __forceinline__ void expand_codes(const uint32_t (&w)[CODES * BITS / 32], uint32_t (&d)[CODES / 4])
+{
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int i = 0; i < CODES / 8; ++i) {
+            if constexpr (PERM) {
+                d[2 * i] = w[i] & 0x0f0f0f0fu;
+                d[2 * i + 1] = (w[i] >> 4) & 0x0f0f0f0fu;
+            } else {
+                expand4(w[i], d[2 * i], d[2 * i + 1]);
+            }
+        }
+    } else if constexpr (BITS == 6) {
+#pragma unroll
+        for (int i = 0; i < CODES / 16; ++i) { // 3 dwords = 4 groups of 24 bits
+            const uint32_t w0 = w[3 * i], w1 = w[3 * i + 1], w2 = w[3 * i + 2];
+            d[4 * i + 0] = spread6(w0);
+            d[4 * i + 1] = spread6(__builtin_amdgcn_alignbit(w1, w0, 24));
+            d[4 * i + 2] = spread6(__builtin_amdgcn_alignbit(w2, w1, 16));
+            d[4 * i + 3] = spread6(w2 >> 8);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < CODES / 4; ++i) d[i] = w[i] ^ 0x80808080u; // code - 128 as a signed byte
+    }
+}
+
+// Registers for two workgroups of eight waves per CU where the loop fits in them (with one workgroup 27648 x 5120 6-bit
+// weights and 16 tokens take 34 instead of 29 us, and 4-bit weights and 32 tokens 23.6 instead of 20.9).
+template <int ABITS, int WBITS, int NT>
+constexpr int SK_WAVES_PER_SIMD = NT == 1 || (NT == 2 && ABITS == 4 && WBITS == 4) ? 4 : 2;
+
+template <int ABITS, int WBITS, typename YT, int NT, int RT, int WAVES, int STEP>
+__global__ __launch_bounds__(64 * WAVES, (SK_WAVES_PER_SIMD<ABITS, WBITS, NT>)) void int_gemm_skinny_kernel(const GemmArgs g)
+{
+    // [WAVES] strips; afterwards reused as [WAVES][NT * RT][64] v4i for the final sum
     extern __shared__ __align__(16) uint8_t sk_lds[];
     constexpr bool PERM = ABITS == 4 && WBITS == 4;
-    constexpr int WPIECES = SK_STEP * WBITS / 8 / 16, APIECES = SK_STEP * ABITS / 8 / 16; // 16-byte pieces per row and step
-    constexpr int WLOADS = 16 * SK_RT * WPIECES / 64, ALOADS = 16 * NT * APIECES / 64;     // load instructions per step
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int CODES = STEP / 4;                                                    // a lane's codes of one row and step
+    constexpr int WB = STEP * WBITS / 8, AB = STEP * ABITS / 8;                        // bytes per row and step
+    constexpr int WPIECES = WB / 16, APIECES = AB / 16;                                // 16-byte pieces per row and step
+    constexpr int WLOADS = 16 * RT * WPIECES / 64, ALOADS = 16 * NT * APIECES / 64; // load instructions per step
+    static_assert(16 * RT * WPIECES % 64 == 0 && 16 * NT * APIECES % 64 == 0, "whole load instructions");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, c = lane >> 4;
-    const int o0 = blockIdx.x * (16 * SK_RT);
-    uint8_t *w_strip = sk_lds + wave * SK_STRIP<ABITS, WBITS, NT>, *a_strip = w_strip + 16 * SK_RT * SK_ROW<WBITS>;
+    const int o0 = blockIdx.x * (16 * RT), n0 = blockIdx.y * (16 * NT);
+    uint8_t *w_strip = sk_lds + wave * SK_STRIP<ABITS, WBITS, NT, RT, STEP>, *a_strip = w_strip + 16 * RT * SK_ROW<WBITS, STEP>;
 
-    // piece lane + 64 t of a step: where it comes from (without the step's offset) and where it goes
-    const uint8_t *w_src[WLOADS], *a_src[ALOADS];
+    // piece lane + 64 t of a step: where it comes from (from the operand's first row and the step's first byte on; past
+    // the edge the last row again) and where it goes
+    const uint8_t *const w_base = g.w_codes + (int64_t)o0 * g.w_row_bytes, *const a_base = g.a_codes + (int64_t)n0 * g.a_row_bytes;
+    uint32_t w_src[WLOADS], a_src[ALOADS];
     int w_dst[WLOADS], a_dst[ALOADS];
 #pragma unroll
     for (int t = 0; t < WLOADS; ++t) {
         const int q = lane + 64 * t, row = q / WPIECES, piece = q % WPIECES;
-        w_src[t] = g.w_codes + (int64_t)min(o0 + row, g.O - 1) * g.w_row_bytes + 16 * piece;
-        w_dst[t] = row * SK_ROW<WBITS> + 16 * piece;
+        w_src[t] = (uint32_t)min(row, g.O - 1 - o0) * (uint32_t)g.w_row_bytes + 16 * piece;
+        w_dst[t] = row * SK_ROW<WBITS, STEP> + 16 * piece;
     }
 #pragma unroll
     for (int t = 0; t < ALOADS; ++t) {
         const int q = lane + 64 * t, row = q / APIECES, piece = q % APIECES;
-        a_src[t] = g.a_codes + (int64_t)min(row, g.N - 1) * g.a_row_bytes + 16 * piece;
-        a_dst[t] = row * SK_ROW<ABITS> + 16 * piece;
+        a_src[t] = (uint32_t)min(row, g.N - 1 - n0) * (uint32_t)g.a_row_bytes + 16 * piece;
+        a_dst[t] = row * SK_ROW<ABITS, STEP> + 16 * piece;
     }
 
-    v4i acc[NT][SK_RT];
+    constexpr size_t EPI_AT = skinny_lds<ABITS, WBITS, NT, RT, WAVES, STEP>() - EPI_BYTES<16 * NT, 16 * RT>;
+    uint8_t *const epi = sk_lds + EPI_AT; // the epilogue's constants, behind strips and partial tiles
+    const EpiRegs epi_regs = load_epilogue<16 * NT, 16 * RT>(g, n0, o0, tid);
+
+    v4i acc[NT][RT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < SK_RT; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+        for (int j = 0; j < RT; ++j) acc[i][j] = v4i{0, 0, 0, 0};
 
     v4i w0[WLOADS], a0[ALOADS], w1[WLOADS], a1[ALOADS]; // two register stages
     auto fetch = [&](v4i (&tw)[WLOADS], v4i (&ta)[ALOADS], int s) {
+        const uint8_t *wp = w_base + (int64_t)s * WB, *ap = a_base + (int64_t)s * AB;
 #pragma unroll
-        for (int k = 0; k < WLOADS; ++k) tw[k] = *reinterpret_cast<const v4i *>(w_src[k] + (int64_t)s * (SK_STEP * WBITS / 8));
+        for (int k = 0; k < WLOADS; ++k) tw[k] = *reinterpret_cast<const v4i *>(wp + w_src[k]);
 #pragma unroll
-        for (int k = 0; k < ALOADS; ++k) ta[k] = *reinterpret_cast<const v4i *>(a_src[k] + (int64_t)s * (SK_STEP * ABITS / 8));
+        for (int k = 0; k < ALOADS; ++k) ta[k] = *reinterpret_cast<const v4i *>(ap + a_src[k]);
     };
     auto work = [&](const v4i (&tw)[WLOADS], const v4i (&ta)[ALOADS]) {
         // a wave's LDS operations complete in order: these writes follow the previous step's reads
@@ -1390,29 +1464,39 @@ __global__ __launch_bounds__(SK_THREADS) void int_gemm_skinny_kernel(const GemmA
         for (int k = 0; k < WLOADS; ++k) *reinterpret_cast<v4i *>(w_strip + w_dst[k]) = tw[k];
 #pragma unroll
         for (int k = 0; k < ALOADS; ++k) *reinterpret_cast<v4i *>(a_strip + a_dst[k]) = ta[k];
-        uint32_t da[NT][16];
+        auto quarter = [&](const uint8_t *strip_row, auto bits, uint32_t (&d)[CODES / 4]) { // lane (r, c)'s codes of a row
+            constexpr int BITS = decltype(bits)::value, DW = CODES * BITS / 32;
+            uint32_t u[DW];
+            const uint8_t *p = strip_row + c * (4 * DW);
+            if constexpr (DW % 4 == 0) {
+#pragma unroll
+                for (int k = 0; k < DW / 4; ++k) {
+                    const v4i v = reinterpret_cast<const v4i *>(p)[k];
+                    u[4 * k] = (uint32_t)v[0]; u[4 * k + 1] = (uint32_t)v[1]; u[4 * k + 2] = (uint32_t)v[2]; u[4 * k + 3] = (uint32_t)v[3];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < DW / 2; ++k) {
+                    const v2i v = reinterpret_cast<const v2i *>(p)[k];
+                    u[2 * k] = (uint32_t)v[0]; u[2 * k + 1] = (uint32_t)v[1];
+                }
+            }
+            expand_codes<BITS, CODES, PERM>(u, d);
+        };
+        uint32_t dw[RT][CODES / 4];
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+            quarter(w_strip + (16 * j + r) * SK_ROW<WBITS, STEP>, std::integral_constant<int, WBITS>{}, dw[j]);
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
-            Unit<ABITS> u;
-            const uint4 *p = reinterpret_cast<const uint4 *>(a_strip + (16 * i + r) * SK_ROW<ABITS> + c * (SK_STEP * ABITS / 8 / 4));
+            uint32_t da[CODES / 4];
+            quarter(a_strip + (16 * i + r) * SK_ROW<ABITS, STEP>, std::integral_constant<int, ABITS>{}, da);
 #pragma unroll
-            for (int k = 0; k < ABITS / 2; ++k) u.r[k] = p[k];
-            expand_unit<ABITS, PERM>(u, da[i]);
-        }
+            for (int m = 0; m < CODES / 16; ++m)
 #pragma unroll
-        for (int j = 0; j < SK_RT; ++j) {
-            Unit<WBITS> u;
-            const uint4 *p = reinterpret_cast<const uint4 *>(w_strip + (16 * j + r) * SK_ROW<WBITS> + c * (SK_STEP * WBITS / 8 / 4));
-#pragma unroll
-            for (int k = 0; k < WBITS / 2; ++k) u.r[k] = p[k];
-            uint32_t dw[16];
-            expand_unit<WBITS, PERM>(u, dw);
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-#pragma unroll
-                for (int i = 0; i < NT; ++i) {
-                    const v4i fw = {(int)dw[4 * m], (int)dw[4 * m + 1], (int)dw[4 * m + 2], (int)dw[4 * m + 3]};
-                    const v4i fa = {(int)da[i][4 * m], (int)da[i][4 * m + 1], (int)da[i][4 * m + 2], (int)da[i][4 * m + 3]};
+                for (int j = 0; j < RT; ++j) {
+                    const v4i fw = {(int)dw[j][4 * m], (int)dw[j][4 * m + 1], (int)dw[j][4 * m + 2], (int)dw[j][4 * m + 3]};
+                    const v4i fa = {(int)da[4 * m], (int)da[4 * m + 1], (int)da[4 * m + 2], (int)da[4 * m + 3]};
                     acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw, fa, acc[i][j], 0, 0, 0);
                 }
         }
@@ -1420,45 +1504,45 @@ __global__ __launch_bounds__(SK_THREADS) void int_gemm_skinny_kernel(const GemmA
 
     // Every fetch is unconditional (past the end a wave re-reads its first step, from cache), so that
     // the number of loads in flight at each wait is known when the code is compiled.
-    const int n_steps = g.Kpad / SK_STEP; // rows are padded to a multiple of 256 codes
+    const int n_steps = g.Kpad / STEP; // rows are padded to a multiple of 256 codes
     int s = wave;
     if (s < n_steps) {
         fetch(w0, a0, s);
-        fetch(w1, a1, s + SK_WAVES < n_steps ? s + SK_WAVES : wave);
+        fetch(w1, a1, s + WAVES < n_steps ? s + WAVES : wave);
         while (true) { // two steps per turn: the register stages alternate without being indexed
             work(w0, a0);
-            fetch(w0, a0, s + 2 * SK_WAVES < n_steps ? s + 2 * SK_WAVES : wave);
-            s += SK_WAVES;
+            fetch(w0, a0, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
+            s += WAVES;
             if (s >= n_steps) break;
             work(w1, a1);
-            fetch(w1, a1, s + 2 * SK_WAVES < n_steps ? s + 2 * SK_WAVES : wave);
-            s += SK_WAVES;
+            fetch(w1, a1, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
+            s += WAVES;
             if (s >= n_steps) break;
         }
     }
 
-    // ---- add the 8 partial tiles up; wave t finishes tile t
+    // ---- add the waves' partial tiles up; wave t finishes token tiles t, t + WAVES, ..
+    store_epilogue<ABITS, WBITS, 16 * NT, 16 * RT, false, WAVES>(g, epi_regs, epi, tid);
     __syncthreads(); // the strips are no longer read
     v4i *red = reinterpret_cast<v4i *>(sk_lds);
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < SK_RT; ++j) red[(wave * (NT * SK_RT) + i * SK_RT + j) * 64 + lane] = acc[i][j];
+        for (int j = 0; j < RT; ++j) red[(wave * (NT * RT) + i * RT + j) * 64 + lane] = acc[i][j];
     __syncthreads();
-    if (wave < NT * SK_RT) {
-        v4i sum[1][1] = {{red[wave * 64 + lane]}};
+    for (int i = wave; i < NT; i += WAVES) {
+        v4i sum[1][RT];
 #pragma unroll
-        for (int w = 1; w < SK_WAVES; ++w) sum[0][0] += red[(w * (NT * SK_RT) + wave) * 64 + lane];
-        finish_wave_tile<ABITS, WBITS, YT, 1, 1>(g, sum, 16 * (wave / SK_RT), o0 + 16 * (wave % SK_RT), lane);
+        for (int j = 0; j < RT; ++j) {
+            sum[0][j] = red[(i * RT + j) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) sum[0][j] += red[(w * (NT * RT) + i * RT + j) * 64 + lane];
+            // 8-bit codes on both sides: places past K were zero codes, -128 times -128 each
+            if constexpr (ABITS == 8 && WBITS == 8) sum[0][j] -= 16384 * (g.Kpad - g.K);
+        }
+        if (finish_from_lds<YT, 16 * NT, 16 * RT>(g, sum, epi, n0, o0, 16 * i, 0, lane)) continue;
+        finish_wave_tile<ABITS, WBITS, YT, 1, RT>(g, sum, n0 + 16 * i, o0, lane, g.K);
     }
-}
-
-template <int ABITS, int WBITS>
-constexpr size_t skinny_lds(int nt)
-{
-    const size_t strips = (size_t)SK_WAVES * (nt == 1 ? SK_STRIP<ABITS, WBITS, 1> : nt == 2 ? SK_STRIP<ABITS, WBITS, 2> : SK_STRIP<ABITS, WBITS, 4>);
-    const size_t red = (size_t)SK_WAVES * nt * SK_RT * 64 * sizeof(v4i);
-    return strips > red ? strips : red;
 }
 
 // kernels whose LDS limit has been raised (once each: every kernel here always asks for the same amount,
@@ -1617,23 +1701,27 @@ int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
-        constexpr size_t lds = (size_t)T8_STAGES * 16 * T8_BLOCK + EPI_BYTES<128, 128>;
-        if (ga.splits > 1) {
-            const int32_t sp = launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, true>, grid, dim3(LTHREADS), lds, ga, stream);
+        constexpr size_t lds3 = (size_t)3 * 16 * T8_BLOCK + EPI_BYTES<128, 128>, lds4 = (size_t)4 * 16 * T8_BLOCK + EPI_BYTES<128, 128>;
+        if (ga.splits > 1) { // at most 256 workgroups
+            const int32_t sp = launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, 4, true>, grid, dim3(LTHREADS), lds4, ga, stream);
             if (sp != QLLM_OK) return sp;
             constexpr int SA = ABITS == 8 ? 1 : 0, SW = WBITS == 8 ? 1 : 0;
             const dim3 fgrid((unsigned)(((int64_t)ga.N * ga.O + 255) / 256));
             if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float, SA, SW>, fgrid, dim3(256), 0, ga, stream);
             return launch_kernel(splitk_finish_kernel<uint16_t, SA, SW>, fgrid, dim3(256), 0, ga, stream);
         }
-        if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2>, grid, dim3(LTHREADS), lds, ga, stream);
-        return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 4, 2>, grid, dim3(LTHREADS), lds, ga, stream);
+        if ((int64_t)grid.x * grid.y <= 256) {
+            if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, 4>, grid, dim3(LTHREADS), lds4, ga, stream);
+            return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 4, 2, 4>, grid, dim3(LTHREADS), lds4, ga, stream);
+        }
+        if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, 3>, grid, dim3(LTHREADS), lds3, ga, stream);
+        return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 4, 2, 3>, grid, dim3(LTHREADS), lds3, ga, stream);
     };
     auto launch_big = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + LBN - 1) / LBN), (unsigned)((ga.N + LBM - 1) / LBM));
-        constexpr size_t lds = (size_t)T8_STAGES * 32 * T8_BLOCK + EPI_BYTES<256, 256>;
-        if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
-        return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 8, 4>, grid, dim3(LTHREADS), lds, ga, stream);
+        constexpr size_t lds = (size_t)3 * 32 * T8_BLOCK + EPI_BYTES<256, 256>;
+        if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
+        return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
     };
     if (g.splits > 1) return launch_small(g); // K is only split where the small tile is the choice
     if (plan.o_split > 0) { // whole rounds of large tiles, then the other output features with small ones
@@ -1646,20 +1734,90 @@ int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
     return plan.small ? launch_small(g) : launch_big(g);
 }
 
-// Up to this many tokens the weight-streaming kernel takes 4-bit codes on both sides (four token tiles per
-// workgroup: its LDS strips hold no more, and none of the wider codes at that count).
-constexpr int SK4_TOKENS = 64;
+template <int ABITS, int WBITS, int NT, int RT, int WAVES, int STEP>
+int32_t launch_skinny(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+{
+    static_assert(16 * NT + 16 * RT <= 64 * WAVES, "a lane stages one token's or one feature's constants");
+    const dim3 grid((unsigned)((g.O + 16 * RT - 1) / (16 * RT)), (unsigned)((g.N + 16 * NT - 1) / (16 * NT)));
+    constexpr size_t lds = skinny_lds<ABITS, WBITS, NT, RT, WAVES, STEP>();
+    if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, float, NT, RT, WAVES, STEP>, grid, dim3(64 * WAVES), lds, g, stream);
+    return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, uint16_t, NT, RT, WAVES, STEP>, grid, dim3(64 * WAVES), lds, g, stream);
+}
+
+// Whether the weight-streaming kernel takes a product, and how.  Up to 32 tokens always, and 4-bit codes up to 64.
+// Beyond, every workgroup passes its token tiles' packed codes through LDS and the vector unit for 32 features only, so
+// its cost grows with K, the tiles per workgroup and, above one workgroup per CU, their number; what the tiled kernels
+// cost beside it are two or three launches (re-laying, product, finish) and weights of 6 or 8 bits per code.  The lines
+// are where the two meet (us, stream : tiled; "cost" = K nt max(1, groups / 256)):
+//   4 / 4  68000: 4096 x 4096, 128 / 512 tokens 10 : 19 / 17 : 26 (cost 33k / 66k); 8192 x 8192, 128 tokens 18 : 24 (66k), 160
+//          25 : 25 (98k), 256 30 : 28 (131k); 13824 -> 5120, 80 tokens 21 : 21 (83k); 5120 -> 27648, 80 40 : 33 (104k)
+//   8 / 4  70000: 8192 x 8192, 128 26 : 30 (66k), 160 35 : 34 (98k); 8192 -> 4096, 256 26 : 26 (66k); 5120 -> 27648, 64 33 : 38 (69k);
+//          48000 up to 128 workgroups (K split over workgroups in the tiled kernels): 4096 -> 1024, 96 10 : 14 (25k), 16384 33 : 26 (98k)
+//   6 / 6, 8 / 8  36000: 8192 -> 4096, 6 / 6, 128 22 : 22 (33k); 4096 x 4096, 160 16 : 22 (25k), 256 25 : 24 (37k); 8 / 8, 128 15 : 20
+//          (33k), 512 28 : 28 (66k); 8192 -> 4096, 8 / 8, 128 25 : 22 (66k); 1024 -> 4096, 512 10 : 26 (16k); 28000 up to 128
+//          workgroups: 4096 -> 1024, 6 / 6, 128 11 : 14 (16k), 96 14 : 14 (25k), 16384 -> 1024, 128 38 : 27 (66k)
+// More than two workgroups per CU take it only where it is cheap: 4096 -> 12288, 160 tokens 4 / 4 24 : 17 (74k, 768 groups),
+// 1024 -> 4096, 512 tokens 6 / 6 15 : 26 (18k, 768 groups).  Where the weight came without its re-laid copy the tiled
+// kernels expand packed codes and take 54-130 us up to 128 tokens: there the line is 100000.
+struct StreamPlan {
+    bool take;
+    int nt;         // 16-token tiles per workgroup
+    int64_t groups; // workgroups, at 32 features each
+};
+StreamPlan plan_stream(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool relaid)
+{
+    const int64_t og = (O + 31) / 32;
+    if (N <= 32) return StreamPlan{true, N <= 16 ? 1 : 2, og};
+    const int64_t most = a_bits == 6 ? 6 : 8; // six-bit codes: registers for six tiles
+    const int64_t tiles = (N + 15) / 16, blocks = (tiles + most - 1) / most, each = (tiles + blocks - 1) / blocks;
+    const int nt = each <= 4 ? 4 : each <= 6 ? 6 : 8;
+    const int64_t groups = og * blocks, cost = K * nt * (groups > 256 ? groups : 256) / 256;
+    const int64_t line = w_bits != 4 ? (groups <= 128 ? 28000 : 36000) : a_bits == 4 ? 68000 : groups <= 128 ? 48000 : 70000;
+    bool take = (a_bits == 4 && N <= 64) || (cost <= line && (groups <= 512 || nt == 4 || cost <= 33000));
+    if (!relaid && w_bits + a_bits != 8) take = take || cost <= 100000;
+    return StreamPlan{take && blocks <= 65535, nt, groups};
+}
+
+template <int ABITS, int WBITS>
+int32_t launch_stream(const GemmArgs &g, const StreamPlan &plan, int32_t y_dtype, hipStream_t stream)
+{
+    constexpr int STEP = ABITS == 8 ? 64 : 128; // 64-byte (6 bits: 96-byte) rows of LDS where there are many
+    // more workgroups than CUs: smaller ones, several to a CU (16 tokens, 5120 -> 27648 4 / 4: 16.4 : 17.7 us)
+    const bool wide = plan.groups > 256;
+    if (plan.nt == 1) {
+        if (wide) return launch_skinny<ABITS, WBITS, 1, 2, 4, 256>(g, y_dtype, stream);
+        return launch_skinny<ABITS, WBITS, 1, 2, 8, 256>(g, y_dtype, stream);
+    }
+    if (plan.nt == 2) {
+        if constexpr (ABITS == 8 && WBITS == 4) { // 5120 -> 27648: 27.3 : 31.7 us, 4096 -> 12288: 9.7 : 13.5
+            if (wide) return launch_skinny<ABITS, WBITS, 2, 4, 8, STEP>(g, y_dtype, stream);
+        } else if constexpr (ABITS == 6) { // 36.2 : 40, 13.8 : 16.8
+            if (wide) return launch_skinny<ABITS, WBITS, 2, 2, 8, STEP>(g, y_dtype, stream);
+        }
+        return launch_skinny<ABITS, WBITS, 2, 2, 8, 256>(g, y_dtype, stream);
+    }
+    if (plan.nt == 4) {
+        if (plan.groups > 512) return launch_skinny<ABITS, WBITS, 4, 4, 4, STEP>(g, y_dtype, stream); // 5120 -> 27648: 26.7 : 29.3 us with 8 waves
+        if (wide) return launch_skinny<ABITS, WBITS, 4, 4, 8, STEP>(g, y_dtype, stream);              // 4096 -> 12288 6 / 6: 16.6 : 19 with 4 waves
+        return launch_skinny<ABITS, WBITS, 4, 2, 8, STEP>(g, y_dtype, stream);
+    }
+    if (plan.nt == 6) {
+        if (wide) return launch_skinny<ABITS, WBITS, 6, 2, 4, STEP>(g, y_dtype, stream);
+        return launch_skinny<ABITS, WBITS, 6, 2, 8, STEP>(g, y_dtype, stream);
+    }
+    if constexpr (ABITS == 6) return QLLM_ERR_SHAPE; // not reached: at most six tiles
+    else {
+        if (wide) return launch_skinny<ABITS, WBITS, 8, 2, 4, STEP>(g, y_dtype, stream);
+        return launch_skinny<ABITS, WBITS, 8, 2, 8, STEP>(g, y_dtype, stream);
+    }
+}
 
 template <int ABITS, int WBITS>
 int32_t launch(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 {
+    const StreamPlan sp = plan_stream(g.N, g.K, g.O, ABITS, WBITS, ABITS == 4 ? g.w_tiles != nullptr : g.w_tiles8 != nullptr);
+    if (sp.take) return launch_stream<ABITS, WBITS>(g, sp, y_dtype, stream);
     if constexpr (ABITS == 4 && WBITS == 4) {
-        if (g.N > 32 && g.N <= SK4_TOKENS) {
-            const dim3 grid((unsigned)((g.O + 16 * SK_RT - 1) / (16 * SK_RT)));
-            const size_t lds = skinny_lds<4, 4>(4);
-            if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_skinny_kernel<4, 4, float, 4>, grid, dim3(SK_THREADS), lds, g, stream);
-            return launch_kernel(int_gemm_skinny_kernel<4, 4, uint16_t, 4>, grid, dim3(SK_THREADS), lds, g, stream);
-        }
         if (g.a_tiles && g.w_tiles) return launch_fp6(g, y_dtype, stream);
         // 4-bit codes on both sides, more than 32 tokens.  256 x 256 tiles run one workgroup per CU, 128 x 128
         // tiles two, at about three quarters of the large tile's rate per matrix-core operation: the
@@ -1697,17 +1855,6 @@ int32_t launch(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
                 return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, float>, grid, dim3(LTHREADS), 2 * LBUF, g, stream);
             return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, uint16_t>, grid, dim3(LTHREADS), 2 * LBUF, g, stream);
         }
-    }
-    if (g.N <= 32) { // decode: stream the weights once
-        const dim3 grid((unsigned)((g.O + 16 * SK_RT - 1) / (16 * SK_RT)));
-        const int nt = g.N <= 16 ? 1 : 2;
-        const size_t lds = skinny_lds<ABITS, WBITS>(nt);
-        if (y_dtype == QLLM_F32) {
-            if (nt == 1) return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, float, 1>, grid, dim3(SK_THREADS), lds, g, stream);
-            return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, float, 2>, grid, dim3(SK_THREADS), lds, g, stream);
-        }
-        if (nt == 1) return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, uint16_t, 1>, grid, dim3(SK_THREADS), lds, g, stream);
-        return launch_kernel(int_gemm_skinny_kernel<ABITS, WBITS, uint16_t, 2>, grid, dim3(SK_THREADS), lds, g, stream);
     }
     if constexpr (ABITS == 4 && WBITS == 4) {
         return QLLM_ERR_SHAPE; // not reached: every 4-bit shape was placed above

@@ -487,6 +487,28 @@ def test_gemm_epilogue_from_lds(oracle, b, a_bits, w_bits, y_dtype, N, K, O, ins
     check_y(oracle, y[rows][:, cols].contiguous(), ref, y_dtype)
 
 
+@pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 8), (8, 4)])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K,O", [(1, 300, 8230), (16, 2304, 50), (17, 520, 8227), (33, 1030, 70), (64, 260, 16410), (49, 260, 8200), (65, 700, 100),
+                                   (96, 64, 8227), (97, 300, 33), (128, 600, 8200), (130, 1300, 257), (300, 260, 31), (512, 128, 1029)])
+def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, y_dtype, N, K, O):
+    """The weight-streaming kernel over its tile counts (1, 2, 4, 6, 8 per workgroup), one and several blocks of tokens,
+    few and many workgroups (4 or 8 waves, 32 or 64 features), K that is no multiple of a step or shorter than one step
+    per wave, ragged tokens and features; zero-points inside the code range (the epilogue from LDS).  The raw
+    accumulators are exact, the call with acc_dump (general epilogue) gives the same bits, and the result matches the
+    oracle.  No workspace is used or needed where K is not split."""
+    rng = np.random.default_rng(N * 7 + K + O + a_bits)
+    a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
+    bx = np.clip(bx, 0, 2 ** a_bits - 1)
+    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=False)
+    y1, acc = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True)
+    ref_acc = a.astype(np.float64) @ w.astype(np.float64).T                  # integers below 2^53: exact
+    assert np.array_equal(acc.cpu().numpy(), ref_acc.astype(np.int64))
+    assert __import__("torch").equal(y, y1)
+    rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
+    check_y(oracle, y, oracle.epilogue(ref_acc.astype(np.int32), K, ax, bx, rs, aw, bw, cs), y_dtype)
+
+
 def test_gemm_extreme_codes(oracle, b):
     """All codes at their maximum: the largest accumulators the shapes allow."""
     for bits, K in [(4, 28672), (6, 8192), (8, 28672)]:
