@@ -308,14 +308,19 @@ def _dp(t):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without the Stream object around it (4 us of a small call's 18), where torch has it.
+_raw_stream, _raw_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is None:
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return C.c_void_p(_raw_stream(_raw_device()))
+        stream = torch.cuda.current_stream()
+    return C.c_void_p(stream.cuda_stream)
 
 
 def _x_dtype(x):
-    torch = _torch()
     if x.dtype == torch.bfloat16:
         return BF16
     if x.dtype == torch.float32:
@@ -385,51 +390,68 @@ def _need(cond, what):
         raise ValueError("libqllm binding: " + what)
 
 
+# The checks run on every call and a small call is host time, so a message is put together only when it is needed:
+# formatted beforehand, the messages alone cost a decode step 8 of its 18 us.
+
+def _fail(what):
+    raise ValueError("libqllm binding: " + what)
+
+
 def _check_tensor(t, name, dtypes=None, shape=None, numel=None, optional=False):
     """A device tensor whose rows are dense (stride 1 along the last axis)."""
     if t is None:
-        _need(optional, f"{name} is required")
+        if not optional:
+            _fail(f"{name} is required")
         return
-    torch = _torch()
-    _need(isinstance(t, torch.Tensor), f"{name} must be a torch tensor")
-    if dtypes is not None:
-        _need(t.dtype in dtypes, f"{name} has dtype {t.dtype}, expected one of {[str(d) for d in dtypes]}")
-    if shape is not None:
-        _need(tuple(t.shape) == tuple(shape), f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    if numel is not None:
-        _need(t.numel() == numel and t.is_contiguous(), f"{name} must hold {numel} contiguous elements, has {t.numel()}")
-    _need(t.dim() == 0 or t.numel() == 0 or t.stride(-1) == 1, f"{name} must have stride 1 along its last axis")
+    if not isinstance(t, torch.Tensor):
+        _fail(f"{name} must be a torch tensor")
+    if dtypes is not None and t.dtype not in dtypes:
+        _fail(f"{name} has dtype {t.dtype}, expected one of {[str(d) for d in dtypes]}")
+    if shape is not None and tuple(t.shape) != tuple(shape):
+        _fail(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+    if numel is not None and (t.numel() != numel or not t.is_contiguous()):
+        _fail(f"{name} must hold {numel} contiguous elements, has {t.numel()}")
+    if t.dim() != 0 and t.stride(-1) != 1 and t.numel() != 0:
+        _fail(f"{name} must have stride 1 along its last axis")
 
 
 def _check_on_device(**tensors):
     """Last of a wrapper's checks, so that shapes and dtypes can be tested without a GPU."""
     for name, t in tensors.items():
-        _need(t is None or t.is_cuda, f"{name} must be a device (cuda) tensor")
+        if t is not None and not t.is_cuda:
+            _fail(f"{name} must be a device (cuda) tensor")
+
+
+_FLOATS, _F32_ONLY, _U8_ONLY = (torch.float32, torch.bfloat16), (torch.float32,), (torch.uint8,)
 
 
 def _check_activation_args(x, norm, gamma, beta, dmap):
-    torch = _torch()
-    _need(hasattr(x, "dim") and x.dim() == 2, "x must be a 2-d tensor [tokens, channels]")
+    if not (hasattr(x, "dim") and x.dim() == 2):
+        _fail("x must be a 2-d tensor [tokens, channels]")
     N, Cc = x.shape
-    _need(int(norm) in (NORM_NONE, NORM_LAYER, NORM_RMS), f"unknown norm kind {norm}")
-    if dmap is not None:
-        _need(dmap.C_in == Cc, f"the map takes {dmap.C_in} channels, x has {Cc}")
+    if int(norm) not in (NORM_NONE, NORM_LAYER, NORM_RMS):
+        _fail(f"unknown norm kind {norm}")
+    if dmap is not None and dmap.C_in != Cc:
+        _fail(f"the map takes {dmap.C_in} channels, x has {Cc}")
     if int(norm) != NORM_NONE:
-        _check_tensor(gamma, "gamma", (torch.float32,), numel=Cc)
-    _check_tensor(beta, "beta", (torch.float32,), numel=Cc, optional=True)
-    _check_tensor(x, "x", (torch.float32, torch.bfloat16))
+        _check_tensor(gamma, "gamma", _F32_ONLY, numel=Cc)
+    if beta is not None:
+        _check_tensor(beta, "beta", _F32_ONLY, numel=Cc)
+    _check_tensor(x, "x", _FLOATS)
     return N, Cc
 
 
 def _check_qact(out, N, K, bits, name="out"):
-    _need(out.N >= N, f"{name} holds {out.N} tokens, {N} needed")
-    _need(out.K == K, f"{name} was made for {out.K} channels, the map makes {K}")
-    _need(out.bits == int(bits), f"{name} was made for {out.bits}-bit codes, {bits} asked for")
+    if out.N < N:
+        _fail(f"{name} holds {out.N} tokens, {N} needed")
+    if out.K != K:
+        _fail(f"{name} was made for {out.K} channels, the map makes {K}")
+    if out.bits != int(bits):
+        _fail(f"{name} was made for {out.bits}-bit codes, {bits} asked for")
 
 
 def _check_output(y, N, O, name="y"):
-    torch = _torch()
-    _check_tensor(y, name, (torch.float32, torch.bfloat16), shape=(N, O))
+    _check_tensor(y, name, _FLOATS, shape=(N, O))
 
 
 def qllm_norm_reassemble_quant(x, norm, gamma, beta, eps, dmap, bits, out, stream=None):
@@ -457,11 +479,11 @@ def qllm_fused_kernel_choice(dmap, x_dtype, N, ldx, norm, has_beta, bits):
 
 
 def qllm_int_gemm(a, weight, y, acc_dump=None, workspace=None, stream=None):
-    torch = _torch()
-    _need(a.K == weight.K, f"activations have {a.K} channels, weights {weight.K}")
+    if a.K != weight.K:
+        _fail(f"activations have {a.K} channels, weights {weight.K}")
     _check_output(y, a.N, weight.O)
     _check_tensor(acc_dump, "acc_dump", (torch.int32,), numel=a.N * weight.O, optional=True)
-    _check_tensor(workspace, "workspace", (torch.uint8,), optional=True)
+    _check_tensor(workspace, "workspace", _U8_ONLY, optional=True)
     _check_on_device(y=y, acc_dump=acc_dump, workspace=workspace)
     _chk(_lib.qllm_int_gemm(C.byref(a.c), a.bits, a.N, C.byref(weight.c), _dp(y), _x_dtype(y), y.stride(0),
                             _dp(acc_dump), _dp(workspace), 0 if workspace is None else workspace.numel(),
@@ -471,9 +493,10 @@ def qllm_int_gemm(a, weight, y, acc_dump=None, workspace=None, stream=None):
 
 def qllm_reassembled_linear(x, norm, gamma, beta, eps, dmap, a_bits, weight, y, workspace, stream=None):
     N, Cc = _check_activation_args(x, norm, gamma, beta, dmap)
-    _need(dmap.C_out == weight.K, f"the map makes {dmap.C_out} channels, the weights take {weight.K}")
+    if dmap.C_out != weight.K:
+        _fail(f"the map makes {dmap.C_out} channels, the weights take {weight.K}")
     _check_output(y, N, weight.O)
-    _check_tensor(workspace, "workspace", (_torch().uint8,))
+    _check_tensor(workspace, "workspace", _U8_ONLY)
     _check_on_device(y=y, workspace=workspace, x=x, gamma=gamma, beta=beta)
     _chk(_lib.qllm_reassembled_linear(_dp(x), _x_dtype(x), N, Cc, x.stride(0), int(norm), _dp(gamma), _dp(beta),
                                       float(eps), C.byref(dmap.c), int(a_bits), C.byref(weight.c), _dp(y),
@@ -488,7 +511,8 @@ STATIC_WORKSPACE_BYTES = 32 << 20
 def qllm_reassembled_linear_static(x, norm, gamma, beta, eps, dmap, a_bits, weight, y, stream=None):
     """The layer with the library's built-in workspace: allocates nothing."""
     N, Cc = _check_activation_args(x, norm, gamma, beta, dmap)
-    _need(dmap.C_out == weight.K, f"the map makes {dmap.C_out} channels, the weights take {weight.K}")
+    if dmap.C_out != weight.K:
+        _fail(f"the map makes {dmap.C_out} channels, the weights take {weight.K}")
     _check_output(y, N, weight.O)
     _check_on_device(y=y, x=x, gamma=gamma, beta=beta)
     _chk(_lib.qllm_reassembled_linear_static(_dp(x), _x_dtype(x), N, Cc, x.stride(0), int(norm), _dp(gamma), _dp(beta),
