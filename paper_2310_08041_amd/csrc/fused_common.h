@@ -33,6 +33,8 @@ struct FusedArgs {
     int64_t row_bytes;
     float *alpha;
     int32_t *zero, *rowsum;
+    uint8_t *tiles8; // not null (6- and 8-bit codes): the codes leave in the layout of qllm_pack_tiles8 instead of packed rows
+    int32_t tiles8_kt; // its K-tiles per row
     // calibration variant
     float *absmax, *y_dump;
     int32_t n_dump;
@@ -69,7 +71,16 @@ __device__ __forceinline__ int32_t quant_code(float x, float inv, int32_t beta, 
 // Launches the planned kernel (fused_planned.hip).  Returns QLLM_ERR_WORKSPACE if the shape or the
 // general groups are more than it holds on chip: the caller then takes the plain kernel.
 int32_t qllm_launch_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
+// The same for 6- and 8-bit codes with the codes written to a.tiles8 (fused_planned_tiles8.hip).
+int32_t qllm_launch_fused_tiles8(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
+
+// qllm_norm_reassemble_quant with the choice of layout: tiles8 not null asks for the codes as qllm_pack_tiles8 lays them
+// out (rows past N in the last block of 16 are left as they are) in place of out->codes; *wrote_tiles8 says whether the
+// kernel that runs does that (the planned one, 6- and 8-bit codes); if not, out->codes holds the packed rows as ever.
+int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
+                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles8,
+                        bool *wrote_tiles8, void *hip_stream);
 
 #endif

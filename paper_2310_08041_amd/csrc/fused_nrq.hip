@@ -494,11 +494,11 @@ int32_t fill_plan(FusedArgs &a, const qllm_map *map, int64_t C)
 
 } // namespace
 
-extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx,
-                                              int32_t norm, const float *gamma, const float *beta, float eps,
-                                              const qllm_map *map, int32_t bits, const qllm_qact *out,
-                                              void *hip_stream)
+int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
+                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles8,
+                        bool *wrote_tiles8, void *hip_stream)
 {
+    *wrote_tiles8 = false;
     int32_t rc = check_common(x, x_dtype, N, C, ldx, norm, gamma);
     if (rc != QLLM_OK) return rc;
     if (!map || !out) return QLLM_ERR_NULL;
@@ -528,11 +528,26 @@ extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, in
     const int max_units = a.S > a.n_groups_pad ? a.S : a.n_groups_pad;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     if (map->plan) {
+        if (tiles8 && bits != 4 && qllm_choose_fused_planned(a, x_dtype, bits) != QLLM_FUSED_WALKS_MAP) {
+            a.tiles8 = tiles8;
+            a.tiles8_kt = (int32_t)((map->C_out + 63) / 64);
+            *wrote_tiles8 = true;
+            return qllm_launch_fused_tiles8(a, x_dtype, bits, stream);
+        }
         rc = qllm_launch_fused_planned(a, x_dtype, bits, stream);
         if (rc != QLLM_ERR_WORKSPACE) return rc; // does not fit on chip: the plain kernel below handles it
     }
     if (x_dtype == QLLM_BF16) return dispatch_bits<uint16_t>(a, bits, max_units, stream);
     return dispatch_bits<float>(a, bits, max_units, stream);
+}
+
+extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx,
+                                              int32_t norm, const float *gamma, const float *beta, float eps,
+                                              const qllm_map *map, int32_t bits, const qllm_qact *out,
+                                              void *hip_stream)
+{
+    bool wrote_tiles8;
+    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles8, hip_stream);
 }
 
 extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,

@@ -42,7 +42,16 @@
 
 using namespace qllm_detail;
 
+// This file is compiled twice: as it is (packed rows), and by fused_planned_tiles8.hip with QLLM_FUSED_TILES8 set, for the
+// kernels of 6- and 8-bit codes that write the byte layout of the GEMM instead.  One kernel with both store passes in it
+// takes longer for either (777 x 5000 8-bit 23.8 us in place of 21.8; 16 x 8192 decode +0.2).
+#ifndef QLLM_FUSED_TILES8
+#define QLLM_FUSED_TILES8 0
+#endif
+
 namespace {
+
+constexpr bool TILES8 = QLLM_FUSED_TILES8 != 0;
 
 // work-list entries (see qllm_plan_map_host): kind << 30 | group << 17 | field
 constexpr int KIND_PLAIN = 0, KIND_COMP = 1, KIND_PAD = 2, KIND_NONE = 3;
@@ -355,6 +364,36 @@ __device__ __forceinline__ void store_group(uint8_t *out_row, int g, uint32_t w0
     }
 }
 
+// The same group in the byte layout of the GEMM (qllm_pack_tiles8): one byte per code, 8-bit codes XOR 0x80, places past K
+// zero bytes; `row_tiles`: the row's first byte in its block of 16 rows.  8 bytes per group, 16 of two neighbours
+// together, the 16 rows of a block interleaved: the rows that are worked on at one time are neighbours on one XCD (see
+// the kernel's first row), so that its L2 puts whole lines together.  For 6-bit codes one store where packed rows take
+// three half-words.  2048 x 28672 6-bit: 72 us + 23 for the re-laying pass before, 86 so (the 16-byte pieces are what L2
+// takes per request: 3.7 M of them); 777 x 5000 8-bit 21.2 + 5.0 -> 21.8; 200 x 13824 6-bit 8.8 + 3.7 -> 9.9.
+template <int BITS>
+__device__ __forceinline__ void store_group_tiles8(uint8_t *row_tiles, int n_kt, int K, int g, uint32_t w0, uint32_t w1)
+{
+    if (g >= 8 * n_kt) return; // packed rows are padded further than the tiles
+    uint32_t b0, b1;
+    if constexpr (BITS == 6) {
+        auto spread = [](uint32_t v) { // four 6-bit codes in the low 24 bits -> four bytes
+            const uint32_t x = (v & 0xfffu) | ((v << 4) & 0x0fff0000u);
+            return (x & 0x003f003fu) | ((x << 2) & 0x3f003f00u);
+        };
+        b0 = spread(w0);
+        b1 = spread(__builtin_amdgcn_alignbit(w1, w0, 24));
+    } else {
+        b0 = w0 ^ 0x80808080u;
+        b1 = w1 ^ 0x80808080u;
+        const int left = K - GROUP * g; // codes of the group that are places of K
+        if (left < GROUP) {
+            b0 = left >= 4 ? b0 : left <= 0 ? 0u : b0 & ((1u << (8 * left)) - 1u);
+            b1 = left <= 4 ? 0u : b1 & ((1u << (8 * (left - 4))) - 1u);
+        }
+    }
+    *reinterpret_cast<uint2 *>(row_tiles + (g >> 3) * 1024 + ((g >> 1) & 3) * 256 + (g & 1) * 8) = make_uint2(b0, b1);
+}
+
 // The 8 codes that start v codes into packed chunk u (0 <= v < 8): chunks u and u + 1 funnel-shifted.
 // The word after the last chunk exists (and is only ever shifted out), and so does the one before the first.
 // In two halves, so that the LDS reads can be issued long before the words are needed.
@@ -510,7 +549,10 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     //      costs about one trip to memory and not one per list.
     const XT *xbase = reinterpret_cast<const XT *>(a.x);
     Raw<XT> raw[ITERS];
+    // Rows blockIdx, + grid, ...; where 16 rows share lines of the output, each XCD (workgroups go to them in turn) takes
+    // neighbouring rows of every sweep over the grid.
     int64_t row = blockIdx.x;
+    if (TILES8 && (gridDim.x & 7u) == 0) row = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     if (PREFETCH && row < a.N) { // the first row
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
@@ -734,6 +776,11 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     auto out_store = [&](OutState &o, int64_t prev, int ltid) {
         int32_t sum = 0;
         uint8_t *out_row = a.codes + prev * a.row_bytes;
+        uint8_t *row_tiles = TILES8 ? a.tiles8 + (prev >> 4) * a.tiles8_kt * 1024 + (prev & 15) * 16 : nullptr;
+        auto put_group = [&](int gr, uint32_t v0, uint32_t v1) {
+            if constexpr (TILES8) store_group_tiles8<BITS>(row_tiles, a.tiles8_kt, a.C_out, gr, v0, v1);
+            else store_group<BITS>(out_row, gr, v0, v1);
+        };
         int g[ITERS];
         uint32_t w0[ITERS], w1[ITERS];
 #pragma unroll
@@ -750,7 +797,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
             if (FULL || ((uint32_t)o.e[it].y >> 30) != KIND_NONE) {
-                store_group<BITS>(out_row, g[it], w0[it], w1[it]);
+                put_group(g[it], w0[it], w1[it]);
                 sum += code_sum<BITS>(w0[it], w1[it]);
             }
         }
@@ -761,7 +808,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
                 if (comp + nt < n_loop) next = rec_fetch(comp + nt);
                 uint32_t c0, c1;
                 const int gc = composite_of(cur, comp, c0, c1);
-                store_group<BITS>(out_row, gc, c0, c1);
+                put_group(gc, c0, c1);
                 sum += code_sum<BITS>(c0, c1);
             }
         }
@@ -1297,7 +1344,9 @@ int32_t dispatch_norm(const FusedArgs &a, const Shape &sh, size_t lds, bool stre
 template <typename XT>
 int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds, bool stream_lists, hipStream_t stream)
 {
-    if (bits == 4) return dispatch_norm<XT, 4>(a, sh, lds, stream_lists, stream);
+    if constexpr (!TILES8) {
+        if (bits == 4) return dispatch_norm<XT, 4>(a, sh, lds, stream_lists, stream);
+    }
     if (bits == 6) return dispatch_norm<XT, 6>(a, sh, lds, stream_lists, stream);
     return dispatch_norm<XT, 8>(a, sh, lds, stream_lists, stream);
 }
@@ -1335,9 +1384,13 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
 
 } // namespace
 
+#if QLLM_FUSED_TILES8
+int32_t qllm_launch_fused_tiles8(const FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream)
+#else
 int32_t qllm_choose_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits) { return choose(a, x_dtype, bits).kind; }
 
 int32_t qllm_launch_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream)
+#endif
 {
     const Choice c = choose(a, x_dtype, bits);
     if (c.kind == QLLM_FUSED_WALKS_MAP) return QLLM_ERR_WORKSPACE;

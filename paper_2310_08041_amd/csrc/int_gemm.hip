@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "qllm.h"
+#include "fused_common.h"
 
 extern "C" void qllm_note_hip_error(const char *step, const char *name);
 
@@ -47,6 +48,7 @@ struct GemmArgs {
     int32_t splits;
     const uint8_t *a_tiles, *w_tiles; // both operands as 6-bit fields in matrix-core order (see TILES6 below), or null
     const uint8_t *a_tiles8, *w_tiles8; // both operands as bytes in matrix-core order (see TILES8 below), or null
+    bool a_laid; // a_tiles8 holds the activations already
     // A launch of the FP6 or the byte-operand kernel may cover the output features o_first .. O - 1 only (the call is
     // then two launches with different tiles, each with its own O); never together with acc_dump, whose rows are O long.
     int32_t o_first;
@@ -1696,8 +1698,10 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 template <int ABITS, int WBITS>
 int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 {
-    const int32_t st = launch_tiles8(g.a_codes, ABITS, g.N, g.K, const_cast<uint8_t *>(g.a_tiles8), stream);
-    if (st != QLLM_OK) return st;
+    if (!g.a_laid) {
+        const int32_t st = launch_tiles8(g.a_codes, ABITS, g.N, g.K, const_cast<uint8_t *>(g.a_tiles8), stream);
+        if (st != QLLM_OK) return st;
+    }
     const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
@@ -1917,9 +1921,20 @@ extern "C" int64_t qllm_gemm_workspace_bytes(int64_t N, int64_t K, int64_t O, in
     return (qllm_tiles8_bytes(N, K) + 255) / 256 * 256 + (s8 > 1 ? (int64_t)s8 * N * O * (int64_t)sizeof(int32_t) : 0);
 }
 
-extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y,
-                                 int32_t y_dtype, int64_t ldy, int32_t *acc_dump, void *workspace,
-                                 int64_t workspace_bytes, void *hip_stream)
+namespace {
+
+// The byte-operand path of the other bit pairs: more than 32 tokens, the weight's tiles at hand and room for the
+// activations' in the workspace.
+bool has_room_for_tiles8(int64_t N, const qllm_weight *w, int32_t a_bits, const void *workspace, int64_t workspace_bytes)
+{
+    return !(a_bits == 4 && w->bits == 4) && w->tiles8 && N > 32 && workspace && workspace_bytes >= qllm_tiles8_bytes(N, w->K) &&
+           qllm_tiles8_bytes(N, w->K) < (1ll << 32) && qllm_tiles8_bytes(w->O, w->K) < (1ll << 32);
+}
+
+// qllm_int_gemm; a_laid: the workspace already starts with the activations' bytes (tiles8 layout), and the byte-operand
+// path is the one that runs.
+int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy,
+                 int32_t *acc_dump, void *workspace, int64_t workspace_bytes, bool a_laid, void *hip_stream)
 {
     if (!a || !w || !y) return QLLM_ERR_NULL;
     if (!a->codes || !a->scale || !a->zero || !a->rowsum) return QLLM_ERR_NULL;
@@ -1962,13 +1977,11 @@ extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, 
         g.a_tiles = static_cast<const uint8_t *>(workspace) + tiles_at;
         g.w_tiles = w->tiles6;
     }
-    // the byte-operand path of the other bit pairs: more than 32 tokens, the weight's tiles at hand and room for the
-    // activations' in the workspace
-    if (!(a_bits == 4 && wb == 4) && w->tiles8 && N > 32 && workspace && workspace_bytes >= qllm_tiles8_bytes(N, w->K) &&
-        qllm_tiles8_bytes(N, w->K) < (1ll << 32) && qllm_tiles8_bytes(w->O, w->K) < (1ll << 32)) {
+    if (has_room_for_tiles8(N, w, a_bits, workspace, workspace_bytes)) {
         if ((reinterpret_cast<uintptr_t>(workspace) & 15u) || (reinterpret_cast<uintptr_t>(w->tiles8) & 15u)) return QLLM_ERR_ALIGN;
         g.a_tiles8 = static_cast<const uint8_t *>(workspace);
         g.w_tiles8 = w->tiles8;
+        g.a_laid = a_laid;
         // K split over workgroups where few tiles would leave most CUs idle, if the workspace also holds the parts
         const int32_t s8 = t8_splits(N, w->K, w->O);
         const int64_t at = (qllm_tiles8_bytes(N, w->K) + 255) / 256 * 256;
@@ -1987,6 +2000,15 @@ extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, 
     if (a_bits == 6) return launch<6, 6>(g, y_dtype, stream);
     if (wb == 8) return launch<8, 8>(g, y_dtype, stream);
     return launch<8, 4>(g, y_dtype, stream);
+}
+
+} // namespace
+
+extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y,
+                                 int32_t y_dtype, int64_t ldy, int32_t *acc_dump, void *workspace,
+                                 int64_t workspace_bytes, void *hip_stream)
+{
+    return int_gemm(a, a_bits, N, w, y, y_dtype, ldy, acc_dump, workspace, workspace_bytes, false, hip_stream);
 }
 
 extern "C" int64_t qllm_tiles6_bytes(int64_t rows, int64_t K)
@@ -2075,10 +2097,15 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     p += up(N * 4);
     q.rowsum = reinterpret_cast<int32_t *>(p);
     p += up(N * 4);
-    int32_t rc = qllm_norm_reassemble_quant(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, hip_stream);
+    const int64_t left = workspace_bytes - (p - static_cast<uint8_t *>(workspace));
+    // Where the GEMM is going to read its activations as bytes in matrix-core order, the fused kernel writes them so:
+    // one launch and a pass over the codes less.
+    const bool tiles8 = N <= INT32_MAX && w->O > 0 && w->O <= INT32_MAX && has_room_for_tiles8(N, w, a_bits, p, left) &&
+                        !plan_stream(N, w->K, w->O, a_bits, w->bits, true).take;
+    bool laid = false;
+    const int32_t rc = qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, tiles8 ? p : nullptr, &laid, hip_stream);
     if (rc != QLLM_OK) return rc;
-    return qllm_int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, workspace_bytes - (p - static_cast<uint8_t *>(workspace)),
-                         hip_stream);
+    return int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, left, laid, hip_stream);
 }
 
 // ---- the layer for callers that cannot allocate: its workspace is a device array of this library

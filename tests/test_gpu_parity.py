@@ -509,6 +509,40 @@ def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, y_dtype, N, K, O):
     check_y(oracle, y, oracle.epilogue(ref_acc.astype(np.int32), K, ax, bx, rs, aw, bw, cs), y_dtype)
 
 
+@pytest.mark.parametrize("a_bits,w_bits", [(6, 6), (8, 8), (8, 4)])
+@pytest.mark.parametrize("N,C,K,norm,x_dtype", [(700, 8200, 8197, "rms", "bf16"), (513, 8192, 8192, "layer", "f32"), (2050, 8200, 8250, "none", "bf16"),
+                                                (257, 28672, 28600, "rms", "bf16"), (600, 8203, 8200, "rms", "bf16")])
+def test_layer_writes_matrix_core_order(b, a_bits, w_bits, N, C, K, norm, x_dtype):
+    """Where the layer's GEMM reads bytes in matrix-core order the fused kernel writes its codes that way: the same bits as
+    the two calls with packed rows in between, at every K mod 64 and N mod 16 that leaves a remainder, for rows that
+    fill whole sweeps of the grid and rows that do not, with lists in LDS and streamed, and for rows that only the
+    plain kernel takes (8203 channels: packed rows and the re-laying pass as before).  The workspace is poisoned."""
+    import torch
+    rng = np.random.default_rng(N + C + K + a_bits + w_bits)
+    row_ptr, src, scale = random_csr_map(rng, C, K, 50)
+    plan = b.qllm_plan_map_host(row_ptr, src, scale, C)[0]
+    dm = b.DeviceMap(row_ptr, src, scale, C, plan)
+    O = 300
+    x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda()
+    x = x if x_dtype == "f32" else x.bfloat16()
+    gamma, beta = torch.rand(C, device="cuda") + 0.5, (torch.rand(C, device="cuda") if norm == "layer" else None)
+    w = rng.integers(0, 2 ** w_bits, (O, K), dtype=np.uint8)
+    dw = b.DeviceWeight(b.qllm_pack_codes_host(w, w_bits), rng.uniform(0.001, 0.05, O).astype(np.float32), rng.integers(0, 2 ** w_bits, O),
+                        w.astype(np.int64).sum(1), K, w_bits, tiles8=True)
+    qa = b.DeviceQAct(N, K, a_bits)
+    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, qa)
+    want = torch.empty((N, O), device="cuda")
+    ws = torch.full((b.qllm_gemm_workspace_bytes(N, K, O, a_bits),), 0xCD, dtype=torch.uint8, device="cuda")
+    b.qllm_int_gemm(qa, dw, want, None, ws)
+    y = torch.full((N, O), float("nan"), device="cuda")
+    ws = torch.full((b.qllm_workspace_bytes(N, K, O, a_bits),), 0xCD, dtype=torch.uint8, device="cuda")
+    b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, dw, y, ws)
+    assert torch.equal(y, want)
+    floor = torch.full((b.qllm_workspace_floor_bytes(N, K, O, a_bits),), 0xCD, dtype=torch.uint8, device="cuda")
+    b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, dw, y.fill_(float("nan")), floor)
+    assert torch.equal(y, want)
+
+
 def test_gemm_extreme_codes(oracle, b):
     """All codes at their maximum: the largest accumulators the shapes allow."""
     for bits, K in [(4, 28672), (6, 8192), (8, 28672)]:
