@@ -1326,26 +1326,51 @@ __global__ __launch_bounds__(256) void tiles8_kernel(const uint8_t *codes, int64
     *reinterpret_cast<uint4 *>(tiles + bk * T8_BLOCK + 16 * l) = make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// Sum of the parts of a split K and the dequantising epilogue, one output per lane; the bracket in 64-bit
-// arithmetic, which gives the same float as the narrow form.  SA / SW: that side's codes are 8-bit and went into
-// the matrix cores as code - 128 in every one of the K places (the byte-operand path), which is added back here.
-template <typename YT, int SA = 0, int SW = 0>
+// Sum of the parts of a split K and the dequantising epilogue, four neighbouring outputs of a token per lane (one where
+// O is no multiple of four: V = 1); the bracket in 64-bit arithmetic, which gives the same float as the narrow form.
+// SA / SW: that side's codes are 8-bit and went into the matrix cores as code - 128 in every one of the K places (the
+// byte-operand path), which is added back here.  Bound by the parts it reads: 16-byte loads where one output per lane had
+// 4-byte ones (three parts of 200 x 5120: 5.4 -> 4.8 us).
+constexpr int MAX_SPLITS = 4; // t8_splits, k_splits
+template <typename YT, int SA, int SW, int V>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const GemmArgs g)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)g.N * g.O) return;
-    const int n = (int)(idx / g.O), o = (int)(idx % g.O);
-    int32_t raw = 0; // the true accumulator fits int32 (checked by the launcher), so wrapping sums are exact
-    for (int z = 0; z < g.splits; ++z) raw += g.partial[(int64_t)z * g.N * g.O + idx];
-    raw += 128 * SW * g.rs[n] + 128 * SA * g.cs[o] - 16384 * SA * SW * g.K;
-    const int64_t bx = g.bx[n], bw = g.bw[o];
-    const int64_t t = (int64_t)raw - bx * g.cs[o] - bw * g.rs[n] + (int64_t)g.K * bx * bw;
-    float v = (float)t;
-    v = v * g.ax[n];
-    v = v * g.aw[o];
-    if constexpr (sizeof(YT) == 4) reinterpret_cast<float *>(g.y)[(int64_t)n * g.ldy + o] = v;
-    else reinterpret_cast<uint16_t *>(g.y)[(int64_t)n * g.ldy + o] = f32_to_bf16_rne(v);
-    if (g.acc_dump) g.acc_dump[idx] = raw;
+    typedef int vi __attribute__((ext_vector_type(V)));
+    const int n = blockIdx.y, o = (int)(blockIdx.x * 256 + threadIdx.x) * V;
+    if (o >= g.O) return;
+    const int64_t idx = (int64_t)n * g.O + o;
+    vi part[MAX_SPLITS]; // all asked for at once; past the last part the last one again
+#pragma unroll
+    for (int z = 0; z < MAX_SPLITS; ++z) part[z] = *reinterpret_cast<const vi *>(g.partial + (int64_t)min(z, g.splits - 1) * g.N * g.O + idx);
+    vi raw = part[0]; // the true accumulator fits int32 (checked by the launcher), so wrapping sums are exact
+#pragma unroll
+    for (int z = 1; z < MAX_SPLITS; ++z) raw += z < g.splits ? part[z] : vi(0);
+    const int32_t rs = g.rs[n];
+    const int64_t bx = g.bx[n];
+    const float ax = g.ax[n];
+    float out[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        const int32_t cs = g.cs[o + e];
+        const int64_t bw = g.bw[o + e];
+        raw[e] += 128 * SW * rs + 128 * SA * cs - 16384 * SA * SW * g.K;
+        const int64_t t = (int64_t)raw[e] - bx * cs - bw * rs + (int64_t)g.K * bx * bw;
+        out[e] = ((float)t * ax) * g.aw[o + e];
+    }
+    const int64_t at = (int64_t)n * g.ldy + o;
+    if constexpr (V == 1) {
+        if constexpr (sizeof(YT) == 4) reinterpret_cast<float *>(g.y)[at] = out[0];
+        else reinterpret_cast<uint16_t *>(g.y)[at] = f32_to_bf16_rne(out[0]);
+    } else if constexpr (sizeof(YT) == 4) {
+        *reinterpret_cast<v4f_any *>(reinterpret_cast<float *>(g.y) + at) = v4f{out[0], out[1], out[2], out[3]};
+    } else {
+        typedef unsigned int v2u_any __attribute__((ext_vector_type(2), aligned(2)));
+        *reinterpret_cast<v2u_any *>(reinterpret_cast<uint16_t *>(g.y) + at) = v2u_any{f32x2_to_bf16x2_rne(out[0], out[1]), f32x2_to_bf16x2_rne(out[2], out[3])};
+    }
+    if (g.acc_dump) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) g.acc_dump[idx + e] = raw[e];
+    }
 }
 
 // ---- few tokens (decode, small batches): the weights are read once from HBM and that is the whole cost.  A
@@ -1580,6 +1605,19 @@ int32_t launch_kernel(K kernel, dim3 grid, dim3 block, size_t lds, const GemmArg
     return QLLM_OK;
 }
 
+template <int SA, int SW>
+int32_t launch_finish(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+{
+    if ((g.O & 3) == 0 && (reinterpret_cast<uintptr_t>(g.partial) & 15u) == 0) {
+        const dim3 grid((unsigned)((g.O / 4 + 255) / 256), (unsigned)g.N);
+        if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float, SA, SW, 4>, grid, dim3(256), 0, g, stream);
+        return launch_kernel(splitk_finish_kernel<uint16_t, SA, SW, 4>, grid, dim3(256), 0, g, stream);
+    }
+    const dim3 grid((unsigned)((g.O + 255) / 256), (unsigned)g.N); // at most 128 tiles of 128 x 128: N <= 16384
+    if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float, SA, SW, 1>, grid, dim3(256), 0, g, stream);
+    return launch_kernel(splitk_finish_kernel<uint16_t, SA, SW, 1>, grid, dim3(256), 0, g, stream);
+}
+
 // How a product with 256 x 256 or 128 x 128 tiles is laid over the chip.  A round of 256 large tiles (one per CU)
 // takes one unit of time, a round of 512 small ones (two per CU; half the outputs at about three quarters of the
 // rate) 0.65.  Large tiles throughout, small tiles throughout, or -- when the large tiles fill whole rounds and
@@ -1634,9 +1672,7 @@ int32_t launch_fp6(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
         if (ga.splits > 1) {
             const int32_t sp = launch_kernel(gemm_w4a4_fp6_kernel<float, 4, 2, true>, grid, dim3(LTHREADS), lds, ga, stream);
             if (sp != QLLM_OK) return sp;
-            const dim3 fgrid((unsigned)(((int64_t)ga.N * ga.O + 255) / 256));
-            if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float>, fgrid, dim3(256), 0, ga, stream);
-            return launch_kernel(splitk_finish_kernel<uint16_t>, fgrid, dim3(256), 0, ga, stream);
+            return launch_finish<0, 0>(ga, y_dtype, stream);
         }
         if (y_dtype == QLLM_F32) return launch_kernel(gemm_w4a4_fp6_kernel<float, 4, 2>, grid, dim3(LTHREADS), lds, ga, stream);
         return launch_kernel(gemm_w4a4_fp6_kernel<uint16_t, 4, 2>, grid, dim3(LTHREADS), lds, ga, stream);
@@ -1688,7 +1724,7 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
     const int64_t tiles = ((O + 127) / 128) * ((N + 127) / 128), n_kt = (K + T8_KT - 1) / T8_KT;
     if (tiles > 128) return 1;
     int64_t s = 256 / tiles;
-    if (s > 4) s = 4;
+    if (s > MAX_SPLITS) s = MAX_SPLITS;
     if (s > n_kt / 8) s = n_kt / 8;
     return s < 2 ? 1 : (int32_t)s;
 }
@@ -1710,9 +1746,7 @@ int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
             const int32_t sp = launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, 4, true>, grid, dim3(LTHREADS), lds4, ga, stream);
             if (sp != QLLM_OK) return sp;
             constexpr int SA = ABITS == 8 ? 1 : 0, SW = WBITS == 8 ? 1 : 0;
-            const dim3 fgrid((unsigned)(((int64_t)ga.N * ga.O + 255) / 256));
-            if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float, SA, SW>, fgrid, dim3(256), 0, ga, stream);
-            return launch_kernel(splitk_finish_kernel<uint16_t, SA, SW>, fgrid, dim3(256), 0, ga, stream);
+            return launch_finish<SA, SW>(ga, y_dtype, stream);
         }
         if ((int64_t)grid.x * grid.y <= 256) {
             if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 4, 2, 4>, grid, dim3(LTHREADS), lds4, ga, stream);
@@ -1761,7 +1795,8 @@ int32_t launch_skinny(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 //          (33k), 512 28 : 28 (66k); 8192 -> 4096, 8 / 8, 128 25 : 22 (66k); 1024 -> 4096, 512 10 : 26 (16k); 28000 up to 128
 //          workgroups: 4096 -> 1024, 6 / 6, 128 11 : 14 (16k), 96 14 : 14 (25k), 16384 -> 1024, 128 38 : 27 (66k)
 // More than two workgroups per CU take it only where it is cheap: 4096 -> 12288, 160 tokens 4 / 4 24 : 17 (74k, 768 groups),
-// 1024 -> 4096, 512 tokens 6 / 6 15 : 26 (18k, 768 groups).  Where the weight came without its re-laid copy the tiled
+// 1024 -> 4096, 512 tokens 6 / 6 15 : 26 (18k, 768 groups); weights wide enough to fill the chip with tiles never do beyond
+// 64 tokens (2048 -> 20480, 96 tokens 4 / 4 15.6 : 12.5, 31k).  Where the weight came without its re-laid copy the tiled
 // kernels expand packed codes and take 54-130 us up to 128 tokens: there the line is 100000.
 struct StreamPlan {
     bool take;
@@ -1777,7 +1812,7 @@ StreamPlan plan_stream(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, 
     const int nt = each <= 4 ? 4 : each <= 6 ? 6 : 8;
     const int64_t groups = og * blocks, cost = K * nt * (groups > 256 ? groups : 256) / 256;
     const int64_t line = w_bits != 4 ? (groups <= 128 ? 28000 : 36000) : a_bits == 4 ? 68000 : groups <= 128 ? 48000 : 70000;
-    bool take = (a_bits == 4 && N <= 64) || (cost <= line && (groups <= 512 || nt == 4 || cost <= 33000));
+    bool take = (a_bits == 4 && N <= 64) || (cost <= line && (N <= 64 || og <= 400) && (groups <= 512 || nt == 4 || cost <= 33000));
     if (!relaid && w_bits + a_bits != 8) take = take || cost <= 100000;
     return StreamPlan{take && blocks <= 65535, nt, groups};
 }
@@ -1837,9 +1872,7 @@ int32_t launch(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
             if (g.splits > 1) {
                 const int32_t st = launch_kernel(int_gemm_w4a4_kernel<float, 4, 2, true>, grid, dim3(LTHREADS), lds, g, stream);
                 if (st != QLLM_OK) return st;
-                const dim3 fgrid((unsigned)(((int64_t)g.N * g.O + 255) / 256));
-                if (y_dtype == QLLM_F32) return launch_kernel(splitk_finish_kernel<float>, fgrid, dim3(256), 0, g, stream);
-                return launch_kernel(splitk_finish_kernel<uint16_t>, fgrid, dim3(256), 0, g, stream);
+                return launch_finish<0, 0>(g, y_dtype, stream);
             }
             if (y_dtype == QLLM_F32)
                 return launch_kernel(int_gemm_w4a4_kernel<float, 4, 2>, grid, dim3(LTHREADS), lds, g, stream);
@@ -1894,7 +1927,7 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
     const int64_t n_kt = (K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD / PKT;
     if (tiles > 128) return 1;
     int64_t s = 256 / tiles;
-    if (s > 4) s = 4;
+    if (s > MAX_SPLITS) s = MAX_SPLITS;
     if (s > n_kt / 8) s = n_kt / 8;
     return s < 2 ? 1 : (int32_t)s;
 }
