@@ -370,7 +370,7 @@ int32_t qllm_build_pruned_map_host(const float *chan_absmax, int64_t C, float th
  *            channel; bits 8..31: p if some computed or long channel reads a channel of this chunk (the
  *            kernel then stages the chunk's x at floats 8p .. 8p+7 of its on-chip table; p = 0 ..
  *            n_pub-1 in chunk order), 0xffffff otherwise.  Float 8*n_pub of that table is a zero.  A map whose
- *            lists could not be held on chip at every setting of the kernel has all chunks staged instead
+ *            lists cannot be held on chip even with 4-bit codes and no shift has all chunks staged instead
  *            (n_pub == n_chunks, p == chunk): a staged position is then the channel number
  *   spec     [n_spec][2]: a computed channel: {s0 | s1 << 16, scale}, s = staged position of the source
  *            channel (s1 = 8*n_pub, the zero, for one entry)

@@ -484,8 +484,8 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // STREAM: for maps whose lists do not fit in LDS next to the row (a 28 672-channel row with a few thousand
 // computed channels).  The lists of the irregular part stay in global memory (every workgroup reads the same
 // few hundred KB: they live in L2), every chunk of the row is staged, in the input's own type, at its own
-// position (the plan then has n_pub == n_chunks, so a staged position IS the channel number), and gamma /
-// beta of a source are read from global memory by that number.
+// position, and gamma / beta of a source are read from global memory by its channel number: a staged position IS
+// that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk.
 template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
@@ -518,6 +518,9 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     // chunks from pk (a plain group; else that of the zero chunk before pk), BITS * position in that chunk (6 bits) |
     // group or composite number << 8 | kind << 30}
     int2 *work = reinterpret_cast<int2 *>(chunkw + ((ITERS * blockDim.x + ((chunkw - reinterpret_cast<uint32_t *>(lds)) & 1)) )); // 8-byte aligned
+    // STREAM, and not every chunk has a staging number: [n_pub + 1] the chunk of a number, then one past the row
+    uint16_t *pubc = reinterpret_cast<uint16_t *>(work + ITERS * blockDim.x);
+    const bool by_table = STREAM && a.n_pub != a.n_chunks;
     const int4 *longs = longs_w;
     const uint4 *rec = rec_w;
     const int2 *spec = spec_w;
@@ -608,6 +611,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     };
     for (int j = tid; j < a.n_comp * W; j += nt) ins[j] = 0u;
     if constexpr (STREAM) {
+        if (by_table && tid == 0) pubc[a.n_pub] = (uint16_t)n_chunks;
         if (tid < GROUP) pubx[a.C + tid] = (XT)0; // the zero (bf16 bits or a float); gamma and beta of it read as 0
     } else if (tid < 4) { // the zero: x = 0, gamma = 0, beta = 0, so that its y is a zero whatever the row's statistics
         pub[GROUP * a.n_pub + tid] = 0.0f;
@@ -633,6 +637,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     for (int it = 0; it < ITERS; ++it) {
         const int sl = tid + it * nt;
         chunkw[sl] = cw0[it];
+        if (by_table && cw0[it] >> 8 != NOT_PUBLISHED) pubc[cw0[it] >> 8] = (uint16_t)sl;
         {
             const uint32_t e = (uint32_t)we0[it], kind = e >> 30;
             const int d = kind == KIND_PLAIN ? (int)(e & 0x1ffffu) : -GROUP; // non-plain: the zero chunk, not shifted
@@ -929,6 +934,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         auto staged_fetch = [&](uint32_t pos) -> Staged {
             Staged v;
             if constexpr (STREAM) {
+                if (by_table) pos = (uint32_t)pubc[pos >> 3] * GROUP + (pos & 7u); // now the channel's number
                 const bool real = pos < (uint32_t)a.C; // else the zero
                 v.x = widen_one(pubx[pos]);
                 v.g = NORM != QLLM_NORM_NONE ? (real ? a.gamma[pos] : 0.0f) : 1.0f;
@@ -1352,7 +1358,7 @@ int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds,
 }
 
 // Which form of the kernel a map gets, with its launch shape and LDS size: the lists of the irregular part in
-// LDS when they fit there next to the row's packed codes; else, if the plan stages every chunk, the lists
+// LDS when they fit there next to the row's packed codes; else the lists
 // streamed from global memory; else none (the caller then runs the kernel that walks the CSR map).
 struct Choice {
     int kind; // QLLM_FUSED_WALKS_MAP / QLLM_FUSED_LISTS_IN_LDS / QLLM_FUSED_LISTS_STREAMED
@@ -1375,7 +1381,6 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
         const int64_t lds = qllm_detail::fused_lists_lds_bytes(p, w, stage_sets, (int64_t)sh.iters * sh.nt);
         if (lds <= MAX_LDS) return Choice{QLLM_FUSED_LISTS_IN_LDS, sh, (size_t)lds};
     }
-    if (a.n_pub != a.n_chunks) return c; // staged positions are not channel numbers
     const Shape sh{4, ((units + 3) / 4 + 63) / 64 * 64};
     const int64_t lds = qllm_detail::fused_streamed_lds_bytes(p, w, a.C, x_dtype == QLLM_BF16 ? 2 : 4, (int64_t)sh.iters * sh.nt);
     if (lds <= MAX_LDS) return Choice{QLLM_FUSED_LISTS_STREAMED, sh, (size_t)lds};

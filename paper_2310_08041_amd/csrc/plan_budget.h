@@ -25,11 +25,13 @@ inline int64_t fused_lists_lds_bytes(const PlanCounts &p, int64_t words_per_chun
            (p.n_comp * w + w + (p.n_chunks + 1) * w) * 4 + (p.n_dest + p.n_segw + 3 * slots + 1) * 4; // + 1: the two-word slots start at an even word
 }
 
-// The same with the lists left in global memory and the whole row staged in the input's own type.
+// The same with the lists left in global memory and the whole row staged in the input's own type; where only some
+// chunks have a staging number, a table says which (two bytes each and one for the zero).
 inline int64_t fused_streamed_lds_bytes(const PlanCounts &p, int64_t words_per_chunk, int64_t C, int64_t elem_bytes, int64_t slots)
 {
     const int64_t w = words_per_chunk, n_dest4 = (p.n_dest + 3) / 4 * 4;
-    return ((C + 8) * elem_bytes + 15) / 16 * 16 + n_dest4 * 4 + (p.n_comp * w + w + (p.n_chunks + 1) * w) * 4 + (3 * slots + 1) * 4;
+    return ((C + 8) * elem_bytes + 15) / 16 * 16 + n_dest4 * 4 + (p.n_comp * w + w + (p.n_chunks + 1) * w) * 4 + (3 * slots + 1) * 4 +
+           (p.n_pub == p.n_chunks ? 0 : (p.n_pub + 2) / 2 * 4);
 }
 
 } // namespace qllm_detail

@@ -543,6 +543,34 @@ def test_layer_writes_matrix_core_order(b, a_bits, w_bits, N, C, K, norm, x_dtyp
     assert torch.equal(y, want)
 
 
+@pytest.mark.parametrize("bits,norm,dtype,choice", [(4, "rms", "bf16", 1), (6, "none", "bf16", 1), (4, "layer", "bf16", 2), (8, "layer", "bf16", 2),
+                                                    (6, "rms", "bf16", 2), (8, "rms", "f32", 0)])
+def test_fused_lists_that_fit_for_some_settings(b, bits, norm, dtype, choice):
+    """A map whose lists fit on chip for some code widths and norms and not for others: its plan numbers only the chunks
+    that hold sources, and the streamed form translates the numbers through its table.  Bit for bit the kernel that
+    walks the CSR map, rows of more than 64 entries and unused inputs included; the forms are the ones expected."""
+    import torch
+    C, N = 28672, 300
+    rng = np.random.default_rng(5)
+    row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
+    at = row_ptr[1001]                                              # channel 1000 gets 69 entries more
+    src, scale = np.insert(src, at, rng.integers(0, C, 69)).astype(np.int32), np.insert(scale, at, np.full(69, 0.01)).astype(np.float32)
+    row_ptr[1001:] += 69
+    plan = b.qllm_plan_map_host(row_ptr, src, scale, C)[0]
+    assert plan[8] < plan[6] and plan[14] > 0                       # some chunks staged, some rows longer than 64 entries
+    planned, walked = b.DeviceMap(row_ptr, src, scale, C, plan), b.DeviceMap(row_ptr, src, scale, C)
+    x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda()
+    x = x if dtype == "f32" else x.bfloat16()
+    gamma, beta = torch.rand(C, device="cuda") + 0.5, (torch.rand(C, device="cuda") if norm == "layer" else None)
+    assert b.qllm_fused_kernel_choice(planned, x.dtype, N, C, NORM_ID[norm], beta is not None, bits) == choice
+    got, want = b.DeviceQAct(N, C, bits), b.DeviceQAct(N, C, bits)
+    got.codes.fill_(0xAB)
+    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, planned, bits, got)
+    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, walked, bits, want)
+    for k in ("codes", "scale", "zero", "rowsum"):
+        assert torch.equal(getattr(got, k), getattr(want, k)), k
+
+
 def test_gemm_extreme_codes(oracle, b):
     """All codes at their maximum: the largest accumulators the shapes allow."""
     for bits, K in [(4, 28672), (6, 8192), (8, 28672)]:
