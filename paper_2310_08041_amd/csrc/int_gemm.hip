@@ -1331,7 +1331,7 @@ __global__ __launch_bounds__(256) void tiles8_kernel(const uint8_t *codes, int64
 // SA / SW: that side's codes are 8-bit and went into the matrix cores as code - 128 in every one of the K places (the
 // byte-operand path), which is added back here.  Bound by the parts it reads: 16-byte loads where one output per lane had
 // 4-byte ones (three parts of 200 x 5120: 5.4 -> 4.8 us).
-constexpr int MAX_SPLITS = 4; // t8_splits, k_splits
+constexpr int MAX_SPLITS = 8; // t8_splits; k_splits stays at four, its parts are part of the workspace's floor
 template <typename YT, int SA, int SW, int V>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const GemmArgs g)
 {
@@ -1339,12 +1339,14 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const GemmArgs g)
     const int n = blockIdx.y, o = (int)(blockIdx.x * 256 + threadIdx.x) * V;
     if (o >= g.O) return;
     const int64_t idx = (int64_t)n * g.O + o;
-    vi part[MAX_SPLITS]; // all asked for at once; past the last part the last one again
+    vi raw = vi(0); // the true accumulator fits int32 (checked by the launcher), so wrapping sums are exact
+    for (int z0 = 0; z0 < g.splits; z0 += 4) { // four parts asked for at once; past the last part the last one again
+        vi part[4];
 #pragma unroll
-    for (int z = 0; z < MAX_SPLITS; ++z) part[z] = *reinterpret_cast<const vi *>(g.partial + (int64_t)min(z, g.splits - 1) * g.N * g.O + idx);
-    vi raw = part[0]; // the true accumulator fits int32 (checked by the launcher), so wrapping sums are exact
+        for (int z = 0; z < 4; ++z) part[z] = *reinterpret_cast<const vi *>(g.partial + (int64_t)min(z0 + z, g.splits - 1) * g.N * g.O + idx);
 #pragma unroll
-    for (int z = 1; z < MAX_SPLITS; ++z) raw += z < g.splits ? part[z] : vi(0);
+        for (int z = 0; z < 4; ++z) raw += z0 + z < g.splits ? part[z] : vi(0);
+    }
     const int32_t rs = g.rs[n];
     const int64_t bx = g.bx[n];
     const float ax = g.ax[n];
@@ -1717,7 +1719,9 @@ int32_t launch_tiles8(const uint8_t *codes, int32_t bits, int64_t rows, int64_t 
 bool t8_small_tile(int64_t N, int64_t O) { return plan_tiles(N, O, false).small; }
 
 // Into how many parts the byte-operand path splits K when it has room for the parts' accumulators: as on the
-// 4-bit path, only where 128 x 128 tiles leave most CUs without a workgroup, every part at least eight K-tiles.
+// 4-bit path, only where 128 x 128 tiles leave most CUs without a workgroup, every part at least eight K-tiles; up to
+// eight parts (16384 -> 1024, 128 tokens: 26.7 us with four, 21 with eight; 28672 -> 2048: 37.6, 29), one workgroup per CU
+// (two: 8192 x 8192, 200 tokens 34 -> 40).
 int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 {
     if (N <= 32 || !t8_small_tile(N, O)) return 1;
@@ -1927,7 +1931,7 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
     const int64_t n_kt = (K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD / PKT;
     if (tiles > 128) return 1;
     int64_t s = 256 / tiles;
-    if (s > MAX_SPLITS) s = MAX_SPLITS;
+    if (s > 4) s = 4;
     if (s > n_kt / 8) s = n_kt / 8;
     return s < 2 ? 1 : (int32_t)s;
 }
@@ -2018,8 +2022,9 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
         // K split over workgroups where few tiles would leave most CUs idle, if the workspace also holds the parts
         const int32_t s8 = t8_splits(N, w->K, w->O);
         const int64_t at = (qllm_tiles8_bytes(N, w->K) + 255) / 256 * 256;
-        if (s8 > 1 && workspace_bytes >= at + (int64_t)s8 * N * w->O * (int64_t)sizeof(int32_t)) {
-            g.splits = s8;
+        const int64_t room = (workspace_bytes - at) / (N * w->O * (int64_t)sizeof(int32_t)); // parts that fit
+        if (s8 > 1 && room > 1) {
+            g.splits = room < s8 ? (int32_t)room : s8;
             g.partial = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + at);
         }
     }

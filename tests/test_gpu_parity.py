@@ -571,6 +571,30 @@ def test_fused_lists_that_fit_for_some_settings(b, bits, norm, dtype, choice):
         assert torch.equal(getattr(got, k), getattr(want, k)), k
 
 
+@pytest.mark.parametrize("a_bits,w_bits", [(6, 6), (8, 8), (8, 4)])
+@pytest.mark.parametrize("parts", [0, 1, 3, 8])
+def test_gemm_split_takes_the_parts_that_fit(b, a_bits, w_bits, parts):
+    """K dealt out to as many workgroups per tile as the workspace holds accumulators for (eight are wanted here): the same
+    bits with room for none, one, three and all of them, for a width that is a multiple of four and one that is not."""
+    import torch
+    for O in (300, 301):
+        N, K = 100, 16300
+        rng = np.random.default_rng(O + parts)
+        a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
+        qa = b.DeviceQAct(N, K, a_bits)
+        qa.codes.copy_(torch.from_numpy(b.qllm_pack_codes_host(a, a_bits)))
+        qa.scale.copy_(torch.from_numpy(ax)), qa.zero.copy_(torch.from_numpy(bx))
+        qa.rowsum.copy_(torch.from_numpy(a.astype(np.int64).sum(1).astype(np.int32)))
+        dw = b.DeviceWeight(b.qllm_pack_codes_host(w, w_bits), aw, bw, w.astype(np.int64).sum(1).astype(np.int32), K, w_bits, tiles8=True)
+        tiles = (b.qllm_tiles8_bytes(N, K) + 255) // 256 * 256
+        assert b.qllm_gemm_workspace_bytes(N, K, O, a_bits) == tiles + 8 * N * O * 4
+        ws = torch.full((tiles + parts * N * O * 4,), 0xCD, dtype=torch.uint8, device="cuda")
+        y, acc = torch.empty((N, O), device="cuda"), torch.empty((N, O), dtype=torch.int32, device="cuda")
+        b.qllm_int_gemm(qa, dw, y, acc, ws)
+        exact = a.astype(np.float64) @ w.astype(np.float64).T               # integers below 2^53: exact
+        assert np.array_equal(acc.cpu().numpy(), exact.astype(np.int64))
+
+
 def test_gemm_extreme_codes(oracle, b):
     """All codes at their maximum: the largest accumulators the shapes allow."""
     for bits, K in [(4, 28672), (6, 8192), (8, 28672)]:
