@@ -148,7 +148,11 @@ int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, in
  *               are required (may be NULL when that is 0: it is non-zero only where the sum over K is
  *               split over workgroups), else QLLM_ERR_WORKSPACE.
  *
- * The FP6 path.  For 4-bit codes on both sides and N > 64 the same acc[n,o] is also available from the FP6
+ * Small batches.  Up to 32 tokens, up to 64 with 4-bit codes on both sides, and for as many as 512 where that is the
+ * cheaper way (small K and O: a rule on N, K, O and the widths), one kernel streams the packed codes of both operands;
+ * it needs none of the copies and none of the workspace below.  Same results.
+ *
+ * The FP6 path.  For 4-bit codes on both sides and more tokens the same acc[n,o] is also available from the FP6
  * matrix cores at close to twice the int8 rate: a code c, zero-extended to 6 bits, is the E2M3 number c/8, the
  * products a*w/64 and all their partial sums (multiples of 1/64 below 2^18, K <= 74564) are exact in fp32, and
  * 64 times the fp32 accumulator is the integer accumulator of Eq. (1), bit for bit.  It is taken when
@@ -157,7 +161,7 @@ int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, in
  * per cent of the GEMM's time); otherwise the int8 path runs.  Same results either way.
  *
  * Byte operands.  For the other bit pairs (6/6, 8/8, 8-bit activations on 4-bit weights; Sec. 5, "Quantization
- * settings") and N > 32 the int8 matrix cores can be fed straight from one-byte-per-code copies of both operands:
+ * settings") and larger batches the int8 matrix cores can be fed straight from one-byte-per-code copies of both operands:
  * taken when w->tiles8 is set and the workspace holds at least qllm_tiles8_bytes(N, w->K) bytes (the activations
  * are re-laid into it first); otherwise the packed codes are expanded inside the GEMM.  Same results either way.
  * With qllm_gemm_workspace_bytes(...) bytes this path also splits the sum over K over workgroups where a small
