@@ -485,7 +485,8 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // computed channels).  The lists of the irregular part stay in global memory (every workgroup reads the same
 // few hundred KB: they live in L2), every chunk of the row is staged, in the input's own type, at its own
 // position, and gamma / beta of a source are read from global memory by its channel number: a staged position IS
-// that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk.
+// that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk (the upper halves of chunkw, whose
+// staging numbers this form has no use for).
 template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
@@ -513,14 +514,16 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     uint32_t *pk = ins + a.n_comp * W + W;                             // [-1 .. n_chunks] * W packed codes, input order; both ends zero
     int32_t *dest_w = reinterpret_cast<int32_t *>(pk + (a.n_chunks + 1) * W); // [n_dest] composite group << 3 | position
     uint32_t *segs_w = reinterpret_cast<uint32_t *>(dest_w + a.n_dest); // [n_segw] segments of the composite groups
-    uint32_t *chunkw = STREAM ? pk + (a.n_chunks + 1) * W : segs_w + a.n_segw; // [ITERS * lanes] pass bits | staging slot << 8
+    uint32_t *chunkw = STREAM ? pk + (a.n_chunks + 1) * W : segs_w + a.n_segw; // [ITERS * lanes] pass bits | staging slot << 8; STREAM: see chunk_of
     // [ITERS * lanes] the lanes' output slots, ready to use: {byte offset of the first of the group's two packed
     // chunks from pk (a plain group; else that of the zero chunk before pk), BITS * position in that chunk (6 bits) |
     // group or composite number << 8 | kind << 30}
     int2 *work = reinterpret_cast<int2 *>(chunkw + ((ITERS * blockDim.x + ((chunkw - reinterpret_cast<uint32_t *>(lds)) & 1)) )); // 8-byte aligned
-    // STREAM, and not every chunk has a staging number: [n_pub + 1] the chunk of a number, then one past the row
-    uint16_t *pubc = reinterpret_cast<uint16_t *>(work + ITERS * blockDim.x);
+    // STREAM: the pass bits of chunk i in the low byte of chunkw[i], and where not every chunk has a staging number the
+    // chunk of number p, p = 0 .. n_pub, in the upper half of chunkw[p] (n_pub < n_chunks <= ITERS * lanes; one past the
+    // row for n_pub, the zero)
     const bool by_table = STREAM && a.n_pub != a.n_chunks;
+    auto chunk_of = [&](uint32_t number) -> uint16_t & { return reinterpret_cast<uint16_t *>(chunkw)[2 * number + 1]; };
     const int4 *longs = longs_w;
     const uint4 *rec = rec_w;
     const int2 *spec = spec_w;
@@ -611,7 +614,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     };
     for (int j = tid; j < a.n_comp * W; j += nt) ins[j] = 0u;
     if constexpr (STREAM) {
-        if (by_table && tid == 0) pubc[a.n_pub] = (uint16_t)n_chunks;
+        if (by_table && tid == 0) chunk_of(a.n_pub) = (uint16_t)n_chunks;
         if (tid < GROUP) pubx[a.C + tid] = (XT)0; // the zero (bf16 bits or a float); gamma and beta of it read as 0
     } else if (tid < 4) { // the zero: x = 0, gamma = 0, beta = 0, so that its y is a zero whatever the row's statistics
         pub[GROUP * a.n_pub + tid] = 0.0f;
@@ -636,8 +639,12 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
         const int sl = tid + it * nt;
-        chunkw[sl] = cw0[it];
-        if (by_table && cw0[it] >> 8 != NOT_PUBLISHED) pubc[cw0[it] >> 8] = (uint16_t)sl;
+        if constexpr (STREAM) {
+            reinterpret_cast<uint8_t *>(chunkw + sl)[0] = (uint8_t)cw0[it];
+            if (by_table && cw0[it] >> 8 != NOT_PUBLISHED) chunk_of(cw0[it] >> 8) = (uint16_t)sl;
+        } else {
+            chunkw[sl] = cw0[it];
+        }
         {
             const uint32_t e = (uint32_t)we0[it], kind = e >> 30;
             const int d = kind == KIND_PLAIN ? (int)(e & 0x1ffffu) : -GROUP; // non-plain: the zero chunk, not shifted
@@ -934,7 +941,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         auto staged_fetch = [&](uint32_t pos) -> Staged {
             Staged v;
             if constexpr (STREAM) {
-                if (by_table) pos = (uint32_t)pubc[pos >> 3] * GROUP + (pos & 7u); // now the channel's number
+                if (by_table) pos = (uint32_t)chunk_of(pos >> 3) * GROUP + (pos & 7u); // now the channel's number
                 const bool real = pos < (uint32_t)a.C; // else the zero
                 v.x = widen_one(pubx[pos]);
                 v.g = NORM != QLLM_NORM_NONE ? (real ? a.gamma[pos] : 0.0f) : 1.0f;
@@ -1211,10 +1218,6 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     }
 }
 
-struct Shape {
-    int iters, nt; // chunks per lane, lanes
-};
-
 int cu_count()
 {
     static int cached = 0;
@@ -1227,39 +1230,6 @@ int cu_count()
     }
     cached = n;
     return n;
-}
-
-// Chunks (or output groups) per lane and the workgroup size for N rows of `units` of them.  A workgroup's
-// waves go to the CU's four SIMDs in turn, so the SIMD with the most of them, ceil(waves / 4), sets the pace:
-// the cost of a row is that count times (chunks per lane + the fixed work of a wave and row, about one
-// chunk's worth).  With fewer rows than CUs every workgroup has one row and the fewest chunks per lane win.
-// The irregular part of the plan (long-row entries, computed channels, composite groups) is dealt out over the
-// lanes, and every further pass over one of its lists is a chain of dependent LDS reads that nothing overlaps:
-// if some shape has enough lanes for the longest of the three lists (`irregular`), only such shapes are
-// considered; if none has, the one with the most lanes.  (Measured at the 5120- and 4096-channel shapes over maps
-// from 1 % to 25 % of the channels merged: the best of the shapes in nine cases of ten, and up to 1.8 times
-// faster than the shape the regular part alone would pick.)
-Shape pick_shape(int units, int64_t N, bool layer_norm, int irregular)
-{
-    Shape best{0, 0};
-    int best_cost = 0;
-    bool best_covers = false;
-    for (int iters = 1; iters <= (layer_norm ? 4 : 5); ++iters) { // LayerNorm at five chunks per lane spills
-        const int nt = ((units + iters - 1) / iters + 63) / 64 * 64;
-        if (nt > (iters == 5 ? 768 : 1024)) continue; // five chunks per lane need the registers of three waves per SIMD
-        const int waves = nt / 64;
-        const int cost = N <= cu_count() ? iters : (waves + 3) / 4 * (iters + 1);
-        const bool covers = nt >= irregular;
-        // a shape that covers beats one that does not; among equals the cheaper one; the first feasible shape has
-        // the most lanes and stays if nothing covers
-        const bool better = best.iters == 0 || (covers && !best_covers) || (covers == best_covers && covers && cost < best_cost);
-        if (better) {
-            best = {iters, nt};
-            best_cost = cost;
-            best_covers = covers;
-        }
-    }
-    return best;
 }
 
 // What the runtime is asked once per kernel, workgroup size and LDS size and then remembered (no runtime
@@ -1358,8 +1328,8 @@ int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds,
 }
 
 // Which form of the kernel a map gets, with its launch shape and LDS size: the lists of the irregular part in
-// LDS when they fit there next to the row's packed codes; else the lists
-// streamed from global memory; else none (the caller then runs the kernel that walks the CSR map).
+// LDS when they fit there next to the row's packed codes; else the lists streamed from global memory; else none (the
+// caller then runs the kernel that walks the CSR map).
 struct Choice {
     int kind; // QLLM_FUSED_WALKS_MAP / QLLM_FUSED_LISTS_IN_LDS / QLLM_FUSED_LISTS_STREAMED
     Shape sh;
@@ -1375,7 +1345,7 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
     const int64_t w = bits == 4 ? 1 : 2;
     {
         const int irregular = std::max(a.n_long, std::max(a.n_spec, a.n_comp));
-        const Shape sh = pick_shape(units, a.N, a.norm == QLLM_NORM_LAYER, irregular);
+        const Shape sh = pick_shape(units, a.N > cu_count(), a.norm == QLLM_NORM_LAYER, irregular);
         // staged x, and gamma / beta at the same positions when there is a norm / a shift
         const int64_t stage_sets = 1 + (a.norm != QLLM_NORM_NONE ? 1 : 0) + (a.norm == QLLM_NORM_LAYER && a.beta ? 1 : 0);
         const int64_t lds = qllm_detail::fused_lists_lds_bytes(p, w, stage_sets, (int64_t)sh.iters * sh.nt);

@@ -218,22 +218,21 @@ int32_t qllm_plan_map_host(const int32_t *row_ptr, const int32_t *src, const flo
     // even with 4-bit codes and a norm without a shift, all chunks are: a staged position then is the channel number,
     // and the kernel that leaves the lists in global memory fetches gamma and beta of a source by it.  In between
     // (lists that fit for some widths and norms only) that kernel translates staged positions through a table, which
-    // has to fit as well wherever it fitted without.  (The line at the most demanding setting instead, 8-bit codes and a
-    // shift: the 2048 x 28672 4-bit layer with 377 merged channels streams its lists, 67 us against 54.)
+    // takes no LDS of its own: every setting has the form it would have with all chunks staged, or the faster one.
+    // 2048 x 28672, a computed channel in every 62, all staged : this (us).  Lists held now: 4-bit RMS 60 : 48, 6-bit
+    // without a norm 74 : 49, 4-bit RMS of fp32 rows 430 : 66 (walked the map before).  By the table: 8-bit RMS 70.0 : 72.0,
+    // 6-bit RMS 82.8 : 84.1, 4-bit LayerNorm with a shift 115.1 : 116.6, 8-bit 130.4 : 132.5.
     int64_t n_pub = 0;
     for (int64_t c = 0; c < n_chunks; ++c) n_pub += pub_slot[(size_t)c] == 0;
     {
         const int64_t units = std::max(n_chunks, (C_out + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD / G);
         const qllm_detail::PlanCounts p{n_comp, n_long, n_pub, n_chunks, n_spec, n_spec + n_rows_long + n_xl, n_segw};
-        qllm_detail::PlanCounts all = p;
-        all.n_pub = n_chunks;
-        bool stage_all = qllm_detail::fused_lists_lds_bytes(p, 1, 2, units + 256) > qllm_detail::FUSED_MAX_LDS;
-        for (const int64_t words : {1, 2})
-            for (const int64_t elem : {2, 4})
-                stage_all = stage_all ||
-                            (qllm_detail::fused_streamed_lds_bytes(all, words, C_in, elem, units + 256) <= qllm_detail::FUSED_MAX_LDS &&
-                             qllm_detail::fused_streamed_lds_bytes(p, words, C_in, elem, units + 256) > qllm_detail::FUSED_MAX_LDS);
-        if (stage_all) std::fill(pub_slot.begin(), pub_slot.end(), 0);
+        bool held = false; // with the launch shape for few rows, or the one for many
+        for (const bool many : {false, true}) {
+            const qllm_detail::Shape sh = qllm_detail::pick_shape(units, many, false, std::max(n_long, std::max(n_spec, n_comp)));
+            held = held || qllm_detail::fused_lists_lds_bytes(p, 1, 2, (int64_t)sh.iters * sh.nt) <= qllm_detail::FUSED_MAX_LDS;
+        }
+        if (!held) std::fill(pub_slot.begin(), pub_slot.end(), 0);
     }
     n_pub = 0;
     for (int64_t c = 0; c < n_chunks; ++c)

@@ -386,6 +386,48 @@ def test_fused_kernel_choice_follows_what_fits_on_chip():
             b.qllm_fused_kernel_choice(m, **args)
 
 
+def expanded_map(rng, C, ratio):
+    """A map as calibration at an expansion ratio makes it: half a per cent of the channels split, as many pairs merged
+    as there are new sub-channels (the pairs drawn at random)."""
+    split, extra = rng.permutation(C)[:C // 200], round(ratio * C)
+    absmax = np.ones(C, np.float32)
+    absmax[split] += np.bincount(rng.integers(0, split.size, extra), minlength=split.size)
+    first = np.concatenate([[0], np.cumsum(absmax.astype(np.int64))])[:-1]
+    a, bb = (np.nonzero((absmax == 1) & (first % 2 == odd))[0] for odd in (0, 1))
+    src = first[a[np.sort(rng.permutation(a.size)[:extra])]]
+    r = b.qllm_build_map_host(absmax, 1.0, src // 2, first[bb[rng.integers(0, bb.size, extra)]] // 2, with_plan=False)
+    return r["row_ptr"], r["src"], r["scale"]
+
+
+@pytest.mark.parametrize("kind", [0.005, 0.01, 30, 42, 62])
+def test_numbering_few_chunks_takes_no_setting_to_a_slower_form(kind):
+    """A plan numbers the chunks that hold sources of computed channels, or all of them.  Over the widths where the LDS
+    limit falls: whichever the builder takes, no code width, norm, dtype or batch runs a slower form than with all chunks
+    numbered; and where 4-bit bfloat16 rows would hold their lists with few, none runs a slower form than with few."""
+    speed = {b.FUSED_LISTS_IN_LDS: 2, b.FUSED_LISTS_STREAMED: 1, b.FUSED_WALKS_MAP: 0}
+    settings = [(dt, N, norm, beta, bits) for dt in (b.BF16, b.F32) for N in (16, 2048) for bits in (4, 6, 8)
+                for norm, beta in ((b.NORM_NONE, False), (b.NORM_RMS, False), (b.NORM_LAYER, False), (b.NORM_LAYER, True))]
+    few = 0
+    for width in range(22528, 28673, 64):
+        rng = np.random.default_rng(width)
+        row_ptr, src, scale = expanded_map(rng, width, kind) if kind < 1 else random_csr_map(rng, width, width, kind)
+        plan = b.qllm_plan_map_host(row_ptr, src, scale, width)[0]
+        ends, copied = row_ptr[1:], (np.diff(row_ptr) == 1)
+        copied[copied] = scale[ends[copied] - 1] == 1.0
+        computed = np.repeat(~copied, np.diff(row_ptr))
+        numbered = {"builder": plan[8], "few": np.unique(src[computed] // 8).size, "all": plan[6]}
+        forms = {}
+        for name, n_pub in numbered.items():
+            plan[8] = n_pub                                     # the form depends on the header's counts alone
+            m = host_map(row_ptr, src, scale, width, plan)
+            forms[name] = [speed[b.qllm_fused_kernel_choice(m, dt, N, width, norm, beta, bits)] for dt, N, norm, beta, bits in settings]
+        assert all(x >= y for x, y in zip(forms["builder"], forms["all"])), width
+        if forms["few"][settings.index((b.BF16, 2048, b.NORM_RMS, False, 4))] == 2 and numbered["builder"] != numbered["few"]:
+            assert forms["builder"] == forms["few"], width
+        few += numbered["builder"] < numbered["all"]
+    assert (few > 0) == (kind not in (30, 42))                  # the widths reach both sides of the line
+
+
 @pytest.mark.parametrize("name,N,C,O", [("tiny", 64, 512, 96), ("llama7b_qkv", 48, 1000, 40),
                                         ("llama70b_down", 32, 2050, 24), ("llama70b_q_decode", 16, 777, 33)])
 def test_host_helpers_match_the_oracle(oracle, name, N, C, O):
