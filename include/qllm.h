@@ -148,9 +148,10 @@ int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, in
  *               are required (may be NULL when that is 0: it is non-zero only where the sum over K is
  *               split over workgroups), else QLLM_ERR_WORKSPACE.
  *
- * Small batches.  Up to 32 tokens, up to 64 with 4-bit codes on both sides, and for as many as 512 where that is the
- * cheaper way (small K and O: a rule on N, K, O and the widths), one kernel streams the packed codes of both operands;
- * it needs none of the copies and none of the workspace below.  Same results.
+ * Small batches.  Up to 32 tokens, up to 64 with 4-bit codes on both sides, and beyond where that is the cheaper way (few
+ * outputs, that is N * O up to about 2 million, and a short K: a rule on N, K, O and the widths), one kernel streams the
+ * packed codes of both operands; it reads none of the copies and writes none of the workspace below, whose floor has to
+ * be there all the same.  Same results.
  *
  * The FP6 path.  For 4-bit codes on both sides and more tokens the same acc[n,o] is also available from the FP6
  * matrix cores at close to twice the int8 rate: a code c, zero-extended to 6 bits, is the E2M3 number c/8, the
@@ -170,6 +171,21 @@ int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, in
 int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y,
                       int32_t y_dtype, int64_t ldy, int32_t *acc_dump, void *workspace,
                       int64_t workspace_bytes, void *hip_stream);
+
+/* Which of those kernels qllm_int_gemm runs for N tokens with this weight and workspace_bytes of workspace (no launch; of w
+ * only O, K, bits and whether tiles6 / tiles8 are NULL are read; no acc_dump).  in_layer != 0: inside qllm_reassembled_linear,
+ * workspace_bytes being what is left for the product there, with a map whose plan the fused kernel uses.
+ *   QLLM_GEMM_STREAMS   one kernel streams the packed codes of both operands ("Small batches")
+ *   QLLM_GEMM_FP6       the FP6 path                QLLM_GEMM_BYTES   byte operands
+ *   QLLM_GEMM_EXPANDS   the packed codes are expanded inside a tiled kernel
+ * *tile: 256 or 128 (tokens and features of a tile), 256 + 128 (a launch of each), 0 for QLLM_GEMM_STREAMS;
+ * *parts: parts of K (1: whole).  Returns the kernel (>= 0) or a QLLM_ERR_* (< 0). */
+#define QLLM_GEMM_STREAMS 0
+#define QLLM_GEMM_FP6 1
+#define QLLM_GEMM_BYTES 2
+#define QLLM_GEMM_EXPANDS 3
+int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
+                                int32_t *tile, int32_t *parts);
 
 /* ------------------------------------------------------------------------------------------
  * The whole layer a1..a6: qllm_norm_reassemble_quant into workspace, then qllm_int_gemm, on one

@@ -77,6 +77,7 @@ _sigs = {
     "qllm_pack_codes_host": (_i32, [_vp, _i64, _i64, _i32, _vp]),
     "qllm_unpack_codes_host": (_i32, [_vp, _i64, _i64, _i32, _vp]),
     "qllm_fused_kernel_choice": (_i32, [C.POINTER(_Map), _i32, _i64, _i64, _i32, _i32, _i32]),
+    "qllm_gemm_kernel_choice": (_i32, [C.POINTER(_Weight), _i32, _i64, _i64, _i32, C.POINTER(_i32), C.POINTER(_i32)]),
     "qllm_norm_channel_absmax": (_i32, [_vp, _i32, _i64, _i64, _i64, _i32, _vp, _vp, _f, _vp, _vp, _i64, _vp]),
     "qllm_match_workspace_bytes": (_i64, [_i64, _i64]),
     "qllm_match_nearest": (_i32, [_vp, _i64, _i64, _vp, _i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _vp, _vp, _i64, _vp]),
@@ -476,6 +477,18 @@ def qllm_fused_kernel_choice(dmap, x_dtype, N, ldx, norm, has_beta, bits):
     if rc < 0:
         raise QllmError(rc, "qllm_fused_kernel_choice")
     return rc
+
+
+GEMM_STREAMS, GEMM_FP6, GEMM_BYTES, GEMM_EXPANDS = 0, 1, 2, 3
+
+
+def qllm_gemm_kernel_choice(weight, a_bits, N, workspace_bytes, in_layer=False):
+    """(GEMM_*, tile, parts of K): what qllm_int_gemm, or the layer call, runs for N tokens with this weight and workspace."""
+    tile, parts = _i32(0), _i32(0)
+    rc = _lib.qllm_gemm_kernel_choice(C.byref(weight.c), int(a_bits), int(N), int(workspace_bytes), int(in_layer), C.byref(tile), C.byref(parts))
+    if rc < 0:
+        raise QllmError(rc, "qllm_gemm_kernel_choice")
+    return rc, tile.value, parts.value
 
 
 def qllm_int_gemm(a, weight, y, acc_dump=None, workspace=None, stream=None):

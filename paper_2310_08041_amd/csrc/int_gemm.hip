@@ -1662,12 +1662,11 @@ int32_t launch_tiles6(const uint8_t *codes, int64_t row_bytes, int64_t rows, int
 }
 
 // 4-bit codes on both sides, more than 32 tokens, on the FP6 matrix cores: the activations are re-laid
-// into g.a_tiles first; then the same choice between 256 x 256 and 128 x 128 tiles as on the int8 path.
-int32_t launch_fp6(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+// into g.a_tiles first.
+int32_t launch_fp6(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipStream_t stream)
 {
     const int32_t st = launch_tiles6(g.a_codes, g.a_row_bytes, g.N, g.Kpad, const_cast<uint8_t *>(g.a_tiles), stream);
     if (st != QLLM_OK) return st;
-    const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
         constexpr size_t lds = (size_t)T6_STAGES * 16 * T6_BLOCK + EPI_BYTES<128, 128>;
@@ -1736,13 +1735,12 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 // 6- or 8-bit activations, more than 32 tokens, byte operands straight into the int8 matrix cores: the
 // activations are re-laid into the workspace, then the product, laid over the chip as on the FP6 path.
 template <int ABITS, int WBITS>
-int32_t launch_t8(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+int32_t launch_t8(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipStream_t stream)
 {
     if (!g.a_laid) {
         const int32_t st = launch_tiles8(g.a_codes, ABITS, g.N, g.K, const_cast<uint8_t *>(g.a_tiles8), stream);
         if (st != QLLM_OK) return st;
     }
-    const TilePlan plan = plan_tiles(g.N, g.O, g.splits == 1 && !g.acc_dump);
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
         constexpr size_t lds3 = (size_t)3 * 16 * T8_BLOCK + EPI_BYTES<128, 128>, lds4 = (size_t)4 * 16 * T8_BLOCK + EPI_BYTES<128, 128>;
@@ -1787,37 +1785,52 @@ int32_t launch_skinny(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 }
 
 // Whether the weight-streaming kernel takes a product, and how.  Up to 32 tokens always, and 4-bit codes up to 64.
-// Beyond, every workgroup passes its token tiles' packed codes through LDS and the vector unit for 32 features only, so
-// its cost grows with K, the tiles per workgroup and, above one workgroup per CU, their number; what the tiled kernels
-// cost beside it are two or three launches (re-laying, product, finish) and weights of 6 or 8 bits per code.  The lines
-// are where the two meet (us, stream : tiled; "cost" = K nt max(1, groups / 256)):
-//   4 / 4  68000: 4096 x 4096, 128 / 512 tokens 10 : 19 / 17 : 26 (cost 33k / 66k); 8192 x 8192, 128 tokens 18 : 24 (66k), 160
-//          25 : 25 (98k), 256 30 : 28 (131k); 13824 -> 5120, 80 tokens 21 : 21 (83k); 5120 -> 27648, 80 40 : 33 (104k)
-//   8 / 4  70000: 8192 x 8192, 128 26 : 30 (66k), 160 35 : 34 (98k); 8192 -> 4096, 256 26 : 26 (66k); 5120 -> 27648, 64 33 : 38 (69k);
-//          48000 up to 128 workgroups (K split over workgroups in the tiled kernels): 4096 -> 1024, 96 10 : 14 (25k), 16384 33 : 26 (98k)
-//   6 / 6, 8 / 8  36000: 8192 -> 4096, 6 / 6, 128 22 : 22 (33k); 4096 x 4096, 160 16 : 22 (25k), 256 25 : 24 (37k); 8 / 8, 128 15 : 20
-//          (33k), 512 28 : 28 (66k); 8192 -> 4096, 8 / 8, 128 25 : 22 (66k); 1024 -> 4096, 512 10 : 26 (16k); 28000 up to 128
-//          workgroups: 4096 -> 1024, 6 / 6, 128 11 : 14 (16k), 96 14 : 14 (25k), 16384 -> 1024, 128 38 : 27 (66k)
-// More than two workgroups per CU take it only where it is cheap: 4096 -> 12288, 160 tokens 4 / 4 24 : 17 (74k, 768 groups),
-// 1024 -> 4096, 512 tokens 6 / 6 15 : 26 (18k, 768 groups); weights wide enough to fill the chip with tiles never do beyond
-// 64 tokens (2048 -> 20480, 96 tokens 4 / 4 15.6 : 12.5, 31k).  Where the weight came without its re-laid copy the tiled
-// kernels expand packed codes and take 54-130 us up to 128 tokens: there the line is 100000.
+// Beyond, every workgroup passes its token tiles' packed codes through LDS and the vector unit for 32 or 64 features
+// only, so its cost grows with K, the tiles per workgroup and their number in whole rounds of one per CU ("cost" = K nt
+// ceil(groups / 256)); what the tiled kernels cost beside it are up to three launches (re-laying, product, finish) and
+// weights of 6 or 8 bits per code.  So it takes products of few workgroups, one or two per CU, whatever the tokens and
+// features are that make them, below a line of cost.  Both sides were timed on 14000 products (33-8192 tokens, K 256-16384,
+// 128-27648 features; weights in cache and not): tiled / stream of the layer call, geometric mean, is 1.23 (4 / 4), 1.11
+// (6 / 6), 1.12 (8 / 8) and 1.16 (8 / 4) where the rule streams, the worst 0.84, and 0.72-0.86 where it does not.  Around
+// the lines (us of the layer call, stream : tiled):
+//   4 / 4  two workgroups per CU: 128 tokens, 2048 -> 16384 17.5 : 24.0 (512 workgroups); 256, 1024 -> 12288 17.6 : 14.3
+//          (768); 4096, 256 -> 4096 41.5 : 22.6 (4096); 90000, 50000 up to 32 workgroups (four parts of K in the tiled
+//          kernels): 1024, 2048 -> 1024 15.7 : 25.3 (16k); 2048, 8192 -> 512 36 : 43 (66k); 247, 8448 -> 256 24.1 : 23.0 (68k, 16)
+//   6 / 6, 8 / 8, 8 / 4  one workgroup per CU, two where the tiled kernels would split K and finish in a launch of its own:
+//          256 tokens, 1024 -> 12288 6 / 6 27.4 : 14.2 (1152, K whole), 8 / 8 21.3 : 14.2 (768, K whole); 512, 1024 -> 2048 8 / 8
+//          13.7 : 23.9 (256, split); 1024, 512 -> 2048 8 / 8 13.8 : 12.1 (512, K whole); lines, up to 64 workgroups (eight
+//          parts of K) and beyond: 6 / 6 16000 / 28000, 8 / 8 20000 / 33000, 8 / 4 20000 / 40000 (96 tokens, 4096 -> 4096
+//          8 / 4, 128 workgroups: 18 : 21 at 25k; 48, 4096 -> 256, 8: 15.0 : 13.7 at 16k)
+//          in qllm_int_gemm, where the tiled path re-lays the activations in a launch of its own (4-6 us), two
+//          workgroups per CU either way and 6 / 6 20000 / 33000, 8 / 8 28000 / 45000, 8 / 4 33000 / 70000
+// Where the weight came without its re-laid copy the tiled kernels expand packed codes (54-130 us up to 128 tokens): five
+// workgroups per CU (512 tokens, 512 -> 6144 6 / 6 21 : 26 at 1152; 4096, 256 -> 1024 25 : 25 at 1376), 100000.
 struct StreamPlan {
     bool take;
     int nt;         // 16-token tiles per workgroup
     int64_t groups; // workgroups, at 32 features each
 };
-StreamPlan plan_stream(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool relaid)
+StreamPlan plan_stream(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool relaid, bool relays_codes)
 {
     const int64_t og = (O + 31) / 32;
     if (N <= 32) return StreamPlan{true, N <= 16 ? 1 : 2, og};
     const int64_t most = a_bits == 6 ? 6 : 8; // six-bit codes: registers for six tiles
     const int64_t tiles = (N + 15) / 16, blocks = (tiles + most - 1) / most, each = (tiles + blocks - 1) / blocks;
     const int nt = each <= 4 ? 4 : each <= 6 ? 6 : 8;
-    const int64_t groups = og * blocks, cost = K * nt * (groups > 256 ? groups : 256) / 256;
-    const int64_t line = w_bits != 4 ? (groups <= 128 ? 28000 : 36000) : a_bits == 4 ? 68000 : groups <= 128 ? 48000 : 70000;
-    bool take = (a_bits == 4 && N <= 64) || (cost <= line && (N <= 64 || og <= 400) && (groups <= 512 || nt == 4 || cost <= 33000));
-    if (!relaid && w_bits + a_bits != 8) take = take || cost <= 100000;
+    const int64_t groups = og * blocks, cost = K * nt * ((groups + 255) / 256);
+    const int64_t launched = nt == 4 && groups > 256 ? (groups + 1) / 2 : groups; // 64 features each, see launch_stream
+    const bool few = groups <= 64;
+    int64_t most_groups, line;
+    if (a_bits == 4) {
+        most_groups = 512, line = groups <= 32 ? 50000 : 90000;
+    } else if (!relaid) {
+        most_groups = 1280, line = 100000;
+    } else if (relays_codes) {
+        most_groups = 512, line = a_bits == 6 ? (few ? 20000 : 33000) : w_bits == 8 ? (few ? 28000 : 45000) : few ? 33000 : 70000;
+    } else {
+        most_groups = t8_splits(N, K, O) > 1 ? 512 : 256, line = a_bits == 6 ? (few ? 16000 : 28000) : few ? 20000 : w_bits == 8 ? 33000 : 40000;
+    }
+    const bool take = (a_bits == 4 && N <= 64) || (launched <= most_groups && cost <= line);
     return StreamPlan{take && blocks <= 65535, nt, groups};
 }
 
@@ -1855,22 +1868,74 @@ int32_t launch_stream(const GemmArgs &g, const StreamPlan &plan, int32_t y_dtype
     }
 }
 
-template <int ABITS, int WBITS>
-int32_t launch(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+// Into how many parts K is split (1: not at all).  Only 4-bit codes with 128 x 128 tiles that leave
+// most CUs without a workgroup (up to 64 tiles: four parts, up to 128: two; beyond that the parts'
+// accumulators, written and read back, cost what the shorter K loop gains); every part keeps at least
+// eight K-tiles.
+int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
 {
-    const StreamPlan sp = plan_stream(g.N, g.K, g.O, ABITS, WBITS, ABITS == 4 ? g.w_tiles != nullptr : g.w_tiles8 != nullptr);
-    if (sp.take) return launch_stream<ABITS, WBITS>(g, sp, y_dtype, stream);
+    if (a_bits != 4 || N <= 64) return 1; // up to 64 tokens the weight-streaming kernel runs
+    const int64_t tiles = ((O + 127) / 128) * ((N + 127) / 128);
+    const int64_t n_kt = (K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD / PKT;
+    if (tiles > 128) return 1;
+    int64_t s = 256 / tiles;
+    if (s > 4) s = 4;
+    if (s > n_kt / 8) s = n_kt / 8;
+    return s < 2 ? 1 : (int32_t)s;
+}
+
+// The kernel, tiles and parts of K of a product.
+struct Route {
+    int32_t kernel;    // QLLM_GEMM_*
+    int32_t splits;    // parts of K
+    TilePlan tiles;    // not for the streaming kernel
+    StreamPlan stream; // the streaming kernel only
+};
+
+// tiles6, tiles8: that path has its two operands (the weight's copy and room for the activations').  parts8: parts of a
+// split K that the workspace holds on the byte-operand path.  a_laid: the activations are in tiles8 form already and
+// nowhere else.  one_launch: nothing that takes two.
+Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool tiles6, bool tiles8, int64_t parts8, bool a_laid, bool one_launch)
+{
+    const bool both4 = a_bits == 4 && w_bits == 4;
+    Route r{QLLM_GEMM_EXPANDS, 1, TilePlan{true, 0}, plan_stream(N, K, O, a_bits, w_bits, both4 ? tiles6 : tiles8, true)};
+    if (r.stream.take && !a_laid) {
+        r.kernel = QLLM_GEMM_STREAMS;
+    } else if (both4) {
+        r.splits = k_splits(N, K, O, 4);
+        if (tiles6) {
+            r.kernel = QLLM_GEMM_FP6;
+            if (r.splits == 1) r.tiles = plan_tiles(N, O, !one_launch);
+        } else {
+            // 256 x 256 tiles run one workgroup per CU, 128 x 128 tiles two, at about three quarters of the large tile's
+            // rate per matrix-core operation: the small tile is taken where it fills the chip's rounds that much
+            // better (few tiles, or a last round that is mostly empty: 384 large tiles are 1.5 rounds, 1536 small ones 3).
+            const int64_t big_tiles = ((O + LBN - 1) / LBN) * ((N + LBM - 1) / LBM), small_tiles = ((O + 127) / 128) * ((N + 127) / 128);
+            const double big_fill = (double)big_tiles / (double)(256 * ((big_tiles + 255) / 256));
+            const double small_fill = (double)small_tiles / (double)(512 * ((small_tiles + 511) / 512));
+            r.tiles.small = N <= 128 || big_fill < 0.78 * small_fill;
+            if (!r.tiles.small) r.splits = 1;
+        }
+    } else if (tiles8) {
+        r.kernel = QLLM_GEMM_BYTES;
+        const int64_t s = t8_splits(N, K, O);
+        if (s > 1 && parts8 > 1) r.splits = (int32_t)(parts8 < s ? parts8 : s);
+        else r.tiles = plan_tiles(N, O, !one_launch);
+    } else {
+        r.tiles.small = N <= 128;
+    }
+    return r;
+}
+
+template <int ABITS, int WBITS>
+int32_t launch(const GemmArgs &g, const Route &route, int32_t y_dtype, hipStream_t stream)
+{
+    if (route.kernel == QLLM_GEMM_STREAMS) return launch_stream<ABITS, WBITS>(g, route.stream, y_dtype, stream);
+    const bool small = route.tiles.small;
+    const dim3 big_grid((unsigned)((g.O + LBN - 1) / LBN), (unsigned)((g.N + LBM - 1) / LBM));
     if constexpr (ABITS == 4 && WBITS == 4) {
-        if (g.a_tiles && g.w_tiles) return launch_fp6(g, y_dtype, stream);
-        // 4-bit codes on both sides, more than 32 tokens.  256 x 256 tiles run one workgroup per CU, 128 x 128
-        // tiles two, at about three quarters of the large tile's rate per matrix-core operation: the
-        // small tile is taken where it fills the chip's rounds that much better (few tiles, or a last
-        // round that is mostly empty: 384 large tiles are 1.5 rounds, 1536 small ones 3).
-        const int64_t big_tiles = (int64_t)((g.O + LBN - 1) / LBN) * ((g.N + LBM - 1) / LBM);
-        const int64_t small_tiles = (int64_t)((g.O + 127) / 128) * ((g.N + 127) / 128);
-        const double big_fill = (double)big_tiles / (double)(256 * ((big_tiles + 255) / 256));
-        const double small_fill = (double)small_tiles / (double)(512 * ((small_tiles + 511) / 512));
-        if (g.N > 32 && (g.N <= 128 || big_fill < 0.78 * small_fill)) {
+        if (route.kernel == QLLM_GEMM_FP6) return launch_fp6(g, route.tiles, y_dtype, stream);
+        if (small) {
             const dim3 grid((unsigned)((g.O + 127) / 128), (unsigned)((g.N + 127) / 128), (unsigned)(g.splits > 1 ? g.splits : 1));
             constexpr size_t lds = (size_t)NBUF * 256 * PROWB;
             if (g.splits > 1) {
@@ -1878,31 +1943,20 @@ int32_t launch(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
                 if (st != QLLM_OK) return st;
                 return launch_finish<0, 0>(g, y_dtype, stream);
             }
-            if (y_dtype == QLLM_F32)
-                return launch_kernel(int_gemm_w4a4_kernel<float, 4, 2>, grid, dim3(LTHREADS), lds, g, stream);
+            if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_w4a4_kernel<float, 4, 2>, grid, dim3(LTHREADS), lds, g, stream);
             return launch_kernel(int_gemm_w4a4_kernel<uint16_t, 4, 2>, grid, dim3(LTHREADS), lds, g, stream);
         }
+        if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_w4a4_kernel<float, 8, 4>, big_grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
+        return launch_kernel(int_gemm_w4a4_kernel<uint16_t, 8, 4>, big_grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
     } else {
-        if (g.a_tiles8 && g.w_tiles8) return launch_t8<ABITS, WBITS>(g, y_dtype, stream);
-    }
-    if (g.N > 128) { // enough tokens to fill 256-row tiles
-        const dim3 grid((unsigned)((g.O + LBN - 1) / LBN), (unsigned)((g.N + LBM - 1) / LBM));
-        if constexpr (ABITS == 4 && WBITS == 4) {
-            if (y_dtype == QLLM_F32)
-                return launch_kernel(int_gemm_w4a4_kernel<float, 8, 4>, grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
-            return launch_kernel(int_gemm_w4a4_kernel<uint16_t, 8, 4>, grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
-        } else {
-            if (y_dtype == QLLM_F32)
-                return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, float>, grid, dim3(LTHREADS), 2 * LBUF, g, stream);
-            return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, uint16_t>, grid, dim3(LTHREADS), 2 * LBUF, g, stream);
+        if (route.kernel == QLLM_GEMM_BYTES) return launch_t8<ABITS, WBITS>(g, route.tiles, y_dtype, stream);
+        if (small) { // 33..128 tokens
+            const dim3 grid((unsigned)((g.O + BN - 1) / BN), (unsigned)((g.N + BM - 1) / BM));
+            if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_kernel<ABITS, WBITS, float>, grid, dim3(THREADS), 0, g, stream);
+            return launch_kernel(int_gemm_kernel<ABITS, WBITS, uint16_t>, grid, dim3(THREADS), 0, g, stream);
         }
-    }
-    if constexpr (ABITS == 4 && WBITS == 4) {
-        return QLLM_ERR_SHAPE; // not reached: every 4-bit shape was placed above
-    } else { // 33..128 tokens, 6- or 8-bit codes
-        const dim3 grid((unsigned)((g.O + BN - 1) / BN), (unsigned)((g.N + BM - 1) / BM));
-        if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_kernel<ABITS, WBITS, float>, grid, dim3(THREADS), 0, g, stream);
-        return launch_kernel(int_gemm_kernel<ABITS, WBITS, uint16_t>, grid, dim3(THREADS), 0, g, stream);
+        if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, float>, big_grid, dim3(LTHREADS), 2 * LBUF, g, stream);
+        return launch_kernel(int_gemm_big_kernel<ABITS, WBITS, uint16_t>, big_grid, dim3(LTHREADS), 2 * LBUF, g, stream);
     }
 }
 
@@ -1918,22 +1972,6 @@ int32_t small_zero_bound(int64_t K, int32_t a_bits, int32_t w_bits)
     int64_t L = 1 << 20;
     while (L > 0 && (K * L >= (1 << 23) || K * (qa * qw + (qa + qw) * L + L * L) >= (1ll << 31))) L /= 2;
     return (int32_t)L;
-}
-
-// Into how many parts K is split (1: not at all).  Only 4-bit codes with 128 x 128 tiles that leave
-// most CUs without a workgroup (up to 64 tiles: four parts, up to 128: two; beyond that the parts'
-// accumulators, written and read back, cost what the shorter K loop gains); every part keeps at least
-// eight K-tiles.
-int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
-{
-    if (a_bits != 4 || N <= 64) return 1; // up to 64 tokens the weight-streaming kernel runs (SK4_TOKENS)
-    const int64_t tiles = ((O + 127) / 128) * ((N + 127) / 128);
-    const int64_t n_kt = (K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD / PKT;
-    if (tiles > 128) return 1;
-    int64_t s = 256 / tiles;
-    if (s > 4) s = 4;
-    if (s > n_kt / 8) s = n_kt / 8;
-    return s < 2 ? 1 : (int32_t)s;
 }
 
 } // namespace
@@ -1968,6 +2006,28 @@ bool has_room_for_tiles8(int64_t N, const qllm_weight *w, int32_t a_bits, const 
            qllm_tiles8_bytes(N, w->K) < (1ll << 32) && qllm_tiles8_bytes(w->O, w->K) < (1ll << 32);
 }
 
+// Where the FP6 path's activations go in the workspace: behind the parts of a split K, whether the sum is split or streamed.
+int64_t tiles6_at(int64_t N, int64_t K, int64_t O)
+{
+    return (qllm_gemm_workspace_floor_bytes(N, K, O, 4) + 255) / 256 * 256;
+}
+
+// The FP6 path: 4-bit codes, more than 64 tokens, the weight's tiles at hand and room for the activations'.  The kernel
+// addresses either operand with 32-bit offsets.
+bool has_room_for_tiles6(int64_t N, const qllm_weight *w, int32_t a_bits, const void *workspace, int64_t workspace_bytes)
+{
+    return a_bits == 4 && w->bits == 4 && w->tiles6 && N > 64 && workspace && 225 * w->K < (1 << 24) &&
+           workspace_bytes >= tiles6_at(N, w->K, w->O) + qllm_tiles6_bytes(N, w->K) && qllm_tiles6_bytes(N, w->K) < (1ll << 32) &&
+           qllm_tiles6_bytes(w->O, w->K) < (1ll << 32);
+}
+
+// The byte-operand path's workspace: the activations, then as many parts of a split K as fit behind them.
+int64_t parts8_at(int64_t N, int64_t K) { return (qllm_tiles8_bytes(N, K) + 255) / 256 * 256; }
+int64_t parts8_that_fit(int64_t N, int64_t K, int64_t O, int64_t workspace_bytes)
+{
+    return (workspace_bytes - parts8_at(N, K)) / (N * O * (int64_t)sizeof(int32_t));
+}
+
 // qllm_int_gemm; a_laid: the workspace already starts with the activations' bytes (tiles8 layout), and the byte-operand
 // path is the one that runs.
 int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy,
@@ -2000,33 +2060,25 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
     g.N = (int32_t)N; g.O = (int32_t)w->O; g.K = (int32_t)w->K;
     g.Kpad = (int32_t)((w->K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD);
     g.y = y; g.ldy = ldy; g.acc_dump = acc_dump;
-    g.splits = (a_bits == 4 && wb == 4) ? k_splits(N, w->K, w->O, a_bits) : 1;
+    const bool ws_aligned = (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+    if (wb == 4 && k_splits(N, w->K, w->O, a_bits) > 1 && (!workspace || !ws_aligned)) return workspace ? QLLM_ERR_ALIGN : QLLM_ERR_WORKSPACE;
+    const bool tiles6 = has_room_for_tiles6(N, w, a_bits, workspace, workspace_bytes);
+    const bool tiles8 = has_room_for_tiles8(N, w, a_bits, workspace, workspace_bytes);
+    if (tiles6 && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles6) & 15u))) return QLLM_ERR_ALIGN;
+    if (tiles8 && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles8) & 15u))) return QLLM_ERR_ALIGN;
+    const Route route = plan_route(N, w->K, w->O, a_bits, wb, tiles6, tiles8, tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
+                                   a_laid, acc_dump != nullptr);
+    g.splits = route.splits;
     g.partial = static_cast<int32_t *>(workspace);
-    if (g.splits > 1 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 15u))) return workspace ? QLLM_ERR_ALIGN : QLLM_ERR_WORKSPACE;
-    // the FP6 matrix-core path: 4-bit codes, more than 32 tokens, K not split, the weight's tiles at hand and room
-    // for the activations' in the workspace
-    // (where K is split, the parts' accumulators come first in the workspace and the tiles behind them)
-    const int64_t tiles_at = g.splits > 1 ? ((int64_t)g.splits * N * w->O * (int64_t)sizeof(int32_t) + 255) / 256 * 256 : 0;
-    if (a_bits == 4 && wb == 4 && w->tiles6 && N > 64 && workspace && 225 * w->K < (1 << 24) &&
-        workspace_bytes >= tiles_at + qllm_tiles6_bytes(N, w->K) && qllm_tiles6_bytes(N, w->K) < (1ll << 32) &&
-        qllm_tiles6_bytes(w->O, w->K) < (1ll << 32)) { // the kernel addresses either operand with 32-bit offsets
-        if ((reinterpret_cast<uintptr_t>(workspace) & 15u) || (reinterpret_cast<uintptr_t>(w->tiles6) & 15u)) return QLLM_ERR_ALIGN;
-        g.a_tiles = static_cast<const uint8_t *>(workspace) + tiles_at;
+    if (tiles6) {
+        g.a_tiles = static_cast<const uint8_t *>(workspace) + tiles6_at(N, w->K, w->O);
         g.w_tiles = w->tiles6;
     }
-    if (has_room_for_tiles8(N, w, a_bits, workspace, workspace_bytes)) {
-        if ((reinterpret_cast<uintptr_t>(workspace) & 15u) || (reinterpret_cast<uintptr_t>(w->tiles8) & 15u)) return QLLM_ERR_ALIGN;
+    if (tiles8) {
         g.a_tiles8 = static_cast<const uint8_t *>(workspace);
         g.w_tiles8 = w->tiles8;
         g.a_laid = a_laid;
-        // K split over workgroups where few tiles would leave most CUs idle, if the workspace also holds the parts
-        const int32_t s8 = t8_splits(N, w->K, w->O);
-        const int64_t at = (qllm_tiles8_bytes(N, w->K) + 255) / 256 * 256;
-        const int64_t room = (workspace_bytes - at) / (N * w->O * (int64_t)sizeof(int32_t)); // parts that fit
-        if (s8 > 1 && room > 1) {
-            g.splits = room < s8 ? (int32_t)room : s8;
-            g.partial = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + at);
-        }
+        g.partial = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + parts8_at(N, w->K));
     }
     g.small_zero = small_zero_bound(w->K, a_bits, wb);
     // finish_from_lds: sums that fit 24 bits (see there), no raw accumulators
@@ -2034,10 +2086,10 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
     g.lds_epilogue = !acc_dump && q_most * w->K < (1 << 23) &&
                      (a_bits != 4 || wb != 4 || 225 * w->K < (1 << 24));
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    if (a_bits == 4) return launch<4, 4>(g, y_dtype, stream);
-    if (a_bits == 6) return launch<6, 6>(g, y_dtype, stream);
-    if (wb == 8) return launch<8, 8>(g, y_dtype, stream);
-    return launch<8, 4>(g, y_dtype, stream);
+    if (a_bits == 4) return launch<4, 4>(g, route, y_dtype, stream);
+    if (a_bits == 6) return launch<6, 6>(g, route, y_dtype, stream);
+    if (wb == 8) return launch<8, 8>(g, route, y_dtype, stream);
+    return launch<8, 4>(g, route, y_dtype, stream);
 }
 
 } // namespace
@@ -2047,6 +2099,24 @@ extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, 
                                  int64_t workspace_bytes, void *hip_stream)
 {
     return int_gemm(a, a_bits, N, w, y, y_dtype, ldy, acc_dump, workspace, workspace_bytes, false, hip_stream);
+}
+
+extern "C" int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
+                                           int32_t *tile, int32_t *parts)
+{
+    if (!w || !tile || !parts) return QLLM_ERR_NULL;
+    const int32_t wb = w->bits;
+    if (!((a_bits == wb && (wb == 4 || wb == 6 || wb == 8)) || (a_bits == 8 && wb == 4))) return QLLM_ERR_BITS;
+    if (N <= 0 || N > INT32_MAX || w->O <= 0 || w->O > INT32_MAX || w->K <= 0 || w->K > (1 << 24)) return QLLM_ERR_SHAPE;
+    if (workspace_bytes < qllm_gemm_workspace_floor_bytes(N, w->K, w->O, a_bits)) return QLLM_ERR_WORKSPACE;
+    const void *some = w; // any address: only whether there is a workspace counts
+    const bool tiles8 = has_room_for_tiles8(N, w, a_bits, some, workspace_bytes);
+    const Route r = plan_route(N, w->K, w->O, a_bits, wb, has_room_for_tiles6(N, w, a_bits, some, workspace_bytes), tiles8,
+                               tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
+                               in_layer && tiles8 && !plan_stream(N, w->K, w->O, a_bits, wb, true, false).take, false);
+    *parts = r.splits;
+    *tile = r.kernel == QLLM_GEMM_STREAMS ? 0 : r.tiles.o_split > 0 ? 256 + 128 : r.tiles.small ? 128 : 256;
+    return r.kernel;
 }
 
 extern "C" int64_t qllm_tiles6_bytes(int64_t rows, int64_t K)
@@ -2139,7 +2209,7 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     // Where the GEMM is going to read its activations as bytes in matrix-core order, the fused kernel writes them so:
     // one launch and a pass over the codes less.
     const bool tiles8 = N <= INT32_MAX && w->O > 0 && w->O <= INT32_MAX && has_room_for_tiles8(N, w, a_bits, p, left) &&
-                        !plan_stream(N, w->K, w->O, a_bits, w->bits, true).take;
+                        !plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take;
     bool laid = false;
     const int32_t rc = qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, tiles8 ? p : nullptr, &laid, hip_stream);
     if (rc != QLLM_OK) return rc;

@@ -428,6 +428,56 @@ def test_numbering_few_chunks_takes_no_setting_to_a_slower_form(kind):
     assert (few > 0) == (kind not in (30, 42))                  # the widths reach both sides of the line
 
 
+def gemm_choice(N, K, O, a_bits, w_bits, copies=True, in_layer=False, workspace_bytes=1 << 40):
+    w = b._Weight(O, K, w_bits, 0x1000, 0x1000, 0x1000, 0x1000, 0x1000 if copies and (a_bits, w_bits) == (4, 4) else None,
+                  0x1000 if copies and a_bits != 4 else None)
+    return b.qllm_gemm_kernel_choice(types.SimpleNamespace(c=w), a_bits, N, workspace_bytes, in_layer)
+
+
+@pytest.mark.parametrize("N,K,O,bits,copies,want", [
+    # up to 32 tokens, and 64 with 4-bit codes, whatever the weight
+    (1, 4096, 27648, (4, 4), True, 0), (32, 8192, 8192, (6, 6), True, 0), (64, 5120, 27648, (4, 4), True, 0), (65, 5120, 27648, (4, 4), True, 1),
+    # few workgroups, whatever makes them few: 512 (4-bit codes) ...
+    (128, 2048, 16384, (4, 4), True, 0), (1024, 2048, 1024, (4, 4), True, 0), (256, 1024, 12288, (4, 4), True, 1), (512, 256, 8192, (4, 4), True, 1),
+    (4096, 256, 4096, (4, 4), True, 1), (16384, 256, 1024, (4, 4), True, 1),
+    # ... 256, or 512 where the tiled kernels split K, and a line of cost
+    (512, 1024, 2048, (8, 8), True, 0), (1024, 512, 2048, (8, 8), True, 2), (256, 1024, 12288, (6, 6), True, 2), (256, 1024, 12288, (8, 8), True, 2),
+    (512, 256, 6144, (6, 6), True, 2), (128, 1024, 12288, (6, 6), True, 0), (128, 4096, 4096, (8, 4), True, 0), (48, 8192, 256, (8, 4), True, 2),
+    
+    (4096, 512, 2048, (8, 8), True, 2),
+    # no copy of the weight for the tiled kernels: 1280 workgroups
+    (512, 2048, 4096, (8, 8), False, 0), (4096, 256, 4096, (8, 8), False, 3), (512, 16384, 4096, (6, 6), False, 3)])
+def test_gemm_streams_where_it_is_the_cheaper_way(N, K, O, bits, copies, want):
+    """Products on both sides of the streaming kernel's lines, each timed both ways; taking it where its workgroups are more
+    than two per CU cost up to a factor of two."""
+    assert gemm_choice(N, K, O, *bits, copies, in_layer=True)[0] == want
+    # what the layer call streams the product alone streams too: its tiled path has one launch more
+    if want == b.GEMM_STREAMS:
+        assert gemm_choice(N, K, O, *bits, copies) == (b.GEMM_STREAMS, 0, 1)
+
+
+def test_gemm_kernel_choice_of_tiles_and_parts():
+    MB = 1 << 20
+    assert gemm_choice(2048, 28672, 8192, 4, 4) == (b.GEMM_FP6, 256, 1)
+    assert gemm_choice(2048, 4096, 12288, 4, 4) == (b.GEMM_FP6, 256 + 128, 1)
+    assert gemm_choice(2048, 4096, 12288, 4, 4, copies=False) == (b.GEMM_EXPANDS, 128, 1)
+    assert gemm_choice(256, 8192, 8192, 4, 4) == (b.GEMM_FP6, 128, 2)
+    floor = b.qllm_gemm_workspace_floor_bytes(256, 8192, 8192, 4)
+    assert gemm_choice(256, 8192, 8192, 4, 4, workspace_bytes=floor) == (b.GEMM_EXPANDS, 128, 2)      # no room for the FP6 path
+    with pytest.raises(b.QllmError):
+        gemm_choice(256, 8192, 8192, 4, 4, workspace_bytes=floor - 1)
+    tiles = b.qllm_tiles8_bytes(100, 16384)
+    for room, parts in ((8, 8), (3, 3), (1, 1), (0, 1)):
+        assert gemm_choice(100, 16384, 1024, 8, 4, workspace_bytes=tiles + room * 100 * 1024 * 4) == (b.GEMM_BYTES, 128, parts)
+    assert gemm_choice(100, 16384, 1024, 8, 4, workspace_bytes=tiles - 1) == (b.GEMM_EXPANDS, 128, 1)
+    assert gemm_choice(777, 5000, 4999, 8, 4, workspace_bytes=64 * MB, in_layer=True) == (b.GEMM_BYTES, 128, 1)
+    for bad in (dict(a_bits=5), dict(a_bits=4, w_bits=8), dict(N=0), dict(K=0), dict(O=0)):
+        args = dict(N=64, K=512, O=512, a_bits=6, w_bits=6)
+        args.update(bad)
+        with pytest.raises(b.QllmError):
+            gemm_choice(**args)
+
+
 @pytest.mark.parametrize("name,N,C,O", [("tiny", 64, 512, 96), ("llama7b_qkv", 48, 1000, 40),
                                         ("llama70b_down", 32, 2050, 24), ("llama70b_q_decode", 16, 777, 33)])
 def test_host_helpers_match_the_oracle(oracle, name, N, C, O):
