@@ -278,8 +278,8 @@ def random_gemm_case(rng, N, K, O, a_bits, w_bits):
     return a, w, ax, aw, bx, bw
 
 
-def run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True, tiles6=True, tiles8=True):
-    """tiles6 (4-bit codes on both sides): give the weight its FP6-path copy; the workspace has room for that path either
+def run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True, tiles6=True, tiles8=True, route=None):
+    """route: the (kernel, tile, parts of K) that the call has to take.  tiles6 (4-bit codes on both sides): give the weight its FP6-path copy; the workspace has room for that path either
     way, so False is what sends a 4-bit shape down the int8 path.  tiles8 (the other bit pairs): give the weight its
     one-byte-per-code copy; False sends the shape to the kernels that expand packed codes themselves."""
     import torch
@@ -296,6 +296,8 @@ def run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True, tiles6
     acc = torch.full((N, O), -1, dtype=torch.int32, device="cuda") if dump else None
     ws_bytes = b.qllm_gemm_workspace_bytes(N, K, O, a_bits)     # partial sums where K is split, else room for the FP6 path
     ws = torch.full((ws_bytes,), 0xCD, dtype=torch.uint8, device="cuda") if ws_bytes else None
+    if route is not None:
+        assert b.qllm_gemm_kernel_choice(dw, a_bits, N, ws_bytes) == route
     b.qllm_int_gemm(qa, dw, y, acc, ws)
     torch.cuda.synchronize()
     return y, acc
@@ -315,18 +317,15 @@ def check_y(oracle, y, ref_f32, y_dtype):
 @pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 8), (8, 4)])
 @pytest.mark.parametrize("N,K,O", [(1, 1, 1), (16, 64, 16), (3, 520, 70), (17, 2300, 33), (32, 4352, 64), (130, 300, 200),
                                    (257, 1030, 129), (64, 2048, 384),
-                                   # 256-row tiles: two K-tiles only (the fetch ring runs past the end at once),
-                                   # three ragged tiles each way, a long K with one row past a tile
-                                   (300, 200, 260), (513, 256, 513), (129, 5000, 257),
-                                   # K split over workgroups (few tiles, long K): 2 and 4 parts, ragged
-                                   (100, 2100, 250), (40, 4100, 130)])
+                                   (300, 200, 260), (513, 256, 513), (129, 5000, 257), (100, 2100, 250), (40, 4100, 130)])
 @pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
 def test_gemm_small_shapes(oracle, b, a_bits, w_bits, N, K, O, y_dtype):
+    """Most of these stream whether or not the weight has its copy; test_gemm_tiled_kernels names its kernels."""
     rng = np.random.default_rng(N * 1000 + K + O + a_bits)
     a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
     ref_acc = oracle.int_gemm(a, w)
     ref_y = oracle.epilogue(ref_acc, K, ax, bx, a.astype(np.int64).sum(1), aw, bw, w.astype(np.int64).sum(1))
-    for tiles in ((True, False) if N > 32 else (True,)):   # FP6 / byte-operand path, and the kernels that unpack
+    for tiles in ((True, False) if N > 32 else (True,)):
         y, acc = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, tiles6=tiles, tiles8=tiles)
         assert np.array_equal(acc.cpu().numpy(), ref_acc), tiles
         check_y(oracle, y, ref_y, y_dtype)
@@ -425,9 +424,55 @@ def test_gemm_large_tiles_ragged(oracle, b, y_dtype):
     ref_acc = oracle.int_gemm(a, w)
     ref_y = oracle.epilogue(ref_acc, K, ax, bx, a.astype(np.int64).sum(1), aw, bw, w.astype(np.int64).sum(1))
     for tiles6 in (True, False):                                    # FP6 and int8 matrix-core paths
-        y, acc = run_gemm(b, a, w, ax, aw, bx, bw, 4, 4, y_dtype, tiles6=tiles6)
+        y, acc = run_gemm(b, a, w, ax, aw, bx, bw, 4, 4, y_dtype, tiles6=tiles6, route=(b.GEMM_FP6 if tiles6 else b.GEMM_EXPANDS, 256, 1))
         assert np.array_equal(acc.cpu().numpy(), ref_acc), tiles6
         check_y(oracle, y, ref_y, y_dtype)
+
+
+BYTE_PAIRS, ALL_PAIRS = [(6, 6), (8, 8), (8, 4)], [(4, 4), (6, 6), (8, 8), (8, 4)]
+TILED = [  # tokens, K, features, code widths, with the weight's copy, tile, parts of K, every zero-point among the codes
+    # 128 x 128 tiles, two K-tiles (four of bytes) only: the fetch ring runs past the end at once
+    (300, 200, 5801, ALL_PAIRS, True, 128, 1, True), (300, 200, 5801, ALL_PAIRS, True, 128, 1, False),
+    (1000, 200, 6000, [(6, 6), (8, 4)], True, 128, 1, True),        # more workgroups than CUs: the byte path's ring of three
+    # 256 x 256 tiles: 9 x 22 and 17 x 13 of them, no multiple of the eight XCDs, bands of tiles of uneven height
+    (2049, 264, 5500, BYTE_PAIRS, True, 256, 1, True), (4100, 200, 3100, [(4, 4), (8, 8)], True, 256, 1, True),
+    # every code at its maximum over the longest K: the widest sums the epilogue from LDS is taken for
+    (1030, 32768, 2050, ALL_PAIRS, True, 128, 1, True),
+    # K in parts, ragged: four, and two
+    (100, 8300, 250, [(4, 4)], True, 128, 4, True), (250, 5700, 5600, [(4, 4)], True, 128, 2, True),
+    # the kernels that expand packed codes: 128- and 256-row tiles, K in parts, two K-tiles only, up to 128 tokens
+    (300, 200, 5801, [(4, 4)], False, 128, 1, False), (100, 8300, 250, [(4, 4)], False, 128, 4, True),
+    (250, 5700, 5600, [(4, 4)], False, 128, 2, True), (300, 16800, 130, BYTE_PAIRS, False, 256, 1, True),
+    (600, 200, 8200, BYTE_PAIRS, False, 256, 1, False), (96, 16800, 130, BYTE_PAIRS, False, 128, 1, True)]
+
+
+@pytest.mark.parametrize("N,K,O,a_bits,w_bits,copies,tile,parts,inside",
+                         [(N, K, O, *p, c, t, k, i) for N, K, O, pairs, c, t, k, i in TILED for p in pairs])
+def test_gemm_tiled_kernels(oracle, b, N, K, O, a_bits, w_bits, copies, tile, parts, inside):
+    """Every tiled kernel at partial tiles on both edges, odd widths (unaligned rows) and zero-points at both ends of the
+    code range, in both output types: the raw accumulators exact against numpy; the call without them (the epilogue
+    that takes its constants from LDS, or, with a token whose zero-point lies outside the codes, the general one in
+    that token's tiles) bit for bit the call with them; and the result against the oracle."""
+    rng = np.random.default_rng(N + K + O + a_bits)
+    a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
+    qa, qw = 2 ** a_bits - 1, 2 ** w_bits - 1
+    bx[:], bw[:] = rng.choice([0, qa // 2, qa], N), rng.choice([0, qw // 2, qw], O)
+    if not inside:
+        bx[N // 2] = -3
+    if K == 32768:
+        a[:], w[:] = qa, qw
+        exact = np.full((N, O), qa * qw * K, np.int64)
+    else:
+        exact = (a.astype(np.float64) @ w.astype(np.float64).T).astype(np.int64)                 # integers below 2^53: exact
+    kernel = b.GEMM_EXPANDS if not copies else b.GEMM_FP6 if a_bits == 4 else b.GEMM_BYTES
+    rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
+    ref = oracle.epilogue(exact.astype(np.int32), K, ax, bx, rs, aw, bw, cs)
+    for y_dtype in ("f32", "bf16"):
+        run = lambda dump: run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump, tiles6=copies, tiles8=copies, route=(kernel, tile, parts))
+        (y, _), (y1, acc) = run(False), run(True)
+        assert np.array_equal(acc.cpu().numpy(), exact)
+        assert __import__("torch").equal(y, y1)
+        check_y(oracle, y, ref, y_dtype)
 
 
 @pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 4)])
@@ -446,7 +491,8 @@ def test_gemm_two_launch_tile_plan(oracle, b, a_bits, w_bits):
     rows = np.sort(rng.choice(N, 32, replace=False))
     rows[-2:] = [N - 2, N - 1]
     rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
-    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, "f32", dump=False)
+    route = (b.GEMM_FP6 if a_bits == 4 else b.GEMM_BYTES, 256 + 128, 1)
+    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, "f32", dump=False, route=route)
     y = y.cpu().numpy()
     ref_cols = oracle.epilogue(oracle.int_gemm(a, w[cols]), K, ax, bx, rs, aw[cols], bw[cols], cs[cols])
     ref_rows = oracle.epilogue(oracle.int_gemm(a[rows], w), K, ax[rows], bx[rows], rs[rows], aw, bw, cs)
@@ -462,51 +508,26 @@ def test_gemm_two_launch_tile_plan(oracle, b, a_bits, w_bits):
 
 
 @pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 8), (8, 4)])
-@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("N,K,O,inside", [(300, 200, 2056, True), (300, 200, 2056, False), (513, 264, 1029, True), (259, 32768, 522, True),
-                                          (2305, 128, 2304, True)])
-def test_gemm_epilogue_from_lds(oracle, b, a_bits, w_bits, y_dtype, N, K, O, inside):
-    """The epilogue that takes its constants from LDS and stores 16 bytes per lane against the general one (which any call
-    with acc_dump runs): the same bits, with zero-points at both ends of the code range (the widest sums it is taken
-    for), with one token whose zero-point lies outside it (its tiles fall back), with odd widths and unaligned rows, with
-    partial tiles on both edges, and for a number of tiles that is no multiple of the eight XCDs; and against the oracle.  The largest K has every code at its maximum."""
-    rng = np.random.default_rng(N + K + O + a_bits)
-    a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
-    qa, qw = 2 ** a_bits - 1, 2 ** w_bits - 1
-    if K == 32768:
-        a[:], w[:] = qa, qw
-    bx[:], bw[:] = rng.choice([0, qa // 2, qa], N), rng.choice([0, qw // 2, qw], O)
-    if not inside:
-        bx[N // 2] = -3
-    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=False)
-    y1, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True)
-    assert __import__("torch").equal(y, y1)
-    rows, cols = np.unique(np.r_[0, N // 2, N - 1, rng.integers(0, N, 13)]), np.unique(np.r_[0, O - 1, rng.integers(0, O, 29)])
-    rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
-    ref = oracle.epilogue(oracle.int_gemm(a[rows], w[cols]), K, ax[rows], bx[rows], rs[rows], aw[cols], bw[cols], cs[cols])
-    check_y(oracle, y[rows][:, cols].contiguous(), ref, y_dtype)
-
-
-@pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 8), (8, 4)])
-@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("N,K,O", [(1, 300, 8230), (16, 2304, 50), (17, 520, 8227), (33, 1030, 70), (64, 260, 16410), (49, 260, 8200), (65, 700, 100),
-                                   (96, 64, 8227), (97, 300, 33), (128, 600, 8200), (130, 1300, 257), (300, 260, 31), (512, 128, 1029)])
-def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, y_dtype, N, K, O):
+@pytest.mark.parametrize("N,K,O", [(1, 300, 8230), (16, 2304, 50), (17, 520, 8227), (33, 1030, 70), (64, 260, 16300), (49, 260, 8200), (65, 700, 100),
+                                   (96, 64, 8227), (97, 300, 33), (128, 600, 8200), (130, 1300, 257), (300, 260, 31), (1400, 128, 1029)])
+def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, N, K, O):
     """The weight-streaming kernel over its tile counts (1, 2, 4, 6, 8 per workgroup), one and several blocks of tokens,
     few and many workgroups (4 or 8 waves, 32 or 64 features), K that is no multiple of a step or shorter than one step
     per wave, ragged tokens and features; zero-points inside the code range (the epilogue from LDS).  The raw
     accumulators are exact, the call with acc_dump (general epilogue) gives the same bits, and the result matches the
-    oracle.  No workspace is used or needed where K is not split."""
+    oracle, in both output types."""
     rng = np.random.default_rng(N * 7 + K + O + a_bits)
     a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
     bx = np.clip(bx, 0, 2 ** a_bits - 1)
-    y, _ = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=False)
-    y1, acc = run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump=True)
     ref_acc = a.astype(np.float64) @ w.astype(np.float64).T                  # integers below 2^53: exact
-    assert np.array_equal(acc.cpu().numpy(), ref_acc.astype(np.int64))
-    assert __import__("torch").equal(y, y1)
     rs, cs = a.astype(np.int64).sum(1), w.astype(np.int64).sum(1)
-    check_y(oracle, y, oracle.epilogue(ref_acc.astype(np.int32), K, ax, bx, rs, aw, bw, cs), y_dtype)
+    ref = oracle.epilogue(ref_acc.astype(np.int32), K, ax, bx, rs, aw, bw, cs)
+    for y_dtype in ("f32", "bf16"):
+        run = lambda dump: run_gemm(b, a, w, ax, aw, bx, bw, a_bits, w_bits, y_dtype, dump, route=(b.GEMM_STREAMS, 0, 1))
+        (y, _), (y1, acc) = run(False), run(True)
+        assert np.array_equal(acc.cpu().numpy(), ref_acc.astype(np.int64))
+        assert __import__("torch").equal(y, y1)
+        check_y(oracle, y, ref, y_dtype)
 
 
 @pytest.mark.parametrize("a_bits,w_bits", [(6, 6), (8, 8), (8, 4)])
@@ -533,6 +554,7 @@ def test_layer_writes_matrix_core_order(b, a_bits, w_bits, N, C, K, norm, x_dtyp
     b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, qa)
     want = torch.empty((N, O), device="cuda")
     ws = torch.full((b.qllm_gemm_workspace_bytes(N, K, O, a_bits),), 0xCD, dtype=torch.uint8, device="cuda")
+    assert b.qllm_gemm_kernel_choice(dw, a_bits, N, ws.numel(), in_layer=True)[0] == b.GEMM_BYTES
     b.qllm_int_gemm(qa, dw, want, None, ws)
     y = torch.full((N, O), float("nan"), device="cuda")
     ws = torch.full((b.qllm_workspace_bytes(N, K, O, a_bits),), 0xCD, dtype=torch.uint8, device="cuda")
@@ -810,8 +832,8 @@ def test_reassembled_linear_full_configs_sampled(oracle, b, name):
 @pytest.mark.parametrize("name,N,C,O,y_dtype", [("tiny", 40, 512, 96, "f32"), ("llama7b_qkv", 300, 4096, 640, "bf16"),
                                                ("llama70b_q_decode", 16, 8192, 256, "bf16")])
 def test_reassembled_linear_w4a8_end_to_end(oracle, b, name, N, C, O, y_dtype):
-    """Sec. 5 "Quantization settings": 4-bit weights with 8-bit activations, through the whole layer (decode-size,
-    small and more than 128 tokens: three different GEMM kernels)."""
+    """Sec. 5 "Quantization settings": 4-bit weights with 8-bit activations, through the whole layer (decode-size
+    and small: the streaming kernel; 300 tokens: the byte-operand path, with codes the fused kernel laid out)."""
     import dataclasses
     import torch
     w = dataclasses.replace(wl.WORKLOADS[name], a_bits=8, w_bits=4)
@@ -856,9 +878,10 @@ def test_fused_full_down_projection_without_norm(oracle, b):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name,N,C,O", [("llama70b_q_decode", 16, 8192, 512), ("llama7b_qkv", 300, 4096, 640)])
-def test_layer_replays_from_a_hip_graph(oracle, b, name, N, C, O):
-    """The two launches of the layer captured once and replayed (decode loops are launch bound): every
+@pytest.mark.parametrize("name,N,C,O,kernel,parts", [("llama70b_q_decode", 16, 8192, 512, 0, 1), ("llama7b_qkv", 300, 4096, 640, 0, 1),
+                                                     ("llama7b_qkv", 250, 8192, 500, 1, 4), ("llama70b_q_decode", 200, 8192, 500, 2, 8)])
+def test_layer_replays_from_a_hip_graph(oracle, b, name, N, C, O, kernel, parts):
+    """The launches of the layer (two, or up to four where the product has its operands re-laid and K split) captured once and replayed (decode loops are launch bound): every
     replay, with eager work and synchronisations in between and fresh inputs each time, must give the
     eager result bit for bit.  The library allocates nothing and records no memset."""
     import torch
@@ -868,6 +891,8 @@ def test_layer_replays_from_a_hip_graph(oracle, b, name, N, C, O):
     dw = device_weight(b, c)
     g = torch.from_numpy(c.gamma).cuda()
     ws = torch.empty(b.qllm_workspace_bytes(c.N, c.K, c.O, w.a_bits), dtype=torch.uint8, device="cuda")
+    room = b.qllm_gemm_workspace_bytes(c.N, c.K, c.O, w.a_bits)
+    assert b.qllm_gemm_kernel_choice(dw, w.a_bits, c.N, room, in_layer=True)[::2] == (kernel, parts)
     x_static = to_torch_x(c.x).clone()
     y_graph = torch.zeros((c.N, c.O), dtype=torch.bfloat16, device="cuda")
     y_eager = torch.zeros_like(y_graph)

@@ -16,7 +16,7 @@ def test_static_workspace_entry_point_matches_the_workspace_one(oracle):
     # first a 4-bit shape whose GEMM takes the FP6 path (the activations re-laid into the workspace), then a small-batch
     # 4-bit shape whose GEMM splits K over workgroups (partial accumulators in the workspace), then a smaller
     # decode-sized 6-bit one: stale contents of the shared array must not matter
-    for name, N, C, O, y_dtype in [("llama7b_qkv", 300, 4096, 8192, torch.bfloat16), ("llama7b_qkv", 96, 4096, 2048, torch.bfloat16),
+    for name, N, C, O, y_dtype in [("llama7b_qkv", 300, 4096, 8192, torch.bfloat16), ("llama7b_qkv", 250, 8192, 500, torch.bfloat16),
                                    ("llama70b_q_decode", 16, 2048, 512, torch.float32)]:
         w = wl.WORKLOADS[name]
         c = make_case(oracle, w, N=N, C=C, O=O)
@@ -28,7 +28,9 @@ def test_static_workspace_entry_point_matches_the_workspace_one(oracle):
         x = to_torch_x(c.x)
         need = b.qllm_workspace_bytes(c.N, c.K, c.O, w.a_bits)
         assert 0 < need <= b.STATIC_WORKSPACE_BYTES
-        if N == 96:
+        kernel, _, parts = b.qllm_gemm_kernel_choice(dw, w.a_bits, N, b.qllm_gemm_workspace_bytes(c.N, c.K, c.O, w.a_bits))
+        assert (kernel, parts) == {300: (b.GEMM_FP6, 1), 250: (b.GEMM_FP6, 4), 16: (b.GEMM_STREAMS, 1)}[N]
+        if N == 250:
             assert b.qllm_gemm_workspace_floor_bytes(c.N, c.K, c.O, w.a_bits) > 0      # partial accumulators live there too
         if N == 300:                                                                    # K not split, room for the tiles
             assert b.qllm_gemm_workspace_floor_bytes(c.N, c.K, c.O, w.a_bits) == 0 and dw.tiles6 is not None
