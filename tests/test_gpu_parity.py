@@ -595,26 +595,33 @@ def test_fused_lists_that_fit_for_some_settings(b, bits, norm, dtype, choice):
 
 @pytest.mark.parametrize("a_bits,w_bits", [(6, 6), (8, 8), (8, 4)])
 @pytest.mark.parametrize("parts", [0, 1, 3, 8])
-def test_gemm_split_takes_the_parts_that_fit(b, a_bits, w_bits, parts):
-    """K dealt out to as many workgroups per tile as the workspace holds accumulators for (eight are wanted here): the same
-    bits with room for none, one, three and all of them, for a width that is a multiple of four and one that is not."""
+def test_gemm_split_takes_the_parts_that_fit(oracle, b, a_bits, w_bits, parts):
+    """K dealt out to as many workgroups per tile as the workspace holds accumulators for (eight are wanted here): the
+    accumulators exact and the result the oracle's with room for none, one, three and all of them, for a width that is a
+    multiple of four and one that is not, in both output types, into rows of an odd stride; nothing written past a row."""
     import torch
     for O in (300, 301):
         N, K = 100, 16300
         rng = np.random.default_rng(O + parts)
         a, w, ax, aw, bx, bw = random_gemm_case(rng, N, K, O, a_bits, w_bits)
+        rs, cs = a.astype(np.int64).sum(1).astype(np.int32), w.astype(np.int64).sum(1).astype(np.int32)
         qa = b.DeviceQAct(N, K, a_bits)
         qa.codes.copy_(torch.from_numpy(b.qllm_pack_codes_host(a, a_bits)))
-        qa.scale.copy_(torch.from_numpy(ax)), qa.zero.copy_(torch.from_numpy(bx))
-        qa.rowsum.copy_(torch.from_numpy(a.astype(np.int64).sum(1).astype(np.int32)))
-        dw = b.DeviceWeight(b.qllm_pack_codes_host(w, w_bits), aw, bw, w.astype(np.int64).sum(1).astype(np.int32), K, w_bits, tiles8=True)
+        qa.scale.copy_(torch.from_numpy(ax)), qa.zero.copy_(torch.from_numpy(bx)), qa.rowsum.copy_(torch.from_numpy(rs))
+        dw = b.DeviceWeight(b.qllm_pack_codes_host(w, w_bits), aw, bw, cs, K, w_bits, tiles8=True)
         tiles = (b.qllm_tiles8_bytes(N, K) + 255) // 256 * 256
         assert b.qllm_gemm_workspace_bytes(N, K, O, a_bits) == tiles + 8 * N * O * 4
         ws = torch.full((tiles + parts * N * O * 4,), 0xCD, dtype=torch.uint8, device="cuda")
-        y, acc = torch.empty((N, O), device="cuda"), torch.empty((N, O), dtype=torch.int32, device="cuda")
-        b.qllm_int_gemm(qa, dw, y, acc, ws)
-        exact = a.astype(np.float64) @ w.astype(np.float64).T               # integers below 2^53: exact
-        assert np.array_equal(acc.cpu().numpy(), exact.astype(np.int64))
+        assert b.qllm_gemm_kernel_choice(dw, a_bits, N, ws.numel()) == (b.GEMM_BYTES, 128, max(parts, 1))
+        exact = (a.astype(np.float64) @ w.astype(np.float64).T).astype(np.int64)     # integers below 2^53: exact
+        ref = oracle.epilogue(exact.astype(np.int32), K, ax, bx, rs, aw, bw, cs)
+        for y_dtype in ("f32", "bf16"):
+            wide = torch.full((N, O + 3 - O % 2), float("nan"), dtype=torch.float32 if y_dtype == "f32" else torch.bfloat16, device="cuda")
+            acc = torch.full((N, O), -1, dtype=torch.int32, device="cuda")
+            b.qllm_int_gemm(qa, dw, wide[:, :O], acc, ws)
+            assert np.array_equal(acc.cpu().numpy(), exact)
+            check_y(oracle, wide[:, :O].contiguous(), ref, y_dtype)
+            assert bool(torch.isnan(wide[:, O:]).all())
 
 
 def test_gemm_extreme_codes(oracle, b):
