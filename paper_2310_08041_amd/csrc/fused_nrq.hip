@@ -335,11 +335,19 @@ __global__ __launch_bounds__(THREADS) void fused_nrq_kernel(const FusedArgs a)
 // ---- calibration statistic: per-channel max |y| (Sec. 4.1.1; vector m of Algorithm 1)
 // A workgroup keeps its maxima in LDS (transposed by 8, every lane touches only its own); the dump's rows go out as whole
 // 16-byte stores where they are aligned.  What bounded it was the maxima of a thousand workgroups meeting in the same C
-// words, one atomic per lane and channel, eight words apart: now there are at most 512 workgroups, a wave's atomics are
+// words, one atomic per lane and channel, eight words apart: now there are few workgroups, a wave's atomics are
 // on consecutive words, workgroups start at different channels, and one first asks for the word and only takes part if
 // it has something to add (the word only grows, so an old value costs at most an atomic too many).
 // 1024 x 4096 bf16 with the dump: 200 -> 35 us.
-constexpr int ABSMAX_GROUPS = 512;
+// 512 workgroups, two per CU, as long as the rows are few enough for the maxima at the end to count (1024 x 4096: 31 us,
+// 43 with 2048; 16384 x 8192 198 : 203); beyond 16384 rows what counts is rows in flight, and rows of up to 8192
+// channels, where eight workgroups fit a CU, take 2048 (65536 x 8192 fp32 LayerNorm 1011 : 830 us, 262144 x 256 1708 :
+// 1298; wider rows, one workgroup of 1024 lanes per CU, gain nothing: 65536 x 8200 bf16 1171 : 1226).
+inline int64_t absmax_groups(int64_t N, int64_t C)
+{
+    const int64_t most = N > 16384 && C <= 8192 ? 2048 : 512;
+    return N < most ? N : most;
+}
 template <typename XT, int THREADS, int ITERS>
 __global__ __launch_bounds__(THREADS) void norm_absmax_kernel(const FusedArgs a)
 {
@@ -586,7 +594,7 @@ extern "C" int32_t qllm_norm_channel_absmax(const void *x, int32_t x_dtype, int6
     if (n_dump > 0 && !y_dump) return QLLM_ERR_NULL;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     const size_t lds = (size_t)a.S * GROUP * sizeof(float);
-    const dim3 grid((unsigned)(N < ABSMAX_GROUPS ? N : ABSMAX_GROUPS));
+    const dim3 grid((unsigned)absmax_groups(N, C));
     const bool big = a.S > 1024;
     if (x_dtype == QLLM_BF16) {
         if (big) return launch_with_lds(norm_absmax_kernel<uint16_t, 1024, 4>, grid, dim3(1024), lds, stream, a);

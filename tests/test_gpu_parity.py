@@ -1176,7 +1176,7 @@ def test_reference_output_tiles(b, N, C, O, pad):
     assert np.all(got[:, O:] == -1.0)
 
 
-@pytest.mark.parametrize("N,C,norm", [(3, 8200, "rms"), (700, 9001, "layer"), (1100, 516, "rms"), (513, 12, "none")])
+@pytest.mark.parametrize("N,C,norm", [(3, 8200, "rms"), (700, 9001, "layer"), (1100, 516, "rms"), (513, 12, "none"), (16385, 260, "layer")])
 def test_channel_absmax_many_rows(oracle, b, N, C, norm):
     """More rows than workgroups, rows of more than 8192 channels, ragged rows: the statistic starts from what the
     caller left in it, and the dump holds the first rows of y."""
