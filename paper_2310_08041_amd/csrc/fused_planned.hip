@@ -368,8 +368,8 @@ __device__ __forceinline__ void store_group(uint8_t *out_row, int g, uint32_t w0
 // zero bytes; `row_tiles`: the row's first byte in its block of 16 rows.  8 bytes per group, 16 of two neighbours
 // together, the 16 rows of a block interleaved: the rows that are worked on at one time are neighbours on one XCD (see
 // the kernel's first row), so that its L2 puts whole lines together.  For 6-bit codes one store where packed rows take
-// three half-words.  2048 x 28672 6-bit: 72 us + 23 for the re-laying pass before, 86 so (the 16-byte pieces are what L2
-// takes per request: 3.7 M of them); 777 x 5000 8-bit 21.2 + 5.0 -> 21.8; 200 x 13824 6-bit 8.8 + 3.7 -> 9.9.
+// three half-words.  Packed rows + the re-laying pass, and so: 2048 x 28672 6-bit without a norm 53.3 + 25.4, 54.7 us;
+// 777 x 5000 8-bit 21.8 + 4.2, 22.0; 200 x 13824 6-bit 9.1 + 3.8, 10.0.
 template <int BITS>
 __device__ __forceinline__ void store_group_tiles8(uint8_t *row_tiles, int n_kt, int K, int g, uint32_t w0, uint32_t w1)
 {

@@ -811,7 +811,6 @@ __device__ __forceinline__ bool finish_from_lds(const GemmArgs &g, const ACC (&a
         const auto third = c[2]; // a value of its own: the compiler's bit cast of a vector's element takes the first one
         const float ax = __builtin_bit_cast(float, third);
         const bool row = n < g.N;
-        const int64_t at = (int64_t)n * g.ldy + o0 + ol + oq;
         auto value = [&](int j, int r) {
             float v;
             if constexpr (FP) {
