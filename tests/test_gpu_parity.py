@@ -565,14 +565,15 @@ def test_layer_writes_matrix_core_order(b, a_bits, w_bits, N, C, K, norm, x_dtyp
     assert torch.equal(y, want)
 
 
-@pytest.mark.parametrize("bits,norm,dtype,choice", [(4, "rms", "bf16", 1), (6, "none", "bf16", 1), (4, "layer", "bf16", 2), (8, "layer", "bf16", 2),
-                                                    (6, "rms", "bf16", 2), (8, "rms", "f32", 0)])
-def test_fused_lists_that_fit_for_some_settings(b, bits, norm, dtype, choice):
+@pytest.mark.parametrize("C,bits,norm,dtype,choice", [
+    (28672, 4, "rms", "bf16", 1), (28672, 6, "none", "bf16", 1), (28672, 4, "layer", "bf16", 2), (28672, 8, "layer", "bf16", 2),
+    (28672, 6, "rms", "bf16", 2), (28672, 8, "rms", "f32", 0), (24064, 6, "layer", "f32", 2), (24064, 8, "layer", "f32", 2)])
+def test_fused_lists_that_fit_for_some_settings(b, C, bits, norm, dtype, choice):
     """A map whose lists fit on chip for some code widths and norms and not for others: its plan numbers only the chunks
     that hold sources, and the streamed form translates the numbers through its table.  Bit for bit the kernel that
     walks the CSR map, rows of more than 64 entries and unused inputs included; the forms are the ones expected."""
     import torch
-    C, N = 28672, 300
+    N = 300
     rng = np.random.default_rng(5)
     row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
     at = row_ptr[1001]                                              # channel 1000 gets 69 entries more
