@@ -1300,13 +1300,14 @@ int32_t dispatch(const FusedArgs &a, const Shape &sh, size_t lds, bool stream_li
     return launch(fused_planned_kernel<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>, a, sh, lds, stream);
 }
 
+// every lane has its chunks and every slot a group (the composite groups all fit in the last pass's slots;
+// otherwise the slots before that pass that the plain groups leave over stay empty)
+bool exact_fit(const FusedArgs &a, const Shape &sh) { return a.n_chunks == sh.iters * sh.nt && a.n_work == a.n_chunks && a.n_comp <= sh.nt; }
+
 template <typename XT, int BITS, int NORM>
 int32_t dispatch_full(const FusedArgs &a, const Shape &sh, size_t lds, bool stream_lists, hipStream_t stream)
 {
-    // every lane has its chunks and every slot a group (the composite groups all fit in the last pass's slots;
-    // otherwise the slots before that pass that the plain groups leave over stay empty)
-    const bool full = a.n_chunks == sh.iters * sh.nt && a.n_work == a.n_chunks && a.n_comp <= sh.nt;
-    return full ? dispatch<XT, BITS, NORM, true>(a, sh, lds, stream_lists, stream) : dispatch<XT, BITS, NORM, false>(a, sh, lds, stream_lists, stream);
+    return exact_fit(a, sh) ? dispatch<XT, BITS, NORM, true>(a, sh, lds, stream_lists, stream) : dispatch<XT, BITS, NORM, false>(a, sh, lds, stream_lists, stream);
 }
 
 template <typename XT, int BITS>
@@ -1329,7 +1330,13 @@ int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds,
 
 // Which form of the kernel a map gets, with its launch shape and LDS size: the lists of the irregular part in
 // LDS when they fit there next to the row's packed codes; else the lists streamed from global memory; else none (the
-// caller then runs the kernel that walks the CSR map).
+// caller then runs the kernel that walks the CSR map).  For bfloat16 rows the streamed form comes first
+//   * with LayerNorm at four chunks per lane, where the other form spills (lists in LDS : streamed, us, 1 % merged:
+//     2048 x 8192 4-bit 52 : 41, 1024 x 13824 48 : 41, 3 x 28032 23 : 21, 1024 x 28032 83 : 70, 8-bit 97 : 73; fp32 rows, one
+//     row in flight, 51 : 58);
+//   * with at most one row per workgroup and more than three chunks per lane of 1024, where copying the lists costs more
+//     than the row saves (16 x 28032 RMS 4-bit 13.3 : 12.3, 6-bit 15.3 : 14.2, 8-bit without a norm 14.5 : 11.8), except
+//     without a norm in lanes that fit the row exactly (16 x 28672 6-bit 12.5 : 13.0).
 struct Choice {
     int kind; // QLLM_FUSED_WALKS_MAP / QLLM_FUSED_LISTS_IN_LDS / QLLM_FUSED_LISTS_STREAMED
     Shape sh;
@@ -1343,17 +1350,16 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
     if (!a.work || units > 4096 || !a.vec_ok || a.C % GROUP != 0) return c;
     const qllm_detail::PlanCounts p{a.n_comp, a.n_long, a.n_pub, a.n_chunks, a.n_spec, a.n_dest, a.n_segw};
     const int64_t w = bits == 4 ? 1 : 2;
-    {
-        const int irregular = std::max(a.n_long, std::max(a.n_spec, a.n_comp));
-        const Shape sh = pick_shape(units, a.N > cu_count(), a.norm == QLLM_NORM_LAYER, irregular);
-        // staged x, and gamma / beta at the same positions when there is a norm / a shift
-        const int64_t stage_sets = 1 + (a.norm != QLLM_NORM_NONE ? 1 : 0) + (a.norm == QLLM_NORM_LAYER && a.beta ? 1 : 0);
-        const int64_t lds = qllm_detail::fused_lists_lds_bytes(p, w, stage_sets, (int64_t)sh.iters * sh.nt);
-        if (lds <= MAX_LDS) return Choice{QLLM_FUSED_LISTS_IN_LDS, sh, (size_t)lds};
-    }
-    const Shape sh{4, ((units + 3) / 4 + 63) / 64 * 64};
-    const int64_t lds = qllm_detail::fused_streamed_lds_bytes(p, w, a.C, x_dtype == QLLM_BF16 ? 2 : 4, (int64_t)sh.iters * sh.nt);
-    if (lds <= MAX_LDS) return Choice{QLLM_FUSED_LISTS_STREAMED, sh, (size_t)lds};
+    const bool layer = a.norm == QLLM_NORM_LAYER, many = a.N > cu_count();
+    // staged x, and gamma / beta at the same positions when there is a norm / a shift
+    const int64_t stage_sets = 1 + (a.norm != QLLM_NORM_NONE ? 1 : 0) + (layer && a.beta ? 1 : 0);
+    const Shape held = pick_shape(units, many, layer, std::max(a.n_long, std::max(a.n_spec, a.n_comp)));
+    const Shape streamed{4, ((units + 3) / 4 + 63) / 64 * 64};
+    const int64_t held_lds = qllm_detail::fused_lists_lds_bytes(p, w, stage_sets, (int64_t)held.iters * held.nt);
+    const int64_t streamed_lds = qllm_detail::fused_streamed_lds_bytes(p, w, a.C, x_dtype == QLLM_BF16 ? 2 : 4, (int64_t)streamed.iters * streamed.nt);
+    const bool first = x_dtype == QLLM_BF16 && ((layer && held.iters == 4) || (!many && units > 3 * 1024 && (a.norm != QLLM_NORM_NONE || !exact_fit(a, held))));
+    if (held_lds <= MAX_LDS && !(first && streamed_lds <= MAX_LDS)) return Choice{QLLM_FUSED_LISTS_IN_LDS, held, (size_t)held_lds};
+    if (streamed_lds <= MAX_LDS) return Choice{QLLM_FUSED_LISTS_STREAMED, streamed, (size_t)streamed_lds};
     return c;
 }
 

@@ -565,15 +565,17 @@ def test_layer_writes_matrix_core_order(b, a_bits, w_bits, N, C, K, norm, x_dtyp
     assert torch.equal(y, want)
 
 
-@pytest.mark.parametrize("C,bits,norm,dtype,choice", [
-    (28672, 4, "rms", "bf16", 1), (28672, 6, "none", "bf16", 1), (28672, 4, "layer", "bf16", 2), (28672, 8, "layer", "bf16", 2),
-    (28672, 6, "rms", "bf16", 2), (28672, 8, "rms", "f32", 0), (24064, 6, "layer", "f32", 2), (24064, 8, "layer", "f32", 2)])
-def test_fused_lists_that_fit_for_some_settings(b, C, bits, norm, dtype, choice):
+@pytest.mark.parametrize("C,bits,norm,dtype,choice,N", [
+    (28672, 4, "rms", "bf16", 1, 300), (28672, 6, "none", "bf16", 1, 300), (28672, 4, "layer", "bf16", 2, 300), (28672, 8, "layer", "bf16", 2, 300),
+    (28672, 6, "rms", "bf16", 2, 300), (28672, 8, "rms", "f32", 0, 300), (24064, 6, "layer", "f32", 2, 300), (24064, 8, "layer", "f32", 2, 300),
+    # lists that fit and are streamed all the same: LayerNorm at four chunks per lane, few rows of more than three
+    (8192, 4, "layer", "bf16", 2, 600), (8192, 4, "layer", "f32", 1, 600), (8192, 4, "layer", "bf16", 1, 40), (28032, 4, "rms", "bf16", 2, 16),
+    (28032, 4, "rms", "bf16", 1, 257), (28672, 6, "none", "bf16", 1, 16)])
+def test_fused_lists_that_fit_for_some_settings(b, C, bits, norm, dtype, choice, N):
     """A map whose lists fit on chip for some code widths and norms and not for others: its plan numbers only the chunks
     that hold sources, and the streamed form translates the numbers through its table.  Bit for bit the kernel that
     walks the CSR map, rows of more than 64 entries and unused inputs included; the forms are the ones expected."""
     import torch
-    N = 300
     rng = np.random.default_rng(5)
     row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
     at = row_ptr[1001]                                              # channel 1000 gets 69 entries more
