@@ -87,10 +87,15 @@ __device__ __forceinline__ int32_t block_sum_i32(int32_t v, int32_t *red)
     return s;
 }
 
-// ---- step a1: load one row and normalise it; lane t holds channels 8 (t + it * THREADS) .. + 7 of y in v[it]
-template <typename XT, int THREADS, int ITERS>
-__device__ __forceinline__ void load_norm(const FusedArgs &a, int64_t row, float (&v)[ITERS][GROUP], double *red_d)
+// ---- step a1: load one row and normalise it; lane t hands channels 8 (t + it * THREADS) .. + 7 of y out in (*out)[it], or
+// with STAGE puts them into LDS (transposed-by-8 layout) as it goes.  Two places for the row in registers, because either
+// kernel spills or schedules worse with the other's: staging from the caller's array costs a row of one workgroup 0.6 us,
+// and the maxima of 16384 x 8200 bfloat16 take 1060 instead of 315 us with a copy.
+template <typename XT, int THREADS, int ITERS, bool STAGE>
+__device__ __forceinline__ void load_norm(const FusedArgs &a, int64_t row, float (*out)[ITERS][GROUP], float *ylds, double *red_d)
 {
+    float local[ITERS][GROUP];
+    float (&v)[ITERS][GROUP] = STAGE ? local : *out;
     const int tid = threadIdx.x;
     const int n_chunks = (a.C + GROUP - 1) / GROUP;
     const XT *xr = reinterpret_cast<const XT *>(a.x) + row * a.ldx;
@@ -199,24 +204,9 @@ __device__ __forceinline__ void load_norm(const FusedArgs &a, int64_t row, float
                     t = t * rstd;
                     t = t * g[j];
                 }
-                v[it][j] = t;
+                if constexpr (STAGE) ylds[j * a.S + i] = t;
+                else v[it][j] = t;
             }
-        }
-    }
-}
-
-// ... and leave y in LDS (transposed-by-8 layout)
-template <typename XT, int THREADS, int ITERS>
-__device__ __forceinline__ void load_norm_stage(const FusedArgs &a, int64_t row, float *ylds, double *red_d)
-{
-    float v[ITERS][GROUP];
-    load_norm<XT, THREADS, ITERS>(a, row, v, red_d);
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        const int i = threadIdx.x + it * THREADS;
-        if (i < a.S) {
-#pragma unroll
-            for (int j = 0; j < GROUP; ++j) ylds[j * a.S + i] = v[it][j];
         }
     }
 }
@@ -232,7 +222,7 @@ __global__ __launch_bounds__(THREADS) void fused_nrq_kernel(const FusedArgs a)
     const int tid = threadIdx.x;
 
     for (int64_t row = blockIdx.x; row < a.N; row += gridDim.x) {
-        load_norm_stage<XT, THREADS, ITERS>(a, row, ylds, red_d);
+        load_norm<XT, THREADS, ITERS, true>(a, row, nullptr, ylds, red_d);
         __syncthreads();
 
         // ---- steps a2 + a3: gather through the map; 8 reassembled channels per lane and step
@@ -359,7 +349,7 @@ __global__ __launch_bounds__(THREADS) void norm_absmax_kernel(const FusedArgs a)
     __syncthreads();
     for (int64_t row = blockIdx.x; row < a.N; row += gridDim.x) {
         float v[ITERS][GROUP];
-        load_norm<XT, THREADS, ITERS>(a, row, v, red_d);
+        load_norm<XT, THREADS, ITERS, false>(a, row, &v, nullptr, red_d);
         const bool dump = a.y_dump && row < a.n_dump;
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
