@@ -453,8 +453,9 @@ int32_t qllm_unpack_codes_host(const uint8_t *packed, int64_t R, int64_t K, int3
  * where the map's lists live while a row is worked on.
  *   QLLM_FUSED_WALKS_MAP       no plan, or it fits neither way: every output channel walks its CSR row
  *   QLLM_FUSED_LISTS_IN_LDS    the planned kernel with the plan's lists copied to LDS once per workgroup
- *   QLLM_FUSED_LISTS_STREAMED  the planned kernel reading the lists from global memory (L2) row by row: maps
- *                              with thousands of computed channels on the longest rows
+ *   QLLM_FUSED_LISTS_STREAMED  the planned kernel reading the lists from global memory (L2) row by row: where
+ *                              they do not fit in LDS, and for bfloat16 rows where copying them there costs
+ *                              more than it saves (LayerNorm on wide rows, few rows of the widest)
  * x is assumed 16-byte aligned; ldx in elements as in qllm_norm_reassemble_quant; has_beta != 0: a LayerNorm shift
  * is given.  Returns one of the three (>= 0) or a QLLM_ERR_* (< 0) for arguments qllm_norm_reassemble_quant
  * would reject too. */

@@ -90,7 +90,10 @@ __device__ __forceinline__ int32_t block_sum_i32(int32_t v, int32_t *red)
 // ---- step a1: load one row and normalise it; lane t hands channels 8 (t + it * THREADS) .. + 7 of y out in (*out)[it], or
 // with STAGE puts them into LDS (transposed-by-8 layout) as it goes.  Two places for the row in registers, because either
 // kernel spills or schedules worse with the other's: staging from the caller's array costs a row of one workgroup 0.6 us,
-// and the maxima of 16384 x 8200 bfloat16 take 1060 instead of 315 us with a copy.
+// and the maxima of 16384 x 8200 bfloat16 take 1060 instead of 313 us with a copy.  One group of calls is
+// faster staging from the caller's array: fp32 rows with LayerNorm, 2048 x 2577 8-bit 53.5 against 60.7 us, 6302 104 against
+// 111, 8102 115 against 121; bfloat16 there is slower that way (2048 x 8102 without a norm 109.8 against 107.1), and fp32
+// rows of 461 channels too (17.8 against 16.5).
 template <typename XT, int THREADS, int ITERS, bool STAGE>
 __device__ __forceinline__ void load_norm(const FusedArgs &a, int64_t row, float (*out)[ITERS][GROUP], float *ylds, double *red_d)
 {

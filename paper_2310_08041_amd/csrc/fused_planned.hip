@@ -1332,7 +1332,7 @@ int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds,
 // LDS when they fit there next to the row's packed codes; else the lists streamed from global memory; else none (the
 // caller then runs the kernel that walks the CSR map).  For bfloat16 rows the streamed form comes first
 //   * with LayerNorm at four chunks per lane, where the other form spills (lists in LDS : streamed, us, 1 % merged:
-//     2048 x 8192 4-bit 52 : 41, 1024 x 13824 48 : 41, 3 x 28032 23 : 21, 1024 x 28032 83 : 70, 8-bit 97 : 73; fp32 rows, one
+//     2048 x 8192 4-bit 46 : 38.5, 1024 x 13824 48 : 41, 3 x 28032 23 : 21, 1024 x 28032 83 : 70, 8-bit 97 : 73; fp32 rows, one
 //     row in flight, 51 : 58);
 //   * with at most one row per workgroup and more than three chunks per lane of 1024, where copying the lists costs more
 //     than the row saves (16 x 28032 RMS 4-bit 13.3 : 12.3, 6-bit 15.3 : 14.2, 8-bit without a norm 14.5 : 11.8), except
