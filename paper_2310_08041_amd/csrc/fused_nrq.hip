@@ -90,10 +90,7 @@ __device__ __forceinline__ int32_t block_sum_i32(int32_t v, int32_t *red)
 // ---- step a1: load one row and normalise it; lane t hands channels 8 (t + it * THREADS) .. + 7 of y out in (*out)[it], or
 // with STAGE puts them into LDS (transposed-by-8 layout) as it goes.  Two places for the row in registers, because either
 // kernel spills or schedules worse with the other's: staging from the caller's array costs a row of one workgroup 0.6 us,
-// and the maxima of 16384 x 8200 bfloat16 take 1060 instead of 313 us with a copy.  One group of calls is
-// faster staging from the caller's array: fp32 rows with LayerNorm, 2048 x 2577 8-bit 53.5 against 60.7 us, 6302 104 against
-// 111, 8102 115 against 121; bfloat16 there is slower that way (2048 x 8102 without a norm 109.8 against 107.1), and fp32
-// rows of 461 channels too (17.8 against 16.5).
+// and the maxima of 16384 x 8200 bfloat16 take 1060 instead of 313 us with a copy.
 template <typename XT, int THREADS, int ITERS, bool STAGE>
 __device__ __forceinline__ void load_norm(const FusedArgs &a, int64_t row, float (*out)[ITERS][GROUP], float *ylds, double *red_d)
 {
@@ -221,11 +218,28 @@ __global__ __launch_bounds__(THREADS) void fused_nrq_kernel(const FusedArgs a)
     __shared__ double red_d[THREADS / 64];
     __shared__ float red_f[2 * (THREADS / 64)];
     __shared__ int32_t red_i[THREADS / 64];
+    // Staged in a pass of its own where that leaves room for a third wave per SIMD, which takes at most 168 registers:
+    // fp32 rows of 4 chunks per lane, 6 and 8 bits, 166 and 165 registers against 174 and 173 (LayerNorm 8-bit, 2048 x 2577
+    // 53.7 : 60.7 us, 6302 104 : 111, 681 x 8102 44 : 55).  At 4 bits (160 : 168) and for bfloat16 (173 : 172) it buys nothing.
+    constexpr bool STAGE = !(sizeof(XT) == 4 && THREADS == 256 && ITERS == 4 && BITS > 4);
     constexpr int QMAX = (1 << BITS) - 1;
     const int tid = threadIdx.x;
 
     for (int64_t row = blockIdx.x; row < a.N; row += gridDim.x) {
-        load_norm<XT, THREADS, ITERS, true>(a, row, nullptr, ylds, red_d);
+        if constexpr (STAGE) {
+            load_norm<XT, THREADS, ITERS, true>(a, row, nullptr, ylds, red_d);
+        } else {
+            float v[ITERS][GROUP];
+            load_norm<XT, THREADS, ITERS, false>(a, row, &v, nullptr, red_d);
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) {
+                const int i = tid + it * THREADS;
+                if (i < a.S) {
+#pragma unroll
+                    for (int j = 0; j < GROUP; ++j) ylds[j * a.S + i] = v[it][j];
+                }
+            }
+        }
         __syncthreads();
 
         // ---- steps a2 + a3: gather through the map; 8 reassembled channels per lane and step

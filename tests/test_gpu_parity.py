@@ -93,6 +93,33 @@ def test_fused_odd_shapes(oracle, b, name, N, C, bits, merge, use_plan):
     check_fused(oracle, c, run_fused(b, c, bits, use_plan), bits)
 
 
+@pytest.mark.parametrize("C", [2041, 2049, 5003, 8191, 8193])
+@pytest.mark.parametrize("bits,norm,shift", [(4, "layer", True), (6, "none", False), (6, "rms", False), (8, "layer", True), (8, "layer", False)])
+def test_fused_f32_rows_without_a_plan(oracle, b, C, bits, norm, shift):
+    """fp32 rows through the kernel that walks the CSR map, one channel either side of where its chunks per lane change:
+    at 6 and 8 bits the 4-chunk kernel stages its row in a pass of its own."""
+    import torch
+    rng = np.random.default_rng(C + bits)
+    row_ptr, src, scale = random_csr_map(rng, C, C, 41)
+    w = wl.WORKLOADS["llama7b_qkv"]
+    x = wl.bf16_bits_to_f32(wl.draw_activations(w, 5, C, 7)[0]) * np.float32(1.0009765625)
+    gamma, beta = wl.draw_norm_params(w, C, 7)[0], rng.standard_normal(C).astype(np.float32) if shift else None
+    kind = NORM_ID[norm]
+    xhat = oracle.apply_map(oracle.norm(x, kind, gamma if kind else None, beta, w.eps), row_ptr, src, scale)
+    codes, alpha, zero, rowsum = oracle.quantize_rows(xhat, bits)
+    dm = b.DeviceMap(row_ptr, src, scale, C)
+    xt = to_torch_x(x)
+    assert b.qllm_fused_kernel_choice(dm, xt.dtype, 5, C, kind, shift, bits) == b.FUSED_WALKS_MAP
+    out = b.DeviceQAct(5, C, bits)
+    out.codes.fill_(0xAB)
+    b.qllm_norm_reassemble_quant(xt, kind, torch.from_numpy(gamma).cuda() if kind else None,
+                                 torch.from_numpy(beta).cuda() if shift else None, w.eps, dm, bits, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.codes.cpu().numpy(), oracle.pack_codes(codes, bits, out.codes.shape[1]))
+    assert np.array_equal(out.scale.cpu().numpy().view(np.uint32), alpha.view(np.uint32))
+    assert np.array_equal(out.zero.cpu().numpy(), zero) and np.array_equal(out.rowsum.cpu().numpy(), rowsum)
+
+
 def many_to_one_case(oracle, counts, N, C, name="llama7b_qkv"):
     """No split channel; B-member j (position 2j + 1) takes counts[j] A-members: rows of counts[j] + 1 entries."""
     c = make_case(oracle, wl.WORKLOADS[name], N=N, C=C, O=8, merge=False, real_weights=False, theta_rule=("fixed", 1.0))
