@@ -1802,6 +1802,10 @@ int32_t launch_skinny(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 //          8 / 4, 128 workgroups: 18 : 21 at 25k; 48, 4096 -> 256, 8: 15.0 : 13.7 at 16k)
 //          in qllm_int_gemm, where the tiled path re-lays the activations in a launch of its own (4-6 us), two
 //          workgroups per CU either way and 6 / 6 20000 / 33000, 8 / 8 28000 / 45000, 8 / 4 33000 / 70000
+//          8 / 4 up to 64 tokens and more than 256 workgroups, which are half as many of 64 features, two per CU either way:
+//          80000 up to 512, where the second round that is charged is not there, and beyond it or alone 100000 (64 tokens,
+//          8960 -> 14336 30.7 : 34.9, weights not in cache 45 : 67; 33, 12288 -> 10240 33.9 : 32.8, alone 27.5 : 28.9; 33,
+//          6144 -> 27648 34.2 : 36.2, alone 29.1 : 33.7).  6 / 6 and 8 / 8 lose there (64, 6144 -> 10240 28.6 : 24.8, 27.4 : 24.6)
 // Where the weight came without its re-laid copy the tiled kernels expand packed codes (54-130 us up to 128 tokens): five
 // workgroups per CU (512 tokens, 512 -> 6144 6 / 6 21 : 26 at 1152; 4096, 256 -> 1024 25 : 25 at 1376), 100000.
 struct StreamPlan {
@@ -1829,6 +1833,7 @@ StreamPlan plan_stream(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, 
     } else {
         most_groups = t8_splits(N, K, O) > 1 ? 512 : 256, line = a_bits == 6 ? (few ? 16000 : 28000) : few ? 20000 : w_bits == 8 ? 33000 : 40000;
     }
+    if (relaid && a_bits == 8 && w_bits == 4 && nt == 4 && groups > 256) most_groups = 512, line = relays_codes || groups > 512 ? 100000 : 80000;
     const bool take = (a_bits == 4 && N <= 64) || (launched <= most_groups && cost <= line);
     return StreamPlan{take && blocks <= 65535, nt, groups};
 }

@@ -443,7 +443,9 @@ def gemm_choice(N, K, O, a_bits, w_bits, copies=True, in_layer=False, workspace_
     # ... 256, or 512 where the tiled kernels split K, and a line of cost
     (512, 1024, 2048, (8, 8), True, 0), (1024, 512, 2048, (8, 8), True, 2), (256, 1024, 12288, (6, 6), True, 2), (256, 1024, 12288, (8, 8), True, 2),
     (512, 256, 6144, (6, 6), True, 2), (128, 1024, 12288, (6, 6), True, 0), (128, 4096, 4096, (8, 4), True, 0), (48, 8192, 256, (8, 4), True, 2),
-    
+    # 8-bit codes and 4-bit weights up to 64 tokens, 64 features per workgroup: 257 to 512 workgroups of 32 are one round
+    (64, 8960, 14336, (8, 4), True, 0), (33, 5120, 10240, (8, 4), True, 0), (33, 12288, 10240, (8, 4), True, 2), (64, 8960, 14336, (8, 8), True, 2),
+    (50, 4096, 16512, (8, 4), True, 0), (64, 6144, 27648, (8, 4), True, 0), (64, 4096, 32832, (8, 4), True, 2),
     (4096, 512, 2048, (8, 8), True, 2),
     # no copy of the weight for the tiled kernels: 1280 workgroups
     (512, 2048, 4096, (8, 8), False, 0), (4096, 256, 4096, (8, 8), False, 3), (512, 16384, 4096, (6, 6), False, 3)])
