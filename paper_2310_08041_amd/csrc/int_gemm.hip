@@ -22,6 +22,7 @@
 
 #include "qllm.h"
 #include "fused_common.h"
+#include "lds_copy.h"
 
 extern "C" void qllm_note_hip_error(const char *step, const char *name);
 
@@ -906,11 +907,9 @@ __device__ __forceinline__ TileAt tile_at(int nb, int ob)
 //
 // Same tiling as the int8 kernel above (2 x 4 waves, MI x NJ operations of 16 x 16 per wave and
 // K-tile), a ring of three stages (48 KB each for the 256 x 256 tile), fetches two K-tiles ahead.
-// One K-tile = MI groups of NJ operations (group i: token rows 16 i ..); token-side operands are
-// requested AHEAD groups before their use into a ring of four, the feature side at the start of the
-// iteration into the register set the previous K-tile does not use; the loop is rotated by AHEAD
-// groups (an iteration starts with the last groups of the K-tile before, zeros the first time), and
-// unrolled by two so that the alternation of the feature-side register sets is static.
+// One K-tile = MI groups of NJ operations (group i: token rows 16 i ..); the loop is rotated by AHEAD groups (an
+// iteration starts with the last groups of the K-tile before, zeros the first time) and unrolled by two, so
+// that the alternation of the two feature-side register sets is static; KTilePlan has the order of reads and loads.
 typedef int v8i __attribute__((ext_vector_type(8)));
 constexpr int T6_BLOCK = 1536, T6_X = 1024, T6_KT = 128, T6_STAGES = 3;
 
@@ -927,6 +926,31 @@ __device__ __forceinline__ Frag6 read6(const uint8_t *block, int lane)
     f.y = *reinterpret_cast<const v2i *>(block + T6_X + 8 * lane);
     return f;
 }
+
+// What a wave issues behind which of a K-tile's MI * NJ matrix-core operations, in gemm_w4a4_fp6_kernel and gemm_tiles8_kernel.
+// The first AHEAD groups of NJ finish the K-tile before, so they need nothing of this one: its operands are read behind
+// them, one block behind an operation, the feature side first, and the matrix cores run from the barrier on.  (All
+// reads of a K-tile's first groups in front of the first operation: eight waves' reads keep the LDS busy for some 300 of
+// the K-tile's 1500 clocks before any of them multiplies.)  The large tile reads a token-side block behind every other
+// operation and loads behind every third from the middle on (a load the CU's address unit has not accepted yet holds its
+// wave up).  Measured with the copies of lds_copy.h, kernel alone, us, before : copies : this order: FP6 2048 x 28672 -> 8192
+// 205-213 : 204-208 : 191-195, 4096 x 5120 -> 27648 286 : 283 : 279; bytes, 6-bit 2048 x 28672 -> 8192 317-333 : 308-327 : 298-302,
+// 8-bit 2048 x 5120 -> 13824 133 : 129 : 121-126, small tiles 777 x 5000 -> 4999 36.7 : 35.2 : 34.1, with K split 200 x 13824 ->
+// 5120 25.9 : 23.9 : 22.2.  Where the token-side reads go (every operation, second, third) changes nothing any more: in
+// clocks the large tiles are at 0.78 (FP6) and 0.88 (int8) of the same loop without reads and loads; the clock under this
+// load is 1.95-2.05 GHz (2.45 on operands of zeros).
+template <int MI, int NJ>
+struct KTilePlan {
+    static constexpr int AHEAD = 2, STEPS = MI * NJ;
+    static constexpr int READ_STEP = MI == 8 ? 2 : 1, FIRST_LOAD = MI == 8 ? 14 : NJ - 1, LOAD_STEP = MI == 8 ? 3 : NJ;
+    static constexpr int MOST_LOADS = (STEPS - 1 - FIRST_LOAD) / LOAD_STEP + 1;
+    // a block's registers are free once the operations on the K-tile before that read them are behind: the last
+    // AHEAD blocks are read after step AHEAD * NJ, and every one before its own first use (step (AHEAD + b) * NJ)
+    static_assert(NJ + (MI - AHEAD) * READ_STEP >= AHEAD * NJ - 1 && NJ <= AHEAD * NJ && NJ + (MI - 1) * READ_STEP < STEPS, "order of reads");
+    static constexpr int feature_read(int s) { return s < NJ ? s : -1; }
+    static constexpr int token_read(int s) { return s >= NJ && (s - NJ) % READ_STEP == 0 && (s - NJ) / READ_STEP < MI ? (s - NJ) / READ_STEP : -1; }
+    static constexpr int load(int s, int n) { return s >= FIRST_LOAD && (s - FIRST_LOAD) % LOAD_STEP == 0 && (s - FIRST_LOAD) / LOAD_STEP < n ? (s - FIRST_LOAD) / LOAD_STEP : -1; }
+};
 
 // SPLIT: K is dealt out to gridDim.z workgroups per tile of Y, as in int_gemm_w4a4_kernel; the parts' sums leave as
 // the integers they stand for.
@@ -960,10 +984,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     auto fetch_one = [&](int kt, int stage, int t) {
         const int ktc = min(kt, all_kt - 1);
         const bool token = (wave * NLOAD + t) * 1024 < TM / 16 * T6_BLOCK;
-        const uint8_t *base = (token ? g.a_tiles : g.w_tiles) + (int64_t)ktc * T6_BLOCK;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + src_off[t]),
-                                         (__attribute__((address_space(3))) void *)(lds + stage * STAGE + (wave * NLOAD + t) * 1024), 16, 0,
-                                         0);
+        qllm_detail::copy_1k_to_lds(token ? g.a_tiles : g.w_tiles, (uint32_t)(token ? a_blocks : w_blocks) * (uint32_t)all_kt * T6_BLOCK,
+                                    src_off[t], (uint32_t)ktc * T6_BLOCK, lds + stage * STAGE + (wave * NLOAD + t) * 1024);
     };
     auto fetch = [&](int kt, int stage) {
 #pragma unroll
@@ -988,15 +1010,13 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
     __syncthreads();
 
-    // Token-side operands: all MI blocks of a K-tile have registers of their own; the large tile requests them two
-    // per group in the first MI / 2 groups of the iteration, so that the wait for "own reads done" before the
-    // barrier finds them long back.
-    constexpr int RING = MI, AHEAD = 2, PER_STEP = MI == 8 ? 2 : 1;
-    // block b is requested in step b / PER_STEP, after the group of the K-tile before that used its registers (step b + AHEAD - MI)
-    static_assert(MI % PER_STEP == 0 && (MI - 1) / PER_STEP > AHEAD - 1 && (MI - AHEAD) / PER_STEP > 0, "group plan");
-    Frag6 ar[RING], wr[2][NJ];
+    // Token-side operands: all MI blocks of a K-tile have registers of their own.
+    typedef KTilePlan<MI, NJ> Plan;
+    constexpr int AHEAD = Plan::AHEAD;
+    static_assert(NLOAD <= Plan::MOST_LOADS, "every load of a K-tile has its place");
+    Frag6 ar[MI], wr[2][NJ];
 #pragma unroll
-    for (int k = 0; k < RING; ++k) ar[k] = Frag6{v4i{0, 0, 0, 0}, v2i{0, 0}};
+    for (int k = 0; k < MI; ++k) ar[k] = Frag6{v4i{0, 0, 0, 0}, v2i{0, 0}};
 #pragma unroll
     for (int j = 0; j < NJ; ++j) wr[0][j] = wr[1][j] = Frag6{v4i{0, 0, 0, 0}, v2i{0, 0}};
 
@@ -1008,30 +1028,20 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
         constexpr int P = decltype(parity)::value;
         const uint8_t *cur = lds + stage * STAGE;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            wr[P][j] = read6(cur + (w_blk0 + j) * T6_BLOCK, lane);
-            __builtin_amdgcn_sched_barrier(0); // also keeps the 8-byte reads of neighbouring blocks from being merged
-        }
-#pragma unroll
         for (int u = 0; u < MI; ++u) {
             const bool old = u < AHEAD;
             const int i = old ? MI - AHEAD + u : u - AHEAD;
-            // The K-tile two ahead, into the stage whose last reader passed the previous barrier: one load per group,
-            // not all at once (the eight waves' loads of a K-tile keep the CU's address unit busy for three quarters of
-            // a K-tile's matrix-core time; a wave whose load is not accepted yet issues nothing else either).
-            if (u < NLOAD) fetch_one(kt + 2, fetch_stage, u);
-            if (PER_STEP * u < MI) {
 #pragma unroll
-                for (int h = 0; h < PER_STEP; ++h) {
-                    ar[PER_STEP * u + h] = read6(cur + (a_blk0 + PER_STEP * u + h) * T6_BLOCK, lane);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j) {
+                const int s = u * NJ + j;
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(operand6(wr[old ? 1 - P : P][j]), operand6(ar[i]),
                                                                              acc[i][j], 2, 2, 0, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                if (Plan::feature_read(s) >= 0) wr[P][Plan::feature_read(s)] = read6(cur + (w_blk0 + Plan::feature_read(s)) * T6_BLOCK, lane);
+                if (Plan::token_read(s) >= 0) ar[Plan::token_read(s)] = read6(cur + (a_blk0 + Plan::token_read(s)) * T6_BLOCK, lane);
+                // the K-tile two ahead, into the stage whose last reader passed the previous barrier
+                if (Plan::load(s, NLOAD) >= 0) fetch_one(kt + 2, fetch_stage, Plan::load(s, NLOAD));
+                __builtin_amdgcn_sched_barrier(0); // this order is the order issued; also keeps the 8-byte reads of neighbouring blocks apart
+            }
         }
         // the next K-tile has landed (this wave's share; the barrier adds the others'), own reads done
         __builtin_amdgcn_s_waitcnt(WAIT_LANDED_LGKM0);
@@ -1168,10 +1178,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     auto fetch_one = [&](int kt, int stage, int t) { // load t of K-tile kt (clamped to the last one) -> that stage
         const int ktc = min(kt, all_kt - 1);
         const bool token = wave * NLOAD + t < TM / 16;
-        const uint8_t *base = (token ? g.a_tiles8 : g.w_tiles8) + (int64_t)ktc * T8_BLOCK;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + src_off[t]),
-                                         (__attribute__((address_space(3))) void *)(lds + stage * STAGE + (wave * NLOAD + t) * 1024), 16, 0,
-                                         0);
+        qllm_detail::copy_1k_to_lds(token ? g.a_tiles8 : g.w_tiles8, (uint32_t)(token ? a_blocks : w_blocks) * (uint32_t)all_kt * T8_BLOCK,
+                                    src_off[t], (uint32_t)ktc * T8_BLOCK, lds + stage * STAGE + (wave * NLOAD + t) * 1024);
     };
     auto fetch = [&](int kt, int stage) {
 #pragma unroll
@@ -1199,11 +1207,12 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
     __syncthreads();
 
-    constexpr int RING = MI, AHEAD = 2, PER_STEP = MI == 8 ? 2 : 1;
-    static_assert(MI % PER_STEP == 0 && (MI - 1) / PER_STEP > AHEAD - 1 && (MI - AHEAD) / PER_STEP > 0, "group plan");
-    v4i ar[RING], wr[2][NJ];
+    typedef KTilePlan<MI, NJ> Plan;
+    constexpr int AHEAD = Plan::AHEAD;
+    static_assert(NLOAD <= Plan::MOST_LOADS, "every load of a K-tile has its place");
+    v4i ar[MI], wr[2][NJ];
 #pragma unroll
-    for (int k = 0; k < RING; ++k) ar[k] = v4i{0, 0, 0, 0};
+    for (int k = 0; k < MI; ++k) ar[k] = v4i{0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < NJ; ++j) wr[0][j] = wr[1][j] = v4i{0, 0, 0, 0};
 
@@ -1212,24 +1221,20 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     auto k_tile = [&](auto parity, int kt) {
         constexpr int P = decltype(parity)::value;
         const uint8_t *cur = lds + stage * STAGE;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) wr[P][j] = *reinterpret_cast<const v4i *>(cur + (w_blk0 + j) * T8_BLOCK + 16 * lane);
-        __builtin_amdgcn_sched_barrier(0);
+        auto operand = [&](int blk) { return *reinterpret_cast<const v4i *>(cur + blk * T8_BLOCK + 16 * lane); };
 #pragma unroll
         for (int u = 0; u < MI; ++u) {
             const bool old = u < AHEAD;
             const int i = old ? MI - AHEAD + u : u - AHEAD;
-            if (u < NLOAD) fetch_one(kt + STAGES - 1, fetch_stage, u); // one load per group, not all at once
-            if (PER_STEP * u < MI) {
 #pragma unroll
-                for (int h = 0; h < PER_STEP; ++h)
-                    ar[PER_STEP * u + h] = *reinterpret_cast<const v4i *>(cur + (a_blk0 + PER_STEP * u + h) * T8_BLOCK + 16 * lane);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j) {
+                const int s = u * NJ + j;
                 acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wr[old ? 1 - P : P][j], ar[i], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                if (Plan::feature_read(s) >= 0) wr[P][Plan::feature_read(s)] = operand(w_blk0 + Plan::feature_read(s));
+                if (Plan::token_read(s) >= 0) ar[Plan::token_read(s)] = operand(a_blk0 + Plan::token_read(s));
+                if (Plan::load(s, NLOAD) >= 0) fetch_one(kt + STAGES - 1, fetch_stage, Plan::load(s, NLOAD));
+                __builtin_amdgcn_sched_barrier(0); // this order is the order issued
+            }
         }
         // the next K-tile has landed (this wave's share; the barrier adds the others'), own reads done
         __builtin_amdgcn_s_waitcnt(WAIT_LANDED_LGKM0);
