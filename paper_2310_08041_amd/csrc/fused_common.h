@@ -33,8 +33,9 @@ struct FusedArgs {
     int64_t row_bytes;
     float *alpha;
     int32_t *zero, *rowsum;
-    uint8_t *tiles8; // not null (6- and 8-bit codes): the codes leave in the layout of qllm_pack_tiles8 instead of packed rows
-    int32_t tiles8_kt; // its K-tiles per row
+    uint8_t *tiles; // not null: the codes leave in the layout of qllm_pack_tiles6 (4 bits) or qllm_pack_tiles8 instead of packed rows
+    int32_t tiles_kt; // its K-tiles per row
+    int32_t row_at; // 4 bits: where in LDS (dwords) the row is put together before it leaves
     // calibration variant
     float *absmax, *y_dump;
     int32_t n_dump;
@@ -66,21 +67,57 @@ __device__ __forceinline__ int32_t quant_code(float x, float inv, int32_t beta, 
     return (int32_t)fmin(fmax(q, 0.0), (double)QMAX);
 }
 
+// ---- TILES6, the operand layout of the FP6 path (see qllm_pack_tiles6): 32 packed 4-bit codes of a row -> what one lane of a
+// matrix-core operand read finds, its first 16 bytes and its last 8
+constexpr int TILES6_BLOCK = 1536, TILES6_X = 1024; // bytes per block of 16 rows and K-tile of 128 codes; where the last 8 bytes lie
+// Where they lie in the block for codes 32 q .. of row r.  Weights: in the order of the lanes, 16 q + r.  Activations are
+// written a row at a time, so there a row's bytes are neighbours, 64 and 32 of them, one request each to the caches
+// where the lanes' order makes four; the pieces of a row are swapped by its number so that an operand read from LDS
+// finds every lane on banks of its own (4.3 clocks per 16-byte read, 8.1 in plain order).
+__device__ __forceinline__ int tiles6_x(int r, int q) { return 64 * r + 16 * (q ^ (r >> 1 & 3)); }
+__device__ __forceinline__ int tiles6_y(int r, int q) { return TILES6_X + 32 * r + 8 * (q ^ (r >> 2)); }
+
+// 4 nibbles in bits 0..15 -> four 6-bit fields in bits 0..23
+__device__ __forceinline__ uint32_t spread4(uint32_t x)
+{
+    const uint32_t y = (x & 0xffu) | ((x & 0xff00u) << 4); // nibbles 0, 1 in bits 0..7; 2, 3 in bits 12..19
+    return (y & 0x00f00fu) | ((y & 0x0f00f0u) << 2);       // nibble k in bits 6 k .. 6 k + 3
+}
+
+struct Lane6 {
+    uint4 x;
+    uint2 y;
+};
+__device__ __forceinline__ Lane6 lane6(const uint4 &codes)
+{
+    const uint32_t w[4] = {codes.x, codes.y, codes.z, codes.w};
+    uint32_t s[8]; // eight pieces of 24 bits
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s[2 * i] = spread4(w[i] & 0xffffu);
+        s[2 * i + 1] = spread4(w[i] >> 16);
+    }
+    return Lane6{make_uint4(s[0] | (s[1] << 24), (s[1] >> 8) | (s[2] << 16), (s[2] >> 16) | (s[3] << 8), s[4] | (s[5] << 24)),
+                 make_uint2((s[5] >> 8) | (s[6] << 16), (s[6] >> 16) | (s[7] << 8))};
+}
+
 } // namespace qllm_detail
 
 // Launches the planned kernel (fused_planned.hip).  Returns QLLM_ERR_WORKSPACE if the shape or the
 // general groups are more than it holds on chip: the caller then takes the plain kernel.
 int32_t qllm_launch_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
-// The same for 6- and 8-bit codes with the codes written to a.tiles8 (fused_planned_tiles8.hip).
-int32_t qllm_launch_fused_tiles8(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
+// The same with the codes written to a.tiles (fused_planned_tiles.hip), where they fit (else the caller takes packed rows).
+bool qllm_fused_tiles_fit(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
+int32_t qllm_launch_fused_tiles(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 
-// qllm_norm_reassemble_quant with the choice of layout: tiles8 not null asks for the codes as qllm_pack_tiles8 lays them
-// out (rows past N in the last block of 16 are left as they are) in place of out->codes; *wrote_tiles8 says whether the
-// kernel that runs does that (the planned one, 6- and 8-bit codes); if not, out->codes holds the packed rows as ever.
+// qllm_norm_reassemble_quant with the choice of layout: tiles not null asks for the codes as qllm_pack_tiles6 (4 bits) or
+// qllm_pack_tiles8 lays them out (rows past N in the last block of 16 are left as they are) in place of out->codes;
+// *wrote_tiles says whether the kernel that runs does that (the planned one); if not, out->codes holds the packed rows as
+// ever.
 int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
-                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles8,
-                        bool *wrote_tiles8, void *hip_stream);
+                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
+                        bool *wrote_tiles, void *hip_stream);
 
 #endif

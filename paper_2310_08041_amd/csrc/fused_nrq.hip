@@ -510,10 +510,10 @@ int32_t fill_plan(FusedArgs &a, const qllm_map *map, int64_t C)
 } // namespace
 
 int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
-                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles8,
-                        bool *wrote_tiles8, void *hip_stream)
+                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
+                        bool *wrote_tiles, void *hip_stream)
 {
-    *wrote_tiles8 = false;
+    *wrote_tiles = false;
     int32_t rc = check_common(x, x_dtype, N, C, ldx, norm, gamma);
     if (rc != QLLM_OK) return rc;
     if (!map || !out) return QLLM_ERR_NULL;
@@ -543,11 +543,11 @@ int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, in
     const int max_units = a.S > a.n_groups_pad ? a.S : a.n_groups_pad;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     if (map->plan) {
-        if (tiles8 && bits != 4 && qllm_choose_fused_planned(a, x_dtype, bits) != QLLM_FUSED_WALKS_MAP) {
-            a.tiles8 = tiles8;
-            a.tiles8_kt = (int32_t)((map->C_out + 63) / 64);
-            *wrote_tiles8 = true;
-            return qllm_launch_fused_tiles8(a, x_dtype, bits, stream);
+        if (tiles && qllm_fused_tiles_fit(a, x_dtype, bits)) {
+            a.tiles = tiles;
+            a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (int32_t)((map->C_out + 63) / 64);
+            *wrote_tiles = true;
+            return qllm_launch_fused_tiles(a, x_dtype, bits, stream);
         }
         rc = qllm_launch_fused_planned(a, x_dtype, bits, stream);
         if (rc != QLLM_ERR_WORKSPACE) return rc; // does not fit on chip: the plain kernel below handles it
@@ -561,8 +561,8 @@ extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, in
                                               const qllm_map *map, int32_t bits, const qllm_qact *out,
                                               void *hip_stream)
 {
-    bool wrote_tiles8;
-    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles8, hip_stream);
+    bool wrote_tiles;
+    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles, hip_stream);
 }
 
 extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,

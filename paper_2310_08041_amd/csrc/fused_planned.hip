@@ -42,16 +42,16 @@
 
 using namespace qllm_detail;
 
-// This file is compiled twice: as it is (packed rows), and by fused_planned_tiles8.hip with QLLM_FUSED_TILES8 set, for the
-// kernels of 6- and 8-bit codes that write the byte layout of the GEMM instead.  One kernel with both store passes in it
-// takes longer for either (777 x 5000 8-bit 23.8 us in place of 21.8; 16 x 8192 decode +0.2).
-#ifndef QLLM_FUSED_TILES8
-#define QLLM_FUSED_TILES8 0
+// This file is compiled twice: as it is (packed rows), and by fused_planned_tiles.hip with QLLM_FUSED_TILES set, for the
+// kernels that write the codes in the layouts the GEMM reads instead.  One kernel with both store passes in it takes
+// longer for either (777 x 5000 8-bit 23.8 us in place of 21.8; 16 x 8192 decode +0.2).
+#ifndef QLLM_FUSED_TILES
+#define QLLM_FUSED_TILES 0
 #endif
 
 namespace {
 
-constexpr bool TILES8 = QLLM_FUSED_TILES8 != 0;
+constexpr bool TILES = QLLM_FUSED_TILES != 0;
 
 // work-list entries (see qllm_plan_map_host): kind << 30 | group << 17 | field
 constexpr int KIND_PLAIN = 0, KIND_COMP = 1, KIND_PAD = 2, KIND_NONE = 3;
@@ -364,7 +364,7 @@ __device__ __forceinline__ void store_group(uint8_t *out_row, int g, uint32_t w0
     }
 }
 
-// The same group in the byte layout of the GEMM (qllm_pack_tiles8): one byte per code, 8-bit codes XOR 0x80, places past K
+// A group in the byte layout of the GEMM (qllm_pack_tiles8): one byte per code, 8-bit codes XOR 0x80, places past K
 // zero bytes; `row_tiles`: the row's first byte in its block of 16 rows.  8 bytes per group, 16 of two neighbours
 // together, the 16 rows of a block interleaved: the rows that are worked on at one time are neighbours on one XCD (see
 // the kernel's first row), so that its L2 puts whole lines together.  For 6-bit codes one store where packed rows take
@@ -536,6 +536,9 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         dest = a.dest;
         segs = reinterpret_cast<const uint32_t *>(a.segs);
     }
+    // TILES6: the row before, packed, between its output groups and its way out
+    constexpr bool LAYS_ROW = TILES && BITS == 4;
+    uint32_t *whole_row = reinterpret_cast<uint32_t *>(lds) + a.row_at;
     __shared__ double red_d[2][16];
     __shared__ float red_f[32];
     __shared__ int32_t red_i[16];
@@ -556,9 +559,14 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     const XT *xbase = reinterpret_cast<const XT *>(a.x);
     Raw<XT> raw[ITERS];
     // Rows blockIdx, + grid, ...; where 16 rows share lines of the output, each XCD (workgroups go to them in turn) takes
-    // neighbouring rows of every sweep over the grid.
+    // whole blocks of 16 of every sweep over the grid, dealt out in turn, so that what is left for the last sweep is
+    // spread over the XCDs as well (a run of neighbours each: 2048 rows on 1280 workgroups leave three XCDs idle in the
+    // second sweep: 2048 x 4096 4-bit RMS 19.9 us, 16.8 so).
     int64_t row = blockIdx.x;
-    if (TILES8 && (gridDim.x & 7u) == 0) row = (int64_t)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (TILES && (gridDim.x & 7u) == 0) {
+        const uint32_t xcd = blockIdx.x & 7u, i = blockIdx.x >> 3, each = gridDim.x >> 3;
+        row = (each & 15u) == 0 ? (int64_t)(((i >> 4) * 8 + xcd) * 16 + (i & 15u)) : (int64_t)(xcd * each + i);
+    }
     if (PREFETCH && row < a.N) { // the first row
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
@@ -718,6 +726,20 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
             if (lane == 0) a.rowsum[r] = s;
         }
     };
+    // A finished row in the layout of the FP6 path (qllm_pack_tiles6): 16 + 8 bytes per 32 codes, from LDS, where its groups
+    // were put one by one.  (Each lane its own groups, a dword and a half-word of 6 bytes per group: 79 us at 2048 x 28672, more
+    // than the packed rows' 53 and the laying-out pass's 12; L2 takes requests, not bytes.)
+    auto lay_row = [&](int64_t r, int ltid) {
+        if constexpr (LAYS_ROW) {
+            uint8_t *block = a.tiles + (r >> 4) * a.tiles_kt * TILES6_BLOCK;
+            for (int j = ltid; j < 4 * a.tiles_kt; j += nt) {
+                const Lane6 v = lane6(reinterpret_cast<const uint4 *>(whole_row)[j]);
+                uint8_t *to = block + (j >> 2) * TILES6_BLOCK;
+                *reinterpret_cast<uint4 *>(to + tiles6_x((int)(r & 15), j & 3)) = v.x;
+                *reinterpret_cast<uint2 *>(to + tiles6_y((int)(r & 15), j & 3)) = v.y;
+            }
+        }
+    };
     // Eq. (2) for one value
     auto one_code = [&](float v, int32_t fast, float inv, int32_t beta) -> uint32_t {
         if (fast) {
@@ -788,9 +810,10 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     auto out_store = [&](OutState &o, int64_t prev, int ltid) {
         int32_t sum = 0;
         uint8_t *out_row = a.codes + prev * a.row_bytes;
-        uint8_t *row_tiles = TILES8 ? a.tiles8 + (prev >> 4) * a.tiles8_kt * 1024 + (prev & 15) * 16 : nullptr;
+        uint8_t *row_tiles = TILES ? a.tiles + (prev >> 4) * a.tiles_kt * 1024 + (prev & 15) * 16 : nullptr;
         auto put_group = [&](int gr, uint32_t v0, uint32_t v1) {
-            if constexpr (TILES8) store_group_tiles8<BITS>(row_tiles, a.tiles8_kt, a.C_out, gr, v0, v1);
+            if constexpr (LAYS_ROW) whole_row[gr] = v0;
+            else if constexpr (TILES) store_group_tiles8<BITS>(row_tiles, a.tiles_kt, a.C_out, gr, v0, v1);
             else store_group<BITS>(out_row, gr, v0, v1);
         };
         int g[ITERS];
@@ -931,8 +954,12 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         // ================= phase 2
         // ---- step a4, second half, of the row before: the words its output groups are made of are requested
         //      first and put together further down, after the dense arithmetic of this row
-        if constexpr (OUT_IN_PHASE_1) finish_rowsum(prev);
-        else out_read_work(o, ltid);
+        if constexpr (OUT_IN_PHASE_1) {
+            finish_rowsum(prev);
+            lay_row(prev, ltid);
+        } else {
+            out_read_work(o, ltid);
+        }
         // What a computed channel reads does not depend on the row's statistics: the first pass's entries and
         // the staged x, gamma (beta) of their sources are requested now and used after rstd is known.
         struct Staged {
@@ -1149,7 +1176,10 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         __syncthreads(); // also: the computed channels' values are complete
 
         // ================= phase 3
-        if constexpr (!OUT_IN_PHASE_1) finish_rowsum(prev);
+        if constexpr (!OUT_IN_PHASE_1) {
+            finish_rowsum(prev);
+            lay_row(prev, ltid);
+        }
         const bool code0 = ltid < a.n_dest;
         const float spec_v0 = code0 ? specv[ltid] : 0.0f; // first pass of the computed channels' codes:
         const int32_t spec_d0 = code0 ? dest[ltid] : 0;    // requested now, used after the range is known
@@ -1215,6 +1245,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         if (lane == 0) red_i[wave] = sum;
         __syncthreads();
         finish_rowsum(prev);
+        lay_row(prev, ltid);
     }
 }
 
@@ -1321,9 +1352,7 @@ int32_t dispatch_norm(const FusedArgs &a, const Shape &sh, size_t lds, bool stre
 template <typename XT>
 int32_t dispatch_bits(const FusedArgs &a, int bits, const Shape &sh, size_t lds, bool stream_lists, hipStream_t stream)
 {
-    if constexpr (!TILES8) {
-        if (bits == 4) return dispatch_norm<XT, 4>(a, sh, lds, stream_lists, stream);
-    }
+    if (bits == 4) return dispatch_norm<XT, 4>(a, sh, lds, stream_lists, stream);
     if (bits == 6) return dispatch_norm<XT, 6>(a, sh, lds, stream_lists, stream);
     return dispatch_norm<XT, 8>(a, sh, lds, stream_lists, stream);
 }
@@ -1365,16 +1394,28 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
 
 } // namespace
 
-#if QLLM_FUSED_TILES8
-int32_t qllm_launch_fused_tiles8(const FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream)
+#if QLLM_FUSED_TILES
+// 4-bit codes: the row in LDS comes on top of what the form and shape of packed rows need
+bool qllm_fused_tiles_fit(const FusedArgs &a, int32_t x_dtype, int32_t bits)
+{
+    const Choice c = choose(a, x_dtype, bits);
+    return c.kind != QLLM_FUSED_WALKS_MAP && (bits != 4 || (c.lds + 15) / 16 * 16 + (size_t)a.n_groups_pad * 4 <= MAX_LDS);
+}
+
+int32_t qllm_launch_fused_tiles(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)
 #else
 int32_t qllm_choose_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits) { return choose(a, x_dtype, bits).kind; }
 
-int32_t qllm_launch_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream)
+int32_t qllm_launch_fused_planned(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)
 #endif
 {
-    const Choice c = choose(a, x_dtype, bits);
+    FusedArgs a = planned;
+    Choice c = choose(a, x_dtype, bits);
     if (c.kind == QLLM_FUSED_WALKS_MAP) return QLLM_ERR_WORKSPACE;
+    if (TILES && bits == 4) {
+        a.row_at = (int32_t)((c.lds + 15) / 16 * 4);
+        c.lds = (size_t)a.row_at * 4 + (size_t)a.n_groups_pad * 4;
+    }
     const bool stream_lists = c.kind == QLLM_FUSED_LISTS_STREAMED;
     if (x_dtype == QLLM_BF16) return dispatch_bits<uint16_t>(a, bits, c.sh, c.lds, stream_lists, stream);
     return dispatch_bits<float>(a, bits, c.sh, c.lds, stream_lists, stream);

@@ -49,7 +49,7 @@ struct GemmArgs {
     int32_t splits;
     const uint8_t *a_tiles, *w_tiles; // both operands as 6-bit fields in matrix-core order (see TILES6 below), or null
     const uint8_t *a_tiles8, *w_tiles8; // both operands as bytes in matrix-core order (see TILES8 below), or null
-    bool a_laid; // a_tiles8 holds the activations already
+    bool a_laid; // a_tiles (a_tiles8) holds the activations already
     // A launch of the FP6 or the byte-operand kernel may cover the output features o_first .. O - 1 only (the call is
     // then two launches with different tiles, each with its own O); never together with acc_dump, whose rows are O long.
     int32_t o_first;
@@ -895,7 +895,8 @@ __device__ __forceinline__ TileAt tile_at(int nb, int ob)
 // 32768), hence a representable fp32 number, so no addition ever rounds.  64 acc is the int32
 // accumulator of Eq. (1), bit for bit.
 //
-// TILES6, the operand format (made once per weight by qllm_pack_tiles6, per call for the activations):
+// TILES6, the operand format (made once per weight by qllm_pack_tiles6, per call for the activations, whose blocks hold
+// the same bytes in another order, see tiles6_x in fused_common.h):
 // rows in blocks of 16, K in tiles of 128 codes; block b, K-tile t is the 1536 bytes at
 // (b * tiles + t) * 1536 and holds what the 64 lanes of one operand read need, lane l = 16 q + r having
 // row 16 b + r and codes 128 t + 32 q + e, e = 0..31, code e in bits 6 e .. 6 e + 3 of a 192-bit
@@ -911,7 +912,7 @@ __device__ __forceinline__ TileAt tile_at(int nb, int ob)
 // iteration starts with the last groups of the K-tile before, zeros the first time) and unrolled by two, so
 // that the alternation of the two feature-side register sets is static; KTilePlan has the order of reads and loads.
 typedef int v8i __attribute__((ext_vector_type(8)));
-constexpr int T6_BLOCK = 1536, T6_X = 1024, T6_KT = 128, T6_STAGES = 3;
+constexpr int T6_BLOCK = qllm_detail::TILES6_BLOCK, T6_X = qllm_detail::TILES6_X, T6_KT = 128, T6_STAGES = 3;
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 struct Frag6 {
@@ -919,11 +920,11 @@ struct Frag6 {
     v2i y;
 };
 __device__ __forceinline__ v8i operand6(const Frag6 &f) { return v8i{f.x[0], f.x[1], f.x[2], f.x[3], f.y[0], f.y[1], 0, 0}; }
-__device__ __forceinline__ Frag6 read6(const uint8_t *block, int lane)
+__device__ __forceinline__ Frag6 read6(const uint8_t *block, int x, int y)
 {
     Frag6 f;
-    f.x = *reinterpret_cast<const v4i *>(block + 16 * lane);
-    f.y = *reinterpret_cast<const v2i *>(block + T6_X + 8 * lane);
+    f.x = *reinterpret_cast<const v4i *>(block + x);
+    f.y = *reinterpret_cast<const v2i *>(block + y);
     return f;
 }
 
@@ -1021,6 +1022,7 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     for (int j = 0; j < NJ; ++j) wr[0][j] = wr[1][j] = Frag6{v4i{0, 0, 0, 0}, v2i{0, 0}};
 
     const int a_blk0 = wm * MI, w_blk0 = TM / 16 + wn * NJ; // the wave's first token-side and feature-side block of a stage
+    const int a_x = qllm_detail::tiles6_x(lane & 15, lane >> 4), a_y = qllm_detail::tiles6_y(lane & 15, lane >> 4);
     int stage = 0, fetch_stage = 2;
     // one K-tile, P = which feature-side register set it reads into (the other one still serves the
     // AHEAD groups left of the K-tile before)
@@ -1036,8 +1038,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
                 const int s = u * NJ + j;
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(operand6(wr[old ? 1 - P : P][j]), operand6(ar[i]),
                                                                              acc[i][j], 2, 2, 0, 0, 0, 0);
-                if (Plan::feature_read(s) >= 0) wr[P][Plan::feature_read(s)] = read6(cur + (w_blk0 + Plan::feature_read(s)) * T6_BLOCK, lane);
-                if (Plan::token_read(s) >= 0) ar[Plan::token_read(s)] = read6(cur + (a_blk0 + Plan::token_read(s)) * T6_BLOCK, lane);
+                if (Plan::feature_read(s) >= 0) wr[P][Plan::feature_read(s)] = read6(cur + (w_blk0 + Plan::feature_read(s)) * T6_BLOCK, 16 * lane, T6_X + 8 * lane);
+                if (Plan::token_read(s) >= 0) ar[Plan::token_read(s)] = read6(cur + (a_blk0 + Plan::token_read(s)) * T6_BLOCK, a_x, a_y);
                 // the K-tile two ahead, into the stage whose last reader passed the previous barrier
                 if (Plan::load(s, NLOAD) >= 0) fetch_one(kt + 2, fetch_stage, Plan::load(s, NLOAD));
                 __builtin_amdgcn_sched_barrier(0); // this order is the order issued; also keeps the 8-byte reads of neighbouring blocks apart
@@ -1099,14 +1101,8 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_w4a4_fp6_kerne
     }
 }
 
-// 4 nibbles in bits 0..15 -> four 6-bit fields in bits 0..23
-__device__ __forceinline__ uint32_t spread4(uint32_t x)
-{
-    const uint32_t y = (x & 0xffu) | ((x & 0xff00u) << 4); // nibbles 0, 1 in bits 0..7; 2, 3 in bits 12..19
-    return (y & 0x00f00fu) | ((y & 0x0f00f0u) << 2);       // nibble k in bits 6 k .. 6 k + 3
-}
-
-// Packed 4-bit rows -> TILES6; one lane per (block, K-tile, lane of the operand read).
+// Packed 4-bit rows -> TILES6; one lane per (block, K-tile, lane of the operand read).  BY_ROW: as activations lie.
+template <bool BY_ROW>
 __global__ __launch_bounds__(256) void tiles6_kernel(const uint8_t *codes, int64_t row_bytes, int32_t rows, int32_t n_kt,
                                                     uint8_t *tiles, int64_t n_items)
 {
@@ -1118,17 +1114,10 @@ __global__ __launch_bounds__(256) void tiles6_kernel(const uint8_t *codes, int64
     const int64_t row = b * 16 + r;
     uint4 p = make_uint4(0u, 0u, 0u, 0u);
     if (row < rows) p = *reinterpret_cast<const uint4 *>(codes + row * row_bytes + kt * (T6_KT / 2) + q * 16);
-    const uint32_t w[4] = {p.x, p.y, p.z, p.w};
-    uint32_t s[8]; // eight pieces of 24 bits
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        s[2 * i] = spread4(w[i] & 0xffffu);
-        s[2 * i + 1] = spread4(w[i] >> 16);
-    }
+    const qllm_detail::Lane6 v = qllm_detail::lane6(p);
     uint8_t *blk = tiles + bk * T6_BLOCK;
-    *reinterpret_cast<uint4 *>(blk + 16 * l) =
-        make_uint4(s[0] | (s[1] << 24), (s[1] >> 8) | (s[2] << 16), (s[2] >> 16) | (s[3] << 8), s[4] | (s[5] << 24));
-    *reinterpret_cast<uint2 *>(blk + T6_X + 8 * l) = make_uint2((s[5] >> 8) | (s[6] << 16), (s[6] >> 16) | (s[7] << 8));
+    *reinterpret_cast<uint4 *>(blk + (BY_ROW ? qllm_detail::tiles6_x(r, q) : 16 * l)) = v.x;
+    *reinterpret_cast<uint2 *>(blk + (BY_ROW ? qllm_detail::tiles6_y(r, q) : T6_X + 8 * l)) = v.y;
 }
 
 // ---- 6- and 8-bit codes (and 8-bit activations on 4-bit weights) straight from LDS into the int8 matrix cores.
@@ -1651,11 +1640,12 @@ TilePlan plan_tiles(int64_t N, int64_t O, bool may_split_launch)
 }
 
 // Packed 4-bit rows (device) -> TILES6 (device).
+template <bool BY_ROW>
 int32_t launch_tiles6(const uint8_t *codes, int64_t row_bytes, int64_t rows, int64_t Kpad, uint8_t *tiles, hipStream_t stream)
 {
     const int64_t n_kt = Kpad / T6_KT, n_items = (rows + 15) / 16 * n_kt * 64;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(tiles6_kernel, dim3((unsigned)((n_items + 255) / 256)), dim3(256), 0, stream, codes, row_bytes, (int32_t)rows,
+    hipLaunchKernelGGL(tiles6_kernel<BY_ROW>, dim3((unsigned)((n_items + 255) / 256)), dim3(256), 0, stream, codes, row_bytes, (int32_t)rows,
                        (int32_t)n_kt, tiles, n_items);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -1666,11 +1656,13 @@ int32_t launch_tiles6(const uint8_t *codes, int64_t row_bytes, int64_t rows, int
 }
 
 // 4-bit codes on both sides, more than 32 tokens, on the FP6 matrix cores: the activations are re-laid
-// into g.a_tiles first.
+// into g.a_tiles first, unless they are there already.
 int32_t launch_fp6(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipStream_t stream)
 {
-    const int32_t st = launch_tiles6(g.a_codes, g.a_row_bytes, g.N, g.Kpad, const_cast<uint8_t *>(g.a_tiles), stream);
-    if (st != QLLM_OK) return st;
+    if (!g.a_laid) {
+        const int32_t st = launch_tiles6<true>(g.a_codes, g.a_row_bytes, g.N, g.Kpad, const_cast<uint8_t *>(g.a_tiles), stream);
+        if (st != QLLM_OK) return st;
+    }
     auto launch_small = [&](const GemmArgs &ga) -> int32_t {
         const dim3 grid((unsigned)((ga.O - ga.o_first + 127) / 128), (unsigned)((ga.N + 127) / 128), (unsigned)(ga.splits > 1 ? ga.splits : 1));
         constexpr size_t lds = (size_t)T6_STAGES * 16 * T6_BLOCK + EPI_BYTES<128, 128>;
@@ -1902,7 +1894,7 @@ struct Route {
 };
 
 // tiles6, tiles8: that path has its two operands (the weight's copy and room for the activations').  parts8: parts of a
-// split K that the workspace holds on the byte-operand path.  a_laid: the activations are in tiles8 form already and
+// split K that the workspace holds on the byte-operand path.  a_laid: the activations are in tiles6 / tiles8 form already and
 // nowhere else.  one_launch: nothing that takes two.
 Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool tiles6, bool tiles8, int64_t parts8, bool a_laid, bool one_launch)
 {
@@ -2037,8 +2029,8 @@ int64_t parts8_that_fit(int64_t N, int64_t K, int64_t O, int64_t workspace_bytes
     return (workspace_bytes - parts8_at(N, K)) / (N * O * (int64_t)sizeof(int32_t));
 }
 
-// qllm_int_gemm; a_laid: the workspace already starts with the activations' bytes (tiles8 layout), and the byte-operand
-// path is the one that runs.
+// qllm_int_gemm; a_laid: the activations already lie where the workspace has them in tiles6 or tiles8 layout, and the
+// path that reads them there is the one that runs.
 int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy,
                  int32_t *acc_dump, void *workspace, int64_t workspace_bytes, bool a_laid, void *hip_stream)
 {
@@ -2083,10 +2075,10 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
         g.a_tiles = static_cast<const uint8_t *>(workspace) + tiles6_at(N, w->K, w->O);
         g.w_tiles = w->tiles6;
     }
+    g.a_laid = a_laid;
     if (tiles8) {
         g.a_tiles8 = static_cast<const uint8_t *>(workspace);
         g.w_tiles8 = w->tiles8;
-        g.a_laid = a_laid;
         g.partial = reinterpret_cast<int32_t *>(static_cast<uint8_t *>(workspace) + parts8_at(N, w->K));
     }
     g.small_zero = small_zero_bound(w->K, a_bits, wb);
@@ -2142,7 +2134,7 @@ extern "C" int32_t qllm_pack_tiles6(const uint8_t *codes, int64_t rows, int64_t 
     if ((reinterpret_cast<uintptr_t>(codes) & 15u) || (reinterpret_cast<uintptr_t>(tiles) & 15u)) return QLLM_ERR_ALIGN;
     if (rows == 0) return QLLM_OK;
     const int64_t Kpad = (K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD;
-    return launch_tiles6(codes, qllm_packed_row_bytes(K, 4), rows, Kpad, tiles, reinterpret_cast<hipStream_t>(hip_stream));
+    return launch_tiles6<false>(codes, qllm_packed_row_bytes(K, 4), rows, Kpad, tiles, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int64_t qllm_tiles8_bytes(int64_t rows, int64_t K)
@@ -2215,12 +2207,15 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     q.rowsum = reinterpret_cast<int32_t *>(p);
     p += up(N * 4);
     const int64_t left = workspace_bytes - (p - static_cast<uint8_t *>(workspace));
-    // Where the GEMM is going to read its activations as bytes in matrix-core order, the fused kernel writes them so:
-    // one launch and a pass over the codes less.
-    const bool tiles8 = N <= INT32_MAX && w->O > 0 && w->O <= INT32_MAX && has_room_for_tiles8(N, w, a_bits, p, left) &&
-                        !plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take;
+    // Where the GEMM is going to read its activations in matrix-core order, the fused kernel writes them so: one launch and
+    // a pass over the codes less.
+    uint8_t *tiles = nullptr;
+    if (N <= INT32_MAX && w->O > 0 && w->O <= INT32_MAX && !plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) {
+        if (has_room_for_tiles6(N, w, a_bits, p, left)) tiles = p + tiles6_at(N, w->K, w->O);
+        else if (has_room_for_tiles8(N, w, a_bits, p, left)) tiles = p;
+    }
     bool laid = false;
-    const int32_t rc = qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, tiles8 ? p : nullptr, &laid, hip_stream);
+    const int32_t rc = qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, tiles, &laid, hip_stream);
     if (rc != QLLM_OK) return rc;
     return int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, left, laid, hip_stream);
 }
