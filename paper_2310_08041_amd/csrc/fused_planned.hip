@@ -715,9 +715,14 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     __syncthreads();
 
     const uint32_t zero_at = (uint32_t)(GROUP * a.n_pub);
-    // `prev`: the row whose output groups are still to be stored.  At first the first row itself: its place in
-    // the output then receives codes made of whatever LDS holds, and the real ones one pass later.
+    // `prev`: the row whose output groups are still to be stored, once there is one (`started`).  Asked for row by row:
+    // in a launch of one row per workgroup the pass over nothing was a tenth of the kernel (fused kernel, us, without the
+    // question : with it: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 64 x 512 fp32 LayerNorm
+    // 6.36 : 6.08, 777 x 5000 fp32 8-bit 22.3 : 20.2, 4096 x 5120 29.8 : 28.8).  Not with five chunks per lane of two words,
+    // where the scheduler loses more by the branches (2048 x 28672 6-bit 57.4 : 58.9; 4-bit 61.9 : 60.8): there the first
+    // row's place in the output receives codes made of whatever LDS holds, and the real ones one pass later.
     int64_t prev = row;
+    bool started = ITERS == 5 && W == 2;
 
     // rowsum of a finished row: the waves' partial sums are complete once a barrier has passed
     auto finish_rowsum = [&](int64_t r) {
@@ -862,7 +867,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         // arithmetic instead of in one burst (a dozen wavefronts asking for 57 KB at once queue up in the address unit).
         OutState o;
         uint32_t slot[ITERS];
-        if constexpr (OUT_IN_PHASE_1) {
+        if (OUT_IN_PHASE_1 && started) {
             out_read_work(o, ltid);
             out_read_codes(o);
         }
@@ -929,7 +934,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
             }
         }
 
-        if constexpr (OUT_IN_PHASE_1) {
+        if (OUT_IN_PHASE_1 && started) {
             int32_t sum = out_store(o, prev, ltid);
             sum = wave_sum_i32(sum);
             if (lane == 0) red_i[wave] = sum;
@@ -955,9 +960,11 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         // ---- step a4, second half, of the row before: the words its output groups are made of are requested
         //      first and put together further down, after the dense arithmetic of this row
         if constexpr (OUT_IN_PHASE_1) {
-            finish_rowsum(prev);
-            lay_row(prev, ltid);
-        } else {
+            if (started) {
+                finish_rowsum(prev);
+                lay_row(prev, ltid);
+            }
+        } else if (started) {
             out_read_work(o, ltid);
         }
         // What a computed channel reads does not depend on the row's statistics: the first pass's entries and
@@ -1065,7 +1072,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
 
         // ---- step a4, second half, of the row before: its output groups put together and stored; the wavefront's
         //      share of that row's code sum goes through the same barrier as this row's min/max
-        if constexpr (!OUT_IN_PHASE_1) {
+        if (!OUT_IN_PHASE_1 && started) {
             out_read_codes(o);
             int32_t sum = out_store(o, prev, ltid);
             sum = wave_sum_i32(sum);
@@ -1176,7 +1183,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         __syncthreads(); // also: the computed channels' values are complete
 
         // ================= phase 3
-        if constexpr (!OUT_IN_PHASE_1) {
+        if (!OUT_IN_PHASE_1 && started) {
             finish_rowsum(prev);
             lay_row(prev, ltid);
         }
@@ -1232,6 +1239,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         // again behind its second
         if constexpr (OUT_IN_PHASE_1) __syncthreads(); // packed words and computed channels' codes complete
         prev = row;
+        started = true;
     }
     // the last row's output groups
     {
