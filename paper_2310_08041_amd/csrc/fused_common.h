@@ -36,6 +36,12 @@ struct FusedArgs {
     uint8_t *tiles; // not null: the codes leave in the layout of qllm_pack_tiles6 (4 bits) or qllm_pack_tiles8 instead of packed rows
     int32_t tiles_kt; // its K-tiles per row
     int32_t row_at; // 4 bits: where in LDS (dwords) the row is put together before it leaves
+    // Workgroups beyond the rows' read weights that the product after this kernel is going to need (see read_ahead)
+    const uint8_t *ahead;
+    int64_t ahead_total;    // bytes of the weights; 0: none of this
+    int32_t ahead_chunk;    // bytes of the weights per workgroup of the product, one chunk after the other
+    int32_t ahead_each;     // of every chunk so many bytes
+    int32_t row_groups;     // workgroups that have rows
     // calibration variant
     float *absmax, *y_dump;
     int32_t n_dump;
@@ -112,12 +118,18 @@ int32_t qllm_launch_fused_tiles(const qllm_detail::FusedArgs &a, int32_t x_dtype
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 
+// Weights of the product that follows: workgroup c of it reads bytes chunk * c .. of `base` and goes to XCD c % 8.
+struct WeightsAhead {
+    const uint8_t *base;
+    int64_t total, chunk;
+};
+
 // qllm_norm_reassemble_quant with the choice of layout: tiles not null asks for the codes as qllm_pack_tiles6 (4 bits) or
 // qllm_pack_tiles8 lays them out (rows past N in the last block of 16 are left as they are) in place of out->codes;
 // *wrote_tiles says whether the kernel that runs does that (the planned one); if not, out->codes holds the packed rows as
-// ever.
+// ever.  ahead: not null where the product's weights may be read into the caches on the side.
 int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
                         const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
-                        bool *wrote_tiles, void *hip_stream);
+                        bool *wrote_tiles, const WeightsAhead *ahead, void *hip_stream);
 
 #endif

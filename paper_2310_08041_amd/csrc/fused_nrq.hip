@@ -511,7 +511,7 @@ int32_t fill_plan(FusedArgs &a, const qllm_map *map, int64_t C)
 
 int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
                         const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
-                        bool *wrote_tiles, void *hip_stream)
+                        bool *wrote_tiles, const WeightsAhead *ahead, void *hip_stream)
 {
     *wrote_tiles = false;
     int32_t rc = check_common(x, x_dtype, N, C, ldx, norm, gamma);
@@ -543,6 +543,11 @@ int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, in
     const int max_units = a.S > a.n_groups_pad ? a.S : a.n_groups_pad;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     if (map->plan) {
+        if (ahead && ahead->chunk < INT32_MAX) {
+            a.ahead = ahead->base;
+            a.ahead_total = ahead->total;
+            a.ahead_chunk = (int32_t)ahead->chunk;
+        }
         if (tiles && qllm_fused_tiles_fit(a, x_dtype, bits)) {
             a.tiles = tiles;
             a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (int32_t)((map->C_out + 63) / 64);
@@ -562,7 +567,7 @@ extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, in
                                               void *hip_stream)
 {
     bool wrote_tiles;
-    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles, hip_stream);
+    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles, nullptr, hip_stream);
 }
 
 extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,

@@ -487,6 +487,35 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // position, and gamma / beta of a source are read from global memory by its channel number: a staged position IS
 // that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk (the upper halves of chunkw, whose
 // staging numbers this form has no use for).
+// A launch of few rows leaves most CUs idle for some microseconds while the product that follows waits to read its weights:
+// workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
+// kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and the product's workgroup c
+// finds its chunk where a workgroup of the same number modulo 8 has read it; where that does not hold, only time is
+// lost.  24 MB where at least every other CU is idle (layer, us, without : with: 100 x 5120 -> 27648 4 / 4 35.5 : 33.9, 70 x 4096 ->
+// 22016 20.8 : 20.3, 48 x 8192 -> 28672 8 / 8 56 : 53.3, 100 x 8192 -> 8192 6 / 6 29.9 : 29.2; 8 MB half of that, 28 MB no more); with
+// fewer the reading takes longer than the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5).
+__device__ __forceinline__ void read_ahead(const FusedArgs &a)
+{
+    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+    const uint32_t xcd = blockIdx.x & 7u, first = a.row_groups + ((xcd - (uint32_t)a.row_groups) & 7u); // this XCD's first such workgroup
+    const uint32_t groups = (gridDim.x - first + 7u) >> 3, waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t pieces = (uint32_t)a.ahead_each >> 10; // 1 KB each, of every chunk
+    const uint32_t n_chunks = (uint32_t)((a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk);
+    const uint32_t total = n_chunks > xcd ? (n_chunks - xcd + 7u) / 8u * pieces : 0u;
+    uint32_t p = ((blockIdx.x - first) >> 3) * waves + (threadIdx.x >> 6);
+    while (p < total) {
+        v4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u, p += groups * waves) {
+            const uint32_t q = p < total ? p : total - 1u, chunk = q / pieces;
+            const int64_t at = (int64_t)(chunk * 8u + xcd) * a.ahead_chunk + (int64_t)(q - chunk * pieces) * 1024 + lane * 16;
+            v[u] = *reinterpret_cast<const v4u *>(a.ahead + (at + 16 <= a.ahead_total ? at : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(v[u]));
+    }
+}
+
 template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
@@ -495,6 +524,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     constexpr int QMAX = (1 << BITS) - 1;
     constexpr uint32_t NOT_PUBLISHED = 0xffffffu;
     extern __shared__ __align__(16) float lds[];
+    if (blockIdx.x >= (uint32_t)a.row_groups) return read_ahead(a);
     const bool shift = LAYER && a.beta != nullptr;
     const int n_stage = GROUP * a.n_pub + 4;  // staged positions: the chunks that hold sources, then a zero
     const int goff = NORM != QLLM_NORM_NONE ? n_stage : 0, boff = goff + (shift ? n_stage : 0);
@@ -563,8 +593,9 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     // spread over the XCDs as well (a run of neighbours each: 2048 rows on 1280 workgroups leave three XCDs idle in the
     // second sweep: 2048 x 4096 4-bit RMS 19.9 us, 16.8 so).
     int64_t row = blockIdx.x;
-    if (TILES && (gridDim.x & 7u) == 0) {
-        const uint32_t xcd = blockIdx.x & 7u, i = blockIdx.x >> 3, each = gridDim.x >> 3;
+    const uint32_t row_groups = (uint32_t)a.row_groups;
+    if (TILES && (row_groups & 7u) == 0) {
+        const uint32_t xcd = blockIdx.x & 7u, i = blockIdx.x >> 3, each = row_groups >> 3;
         row = (each & 15u) == 0 ? (int64_t)(((i >> 4) * 8 + xcd) * 16 + (i & 15u)) : (int64_t)(xcd * each + i);
     }
     if (PREFETCH && row < a.N) { // the first row
@@ -855,7 +886,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         return sum;
     };
 
-    for (; row < a.N; row += gridDim.x) {
+    for (; row < a.N; row += row_groups) {
         // Addresses derived from the lane's number cost an instruction or two per row to recompute, but a
         // register each to keep: hide from the optimiser that the number does not change from row to row.
         int ltid = threadIdx.x;
@@ -910,7 +941,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         //      retire through one counter, and a wait for the row placed after those stores would wait for them too.
         double s0 = 0.0, s1 = 0.0;
         {
-            const int64_t next = row + gridDim.x, again = next < a.N ? next : row;
+            const int64_t next = row + row_groups, again = next < a.N ? next : row;
 #pragma unroll
             for (int it = 0; it < ITERS; ++it) {
                 if constexpr (PREFETCH) {
@@ -1274,6 +1305,7 @@ int cu_count()
 // What the runtime is asked once per kernel, workgroup size and LDS size and then remembered (no runtime
 // query sits between a caller's stream capture and the launch): the raised LDS limit and the number of
 // resident workgroups per CU.
+constexpr int64_t AHEAD_BYTES = 24000000; // of the L2s' 32 MB; see read_ahead
 constexpr int MAX_LDS = (int)qllm_detail::FUSED_MAX_LDS; // dynamic LDS a launch may ask for
 struct LaunchFacts {
     const void *kernel;
@@ -1284,8 +1316,20 @@ struct LaunchFacts {
 std::mutex facts_lock;
 std::vector<LaunchFacts> facts;
 
+// Workgroups that read weights ahead, and how much of every chunk: one per CU without a row.
+int32_t ahead_groups(FusedArgs &a)
+{
+    const int idle = cu_count() - a.row_groups;
+    if (a.ahead_total <= 0 || a.ahead_chunk <= 0 || idle < cu_count() / 2) return 0;
+    const int64_t chunks = (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk;
+    int64_t each = AHEAD_BYTES / chunks;
+    if (each > a.ahead_chunk) each = a.ahead_chunk;
+    a.ahead_each = (int32_t)(each / 1024 * 1024);
+    return a.ahead_each > 0 ? idle : 0;
+}
+
 template <typename K>
-int32_t launch(K kernel, const FusedArgs &a, const Shape &sh, size_t lds, hipStream_t stream)
+int32_t launch(K kernel, const FusedArgs &args, const Shape &sh, size_t lds, hipStream_t stream)
 {
     const void *fn = reinterpret_cast<const void *>(kernel);
     int per_cu = 0;
@@ -1314,7 +1358,10 @@ int32_t launch(K kernel, const FusedArgs &a, const Shape &sh, size_t lds, hipStr
         }
     }
     int64_t grid = (int64_t)cu_count() * per_cu;
-    if (grid > a.N) grid = a.N;
+    if (grid > args.N) grid = args.N;
+    FusedArgs a = args;
+    a.row_groups = (int32_t)grid;
+    grid += ahead_groups(a);
     (void)hipGetLastError();
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)sh.nt), lds, stream, a);
     const hipError_t e = hipGetLastError();

@@ -904,15 +904,19 @@ def test_reassembled_linear_w4a8_end_to_end(oracle, b, name, N, C, O, y_dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("N,C,K,O,norm,dtype,every,form", [
-    (517, 4096, 4096, 6144, "rms", "bf16", 40, 1),      # rows past a block of 16, whole K-tiles
-    (1030, 5000, 4999, 5000, "layer", "f32", 25, 1),    # places past K in the last K-tiles, fp32 rows
-    (700, 512, 301, 12288, "none", "bf16", 3, 1),       # more composite groups than plain ones
-    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2),  # lists streamed, K split over workgroups
-    (65, 8192, 8192, 20480, "rms", "bf16", 62, 1)])     # a row per workgroup
-def test_layer_lays_out_4bit_codes(b, N, C, K, O, norm, dtype, every, form):
-    """Where the product runs on the FP6 path the fused kernel of the layer call writes its operand layout itself: bit for
-    bit the result of the two entry points by themselves, packed rows and a launch that lays them out."""
+@pytest.mark.parametrize("N,C,K,O,norm,dtype,every,form,bits", [
+    (517, 4096, 4096, 6144, "rms", "bf16", 40, 1, 4),      # rows past a block of 16, whole K-tiles
+    (1030, 5000, 4999, 5000, "layer", "f32", 25, 1, 4),    # places past K in the last K-tiles, fp32 rows
+    (700, 512, 301, 12288, "none", "bf16", 3, 1, 4),       # more composite groups than plain ones
+    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2, 4),  # lists streamed, K split over workgroups
+    (65, 8192, 8192, 20480, "rms", "bf16", 62, 1, 4),      # a row per workgroup, the others read a part of every tile's weights
+    (128, 512, 301, 16500, "none", "bf16", 3, 1, 4),       # ... and all of them, the last tile ragged
+    (40, 512, 301, 16500, "none", "bf16", 3, 1, 8),
+    (128, 5000, 4999, 5000, "layer", "f32", 25, 1, 6)])
+def test_layer_lays_codes_out(b, N, C, K, O, norm, dtype, every, form, bits):
+    """Where the product runs on re-laid operands the fused kernel of the layer call writes the activations so itself, and
+    with few tokens reads weights ahead: bit for bit the result of the two entry points by themselves, packed rows and a
+    launch that lays them out."""
     import torch
     rng = np.random.default_rng(7)
     row_ptr, src, scale = random_csr_map(rng, C, K, every, longest=3)
@@ -920,17 +924,17 @@ def test_layer_lays_out_4bit_codes(b, N, C, K, O, norm, dtype, every, form):
     x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda()
     x = x if dtype == "f32" else x.bfloat16()
     gamma, beta = torch.rand(C, device="cuda") + 0.5, (torch.rand(C, device="cuda") if norm == "layer" else None)
-    assert b.qllm_fused_kernel_choice(dm, x.dtype, N, C, NORM_ID[norm], beta is not None, 4) == form
-    w = rng.integers(0, 16, (O, K), dtype=np.uint8)
-    dw = b.DeviceWeight(b.qllm_pack_codes_host(w, 4), rng.random(O).astype(np.float32), rng.integers(0, 16, O).astype(np.int32),
-                        w.astype(np.int64).sum(1).astype(np.int32), K, 4)
-    gws = torch.full((b.qllm_gemm_workspace_bytes(N, K, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
-    ws = torch.full((b.qllm_workspace_bytes(N, K, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
-    assert b.qllm_gemm_kernel_choice(dw, 4, N, gws.numel(), True)[0] == b.GEMM_FP6
+    assert b.qllm_fused_kernel_choice(dm, x.dtype, N, C, NORM_ID[norm], beta is not None, bits) == form
+    w = rng.integers(0, 1 << bits, (O, K), dtype=np.uint8)
+    dw = b.DeviceWeight(b.qllm_pack_codes_host(w, bits), rng.random(O).astype(np.float32), rng.integers(0, 16, O).astype(np.int32),
+                        w.astype(np.int64).sum(1).astype(np.int32), K, bits)
+    gws = torch.full((b.qllm_gemm_workspace_bytes(N, K, O, bits),), 0xAB, dtype=torch.uint8, device="cuda")
+    ws = torch.full((b.qllm_workspace_bytes(N, K, O, bits),), 0xAB, dtype=torch.uint8, device="cuda")
+    assert b.qllm_gemm_kernel_choice(dw, bits, N, gws.numel(), True)[0] == (b.GEMM_FP6 if bits == 4 else b.GEMM_BYTES)
     y, want = (torch.full((N, O), float("nan"), dtype=x.dtype, device="cuda") for _ in range(2))
-    b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, 4, dw, y, ws)
-    qa = b.DeviceQAct(N, K, 4)
-    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, 4, qa)
+    b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, bits, dw, y, ws)
+    qa = b.DeviceQAct(N, K, bits)
+    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, bits, qa)
     b.qllm_int_gemm(qa, dw, want, None, gws)
     assert torch.equal(y, want)
 
