@@ -196,6 +196,32 @@ def bench_matching(args, w, norm, dev):
     print(json.dumps(result))
 
 
+def laid_out_codes(b, dw, w, K, ws):
+    """[N, K] codes from the workspace of a layer call whose fused kernel laid them out for the product: behind the packed
+    rows and three values per token, 6 bits per code in blocks of 16 rows x 128 codes (a row's 64 + 32 bytes together,
+    their 16- and 8-byte pieces swapped by the row's number), or one byte per code in blocks of 16 x 64."""
+    import numpy as np
+    up = lambda v: (v + 255) // 256 * 256
+    at = up(w.N * b.qllm_packed_row_bytes(K, w.a_bits)) + 3 * up(4 * w.N)
+    kernel = b.qllm_gemm_kernel_choice(dw, w.a_bits, w.N, ws.size - at, True)[0]
+    blocks = (w.N + 15) // 16
+    r, q = np.arange(16)[:, None], np.arange(4)[None, :]
+    if kernel == b.GEMM_FP6:
+        at += up(b.qllm_gemm_workspace_floor_bytes(w.N, K, w.O, w.a_bits))
+        n = b.qllm_tiles6_bytes(w.N, K)
+        tiles = ws[at:at + n].reshape(blocks, -1, 1536)
+        x = (64 * r + 16 * (q ^ (r >> 1 & 3)))[..., None] + np.arange(16)
+        y = (1024 + 32 * r + 8 * (q ^ (r >> 2)))[..., None] + np.arange(8)
+        s = tiles[:, :, np.concatenate([x, y], -1)].reshape(blocks, -1, 16, 4, 8, 3)       # 3 bytes hold 4 codes
+        c = np.stack([s[..., 0] & 63, (s[..., 0] >> 6) | (s[..., 1] & 15) << 2, (s[..., 1] >> 4) | (s[..., 2] & 3) << 4, s[..., 2] >> 2], -1)
+    elif kernel == b.GEMM_BYTES:
+        tiles = ws[at:at + b.qllm_tiles8_bytes(w.N, K)].reshape(blocks, -1, 4, 16, 16)     # 16 codes of row r at 16 (16 q + r)
+        c = tiles.transpose(0, 1, 3, 2, 4) ^ (0x80 if w.a_bits == 8 else 0)
+    else:
+        return None
+    return c.reshape(blocks, c.shape[1], 16, -1).transpose(0, 2, 1, 3).reshape(blocks * 16, -1)[:w.N, :K]
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -344,7 +370,7 @@ def main():
     ms_per_step = wall * 1e3 / args.steps
     # what the timed launches wrote, kept for the parity check below (the instrumented pass writes ys again)
     ys_timed = [y.cpu() for y in ys[:min(N_ROTATE, args.steps)]]
-    ws_codes_timed = ws[:w.N * b.qllm_packed_row_bytes(K, w.a_bits)].cpu()      # activation codes of the last timed step
+    ws_timed = ws.cpu()                                                         # activation codes of the last timed step, in one of two forms
     last_buf = (args.steps - 1) % N_ROTATE
 
     # ---- instrumented pass: the same K steps as two calls with HIP events (recorded on the launch
@@ -577,8 +603,12 @@ def main():
             y_max_rel = max(y_max_rel, float((np.abs(got - ref["y"]) / den).max()))
             rows_checked += ns
         rows = (np.arange(ns) + last_buf) % w.N
-        got_codes = ws_codes_timed.numpy().reshape(w.N, -1)[rows]
-        codes_exact = bool(Ko == K and np.array_equal(got_codes, oracle.pack_codes(ref["codes"], w.a_bits, got_codes.shape[1])))
+        row_bytes = b.qllm_packed_row_bytes(K, w.a_bits)
+        got_codes = ws_timed[:w.N * row_bytes].numpy().reshape(w.N, -1)[rows]
+        codes_exact = bool(Ko == K and np.array_equal(got_codes, oracle.pack_codes(ref["codes"], w.a_bits, row_bytes)))
+        if not codes_exact and Ko == K:                            # not packed rows: the product's operand layout
+            laid = laid_out_codes(b, dw, w, K, ws_timed.numpy())
+            codes_exact = laid is not None and bool(np.array_equal(laid[rows], ref["codes"]))
         result["parity_checked"] = {"against": "the cpu_baseline oracle run (its own map and weights)",
                                     "maps_identical": bool(same_map), "timed_buffers": len(ys_timed),
                                     "token_rows_x_all_features": rows_checked, "y_bit_exact_bf16": bool(y_exact),
