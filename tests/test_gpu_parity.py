@@ -1150,6 +1150,29 @@ def test_calibration_with_eq5_matches_the_oracle(oracle, b):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("ldw", [20032, 37440, 40000])
+def test_match_nearest_rows_far_apart(b, ldw):
+    """Weight rows as 32-bit offsets (up to 4 GiB: 2.3 and 4.29 GB here) and as pointers beyond: the same members, bit for bit,
+    as from the same columns close together."""
+    import torch
+    C, O = 28672, 64
+    W = torch.randn((C, O), device="cuda")
+    far = torch.empty((C, ldw), device="cuda")[:, :O]
+    far.copy_(W)
+    y = torch.randn((32, C), device="cuda")
+    pick = torch.randperm(C - 1, device="cuda").int()
+    chan_a, chan_b = pick[:200].sort().values.contiguous(), pick[200:700].sort().values.contiguous()
+    chan_a[-1] = C - 1
+    ws = torch.empty(b.qllm_match_workspace_bytes(200, 500), dtype=torch.uint8, device="cuda")
+    got = []
+    for w in (W, far):
+        j, d = torch.empty(200, dtype=torch.int32, device="cuda"), torch.empty(200, dtype=torch.float64, device="cuda")
+        b.qllm_match_nearest(y, w, chan_a, chan_b, j, d, ws)
+        got.append((j, d))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("C,n,n_split,twins,integers", [(301, 40, 7, 3, False), (2048, 256, 30, 0, False), (130, 5, 4, 0, True)])
 def test_match_nearest_plain_l2(oracle, b, C, n, n_split, twins, integers):
     """W == NULL: nearest member of B under |x_i - x_j|^2, against the oracle's explicit differences.  With small
