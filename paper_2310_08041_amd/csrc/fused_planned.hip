@@ -749,11 +749,11 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     // `prev`: the row whose output groups are still to be stored, once there is one (`started`).  Asked for row by row:
     // in a launch of one row per workgroup the pass over nothing was a tenth of the kernel (fused kernel, us, without the
     // question : with it: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 64 x 512 fp32 LayerNorm
-    // 6.36 : 6.08, 777 x 5000 fp32 8-bit 22.3 : 20.2, 4096 x 5120 29.8 : 28.8).  Not with five chunks per lane of two words,
+    // 6.36 : 6.08, 777 x 5000 fp32 8-bit 22.3 : 20.2, 4096 x 5120 29.8 : 28.8).  Not with lists streamed, nor with five chunks per lane of two words,
     // where the scheduler loses more by the branches (2048 x 28672 6-bit 57.4 : 58.9; 4-bit 61.9 : 60.8): there the first
     // row's place in the output receives codes made of whatever LDS holds, and the real ones one pass later.
     int64_t prev = row;
-    bool started = ITERS == 5 && W == 2;
+    bool started = STREAM || (ITERS == 5 && W == 2);
 
     // rowsum of a finished row: the waves' partial sums are complete once a barrier has passed
     auto finish_rowsum = [&](int64_t r) {
@@ -1450,11 +1450,15 @@ Choice choose(const FusedArgs &a, int32_t x_dtype, int32_t bits)
 } // namespace
 
 #if QLLM_FUSED_TILES
-// 4-bit codes: the row in LDS comes on top of what the form and shape of packed rows need
+// 4-bit codes: the row in LDS comes on top of what the form and shape of packed rows need, and only with the lists in LDS:
+// the streamed form loses more than the laying-out pass takes, and so do longer fp32 rows (layer, 2048 tokens, us, packed
+// rows : laid out: 24576 bf16 RMS streamed 186 : 204, 16384 fp32 LayerNorm streamed 218 : 251, 14336 fp32 LayerNorm 128 : 136; 14336
+// bf16 RMS in LDS 89 : 76, 8192 fp32 LayerNorm 77 : 66).
 bool qllm_fused_tiles_fit(const FusedArgs &a, int32_t x_dtype, int32_t bits)
 {
     const Choice c = choose(a, x_dtype, bits);
-    return c.kind != QLLM_FUSED_WALKS_MAP && (bits != 4 || (c.lds + 15) / 16 * 16 + (size_t)a.n_groups_pad * 4 <= MAX_LDS);
+    if (bits != 4) return c.kind != QLLM_FUSED_WALKS_MAP;
+    return c.kind == QLLM_FUSED_LISTS_IN_LDS && (x_dtype == QLLM_BF16 || a.n_chunks <= 1024) && (c.lds + 15) / 16 * 16 + (size_t)a.n_groups_pad * 4 <= MAX_LDS;
 }
 
 int32_t qllm_launch_fused_tiles(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)

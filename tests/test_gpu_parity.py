@@ -908,7 +908,7 @@ def test_reassembled_linear_w4a8_end_to_end(oracle, b, name, N, C, O, y_dtype):
     (517, 4096, 4096, 6144, "rms", "bf16", 40, 1, 4),      # rows past a block of 16, whole K-tiles
     (1030, 5000, 4999, 5000, "layer", "f32", 25, 1, 4),    # places past K in the last K-tiles, fp32 rows
     (700, 512, 301, 12288, "none", "bf16", 3, 1, 4),       # more composite groups than plain ones
-    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2, 4),  # lists streamed, K split over workgroups
+    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2, 4),  # lists streamed (packed rows), K split over workgroups
     (65, 8192, 8192, 20480, "rms", "bf16", 62, 1, 4),      # a row per workgroup, the others read a part of every tile's weights
     (128, 512, 301, 16500, "none", "bf16", 3, 1, 4),       # ... and all of them, the last tile ragged
     (40, 512, 301, 16500, "none", "bf16", 3, 1, 8),
