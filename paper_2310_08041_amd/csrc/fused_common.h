@@ -124,12 +124,16 @@ struct WeightsAhead {
     int64_t total, chunk;
 };
 
-// qllm_norm_reassemble_quant with the choice of layout: tiles not null asks for the codes as qllm_pack_tiles6 (4 bits) or
+// qllm_norm_reassemble_quant in two halves, so that the layer call has checked all of its arguments before it launches anything.
+// The checks, and the arguments of the kernel (N == 0: none, nothing is to be launched).
+int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
+                           const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out,
+                           qllm_detail::FusedArgs *args);
+// The launch, with the choice of layout: tiles not null asks for the codes as qllm_pack_tiles6 (4 bits) or
 // qllm_pack_tiles8 lays them out (rows past N in the last block of 16 are left as they are) in place of out->codes;
 // *wrote_tiles says whether the kernel that runs does that (the planned one); if not, out->codes holds the packed rows as
 // ever.  ahead: not null where the product's weights may be read into the caches on the side.
-int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
-                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
-                        bool *wrote_tiles, const WeightsAhead *ahead, void *hip_stream);
+int32_t qllm_fused_run(const qllm_detail::FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,
+                       const WeightsAhead *ahead, void *hip_stream);
 
 #endif

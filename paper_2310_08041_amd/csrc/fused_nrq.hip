@@ -509,11 +509,9 @@ int32_t fill_plan(FusedArgs &a, const qllm_map *map, int64_t C)
 
 } // namespace
 
-int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
-                        const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, uint8_t *tiles,
-                        bool *wrote_tiles, const WeightsAhead *ahead, void *hip_stream)
+int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
+                           const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out, FusedArgs *args)
 {
-    *wrote_tiles = false;
     int32_t rc = check_common(x, x_dtype, N, C, ldx, norm, gamma);
     if (rc != QLLM_OK) return rc;
     if (!map || !out) return QLLM_ERR_NULL;
@@ -525,7 +523,7 @@ int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, in
     if (reinterpret_cast<uintptr_t>(out->codes) & 15u) return QLLM_ERR_ALIGN;
     if (N == 0) return QLLM_OK;
 
-    FusedArgs a{};
+    FusedArgs &a = *args;
     fill_input(a, x, x_dtype, N, C, ldx, norm, gamma, beta, eps);
     a.row_ptr = map->row_ptr;
     a.src = map->src;
@@ -540,9 +538,17 @@ int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, in
     a.alpha = out->scale;
     a.zero = out->zero;
     a.rowsum = out->rowsum;
+    return QLLM_OK;
+}
+
+int32_t qllm_fused_run(const FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,
+                       const WeightsAhead *ahead, void *hip_stream)
+{
+    FusedArgs a = prepared;
+    *wrote_tiles = false;
     const int max_units = a.S > a.n_groups_pad ? a.S : a.n_groups_pad;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    if (map->plan) {
+    if (a.work) {
         if (ahead && ahead->chunk < INT32_MAX) {
             a.ahead = ahead->base;
             a.ahead_total = ahead->total;
@@ -550,11 +556,11 @@ int32_t qllm_fused_into(const void *x, int32_t x_dtype, int64_t N, int64_t C, in
         }
         if (tiles && qllm_fused_tiles_fit(a, x_dtype, bits)) {
             a.tiles = tiles;
-            a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (int32_t)((map->C_out + 63) / 64);
+            a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
             *wrote_tiles = true;
             return qllm_launch_fused_tiles(a, x_dtype, bits, stream);
         }
-        rc = qllm_launch_fused_planned(a, x_dtype, bits, stream);
+        const int32_t rc = qllm_launch_fused_planned(a, x_dtype, bits, stream);
         if (rc != QLLM_ERR_WORKSPACE) return rc; // does not fit on chip: the plain kernel below handles it
     }
     if (x_dtype == QLLM_BF16) return dispatch_bits<uint16_t>(a, bits, max_units, stream);
@@ -566,8 +572,11 @@ extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, in
                                               const qllm_map *map, int32_t bits, const qllm_qact *out,
                                               void *hip_stream)
 {
+    FusedArgs a{};
+    const int32_t rc = qllm_fused_prepare(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, &a);
+    if (rc != QLLM_OK || N == 0) return rc;
     bool wrote_tiles;
-    return qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, bits, out, nullptr, &wrote_tiles, nullptr, hip_stream);
+    return qllm_fused_run(a, x_dtype, bits, nullptr, &wrote_tiles, nullptr, hip_stream);
 }
 
 extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,

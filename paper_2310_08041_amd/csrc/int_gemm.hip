@@ -2029,10 +2029,9 @@ int64_t parts8_that_fit(int64_t N, int64_t K, int64_t O, int64_t workspace_bytes
     return (workspace_bytes - parts8_at(N, K)) / (N * O * (int64_t)sizeof(int32_t));
 }
 
-// qllm_int_gemm; a_laid: the activations already lie where the workspace has them in tiles6 or tiles8 layout, and the
-// path that reads them there is the one that runs.
-int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy,
-                 int32_t *acc_dump, void *workspace, int64_t workspace_bytes, bool a_laid, void *hip_stream)
+// The arguments of qllm_int_gemm.
+int32_t check_product(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, const void *y, int32_t y_dtype, int64_t ldy,
+                      const void *workspace, int64_t workspace_bytes)
 {
     if (!a || !w || !y) return QLLM_ERR_NULL;
     if (!a->codes || !a->scale || !a->zero || !a->rowsum) return QLLM_ERR_NULL;
@@ -2050,6 +2049,23 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
         return QLLM_ERR_ALIGN;
     if (workspace_bytes < qllm_gemm_workspace_floor_bytes(N, w->K, w->O, a_bits)) return QLLM_ERR_WORKSPACE;
     if (N == 0) return QLLM_OK;
+    const bool ws_aligned = (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+    if (wb == 4 && k_splits(N, w->K, w->O, a_bits) > 1 && (!workspace || !ws_aligned)) return workspace ? QLLM_ERR_ALIGN : QLLM_ERR_WORKSPACE;
+    if (has_room_for_tiles6(N, w, a_bits, workspace, workspace_bytes) && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles6) & 15u)))
+        return QLLM_ERR_ALIGN;
+    if (has_room_for_tiles8(N, w, a_bits, workspace, workspace_bytes) && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles8) & 15u)))
+        return QLLM_ERR_ALIGN;
+    return QLLM_OK;
+}
+
+// qllm_int_gemm; a_laid: the activations already lie where the workspace has them in tiles6 or tiles8 layout, and the
+// path that reads them there is the one that runs.
+int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy,
+                 int32_t *acc_dump, void *workspace, int64_t workspace_bytes, bool a_laid, void *hip_stream)
+{
+    const int32_t rc = check_product(a, a_bits, N, w, y, y_dtype, ldy, workspace, workspace_bytes);
+    if (rc != QLLM_OK || N == 0) return rc;
+    const int32_t wb = w->bits;
 
     GemmArgs g{};
     g.a_codes = a->codes;
@@ -2061,12 +2077,8 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
     g.N = (int32_t)N; g.O = (int32_t)w->O; g.K = (int32_t)w->K;
     g.Kpad = (int32_t)((w->K + QLLM_K_PAD - 1) / QLLM_K_PAD * QLLM_K_PAD);
     g.y = y; g.ldy = ldy; g.acc_dump = acc_dump;
-    const bool ws_aligned = (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-    if (wb == 4 && k_splits(N, w->K, w->O, a_bits) > 1 && (!workspace || !ws_aligned)) return workspace ? QLLM_ERR_ALIGN : QLLM_ERR_WORKSPACE;
     const bool tiles6 = has_room_for_tiles6(N, w, a_bits, workspace, workspace_bytes);
     const bool tiles8 = has_room_for_tiles8(N, w, a_bits, workspace, workspace_bytes);
-    if (tiles6 && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles6) & 15u))) return QLLM_ERR_ALIGN;
-    if (tiles8 && (!ws_aligned || (reinterpret_cast<uintptr_t>(w->tiles8) & 15u))) return QLLM_ERR_ALIGN;
     const Route route = plan_route(N, w->K, w->O, a_bits, wb, tiles6, tiles8, tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
                                    a_laid, acc_dump != nullptr);
     g.splits = route.splits;
@@ -2083,7 +2095,7 @@ int32_t int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_weigh
     }
     g.small_zero = small_zero_bound(w->K, a_bits, wb);
     // finish_from_lds: sums that fit 24 bits (see there), no raw accumulators
-    const int64_t q_most = qa > qw ? qa : qw;
+    const int64_t q_most = (1 << (a_bits > wb ? a_bits : wb)) - 1;
     g.lds_epilogue = !acc_dump && q_most * w->K < (1 << 23) &&
                      (a_bits != 4 || wb != 4 || 225 * w->K < (1 << 24));
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
@@ -2218,18 +2230,24 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     q.rowsum = reinterpret_cast<int32_t *>(p);
     p += up(N * 4);
     const int64_t left = workspace_bytes - (p - static_cast<uint8_t *>(workspace));
+    // both halves' arguments before either is launched: a call that is refused touches nothing, the weights neither
+    qllm_detail::FusedArgs fused{};
+    int32_t rc = qllm_fused_prepare(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, &fused);
+    if (rc != QLLM_OK) return rc;
+    rc = check_product(&q, a_bits, N, w, y, y_dtype, ldy, p, left);
+    if (rc != QLLM_OK) return rc;
     // Where the GEMM is going to read its activations in matrix-core order, the fused kernel writes them so: one launch and
     // a pass over the codes less.
     uint8_t *tiles = nullptr;
     WeightsAhead ahead{nullptr, 0, 0};
-    if (N <= INT32_MAX && w->O > 0 && w->O <= INT32_MAX && !plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) {
+    if (!plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) {
         const bool tiles6 = has_room_for_tiles6(N, w, a_bits, p, left);
         if (tiles6) tiles = p + tiles6_at(N, w->K, w->O);
         else if (has_room_for_tiles8(N, w, a_bits, p, left)) tiles = p;
         if (tiles) ahead = weights_ahead(N, w, tiles6);
     }
     bool laid = false;
-    const int32_t rc = qllm_fused_into(x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, &q, tiles, &laid, ahead.base ? &ahead : nullptr, hip_stream);
+    rc = qllm_fused_run(fused, x_dtype, a_bits, tiles, &laid, ahead.base ? &ahead : nullptr, hip_stream);
     if (rc != QLLM_OK) return rc;
     return int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, left, laid, hip_stream);
 }

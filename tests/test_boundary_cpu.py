@@ -175,6 +175,31 @@ def test_tiles8_entry_points_reject_bad_arguments_before_launching():
     assert g(C.byref(q), 6, 64, C.byref(good), 0x9000, b.F32, 32, None, 0x4008, 1 << 20, None) == -6
 
 
+def test_layer_entry_point_refuses_what_the_product_refuses_before_launching():
+    """The layer's first kernel may read the weight's re-laid copy ahead of the product: what the product refuses is refused before
+    either kernel is launched (with a launch in front these calls fail in the runtime where there is no device)."""
+    m = b._Map(64, 64, 64, 0x1000, 0x1000, 0x1000)
+
+    def call(N, a_bits, w, y=0x9000, ydt=b.F32, ldy=4096):
+        return b.raw().qllm_reassembled_linear(0x1000, b.BF16, N, 64, 64, b.NORM_RMS, 0x2000, None, 1e-5, C.byref(m), a_bits, C.byref(w), y, ydt,
+                                               ldy, 0x40000, 1 << 24, None)
+
+    def weight(bits, **kw):
+        w = b._Weight(4096, 64, bits, 0x1000, 0x1000, 0x1000, 0x1000, 0x1000 if bits == 4 else None, None if bits == 4 else 0x1000)
+        for k, v in kw.items():
+            setattr(w, k, v)
+        return w
+
+    assert call(100, 4, weight(4, tiles6=0x5008)) == -6 and call(1024, 6, weight(6, tiles8=0x5004)) == -6   # copies not 16-byte aligned
+    assert call(100, 4, weight(4, codes=0x1008)) == -6
+    assert call(100, 4, weight(4, colsum=None)) == -1 and call(100, 4, weight(4), y=None) == -1
+    assert call(100, 4, weight(4), ydt=5) == -4 and call(100, 4, weight(4), ldy=4095) == -2
+    assert call(100, 4, weight(6)) == -3 and call(1024, 8, weight(6)) == -3                                  # no such pair of widths
+    # what the first half refuses comes first, as ever
+    assert b.raw().qllm_reassembled_linear(None, b.BF16, 100, 64, 64, b.NORM_RMS, 0x2000, None, 1e-5, C.byref(m), 4, C.byref(weight(4)),
+                                           0x9000, 5, 4096, 0x40000, 1 << 24, None) == -1
+
+
 def test_swiglu_entry_point_rejects_bad_arguments_before_launching():
     f = b.raw().qllm_swiglu
     G, U, X = 0x1000, 0x2000, 0x3000
