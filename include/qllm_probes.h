@@ -8,6 +8,8 @@
 
 #include <stdint.h>
 
+#include "qllm.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -25,6 +27,22 @@ extern "C" {
 int32_t qllm_probe_mfma(int32_t workgroups, int32_t iters, int32_t *sink, void *hip_stream);
 int32_t qllm_probe_mfma_fp6(int32_t workgroups, int32_t iters, float *sink, void *hip_stream);
 int32_t qllm_probe_stream(const void *src, void *dst, int64_t bytes, int32_t workgroups, void *hip_stream);
+
+/*
+ * What the fused kernel of qllm_reassembled_linear does for a map, a weight and N > 0 tokens (no launch; of the weight only O, K,
+ * bits and whether tiles6 / tiles8 are NULL are read, x is taken as 16-byte aligned with rows of ldx elements).
+ *   form             QLLM_FUSED_*
+ *   laid_out         1: it writes the codes as the product reads them, and the workspace's packed rows stay as they were
+ *   chunks_per_lane, lanes   the shape of a row's workgroup (0 where it walks the map)
+ *   ahead_bytes      how much of the weight's re-laid copy idle CUs read ahead of the product
+ * Errors: NULL / SHAPE / BITS / DTYPE / MAP / WORKSPACE.
+ */
+typedef struct {
+    int32_t form, laid_out, chunks_per_lane, lanes;
+    int64_t ahead_bytes;
+} qllm_layer_launch;
+int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta,
+                                int32_t a_bits, const qllm_weight *w, int64_t workspace_bytes, qllm_layer_launch *out);
 
 #ifdef __cplusplus
 }

@@ -46,6 +46,10 @@ class _QAct(C.Structure):
     _fields_ = [("codes", C.c_void_p), ("scale", C.c_void_p), ("zero", C.c_void_p), ("rowsum", C.c_void_p)]
 
 
+class _LayerLaunch(C.Structure):
+    _fields_ = [("form", C.c_int32), ("laid_out", C.c_int32), ("chunks_per_lane", C.c_int32), ("lanes", C.c_int32), ("ahead_bytes", C.c_int64)]
+
+
 _i64, _i32, _vp, _f = C.c_int64, C.c_int32, C.c_void_p, C.c_float
 _sigs = {
     "qllm_norm_reassemble_quant": (_i32, [_vp, _i32, _i64, _i64, _i64, _i32, _vp, _vp, _f, C.POINTER(_Map), _i32,
@@ -92,6 +96,7 @@ _sigs = {
     "qllm_probe_mfma": (_i32, [_i32, _i32, _vp, _vp]),
     "qllm_probe_mfma_fp6": (_i32, [_i32, _i32, _vp, _vp]),
     "qllm_probe_stream": (_i32, [_vp, _vp, _i64, _i32, _vp]),
+    "qllm_probe_layer_launch": (_i32, [C.POINTER(_Map), _i32, _i64, _i64, _i32, _i32, _i32, C.POINTER(_Weight), _i64, C.POINTER(_LayerLaunch)]),
 }
 EXPORTS = tuple(_sigs)
 for _name, (_res, _args) in _sigs.items():
@@ -675,6 +680,16 @@ def qllm_probe_mfma_fp6(workgroups, iters, sink, stream=None):
 def qllm_probe_stream(src, dst, workgroups, stream=None):
     _chk(_lib.qllm_probe_stream(_dp(src), _dp(dst), src.numel() * src.element_size(), int(workgroups), _stream(stream)),
          "qllm_probe_stream")
+
+
+def qllm_probe_layer_launch(dmap, x_dtype, N, ldx, norm, has_beta, a_bits, weight, workspace_bytes):
+    """What the fused kernel of qllm_reassembled_linear does: an object with form (FUSED_*), laid_out, chunks_per_lane, lanes, ahead_bytes."""
+    if not isinstance(x_dtype, int):
+        x_dtype = BF16 if "bfloat16" in str(x_dtype) else F32
+    out = _LayerLaunch()
+    _chk(_lib.qllm_probe_layer_launch(C.byref(dmap.c), int(x_dtype), int(N), int(ldx), int(norm), int(bool(has_beta)), int(a_bits),
+                                      C.byref(weight.c), int(workspace_bytes), C.byref(out)), "qllm_probe_layer_launch")
+    return out
 
 
 def raw():

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "qllm.h"
+#include "qllm_probes.h"
 
 extern "C" void qllm_note_hip_error(const char *step, const char *name);
 
@@ -115,6 +116,8 @@ int32_t qllm_launch_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dty
 // The same with the codes written to a.tiles (fused_planned_tiles.hip), where they fit (else the caller takes packed rows).
 bool qllm_fused_tiles_fit(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 int32_t qllm_launch_fused_tiles(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
+// The shape of the planned kernel's launch, and the bytes of a.ahead that it reads
+int64_t qllm_fused_ahead(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes);
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 
@@ -135,5 +138,10 @@ int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C,
 // ever.  ahead: not null where the product's weights may be read into the caches on the side.
 int32_t qllm_fused_run(const qllm_detail::FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,
                        const WeightsAhead *ahead, void *hip_stream);
+// As much of the arguments as the choice of a launch depends on, and that choice.
+int32_t qllm_fused_describe(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta, int32_t bits,
+                            qllm_detail::FusedArgs *args);
+int32_t qllm_fused_launch_facts(const qllm_detail::FusedArgs &described, int32_t x_dtype, int32_t bits, uint8_t *tiles,
+                                const WeightsAhead *ahead, qllm_layer_launch *out);
 
 #endif

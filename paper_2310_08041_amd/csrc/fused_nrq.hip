@@ -541,25 +541,34 @@ int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C,
     return QLLM_OK;
 }
 
+namespace {
+
+// What the layer call asks for, put into the arguments; whether the planned kernel lays the codes out.
+bool take_asks(FusedArgs &a, int32_t x_dtype, int32_t bits, uint8_t *tiles, const WeightsAhead *ahead)
+{
+    if (!a.work) return false;
+    if (ahead && ahead->chunk < INT32_MAX) {
+        a.ahead = ahead->base;
+        a.ahead_total = ahead->total;
+        a.ahead_chunk = (int32_t)ahead->chunk;
+    }
+    if (!tiles || !qllm_fused_tiles_fit(a, x_dtype, bits)) return false;
+    a.tiles = tiles;
+    a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
+    return true;
+}
+
+} // namespace
+
 int32_t qllm_fused_run(const FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,
                        const WeightsAhead *ahead, void *hip_stream)
 {
     FusedArgs a = prepared;
-    *wrote_tiles = false;
+    *wrote_tiles = take_asks(a, x_dtype, bits, tiles, ahead);
     const int max_units = a.S > a.n_groups_pad ? a.S : a.n_groups_pad;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+    if (*wrote_tiles) return qllm_launch_fused_tiles(a, x_dtype, bits, stream);
     if (a.work) {
-        if (ahead && ahead->chunk < INT32_MAX) {
-            a.ahead = ahead->base;
-            a.ahead_total = ahead->total;
-            a.ahead_chunk = (int32_t)ahead->chunk;
-        }
-        if (tiles && qllm_fused_tiles_fit(a, x_dtype, bits)) {
-            a.tiles = tiles;
-            a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
-            *wrote_tiles = true;
-            return qllm_launch_fused_tiles(a, x_dtype, bits, stream);
-        }
         const int32_t rc = qllm_launch_fused_planned(a, x_dtype, bits, stream);
         if (rc != QLLM_ERR_WORKSPACE) return rc; // does not fit on chip: the plain kernel below handles it
     }
@@ -579,8 +588,8 @@ extern "C" int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, in
     return qllm_fused_run(a, x_dtype, bits, nullptr, &wrote_tiles, nullptr, hip_stream);
 }
 
-extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,
-                                            int32_t has_beta, int32_t bits)
+int32_t qllm_fused_describe(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta, int32_t bits,
+                            FusedArgs *args)
 {
     if (!map) return QLLM_ERR_NULL;
     if (x_dtype != QLLM_F32 && x_dtype != QLLM_BF16) return QLLM_ERR_DTYPE;
@@ -589,13 +598,32 @@ extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype
     const int64_t C = map->C_in;
     if (N < 0 || N > INT32_MAX || C <= 0 || C > QLLM_MAX_CHANNELS || ldx < C || map->C_out <= 0 || map->C_out > QLLM_MAX_CHANNELS)
         return QLLM_ERR_SHAPE;
-    FusedArgs a{};
     // stand-ins for the buffers: 16-byte aligned, and only their being there or not matters here
     static const float present[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    fill_input(a, nullptr, x_dtype, N, C, ldx, norm, present, has_beta ? present : nullptr, 0.0f);
-    const int32_t rc = fill_plan(a, map, C);
-    if (rc != QLLM_OK) return rc;
-    return qllm_choose_fused_planned(a, x_dtype, bits);
+    fill_input(*args, nullptr, x_dtype, N, C, ldx, norm, present, has_beta ? present : nullptr, 0.0f);
+    args->C_out = (int32_t)map->C_out;
+    args->n_groups_pad = (int32_t)(qllm_packed_row_bytes(map->C_out, bits) * 8 / bits / GROUP);
+    return fill_plan(*args, map, C);
+}
+
+int32_t qllm_fused_launch_facts(const FusedArgs &described, int32_t x_dtype, int32_t bits, uint8_t *tiles, const WeightsAhead *ahead,
+                                qllm_layer_launch *out)
+{
+    FusedArgs a = described;
+    out->laid_out = take_asks(a, x_dtype, bits, tiles, ahead) ? 1 : 0;
+    out->form = qllm_choose_fused_planned(a, x_dtype, bits);
+    out->chunks_per_lane = out->lanes = 0;
+    out->ahead_bytes = 0;
+    if (out->form != QLLM_FUSED_WALKS_MAP) out->ahead_bytes = qllm_fused_ahead(a, x_dtype, bits, &out->chunks_per_lane, &out->lanes);
+    return QLLM_OK;
+}
+
+extern "C" int32_t qllm_fused_kernel_choice(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm,
+                                            int32_t has_beta, int32_t bits)
+{
+    FusedArgs a{};
+    const int32_t rc = qllm_fused_describe(map, x_dtype, N, ldx, norm, has_beta, bits, &a);
+    return rc != QLLM_OK ? rc : qllm_choose_fused_planned(a, x_dtype, bits);
 }
 
 extern "C" int32_t qllm_norm_channel_absmax(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx,

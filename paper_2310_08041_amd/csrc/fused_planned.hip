@@ -487,13 +487,12 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // position, and gamma / beta of a source are read from global memory by its channel number: a staged position IS
 // that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk (the upper halves of chunkw, whose
 // staging numbers this form has no use for).
+
 // A launch of few rows leaves most CUs idle for some microseconds while the product that follows waits to read its weights:
 // workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
 // kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and the product's workgroup c
-// finds its chunk where a workgroup of the same number modulo 8 has read it; where that does not hold, only time is
-// lost.  24 MB where at least every other CU is idle (layer, us, without : with: 100 x 5120 -> 27648 4 / 4 35.5 : 33.9, 70 x 4096 ->
-// 22016 20.8 : 20.3, 48 x 8192 -> 28672 8 / 8 56 : 53.3, 100 x 8192 -> 8192 6 / 6 29.9 : 29.2; 8 MB half of that, 28 MB no more); with
-// fewer the reading takes longer than the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5).
+// finds its chunk where a workgroup of the same number modulo 8 has read it; where that does not hold, it comes from the
+// cache behind the L2s all the same.  How much: see read_ahead_each.
 __device__ __forceinline__ void read_ahead(const FusedArgs &a)
 {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
@@ -1306,7 +1305,6 @@ int cu_count()
 // What the runtime is asked once per kernel, workgroup size and LDS size and then remembered (no runtime
 // query sits between a caller's stream capture and the launch): the raised LDS limit and the number of
 // resident workgroups per CU.
-constexpr int64_t AHEAD_BYTES = 24000000; // of the L2s' 32 MB; see read_ahead
 constexpr int MAX_LDS = (int)qllm_detail::FUSED_MAX_LDS; // dynamic LDS a launch may ask for
 struct LaunchFacts {
     const void *kernel;
@@ -1317,15 +1315,12 @@ struct LaunchFacts {
 std::mutex facts_lock;
 std::vector<LaunchFacts> facts;
 
-// Workgroups that read weights ahead, and how much of every chunk: one per CU without a row.
-int32_t ahead_groups(FusedArgs &a)
+// Workgroups that read weights ahead, one per CU without a row, and how much of every chunk (a.ahead_each).
+int32_t ahead_groups(FusedArgs &a, const Shape &sh)
 {
     const int idle = cu_count() - a.row_groups;
     if (a.ahead_total <= 0 || a.ahead_chunk <= 0 || idle < cu_count() / 2) return 0;
-    const int64_t chunks = (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk;
-    int64_t each = AHEAD_BYTES / chunks;
-    if (each > a.ahead_chunk) each = a.ahead_chunk;
-    a.ahead_each = (int32_t)(each / 1024 * 1024);
+    a.ahead_each = (int32_t)qllm_detail::read_ahead_each(a.ahead_total, a.ahead_chunk, (int64_t)idle * (sh.nt / 64));
     return a.ahead_each > 0 ? idle : 0;
 }
 
@@ -1362,7 +1357,7 @@ int32_t launch(K kernel, const FusedArgs &args, const Shape &sh, size_t lds, hip
     if (grid > args.N) grid = args.N;
     FusedArgs a = args;
     a.row_groups = (int32_t)grid;
-    grid += ahead_groups(a);
+    grid += ahead_groups(a, sh);
     (void)hipGetLastError();
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)sh.nt), lds, stream, a);
     const hipError_t e = hipGetLastError();
@@ -1465,6 +1460,16 @@ bool qllm_fused_tiles_fit(const FusedArgs &a, int32_t x_dtype, int32_t bits)
 int32_t qllm_launch_fused_tiles(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)
 #else
 int32_t qllm_choose_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits) { return choose(a, x_dtype, bits).kind; }
+
+int64_t qllm_fused_ahead(const FusedArgs &planned, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes)
+{
+    FusedArgs a = planned;
+    const Choice c = choose(a, x_dtype, bits);
+    *chunks_per_lane = c.sh.iters;
+    *lanes = c.sh.nt;
+    a.row_groups = a.N;
+    return ahead_groups(a, c.sh) > 0 ? (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk * a.ahead_each : 0;
+}
 
 int32_t qllm_launch_fused_planned(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)
 #endif

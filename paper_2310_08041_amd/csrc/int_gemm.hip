@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "qllm.h"
+#include "qllm_probes.h"
 #include "fused_common.h"
 #include "lds_copy.h"
 
@@ -2189,6 +2190,24 @@ WeightsAhead weights_ahead(int64_t N, const qllm_weight *w, bool tiles6)
     return WeightsAhead{w->tiles8, qllm_tiles8_bytes(w->O, w->K), qllm_tiles8_bytes(128, w->K)};
 }
 
+// What the layer call asks of the fused kernel beyond packed rows: where the product is going to read its activations in
+// matrix-core order, the fused kernel writes them so (one launch and a pass over the codes less), and with few tokens reads
+// the product's weights ahead.  p, left: the workspace behind the packed rows.
+struct LayerAsks {
+    uint8_t *tiles; // null: packed rows
+    WeightsAhead ahead;
+};
+LayerAsks layer_asks(int64_t N, const qllm_weight *w, int32_t a_bits, uint8_t *p, int64_t left)
+{
+    LayerAsks l{nullptr, {nullptr, 0, 0}};
+    if (plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) return l;
+    const bool tiles6 = has_room_for_tiles6(N, w, a_bits, p, left);
+    if (tiles6) l.tiles = p + tiles6_at(N, w->K, w->O);
+    else if (has_room_for_tiles8(N, w, a_bits, p, left)) l.tiles = p;
+    if (l.tiles) l.ahead = weights_ahead(N, w, tiles6);
+    return l;
+}
+
 } // namespace
 
 extern "C" int64_t qllm_workspace_floor_bytes(int64_t N, int64_t K, int64_t O, int32_t a_bits)
@@ -2236,20 +2255,28 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     if (rc != QLLM_OK) return rc;
     rc = check_product(&q, a_bits, N, w, y, y_dtype, ldy, p, left);
     if (rc != QLLM_OK) return rc;
-    // Where the GEMM is going to read its activations in matrix-core order, the fused kernel writes them so: one launch and
-    // a pass over the codes less.
-    uint8_t *tiles = nullptr;
-    WeightsAhead ahead{nullptr, 0, 0};
-    if (!plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) {
-        const bool tiles6 = has_room_for_tiles6(N, w, a_bits, p, left);
-        if (tiles6) tiles = p + tiles6_at(N, w->K, w->O);
-        else if (has_room_for_tiles8(N, w, a_bits, p, left)) tiles = p;
-        if (tiles) ahead = weights_ahead(N, w, tiles6);
-    }
+    const LayerAsks ask = layer_asks(N, w, a_bits, p, left);
     bool laid = false;
-    rc = qllm_fused_run(fused, x_dtype, a_bits, tiles, &laid, ahead.base ? &ahead : nullptr, hip_stream);
+    rc = qllm_fused_run(fused, x_dtype, a_bits, ask.tiles, &laid, ask.ahead.base ? &ask.ahead : nullptr, hip_stream);
     if (rc != QLLM_OK) return rc;
     return int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, left, laid, hip_stream);
+}
+
+extern "C" int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta,
+                                           int32_t a_bits, const qllm_weight *w, int64_t workspace_bytes, qllm_layer_launch *out)
+{
+    if (!map || !w || !out) return QLLM_ERR_NULL;
+    if (w->K != map->C_out || N <= 0) return QLLM_ERR_SHAPE;
+    const int64_t need = layer_workspace_floor(N, map->C_out, w->O, a_bits);
+    if (need < 0) return (int32_t)need;
+    if (workspace_bytes < need) return QLLM_ERR_WORKSPACE;
+    qllm_detail::FusedArgs fused{};
+    const int32_t rc = qllm_fused_describe(map, x_dtype, N, ldx, norm, has_beta, a_bits, &fused);
+    if (rc != QLLM_OK) return rc;
+    uint8_t *const some = reinterpret_cast<uint8_t *>(4096); // any address: only whether there is a workspace counts
+    auto up = [](int64_t v) { return (v + 255) / 256 * 256; };
+    const LayerAsks ask = layer_asks(N, w, a_bits, some, workspace_bytes - up(N * qllm_packed_row_bytes(w->K, a_bits)) - 3 * up(N * 4));
+    return qllm_fused_launch_facts(fused, x_dtype, a_bits, ask.tiles, ask.ahead.base ? &ask.ahead : nullptr, out);
 }
 
 // ---- the layer for callers that cannot allocate: its workspace is a device array of this library

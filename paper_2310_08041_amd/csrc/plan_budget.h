@@ -69,6 +69,28 @@ inline Shape pick_shape(int64_t units, bool more_rows_than_cus, bool layer_norm,
     return best;
 }
 
+// How many bytes of every chunk of the product's weights the idle CUs of the fused launch read ahead (a chunk per workgroup of
+// the product).  24 MB of the L2s' 32, and no more than four times what the reading wavefronts have in flight at once (4 KB each):
+// they have the lanes of a row's workgroup, and a short row is done in the time of some four trips to memory; what is still
+// being read then holds the product up.  Layer, us, no reading : 24 MB whatever the row : four trips (weights in the cache
+// behind the L2s / not):
+//   512 -> 27648, 128 tokens 8 / 8       13.1 : 21.3 : 12.7    14.0 : 26.5 : 13.7     (64 lanes)
+//   1024 -> 27648, 128 tokens 6 / 6      15.8 : 22.5 : 15.4    16.9 : 28.3 : 16.5
+//   5120 -> 11008, 100 tokens 6 / 6      26.1 : 26.1 : 25.6    32.9 : 30.6 : 29.9     (K in two parts, 86 columns of tiles)
+//   4096 -> 20500, 100 tokens 4 / 4      22.1 : 21.3 : 21.2    27.8 : 27.2 : 27.0
+//   13824 -> 8192, 40 tokens 8 / 4       32.8 : 34.2 : 34.0    (the worst of 351 shapes in cache; none loses more than 2 % out of it)
+// Geometric mean over 351 shapes (33-128 tokens, 512-16384 channels, 4096-28672 features): 1.019 and 1.040 of no reading.  Where
+// K is split and the columns of tiles are not a multiple of 8, most workgroups of the product find their weights on another
+// XCD, and still gain: 1.016 and 1.045 over 32 of those shapes.  With fewer idle CUs than rows the reading takes longer than
+// the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5): there is none.
+constexpr int64_t READ_AHEAD_BYTES = 24000000, READ_AHEAD_TRIPS = 4, READ_AHEAD_IN_FLIGHT = 4096;
+inline int64_t read_ahead_each(int64_t total, int64_t chunk, int64_t waves)
+{
+    const int64_t chunks = (total + chunk - 1) / chunk, trips = READ_AHEAD_TRIPS * READ_AHEAD_IN_FLIGHT * waves;
+    const int64_t each = (trips < READ_AHEAD_BYTES ? trips : READ_AHEAD_BYTES) / chunks;
+    return (each < chunk ? each : chunk) / 1024 * 1024;
+}
+
 } // namespace qllm_detail
 
 #endif

@@ -505,6 +505,41 @@ def test_gemm_kernel_choice_of_tiles_and_parts():
             gemm_choice(**args)
 
 
+def layer_launch(N, K, O, a_bits, w_bits, dt=b.BF16, norm=b.NORM_RMS, every=100, workspace_bytes=1 << 40, copies=True):
+    row_ptr, src, scale = random_csr_map(np.random.default_rng(3), K, K, every, longest=3)
+    m = host_map(row_ptr, src, scale, K, b.qllm_plan_map_host(row_ptr, src, scale, K)[0])
+    w = b._Weight(O, K, w_bits, 0x1000, 0x1000, 0x1000, 0x1000, 0x1000 if copies and (a_bits, w_bits) == (4, 4) else None,
+                  0x1000 if copies and a_bits != 4 else None)
+    return b.qllm_probe_layer_launch(m, dt, N, K, norm, False, a_bits, types.SimpleNamespace(c=w), workspace_bytes)
+
+
+@pytest.mark.parametrize("N,K,O,bits", [(128, 512, 27648, (8, 8)), (128, 512, 27648, (4, 4)), (100, 1024, 27648, (6, 6)), (100, 1024, 20500, (8, 4)),
+                                        (70, 2048, 20500, (4, 4)), (100, 4096, 27648, (4, 4)), (100, 5120, 27648, (4, 4)), (48, 8192, 28672, (8, 8)),
+                                        (100, 5120, 11008, (6, 6))])
+def test_weights_read_ahead_fit_behind_the_rows(N, K, O, bits):
+    """The wavefronts that read weights ahead have the lanes of a row's workgroup: no more than four times the 4 KB that each has
+    in flight, 24 MB, and every workgroup of the product its own share.  (24 MB whatever the row doubled the time of a
+    layer of 512 channels.)"""
+    f = layer_launch(N, K, O, *bits)
+    assert f.laid_out and f.lanes * f.chunks_per_lane * 8 >= K
+    nb = (b.qllm_tiles6_bytes if bits == (4, 4) else b.qllm_tiles8_bytes)(O, K)
+    chunk = (b.qllm_tiles6_bytes if bits == (4, 4) else b.qllm_tiles8_bytes)(128, K)
+    chunks = -(-nb // chunk)
+    most = min(24000000, 4 * 4096 * (256 - N) * f.lanes // 64)
+    assert f.ahead_bytes == chunks * (min(most // chunks, chunk) // 1024 * 1024) and f.ahead_bytes <= most
+
+
+def test_weights_are_read_ahead_only_where_most_cus_are_idle():
+    assert layer_launch(128, 5120, 27648, 4, 4).ahead_bytes > 0
+    assert layer_launch(129, 5120, 27648, 4, 4).ahead_bytes == 0 and layer_launch(129, 5120, 27648, 4, 4).laid_out
+    assert layer_launch(64, 5120, 27648, 4, 4).ahead_bytes == 0                       # the streaming kernel follows
+    assert layer_launch(100, 5120, 27648, 4, 4, copies=False).ahead_bytes == 0        # a kernel that expands packed codes follows
+    floor = b.qllm_workspace_floor_bytes(100, 5120, 27648, 4)
+    assert layer_launch(100, 5120, 27648, 4, 4, workspace_bytes=floor).ahead_bytes == 0
+    with pytest.raises(b.QllmError):
+        layer_launch(100, 5120, 27648, 4, 4, workspace_bytes=floor - 1)
+
+
 @pytest.mark.parametrize("name,N,C,O", [("tiny", 64, 512, 96), ("llama7b_qkv", 48, 1000, 40),
                                         ("llama70b_down", 32, 2050, 24), ("llama70b_q_decode", 16, 777, 33)])
 def test_host_helpers_match_the_oracle(oracle, name, N, C, O):
