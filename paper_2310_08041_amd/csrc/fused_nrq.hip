@@ -543,18 +543,17 @@ int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C,
 
 namespace {
 
-// What the layer call asks for, put into the arguments; whether the planned kernel lays the codes out.
+// What the layer call asks for, put into the arguments where the planned kernel lays the codes out; whether it does.
 bool take_asks(FusedArgs &a, int32_t x_dtype, int32_t bits, uint8_t *tiles, const WeightsAhead *ahead)
 {
-    if (!a.work) return false;
+    if (!a.work || !tiles || !qllm_fused_tiles_fit(a, x_dtype, bits)) return false;
+    a.tiles = tiles;
+    a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
     if (ahead && ahead->chunk < INT32_MAX) {
         a.ahead = ahead->base;
         a.ahead_total = ahead->total;
         a.ahead_chunk = (int32_t)ahead->chunk;
     }
-    if (!tiles || !qllm_fused_tiles_fit(a, x_dtype, bits)) return false;
-    a.tiles = tiles;
-    a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
     return true;
 }
 

@@ -492,7 +492,8 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
 // kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and the product's workgroup c
 // finds its chunk where a workgroup of the same number modulo 8 has read it; where that does not hold, it comes from the
-// cache behind the L2s all the same.  How much: see read_ahead_each.
+// cache behind the L2s all the same.  How much: see read_ahead_each.  Not in the kernels of packed rows, which mostly go without:
+// the question and its arguments alone cost them 1.3 % (geometric mean over 2300 launches of 1-4096 rows).
 __device__ __forceinline__ void read_ahead(const FusedArgs &a)
 {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
@@ -523,7 +524,9 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     constexpr int QMAX = (1 << BITS) - 1;
     constexpr uint32_t NOT_PUBLISHED = 0xffffffu;
     extern __shared__ __align__(16) float lds[];
-    if (blockIdx.x >= (uint32_t)a.row_groups) return read_ahead(a);
+    if constexpr (TILES) {
+        if (blockIdx.x >= (uint32_t)a.row_groups) return read_ahead(a);
+    }
     const bool shift = LAYER && a.beta != nullptr;
     const int n_stage = GROUP * a.n_pub + 4;  // staged positions: the chunks that hold sources, then a zero
     const int goff = NORM != QLLM_NORM_NONE ? n_stage : 0, boff = goff + (shift ? n_stage : 0);
@@ -592,7 +595,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     // spread over the XCDs as well (a run of neighbours each: 2048 rows on 1280 workgroups leave three XCDs idle in the
     // second sweep: 2048 x 4096 4-bit RMS 19.9 us, 16.8 so).
     int64_t row = blockIdx.x;
-    const uint32_t row_groups = (uint32_t)a.row_groups;
+    const uint32_t row_groups = TILES ? (uint32_t)a.row_groups : gridDim.x;
     if (TILES && (row_groups & 7u) == 0) {
         const uint32_t xcd = blockIdx.x & 7u, i = blockIdx.x >> 3, each = row_groups >> 3;
         row = (each & 15u) == 0 ? (int64_t)(((i >> 4) * 8 + xcd) * 16 + (i & 15u)) : (int64_t)(xcd * each + i);
@@ -1357,7 +1360,7 @@ int32_t launch(K kernel, const FusedArgs &args, const Shape &sh, size_t lds, hip
     if (grid > args.N) grid = args.N;
     FusedArgs a = args;
     a.row_groups = (int32_t)grid;
-    grid += ahead_groups(a, sh);
+    if constexpr (TILES) grid += ahead_groups(a, sh);
     (void)hipGetLastError();
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)sh.nt), lds, stream, a);
     const hipError_t e = hipGetLastError();

@@ -534,6 +534,8 @@ def test_weights_are_read_ahead_only_where_most_cus_are_idle():
     assert layer_launch(129, 5120, 27648, 4, 4).ahead_bytes == 0 and layer_launch(129, 5120, 27648, 4, 4).laid_out
     assert layer_launch(64, 5120, 27648, 4, 4).ahead_bytes == 0                       # the streaming kernel follows
     assert layer_launch(100, 5120, 27648, 4, 4, copies=False).ahead_bytes == 0        # a kernel that expands packed codes follows
+    f = layer_launch(100, 28032, 16384, 4, 4, norm=b.NORM_LAYER)                      # packed rows: those kernels go without
+    assert (f.form, f.laid_out, f.ahead_bytes) == (b.FUSED_LISTS_STREAMED, 0, 0)
     floor = b.qllm_workspace_floor_bytes(100, 5120, 27648, 4)
     assert layer_launch(100, 5120, 27648, 4, 4, workspace_bytes=floor).ahead_bytes == 0
     with pytest.raises(b.QllmError):
