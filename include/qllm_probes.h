@@ -34,11 +34,12 @@ int32_t qllm_probe_stream(const void *src, void *dst, int64_t bytes, int32_t wor
  *   form             QLLM_FUSED_*
  *   laid_out         1: it writes the codes as the product reads them, and the workspace's packed rows stay as they were
  *   chunks_per_lane, lanes   the shape of a row's workgroup (0 where it walks the map)
+ *   empty_pass       1: every workgroup puts out a row of nothing before its first one
  *   ahead_bytes      how much of the weight's re-laid copy idle CUs read ahead of the product
  * Errors: NULL / SHAPE / BITS / DTYPE / MAP / WORKSPACE.
  */
 typedef struct {
-    int32_t form, laid_out, chunks_per_lane, lanes;
+    int32_t form, laid_out, chunks_per_lane, lanes, empty_pass;
     int64_t ahead_bytes;
 } qllm_layer_launch;
 int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta,

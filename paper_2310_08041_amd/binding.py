@@ -47,7 +47,8 @@ class _QAct(C.Structure):
 
 
 class _LayerLaunch(C.Structure):
-    _fields_ = [("form", C.c_int32), ("laid_out", C.c_int32), ("chunks_per_lane", C.c_int32), ("lanes", C.c_int32), ("ahead_bytes", C.c_int64)]
+    _fields_ = [("form", C.c_int32), ("laid_out", C.c_int32), ("chunks_per_lane", C.c_int32), ("lanes", C.c_int32), ("empty_pass", C.c_int32),
+                ("ahead_bytes", C.c_int64)]
 
 
 _i64, _i32, _vp, _f = C.c_int64, C.c_int32, C.c_void_p, C.c_float
@@ -683,7 +684,7 @@ def qllm_probe_stream(src, dst, workgroups, stream=None):
 
 
 def qllm_probe_layer_launch(dmap, x_dtype, N, ldx, norm, has_beta, a_bits, weight, workspace_bytes):
-    """What the fused kernel of qllm_reassembled_linear does: an object with form (FUSED_*), laid_out, chunks_per_lane, lanes, ahead_bytes."""
+    """What the fused kernel of qllm_reassembled_linear does: an object with form (FUSED_*), laid_out, chunks_per_lane, lanes, empty_pass, ahead_bytes."""
     if not isinstance(x_dtype, int):
         x_dtype = BF16 if "bfloat16" in str(x_dtype) else F32
     out = _LayerLaunch()

@@ -116,8 +116,8 @@ int32_t qllm_launch_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dty
 // The same with the codes written to a.tiles (fused_planned_tiles.hip), where they fit (else the caller takes packed rows).
 bool qllm_fused_tiles_fit(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 int32_t qllm_launch_fused_tiles(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, hipStream_t stream);
-// The shape of the planned kernel's launch, and the bytes of a.ahead that it reads
-int64_t qllm_fused_ahead(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes);
+// The shape of the planned kernel's launch, whether it begins with an empty output pass, and the bytes of a.ahead that it reads
+int64_t qllm_fused_ahead(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes, int32_t *empty_pass);
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 

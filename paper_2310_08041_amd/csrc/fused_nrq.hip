@@ -611,9 +611,9 @@ int32_t qllm_fused_launch_facts(const FusedArgs &described, int32_t x_dtype, int
     FusedArgs a = described;
     out->laid_out = take_asks(a, x_dtype, bits, tiles, ahead) ? 1 : 0;
     out->form = qllm_choose_fused_planned(a, x_dtype, bits);
-    out->chunks_per_lane = out->lanes = 0;
+    out->chunks_per_lane = out->lanes = out->empty_pass = 0;
     out->ahead_bytes = 0;
-    if (out->form != QLLM_FUSED_WALKS_MAP) out->ahead_bytes = qllm_fused_ahead(a, x_dtype, bits, &out->chunks_per_lane, &out->lanes);
+    if (out->form != QLLM_FUSED_WALKS_MAP) out->ahead_bytes = qllm_fused_ahead(a, x_dtype, bits, &out->chunks_per_lane, &out->lanes, &out->empty_pass);
     return QLLM_OK;
 }
 

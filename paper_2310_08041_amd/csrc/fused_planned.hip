@@ -516,7 +516,8 @@ __device__ __forceinline__ void read_ahead(const FusedArgs &a)
     }
 }
 
-template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false>
+template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false,
+          bool EMPTY_PASS = qllm_detail::fused_empty_pass(TILES, sizeof(XT) == 4, NORM == QLLM_NORM_LAYER, BITS, ITERS, FULL, STREAM)>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
     constexpr bool LAYER = NORM == QLLM_NORM_LAYER, RMS = NORM == QLLM_NORM_RMS;
@@ -748,15 +749,10 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     __syncthreads();
 
     const uint32_t zero_at = (uint32_t)(GROUP * a.n_pub);
-    // `prev`: the row whose output groups are still to be stored, once there is one (`started`).  Asked for row by row:
-    // in a launch of one row per workgroup the pass over nothing was a tenth of the kernel (fused kernel, us, without the
-    // question : with it: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 64 x 512 fp32 LayerNorm
-    // 6.36 : 6.08, 777 x 5000 fp32 8-bit 22.3 : 20.2, 4096 x 5120 29.8 : 28.8).  Not with lists streamed, nor with five chunks per lane of two words,
-    // where the scheduler loses more by the branches (2048 x 28672 6-bit 57.4 : 58.9; 4-bit 61.9 : 60.8): there the first
-    // row's place in the output receives codes made of whatever LDS holds, and the real ones one pass later.
+    // `prev`: the row whose output groups are still to be stored, once there is one (`started`).  With EMPTY_PASS nobody asks:
+    // the first row's place in the output then receives codes made of whatever LDS holds, and the real ones one pass later.
     int64_t prev = row;
-    // Nor for 4-bit codes of long fp32 rows with LayerNorm (layer, 2048 tokens, 11008 channels 92.6 : 99.1, 24576 213 : 223).
-    bool started = STREAM || (ITERS == 5 && W == 2) || (LAYER && sizeof(XT) == 4 && W == 1 && ITERS >= 3);
+    bool started = EMPTY_PASS;
 
     // rowsum of a finished row: the waves' partial sums are complete once a barrier has passed
     auto finish_rowsum = [&](int64_t r) {
@@ -1379,6 +1375,9 @@ int32_t dispatch(const FusedArgs &a, const Shape &sh, size_t lds, bool stream_li
     if (sh.iters == 1) return launch(fused_planned_kernel<XT, BITS, 1, 1024, true, NORM, FULL>, a, sh, lds, stream);
     if (sh.iters == 2) return launch(fused_planned_kernel<XT, BITS, 2, 1024, true, NORM, FULL>, a, sh, lds, stream);
     if (sh.iters == 3) return launch(fused_planned_kernel<XT, BITS, 3, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>, a, sh, lds, stream);
+    if constexpr (qllm_detail::fused_empty_pass(TILES, sizeof(XT) == 4, NORM == QLLM_NORM_LAYER, BITS, 4, FULL, false)) {
+        if (sh.iters == 4 && qllm_detail::fused_few_rows(a.N, sh.nt, cu_count())) return launch(fused_planned_kernel<XT, BITS, 4, 1024, false, NORM, FULL, false, false>, a, sh, lds, stream);
+    }
     if constexpr (NORM != QLLM_NORM_LAYER) {
         if (sh.iters == 5) return launch(fused_planned_kernel<XT, BITS, 5, 768, true, NORM, FULL>, a, sh, lds, stream);
     }
@@ -1464,12 +1463,15 @@ int32_t qllm_launch_fused_tiles(const FusedArgs &planned, int32_t x_dtype, int32
 #else
 int32_t qllm_choose_fused_planned(const FusedArgs &a, int32_t x_dtype, int32_t bits) { return choose(a, x_dtype, bits).kind; }
 
-int64_t qllm_fused_ahead(const FusedArgs &planned, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes)
+int64_t qllm_fused_ahead(const FusedArgs &planned, int32_t x_dtype, int32_t bits, int32_t *chunks_per_lane, int32_t *lanes, int32_t *empty_pass)
 {
     FusedArgs a = planned;
     const Choice c = choose(a, x_dtype, bits);
     *chunks_per_lane = c.sh.iters;
     *lanes = c.sh.nt;
+    const bool f32 = x_dtype == QLLM_F32, layer = a.norm == QLLM_NORM_LAYER, full = exact_fit(a, c.sh), streams = c.kind == QLLM_FUSED_LISTS_STREAMED;
+    *empty_pass = qllm_detail::fused_empty_pass(a.tiles != nullptr, f32, layer, bits, c.sh.iters, full, streams) &&
+                  !(f32 && layer && bits == 4 && c.sh.iters == 4 && !streams && qllm_detail::fused_few_rows(a.N, c.sh.nt, cu_count()));
     a.row_groups = a.N;
     return ahead_groups(a, c.sh) > 0 ? (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk * a.ahead_each : 0;
 }

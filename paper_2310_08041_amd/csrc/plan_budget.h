@@ -69,6 +69,27 @@ inline Shape pick_shape(int64_t units, bool more_rows_than_cus, bool layer_norm,
     return best;
 }
 
+// Whether the planned kernel begins with an output pass over whatever LDS holds, so that its row loop need not ask whether a
+// row is waiting to be put out.  In a launch of one row per workgroup that pass is a tenth of the kernel (fused kernel, us, with
+// it : asked: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 777 x 5000 fp32 8-bit 22.3 : 20.2,
+// 4096 x 5120 29.8 : 28.8).  It stays where the branches cost the scheduler more, which goes by registers and not by the
+// row's length:
+//   lists streamed;
+//   five chunks per lane of two words (2048 x 28672 6-bit 57.4 : 58.9; 4-bit 61.9 : 60.8);
+//   4-bit codes of fp32 rows with LayerNorm at three chunks per lane (packed rows, 2048 tokens: 5120 channels 24.0 : 24.4, 9216
+//   33.4 : 35.0, 11264 42.2 : 46.7, 17408 66.5 : 77.6) and at four that fit exactly with more than two rows per workgroup (see
+//   below); not at four with bounds, whose registers spill either way (7168 51.5 : 46.7, 13312 85.4 : 81.5, 23552 159.8 : 152.7), nor where
+//   the codes are laid out for the product (8192, layer 88.6 : 84.8).
+constexpr bool fused_empty_pass(bool tiles, bool f32, bool layer_norm, int bits, int iters, bool exact_fit, bool streams)
+{
+    if (streams || (iters == 5 && bits != 4)) return true;
+    return f32 && layer_norm && bits == 4 && (iters == 3 || (iters == 4 && exact_fit && !tiles));
+}
+// Up to two rows per resident workgroup (128 registers: 16 wavefronts per CU): packed rows of 512 lanes and four chunks, us, with
+// it : asked, 400 tokens 26.2 : 25.4, 512 27.8 : 27.5, 1536 62.9 : 66.8; 448 lanes 400 22.5 : 19.3, 1024 37.7 : 36.8, 1536 49.6 : 50.6; 768
+// lanes 512 36.6 : 35.1, 1024 62.0 : 63.5, 2048 108 : 117; 256 lanes 2048 39.9 : 38.8, 4096 65.3 : 68.2.
+inline bool fused_few_rows(int64_t rows, int lanes, int cus) { return rows <= 2 * (int64_t)cus * (1024 / lanes); }
+
 // How many bytes of every chunk of the product's weights the idle CUs of the fused launch read ahead (a chunk per workgroup of
 // the product).  24 MB of the L2s' 32, and no more than four times what the reading wavefronts have in flight at once (4 KB each):
 // they have the lanes of a row's workgroup, and a short row is done in the time of some four trips to memory; what is still

@@ -542,6 +542,25 @@ def test_weights_are_read_ahead_only_where_most_cus_are_idle():
         layer_launch(100, 5120, 27648, 4, 4, workspace_bytes=floor - 1)
 
 
+@pytest.mark.parametrize("N,K,dt,norm,bits,iters,empty", [
+    (2048, 5120, b.F32, b.NORM_LAYER, 4, 3, 1), (2048, 11008, b.F32, b.NORM_LAYER, 4, 3, 1), (300, 9216, b.F32, b.NORM_LAYER, 4, 3, 1),
+    (2048, 7168, b.F32, b.NORM_LAYER, 4, 4, 0), (2048, 13312, b.F32, b.NORM_LAYER, 4, 4, 0), (2048, 23552, b.F32, b.NORM_LAYER, 4, 4, 0),
+    (2048, 8192, b.F32, b.NORM_LAYER, 4, 4, 0), (2049, 8192, b.F32, b.NORM_LAYER, 4, 4, 1),      # an exact fit: two rows per workgroup, more
+    (1024, 16384, b.F32, b.NORM_LAYER, 4, 4, 0), (1025, 16384, b.F32, b.NORM_LAYER, 4, 4, 1),
+    (512, 24576, b.F32, b.NORM_LAYER, 4, 4, 0), (513, 24576, b.F32, b.NORM_LAYER, 4, 4, 1),
+    (2048, 11008, b.F32, b.NORM_LAYER, 8, 3, 0), (2048, 11008, b.F32, b.NORM_RMS, 4, 3, 0), (2048, 5120, b.BF16, b.NORM_LAYER, 4, 3, 0),
+    (2048, 28672, b.BF16, b.NORM_RMS, 4, 5, 0), (2048, 28672, b.BF16, b.NORM_RMS, 6, 5, 1)])
+def test_fused_kernels_that_begin_with_an_empty_pass(N, K, dt, norm, bits, iters, empty):
+    """By registers (chunks per lane, bounds), not by the row's length: packed rows."""
+    f = layer_launch(N, K, 512, bits, bits, dt=dt, norm=norm, copies=False)
+    assert (f.laid_out, f.chunks_per_lane, f.empty_pass) == (0, iters, empty)
+
+
+def test_laid_out_rows_of_four_chunks_begin_with_a_row():
+    f = layer_launch(4096, 8192, 4096, 4, 4, dt=b.F32, norm=b.NORM_LAYER)
+    assert (f.laid_out, f.chunks_per_lane, f.empty_pass) == (1, 4, 0)
+
+
 @pytest.mark.parametrize("name,N,C,O", [("tiny", 64, 512, 96), ("llama7b_qkv", 48, 1000, 40),
                                         ("llama70b_down", 32, 2050, 24), ("llama70b_q_decode", 16, 777, 33)])
 def test_host_helpers_match_the_oracle(oracle, name, N, C, O):
