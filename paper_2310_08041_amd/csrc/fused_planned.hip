@@ -516,8 +516,7 @@ __device__ __forceinline__ void read_ahead(const FusedArgs &a)
     }
 }
 
-template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false,
-          bool EMPTY_PASS = qllm_detail::fused_empty_pass(TILES, sizeof(XT) == 4, NORM == QLLM_NORM_LAYER, BITS, ITERS, FULL, STREAM)>
+template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM, bool EMPTY_PASS>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
     constexpr bool LAYER = NORM == QLLM_NORM_LAYER, RMS = NORM == QLLM_NORM_RMS;
@@ -1367,21 +1366,31 @@ int32_t launch(K kernel, const FusedArgs &args, const Shape &sh, size_t lds, hip
     return QLLM_OK;
 }
 
+static_assert(QLLM_NORM_NONE == EMPTY_PASS_NO_NORM && QLLM_NORM_LAYER == EMPTY_PASS_LAYER && QLLM_NORM_RMS == EMPTY_PASS_RMS, "norms of empty_pass_rows");
+
+template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM = false>
+int32_t launch_rows(const FusedArgs &a, const Shape &sh, size_t lds, hipStream_t stream)
+{
+    constexpr int rows = empty_pass_rows(TILES, sizeof(XT) == 4, NORM, BITS, ITERS, FULL, STREAM);
+    if constexpr (rows != EMPTY_PASS_NEVER) {
+        if (rows == 0 || begins_with_empty_pass(rows, a.N, sh.nt, cu_count()))
+            return launch(fused_planned_kernel<XT, BITS, ITERS, NT_MAX, GAM_REG, NORM, FULL, STREAM, true>, a, sh, lds, stream);
+    }
+    if constexpr (rows != 0) return launch(fused_planned_kernel<XT, BITS, ITERS, NT_MAX, GAM_REG, NORM, FULL, STREAM, false>, a, sh, lds, stream);
+}
+
 template <typename XT, int BITS, int NORM, bool FULL>
 int32_t dispatch(const FusedArgs &a, const Shape &sh, size_t lds, bool stream_lists, hipStream_t stream)
 {
     // 4 chunks per lane: gamma fits in registers next to y and the prefetched row, except with LayerNorm
-    if (stream_lists) return launch(fused_planned_kernel<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL, true>, a, sh, lds, stream);
-    if (sh.iters == 1) return launch(fused_planned_kernel<XT, BITS, 1, 1024, true, NORM, FULL>, a, sh, lds, stream);
-    if (sh.iters == 2) return launch(fused_planned_kernel<XT, BITS, 2, 1024, true, NORM, FULL>, a, sh, lds, stream);
-    if (sh.iters == 3) return launch(fused_planned_kernel<XT, BITS, 3, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>, a, sh, lds, stream);
-    if constexpr (qllm_detail::fused_empty_pass(TILES, sizeof(XT) == 4, NORM == QLLM_NORM_LAYER, BITS, 4, FULL, false)) {
-        if (sh.iters == 4 && qllm_detail::fused_few_rows(a.N, sh.nt, cu_count())) return launch(fused_planned_kernel<XT, BITS, 4, 1024, false, NORM, FULL, false, false>, a, sh, lds, stream);
-    }
+    if (stream_lists) return launch_rows<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL, true>(a, sh, lds, stream);
+    if (sh.iters == 1) return launch_rows<XT, BITS, 1, 1024, true, NORM, FULL>(a, sh, lds, stream);
+    if (sh.iters == 2) return launch_rows<XT, BITS, 2, 1024, true, NORM, FULL>(a, sh, lds, stream);
+    if (sh.iters == 3) return launch_rows<XT, BITS, 3, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>(a, sh, lds, stream);
     if constexpr (NORM != QLLM_NORM_LAYER) {
-        if (sh.iters == 5) return launch(fused_planned_kernel<XT, BITS, 5, 768, true, NORM, FULL>, a, sh, lds, stream);
+        if (sh.iters == 5) return launch_rows<XT, BITS, 5, 768, true, NORM, FULL>(a, sh, lds, stream);
     }
-    return launch(fused_planned_kernel<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>, a, sh, lds, stream);
+    return launch_rows<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>(a, sh, lds, stream);
 }
 
 // every lane has its chunks and every slot a group (the composite groups all fit in the last pass's slots;
@@ -1469,9 +1478,8 @@ int64_t qllm_fused_ahead(const FusedArgs &planned, int32_t x_dtype, int32_t bits
     const Choice c = choose(a, x_dtype, bits);
     *chunks_per_lane = c.sh.iters;
     *lanes = c.sh.nt;
-    const bool f32 = x_dtype == QLLM_F32, layer = a.norm == QLLM_NORM_LAYER, full = exact_fit(a, c.sh), streams = c.kind == QLLM_FUSED_LISTS_STREAMED;
-    *empty_pass = qllm_detail::fused_empty_pass(a.tiles != nullptr, f32, layer, bits, c.sh.iters, full, streams) &&
-                  !(f32 && layer && bits == 4 && c.sh.iters == 4 && !streams && qllm_detail::fused_few_rows(a.N, c.sh.nt, cu_count()));
+    const int rows = empty_pass_rows(a.tiles != nullptr, x_dtype == QLLM_F32, a.norm, bits, c.sh.iters, exact_fit(a, c.sh), c.kind == QLLM_FUSED_LISTS_STREAMED);
+    *empty_pass = rows == 0 || (rows != EMPTY_PASS_NEVER && begins_with_empty_pass(rows, a.N, c.sh.nt, cu_count()));
     a.row_groups = a.N;
     return ahead_groups(a, c.sh) > 0 ? (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk * a.ahead_each : 0;
 }

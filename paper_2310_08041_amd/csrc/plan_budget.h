@@ -69,26 +69,44 @@ inline Shape pick_shape(int64_t units, bool more_rows_than_cus, bool layer_norm,
     return best;
 }
 
-// Whether the planned kernel begins with an output pass over whatever LDS holds, so that its row loop need not ask whether a
-// row is waiting to be put out.  In a launch of one row per workgroup that pass is a tenth of the kernel (fused kernel, us, with
-// it : asked: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 777 x 5000 fp32 8-bit 22.3 : 20.2,
-// 4096 x 5120 29.8 : 28.8).  It stays where the branches cost the scheduler more, which goes by registers and not by the
-// row's length:
-//   lists streamed;
-//   five chunks per lane of two words (2048 x 28672 6-bit 57.4 : 58.9; 4-bit 61.9 : 60.8);
-//   4-bit codes of fp32 rows with LayerNorm at three chunks per lane (packed rows, 2048 tokens: 5120 channels 24.0 : 24.4, 9216
-//   33.4 : 35.0, 11264 42.2 : 46.7, 17408 66.5 : 77.6) and at four that fit exactly with more than two rows per workgroup (see
-//   below); not at four with bounds, whose registers spill either way (7168 51.5 : 46.7, 13312 85.4 : 81.5, 23552 159.8 : 152.7), nor where
-//   the codes are laid out for the product (8192, layer 88.6 : 84.8).
-constexpr bool fused_empty_pass(bool tiles, bool f32, bool layer_norm, int bits, int iters, bool exact_fit, bool streams)
+// The planned kernel begins with an output pass over whatever LDS holds where there are more rows per resident workgroup than
+// this (0: always), and its row loop need not ask then whether a row is waiting to be put out.  In a launch of one row per
+// workgroup that pass is a tenth of the kernel (fused kernel, us, with it : asked: 200 x 13824 6-bit 10.0 : 8.6, 100 x 5120 4-bit
+// 7.4 : 6.8, 1 x 4096 4.96 : 4.56, 777 x 5000 fp32 8-bit 22.3 : 20.2, 4096 x 5120 29.8 : 28.8).  Over many rows the branches cost more
+// where the registers are short: both kernels of every kind, 1254 launches of 300-4096 rows, geometric means of with : asked (packed
+// rows; layer with the codes laid out for the product), at most one row per workgroup / more than four:
+//   lists streamed                                            1.00, no difference
+//   four chunks per lane that fit exactly, no LayerNorm:
+//     bf16 RMS 4-bit 1.00 / 1.05 (1.00 / 1.01), 6-bit 0.98 / 1.11 (0.99 / 1.04), 8-bit 1.00 / 1.15 (1.01 / 1.08)
+//     bf16 without a norm 6-bit 1.02 / 1.12 (0.98 / 1.05), 8-bit 0.96 / 1.18 (0.95 / 1.03); fp32 RMS 6-bit 1.00 / 1.05 (0.99 / 1.03)
+//     the others of this shape                                0.90-0.98 / 0.97-1.00
+//   four with bounds, 6-bit, laid out                         (0.86-0.95 / 1.02-1.11; packed rows 0.88-0.91 / 0.93-0.98)
+//     8-bit without a norm                                    (0.92-0.96, 1.01-1.04 from two rows; packed 0.80-0.87 / 0.87-0.94)
+//   LayerNorm, three chunks, fp32 4-bit                       0.99-1.05 / 1.08-1.10 (1.00-1.01 from two rows)
+//     bf16 4-bit 0.96 / 1.03-1.05 (exact fit 0.96 / 1.02, with bounds 0.96 at every size), fp32 6-bit 0.87 / 1.01 (0.95 / 1.03),
+//     8-bit exact fit 0.93 / 1.04 (0.97 / 1.05), 1.02 (1.01) from two rows
+//   LayerNorm, four that fit exactly, fp32 4-bit, packed      0.90 / 1.08, 1.03 from two rows
+//   RMS, two chunks, 4-bit, packed: 0.94-0.96 / 1.01-1.07, where asking takes a register more than five workgroups per CU
+//     leave (bf16 2048 x 4096 11.2 : 11.7, 4096 x 2560 14.8 : 15.7; at most one row 0.95)
+//   five chunks of two words                                  0.89-0.98 / 0.95-1.05 (0.95-1.01 / 1.00-1.05)
+//   all others                                                0.80-0.97 / 0.87-0.99 (the worst single launches, packed fp32 4-bit of 256
+//     lanes at exactly two rows: 2048 x 8192 RMS 19.4 : 20.4, 2048 x 7168 without a norm 16.4 : 18.0)
+constexpr int EMPTY_PASS_NEVER = 1 << 20;
+enum { EMPTY_PASS_NO_NORM, EMPTY_PASS_LAYER, EMPTY_PASS_RMS };
+constexpr int empty_pass_rows(bool tiles, bool f32, int norm, int bits, int iters, bool exact_fit, bool streams)
 {
-    if (streams || (iters == 5 && bits != 4)) return true;
-    return f32 && layer_norm && bits == 4 && (iters == 3 || (iters == 4 && exact_fit && !tiles));
+    const bool layer = norm == EMPTY_PASS_LAYER, two_words = bits != 4;
+    if (streams || (iters == 5 && two_words)) return 0;
+    if (layer && iters == 3 && f32 && !two_words) return 0;
+    if (layer && iters == 3 && (f32 ? exact_fit || (tiles && bits == 6) : !two_words && (exact_fit || !tiles))) return bits == 8 ? 2 : 4;
+    if (layer && iters == 4 && f32 && !two_words && exact_fit && !tiles) return 2;
+    if (!layer && iters == 4 && exact_fit && (f32 ? norm == EMPTY_PASS_RMS && bits == 6 : norm == EMPTY_PASS_RMS || two_words)) return 0;
+    if (!layer && iters == 4 && !exact_fit && tiles && two_words && (bits == 6 || norm == EMPTY_PASS_NO_NORM)) return bits == 8 ? 2 : 4;
+    if (norm == EMPTY_PASS_RMS && iters == 2 && !two_words && !tiles && !(f32 && exact_fit)) return exact_fit ? 1 : 2;
+    return EMPTY_PASS_NEVER;
 }
-// Up to two rows per resident workgroup (128 registers: 16 wavefronts per CU): packed rows of 512 lanes and four chunks, us, with
-// it : asked, 400 tokens 26.2 : 25.4, 512 27.8 : 27.5, 1536 62.9 : 66.8; 448 lanes 400 22.5 : 19.3, 1024 37.7 : 36.8, 1536 49.6 : 50.6; 768
-// lanes 512 36.6 : 35.1, 1024 62.0 : 63.5, 2048 108 : 117; 256 lanes 2048 39.9 : 38.8, 4096 65.3 : 68.2.
-inline bool fused_few_rows(int64_t rows, int lanes, int cus) { return rows <= 2 * (int64_t)cus * (1024 / lanes); }
+// Most of these kernels take 97 to 128 registers: 16 wavefronts per CU.
+inline bool begins_with_empty_pass(int rows, int64_t N, int lanes, int cus) { return N > rows * (int64_t)cus * (lanes < 1024 ? 1024 / lanes : 1); }
 
 // How many bytes of every chunk of the product's weights the idle CUs of the fused launch read ahead (a chunk per workgroup of
 // the product).  24 MB of the L2s' 32, and no more than four times what the reading wavefronts have in flight at once (4 KB each):

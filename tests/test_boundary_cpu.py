@@ -548,17 +548,27 @@ def test_weights_are_read_ahead_only_where_most_cus_are_idle():
     (2048, 8192, b.F32, b.NORM_LAYER, 4, 4, 0), (2049, 8192, b.F32, b.NORM_LAYER, 4, 4, 1),      # an exact fit: two rows per workgroup, more
     (1024, 16384, b.F32, b.NORM_LAYER, 4, 4, 0), (1025, 16384, b.F32, b.NORM_LAYER, 4, 4, 1),
     (512, 24576, b.F32, b.NORM_LAYER, 4, 4, 0), (513, 24576, b.F32, b.NORM_LAYER, 4, 4, 1),
-    (2048, 11008, b.F32, b.NORM_LAYER, 8, 3, 0), (2048, 11008, b.F32, b.NORM_RMS, 4, 3, 0), (2048, 5120, b.BF16, b.NORM_LAYER, 4, 3, 0),
-    (2048, 28672, b.BF16, b.NORM_RMS, 4, 5, 0), (2048, 28672, b.BF16, b.NORM_RMS, 6, 5, 1)])
+    (4096, 5120, b.BF16, b.NORM_LAYER, 4, 3, 0), (4097, 5120, b.BF16, b.NORM_LAYER, 4, 3, 1), (4097, 5120, b.BF16, b.NORM_LAYER, 6, 3, 0),
+    (1024, 12288, b.F32, b.NORM_LAYER, 8, 3, 0), (1025, 12288, b.F32, b.NORM_LAYER, 8, 3, 1), (2048, 12288, b.F32, b.NORM_LAYER, 6, 3, 0),
+    (1024, 4096, b.BF16, b.NORM_RMS, 4, 2, 0), (2048, 4096, b.BF16, b.NORM_RMS, 4, 2, 1), (2048, 4096, b.F32, b.NORM_RMS, 4, 2, 0),
+    (2049, 11008, b.F32, b.NORM_LAYER, 8, 3, 0),
+    (300, 16384, b.BF16, b.NORM_RMS, 4, 4, 1), (300, 16384, b.BF16, b.NORM_NONE, 4, 4, 0), (300, 16384, b.BF16, b.NORM_NONE, 8, 4, 1),
+    (2048, 16384, b.F32, b.NORM_RMS, 6, 4, 1), (2048, 16384, b.F32, b.NORM_RMS, 8, 4, 0), (2048, 13824, b.BF16, b.NORM_RMS, 4, 4, 0),
+    (2048, 11008, b.F32, b.NORM_RMS, 4, 3, 0), (2048, 28672, b.BF16, b.NORM_RMS, 4, 5, 0), (2048, 28672, b.BF16, b.NORM_RMS, 6, 5, 1)])
 def test_fused_kernels_that_begin_with_an_empty_pass(N, K, dt, norm, bits, iters, empty):
-    """By registers (chunks per lane, bounds), not by the row's length: packed rows."""
+    """Packed rows: by what decides the registers (chunks per lane, bounds, norm, type, bits) and the rows per resident workgroup."""
     f = layer_launch(N, K, 512, bits, bits, dt=dt, norm=norm, copies=False)
     assert (f.laid_out, f.chunks_per_lane, f.empty_pass) == (0, iters, empty)
 
 
-def test_laid_out_rows_of_four_chunks_begin_with_a_row():
-    f = layer_launch(4096, 8192, 4096, 4, 4, dt=b.F32, norm=b.NORM_LAYER)
-    assert (f.laid_out, f.chunks_per_lane, f.empty_pass) == (1, 4, 0)
+@pytest.mark.parametrize("N,K,dt,norm,bits,iters,empty", [
+    (4096, 8192, b.F32, b.NORM_LAYER, 4, 4, 0), (4097, 5120, b.BF16, b.NORM_LAYER, 4, 3, 0), (2049, 12288, b.BF16, b.NORM_LAYER, 4, 3, 1),
+    (2048, 13824, b.BF16, b.NORM_NONE, 6, 4, 0), (2049, 13824, b.BF16, b.NORM_NONE, 6, 4, 1), (300, 13824, b.BF16, b.NORM_NONE, 6, 4, 0),
+    (1024, 15616, b.BF16, b.NORM_NONE, 8, 4, 0), (1025, 15616, b.BF16, b.NORM_NONE, 8, 4, 1), (2049, 15616, b.BF16, b.NORM_RMS, 8, 4, 0),
+    (2048, 24576, b.BF16, b.NORM_RMS, 6, 4, 1)])
+def test_laid_out_rows_that_begin_with_an_empty_pass(N, K, dt, norm, bits, iters, empty):
+    f = layer_launch(N, K, 4096, bits, bits, dt=dt, norm=norm)
+    assert (f.laid_out, f.chunks_per_lane, f.empty_pass) == (1, iters, empty)
 
 
 @pytest.mark.parametrize("name,N,C,O", [("tiny", 64, 512, 96), ("llama7b_qkv", 48, 1000, 40),
