@@ -18,6 +18,13 @@ constexpr float MAGIC = 12582912.0f;  // 1.5 * 2^23: x + MAGIC rounds x to an in
 constexpr int32_t MAGIC_BITS = 0x4B400000;
 constexpr float FAST_LIMIT = 2097152.0f; // 2^21: below it the MAGIC trick is exact
 
+// x / d by one multiplication, exact for x d < 2^32: x ceil(2^32 / d) / 2^32 is less than x d / 2^32 / d too large
+struct QuotientBy {
+    uint32_t d, m;
+    __device__ __forceinline__ uint32_t divide(uint32_t x) const { return d == 1u ? x : __umulhi(x, m); }
+};
+inline QuotientBy quotient_by(uint32_t d) { return QuotientBy{d, d > 1u ? 0xffffffffu / d + 1u : 0u}; }
+
 struct FusedArgs {
     const void *x;
     int64_t ldx;
@@ -40,8 +47,11 @@ struct FusedArgs {
     // Workgroups beyond the rows' read weights that the product after this kernel is going to need (see read_ahead)
     const uint8_t *ahead;
     int64_t ahead_total;    // bytes of the weights; 0: none of this
-    int32_t ahead_chunk;    // bytes of the weights per workgroup of the product, one chunk after the other
-    int32_t ahead_each;     // of every chunk so many bytes
+    int32_t ahead_block;    // of a block of 16 features
+    uint32_t ahead_tile, ahead_kt;      // of one of its K-tiles; their number
+    QuotientBy ahead_cols, ahead_splits; // the product's workgroups: 8 blocks each, one after the other, times parts of K
+    int32_t ahead_each;     // bytes to read for every workgroup: its first blocks
+    QuotientBy ahead_pieces, ahead_of_block; // the same in KB; KB of a block's part of K
     int32_t row_groups;     // workgroups that have rows
     // calibration variant
     float *absmax, *y_dump;
@@ -121,10 +131,12 @@ int64_t qllm_fused_ahead(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32
 // QLLM_FUSED_*: the form of the fused kernel that qllm_launch_fused_planned would run for these arguments
 int32_t qllm_choose_fused_planned(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits);
 
-// Weights of the product that follows: workgroup c of it reads bytes chunk * c .. of `base` and goes to XCD c % 8.
+// Weights of the product that follows, in blocks of 16 features, `block` bytes each, made of K-tiles of `tile` bytes.  Workgroup
+// c of it goes to XCD c % 8 and reads 8 blocks from 8 (c % cols) on, part c / cols of `splits` of their K-tiles.
 struct WeightsAhead {
     const uint8_t *base;
-    int64_t total, chunk;
+    int64_t total;
+    int32_t block, tile, cols, splits;
 };
 
 // qllm_norm_reassemble_quant in two halves, so that the layer call has checked all of its arguments before it launches anything.

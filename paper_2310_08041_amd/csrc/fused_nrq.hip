@@ -549,10 +549,13 @@ bool take_asks(FusedArgs &a, int32_t x_dtype, int32_t bits, uint8_t *tiles, cons
     if (!a.work || !tiles || !qllm_fused_tiles_fit(a, x_dtype, bits)) return false;
     a.tiles = tiles;
     a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
-    if (ahead && ahead->chunk < INT32_MAX) {
+    if (ahead) {
         a.ahead = ahead->base;
         a.ahead_total = ahead->total;
-        a.ahead_chunk = (int32_t)ahead->chunk;
+        a.ahead_block = ahead->block;
+        a.ahead_tile = (uint32_t)ahead->tile;
+        a.ahead_cols = quotient_by((uint32_t)ahead->cols);
+        a.ahead_splits = quotient_by((uint32_t)ahead->splits);
     }
     return true;
 }

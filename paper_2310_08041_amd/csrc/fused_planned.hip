@@ -490,26 +490,33 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 
 // A launch of few rows leaves most CUs idle for some microseconds while the product that follows waits to read its weights:
 // workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
-// kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and the product's workgroup c
-// finds its chunk where a workgroup of the same number modulo 8 has read it; where that does not hold, it comes from the
-// cache behind the L2s all the same.  How much: see read_ahead_each.  Not in the kernels of packed rows, which mostly go without:
-// the question and its arguments alone cost them 1.3 % (geometric mean over 2300 launches of 1-4096 rows).
+// kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and workgroup c of the product, on XCD
+// c % 8, finds the first blocks of its features and of its part of K where a workgroup of the same number modulo 8 has read them.
+// How much: see read_ahead_each.  Not in the kernels of packed rows, which mostly go without: the question and its
+// arguments alone cost them 1.3 % (geometric mean over 2300 launches of 1-4096 rows).
 __device__ __forceinline__ void read_ahead(const FusedArgs &a)
 {
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
     const uint32_t xcd = blockIdx.x & 7u, first = a.row_groups + ((xcd - (uint32_t)a.row_groups) & 7u); // this XCD's first such workgroup
     const uint32_t groups = (gridDim.x - first + 7u) >> 3, waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
-    const uint32_t pieces = (uint32_t)a.ahead_each >> 10; // 1 KB each, of every chunk
-    const uint32_t n_chunks = (uint32_t)((a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk);
-    const uint32_t total = n_chunks > xcd ? (n_chunks - xcd + 7u) / 8u * pieces : 0u;
-    uint32_t p = ((blockIdx.x - first) >> 3) * waves + (threadIdx.x >> 6);
-    while (p < total) {
+    const uint32_t pieces = (uint32_t)a.ahead_each >> 10, of_block = a.ahead_of_block.d; // of 1 KB, per workgroup of the product, per block
+    const uint32_t all = a.ahead_cols.d * a.ahead_splits.d, units = all > xcd ? (all - xcd + 7u) >> 3 : 0u; // this XCD's workgroups of the product
+    // All of this is the wavefront's, stays in scalar registers and is free of divisions: three per load take longer than the
+    // load, in a kernel of seven microseconds (100 x 5120 -> 27648 4 / 4, layer 37.6 us with them, 36.5 without any reading).
+    const uint32_t p = ((blockIdx.x - first) >> 3) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), step = groups * waves;
+    const uint32_t step_units = a.ahead_pieces.divide(step), step_pieces = step - step_units * pieces;
+    uint32_t i = a.ahead_pieces.divide(p), piece = p - i * pieces;
+    while (i < units) {
         v4u v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u, p += groups * waves) {
-            const uint32_t q = p < total ? p : total - 1u, chunk = q / pieces;
-            const int64_t at = (int64_t)(chunk * 8u + xcd) * a.ahead_chunk + (int64_t)(q - chunk * pieces) * 1024 + lane * 16;
-            v[u] = *reinterpret_cast<const v4u *>(a.ahead + (at + 16 <= a.ahead_total ? at : 0));
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t unit = 8u * i + xcd, part = a.ahead_cols.divide(unit), block = a.ahead_of_block.divide(piece);
+            const int64_t at = (int64_t)((unit - part * a.ahead_cols.d) * 8u + block) * a.ahead_block +
+                               (int64_t)(a.ahead_splits.divide(a.ahead_kt * part) * a.ahead_tile + (piece - block * of_block) * 1024u);
+            v[u] = *reinterpret_cast<const v4u *>(a.ahead + (i < units && at + 1024 <= a.ahead_total ? at : 0) + lane * 16u);
+            i += step_units;
+            piece += step_pieces;
+            if (piece >= pieces) piece -= pieces, ++i;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(v[u]));
@@ -525,7 +532,10 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     constexpr uint32_t NOT_PUBLISHED = 0xffffffu;
     extern __shared__ __align__(16) float lds[];
     if constexpr (TILES) {
-        if (blockIdx.x >= (uint32_t)a.row_groups) return read_ahead(a);
+        if (blockIdx.x >= (uint32_t)a.row_groups) {
+            if constexpr (NORM != QLLM_NORM_NONE && ITERS > 1 && !STREAM) __builtin_amdgcn_s_sleep(64); // 4096 clocks: the rows' own loads first
+            return read_ahead(a);
+        }
     }
     const bool shift = LAYER && a.beta != nullptr;
     const int n_stage = GROUP * a.n_pub + 4;  // staged positions: the chunks that hold sources, then a zero
@@ -1317,9 +1327,14 @@ std::vector<LaunchFacts> facts;
 int32_t ahead_groups(FusedArgs &a, const Shape &sh)
 {
     const int idle = cu_count() - a.row_groups;
-    if (a.ahead_total <= 0 || a.ahead_chunk <= 0 || idle < cu_count() / 2) return 0;
-    a.ahead_each = (int32_t)qllm_detail::read_ahead_each(a.ahead_total, a.ahead_chunk, (int64_t)idle * (sh.nt / 64));
-    return a.ahead_each > 0 ? idle : 0;
+    if (a.ahead_total <= 0 || idle < cu_count() / 2) return 0;
+    const int64_t each = read_ahead_each(a.ahead_block, a.ahead_tile, a.ahead_cols.d, a.ahead_splits.d, (int64_t)idle * (sh.nt / 64), a.norm != QLLM_NORM_NONE);
+    if (each <= 0) return 0;
+    a.ahead_each = (int32_t)each;
+    a.ahead_kt = (uint32_t)(a.ahead_block / a.ahead_tile);
+    a.ahead_pieces = quotient_by((uint32_t)(each >> 10));
+    a.ahead_of_block = quotient_by(a.ahead_kt / a.ahead_splits.d * a.ahead_tile >> 10);
+    return idle;
 }
 
 template <typename K>
@@ -1481,7 +1496,7 @@ int64_t qllm_fused_ahead(const FusedArgs &planned, int32_t x_dtype, int32_t bits
     const int rows = empty_pass_rows(a.tiles != nullptr, x_dtype == QLLM_F32, a.norm, bits, c.sh.iters, exact_fit(a, c.sh), c.kind == QLLM_FUSED_LISTS_STREAMED);
     *empty_pass = rows == 0 || (rows != EMPTY_PASS_NEVER && begins_with_empty_pass(rows, a.N, c.sh.nt, cu_count()));
     a.row_groups = a.N;
-    return ahead_groups(a, c.sh) > 0 ? (a.ahead_total + a.ahead_chunk - 1) / a.ahead_chunk * a.ahead_each : 0;
+    return ahead_groups(a, c.sh) > 0 ? (int64_t)a.ahead_cols.d * a.ahead_splits.d * a.ahead_each : 0;
 }
 
 int32_t qllm_launch_fused_planned(const FusedArgs &planned, int32_t x_dtype, int32_t bits, hipStream_t stream)

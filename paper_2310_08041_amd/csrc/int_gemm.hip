@@ -2183,11 +2183,12 @@ int64_t layer_workspace_floor(int64_t N, int64_t K, int64_t O, int32_t a_bits)
 // tokens, which are numbered along the features.  Not for the streaming kernel, which loses as often as it gains by it
 // (layer, us, without : with: 16 tokens 8192 -> 28672 4 / 4 33.5 : 32.6, 28672 -> 8192 6 / 6 57.2 : 58.0, 90 tokens 13824 -> 5120
 // 28.8 : 30.0: unpacking bounds it, not the weights' way).
-WeightsAhead weights_ahead(int64_t N, const qllm_weight *w, bool tiles6)
+WeightsAhead weights_ahead(int64_t N, const qllm_weight *w, bool tiles6, int32_t splits)
 {
-    if (N > 128) return WeightsAhead{nullptr, 0, 0};
-    if (tiles6) return WeightsAhead{w->tiles6, qllm_tiles6_bytes(w->O, w->K), qllm_tiles6_bytes(128, w->K)};
-    return WeightsAhead{w->tiles8, qllm_tiles8_bytes(w->O, w->K), qllm_tiles8_bytes(128, w->K)};
+    if (N > 128) return WeightsAhead{nullptr, 0, 0, 0, 0, 0};
+    const int32_t cols = (int32_t)((w->O + 127) / 128);
+    if (tiles6) return WeightsAhead{w->tiles6, qllm_tiles6_bytes(w->O, w->K), (int32_t)qllm_tiles6_bytes(16, w->K), T6_BLOCK, cols, splits};
+    return WeightsAhead{w->tiles8, qllm_tiles8_bytes(w->O, w->K), (int32_t)qllm_tiles8_bytes(16, w->K), T8_BLOCK, cols, splits};
 }
 
 // What the layer call asks of the fused kernel beyond packed rows: where the product is going to read its activations in
@@ -2199,12 +2200,13 @@ struct LayerAsks {
 };
 LayerAsks layer_asks(int64_t N, const qllm_weight *w, int32_t a_bits, uint8_t *p, int64_t left)
 {
-    LayerAsks l{nullptr, {nullptr, 0, 0}};
+    LayerAsks l{nullptr, {nullptr, 0, 0, 0, 0, 0}};
     if (plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) return l;
     const bool tiles6 = has_room_for_tiles6(N, w, a_bits, p, left);
     if (tiles6) l.tiles = p + tiles6_at(N, w->K, w->O);
     else if (has_room_for_tiles8(N, w, a_bits, p, left)) l.tiles = p;
-    if (l.tiles) l.ahead = weights_ahead(N, w, tiles6);
+    const int64_t parts8 = l.tiles && !tiles6 ? parts8_that_fit(N, w->K, w->O, left) : 0;
+    if (l.tiles) l.ahead = weights_ahead(N, w, tiles6, plan_route(N, w->K, w->O, a_bits, w->bits, tiles6, !tiles6, parts8, true, false).splits);
     return l;
 }
 

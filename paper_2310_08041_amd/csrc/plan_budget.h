@@ -108,26 +108,28 @@ constexpr int empty_pass_rows(bool tiles, bool f32, int norm, int bits, int iter
 // Most of these kernels take 97 to 128 registers: 16 wavefronts per CU.
 inline bool begins_with_empty_pass(int rows, int64_t N, int lanes, int cus) { return N > rows * (int64_t)cus * (lanes < 1024 ? 1024 / lanes : 1); }
 
-// How many bytes of every chunk of the product's weights the idle CUs of the fused launch read ahead (a chunk per workgroup of
-// the product).  24 MB of the L2s' 32, and no more than four times what the reading wavefronts have in flight at once (4 KB each):
+// How many bytes of its weights the idle CUs of the fused launch read ahead for every workgroup of the product: its first blocks,
+// whole (the first K-tiles of all of them leave the memory idle first and the matrix cores after that).  24 MB of the L2s' 32,
+// and no more than four times what the reading wavefronts have in flight at once (4 KB each), twice where the row has no norm:
 // they have the lanes of a row's workgroup, and a short row is done in the time of some four trips to memory; what is still
-// being read then holds the product up.  Layer, us, no reading : 24 MB whatever the row : four trips (weights in the cache
-// behind the L2s / not):
-//   512 -> 27648, 128 tokens 8 / 8       13.1 : 21.3 : 12.7    14.0 : 26.5 : 13.7     (64 lanes)
-//   1024 -> 27648, 128 tokens 6 / 6      15.8 : 22.5 : 15.4    16.9 : 28.3 : 16.5
-//   5120 -> 11008, 100 tokens 6 / 6      26.1 : 26.1 : 25.6    32.9 : 30.6 : 29.9     (K in two parts, 86 columns of tiles)
-//   4096 -> 20500, 100 tokens 4 / 4      22.1 : 21.3 : 21.2    27.8 : 27.2 : 27.0
-//   13824 -> 8192, 40 tokens 8 / 4       32.8 : 34.2 : 34.0    (the worst of 351 shapes in cache; none loses more than 2 % out of it)
-// Geometric mean over 351 shapes (33-128 tokens, 512-16384 channels, 4096-28672 features): 1.019 and 1.040 of no reading.  Where
-// K is split and the columns of tiles are not a multiple of 8, most workgroups of the product find their weights on another
-// XCD, and still gain: 1.016 and 1.045 over 32 of those shapes.  With fewer idle CUs than rows the reading takes longer than
-// the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5): there is none.
+// being read then holds the product up.  Layer, us, no reading : 24 MB whatever the row and the split of K : now, three sets of
+// weights in turn (in the cache behind the L2s; out of it, with 5 for the measurement itself):
+//   512 -> 27648, 128 tokens 8 / 8       12.5 : 21.0 : 12.2    18.2 : 31.0 : 18.1     (64 lanes)
+//   1024 -> 27648, 128 tokens 6 / 6      15.3 : 22.8 : 14.8    23.3 : 33.9 : 22.2
+//   5120 -> 27648, 100 tokens 4 / 4      36.6 : 34.9 : 34.9    54.9 : 51.6 : 51.8
+//   5120 -> 11008, 100 tokens 6 / 6      25.1 : 25.0 : 24.6    42.0 : 40.7 : 41.2     (K in two parts, 86 columns of tiles)
+//   13824 -> 8192, 40 tokens 8 / 4       38.5 : 39.0 : 37.4    62.7 : 58.4 : 57.3     (three parts, 64 columns)
+//   10752 -> 3968, 53 tokens 8 / 8       22.8 : 24.2 : 21.3    37.5 : 33.3 : 33.8     (eight parts, 31 columns)
+//   23040 -> 1664, 68 tokens 8 / 8       27.9 : 30.0 : 27.6    42.5 : 44.2 : 42.9
+// Geometric mean over 96 shapes that read (33-128 tokens, 512-28672 channels, 256-27648 features): 1.010 and 1.041 of no reading, 24 MB
+// 0.970 and 1.021; the worst, lists streamed, 23168 -> 2304, 60 tokens 38.6 : 40.9 : 40.1.  With fewer idle CUs than rows the reading
+// takes longer than the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5): there is none.
 constexpr int64_t READ_AHEAD_BYTES = 24000000, READ_AHEAD_TRIPS = 4, READ_AHEAD_IN_FLIGHT = 4096;
-inline int64_t read_ahead_each(int64_t total, int64_t chunk, int64_t waves)
+inline int64_t read_ahead_each(int64_t block, int64_t tile, int64_t cols, int64_t splits, int64_t waves, bool norm)
 {
-    const int64_t chunks = (total + chunk - 1) / chunk, trips = READ_AHEAD_TRIPS * READ_AHEAD_IN_FLIGHT * waves;
-    const int64_t each = (trips < READ_AHEAD_BYTES ? trips : READ_AHEAD_BYTES) / chunks;
-    return (each < chunk ? each : chunk) / 1024 * 1024;
+    const int64_t trips = (norm ? READ_AHEAD_TRIPS : READ_AHEAD_TRIPS / 2) * READ_AHEAD_IN_FLIGHT * waves, part = block / tile / splits * tile; // of a block, per part of K
+    const int64_t each = (trips < READ_AHEAD_BYTES ? trips : READ_AHEAD_BYTES) / (cols * splits), most = 8 * (part / 1024) * 1024;
+    return each < most ? each / 1024 * 1024 : most;
 }
 
 } // namespace qllm_detail

@@ -513,20 +513,24 @@ def layer_launch(N, K, O, a_bits, w_bits, dt=b.BF16, norm=b.NORM_RMS, every=100,
     return b.qllm_probe_layer_launch(m, dt, N, K, norm, False, a_bits, types.SimpleNamespace(c=w), workspace_bytes)
 
 
-@pytest.mark.parametrize("N,K,O,bits", [(128, 512, 27648, (8, 8)), (128, 512, 27648, (4, 4)), (100, 1024, 27648, (6, 6)), (100, 1024, 20500, (8, 4)),
-                                        (70, 2048, 20500, (4, 4)), (100, 4096, 27648, (4, 4)), (100, 5120, 27648, (4, 4)), (48, 8192, 28672, (8, 8)),
-                                        (100, 5120, 11008, (6, 6))])
-def test_weights_read_ahead_fit_behind_the_rows(N, K, O, bits):
+@pytest.mark.parametrize("N,K,O,bits,want_splits", [
+    (128, 512, 27648, (8, 8), 1), (128, 512, 27648, (4, 4), 1), (100, 1024, 27648, (6, 6), 1), (100, 1024, 20500, (8, 4), 1),
+    (70, 2048, 20500, (4, 4), 1), (100, 4096, 27648, (4, 4), 1), (100, 5120, 27648, (4, 4), 1), (48, 8192, 28672, (8, 8), 1),
+    (100, 5120, 11008, (6, 6), 2), (100, 13824, 2304, (8, 4), 8), (70, 20224, 2176, (4, 4), 4)])
+def test_weights_read_ahead_fit_behind_the_rows(N, K, O, bits, want_splits):
     """The wavefronts that read weights ahead have the lanes of a row's workgroup: no more than four times the 4 KB that each has
     in flight, 24 MB, and every workgroup of the product its own share.  (24 MB whatever the row doubled the time of a
     layer of 512 channels.)"""
     f = layer_launch(N, K, O, *bits)
     assert f.laid_out and f.lanes * f.chunks_per_lane * 8 >= K
-    nb = (b.qllm_tiles6_bytes if bits == (4, 4) else b.qllm_tiles8_bytes)(O, K)
-    chunk = (b.qllm_tiles6_bytes if bits == (4, 4) else b.qllm_tiles8_bytes)(128, K)
-    chunks = -(-nb // chunk)
+    tile, codes = (1536, 128) if bits == (4, 4) else (1024, 64)
+    w = b._Weight(O, K, bits[1], 0x1000, 0x1000, 0x1000, 0x1000, 0x1000 if bits == (4, 4) else None, None if bits == (4, 4) else 0x1000)
+    splits = b.qllm_gemm_kernel_choice(types.SimpleNamespace(c=w), bits[0], N, 1 << 40, True)[2]
+    parts = -(-O // 128) * splits                           # the product's workgroups
     most = min(24000000, 4 * 4096 * (256 - N) * f.lanes // 64)
-    assert f.ahead_bytes == chunks * (min(most // chunks, chunk) // 1024 * 1024) and f.ahead_bytes <= most
+    assert splits == want_splits
+    of_block = -(-K // codes) // splits * tile // 1024      # KB of a block of 16 features that a workgroup reads
+    assert 0 < f.ahead_bytes == parts * min(most // parts // 1024, 8 * of_block) * 1024 <= most
 
 
 def test_weights_are_read_ahead_only_where_most_cus_are_idle():
