@@ -445,6 +445,41 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
     funnel_shift<BITS>(funnel_fetch<BITS>(pk, u), (uint32_t)(BITS * v), w0, w1);
 }
 
+// A launch of few rows leaves most CUs idle for some microseconds while the product that follows waits to read its weights:
+// workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
+// kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and workgroup c of the product, on XCD
+// c % 8, finds the first blocks of its features and of its part of K where a workgroup of the same number modulo 8 has read them.
+// How much: see read_ahead_each.  Not in the kernels of packed rows, which mostly go without: the question and its
+// arguments alone cost them 1.3 % (geometric mean over 2300 launches of 1-4096 rows).
+__device__ __forceinline__ void read_ahead(const FusedArgs &a)
+{
+    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+    const uint32_t xcd = blockIdx.x & 7u, first = a.row_groups + ((xcd - (uint32_t)a.row_groups) & 7u); // this XCD's first such workgroup
+    const uint32_t groups = (gridDim.x - first + 7u) >> 3, waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+    const uint32_t pieces = (uint32_t)a.ahead_each >> 10, of_block = a.ahead_of_block.d; // of 1 KB, per workgroup of the product, per block
+    const uint32_t all = a.ahead_cols.d * a.ahead_splits.d, units = all > xcd ? (all - xcd + 7u) >> 3 : 0u; // this XCD's workgroups of the product
+    // All of this is the wavefront's, stays in scalar registers and is free of divisions: three per load take longer than the
+    // load, in a kernel of seven microseconds (100 x 5120 -> 27648 4 / 4, layer 37.6 us with them, 36.5 without any reading).
+    const uint32_t p = ((blockIdx.x - first) >> 3) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), step = groups * waves;
+    const uint32_t step_units = a.ahead_pieces.divide(step), step_pieces = step - step_units * pieces;
+    uint32_t i = a.ahead_pieces.divide(p), piece = p - i * pieces;
+    while (i < units) {
+        v4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t unit = 8u * i + xcd, part = a.ahead_cols.divide(unit), block = a.ahead_of_block.divide(piece);
+            const int64_t at = (int64_t)((unit - part * a.ahead_cols.d) * 8u + block) * a.ahead_block +
+                               (int64_t)(a.ahead_splits.divide(a.ahead_kt * part) * a.ahead_tile + (piece - block * of_block) * 1024u);
+            v[u] = *reinterpret_cast<const v4u *>(a.ahead + (i < units && at + 1024 <= a.ahead_total ? at : 0) + lane * 16u);
+            i += step_units;
+            piece += step_pieces;
+            if (piece >= pieces) piece -= pieces, ++i;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(v[u]));
+    }
+}
+
 // The row loop is software-pipelined over three phases with TWO barriers per row, so that work bound by
 // latency (LDS round trips, cross-lane reductions, dependent scalar chains) has dense arithmetic of another
 // step of the path next to it between the same two barriers:
@@ -487,42 +522,6 @@ __device__ __forceinline__ void funnel(const uint32_t *pk, int u, int v, uint32_
 // position, and gamma / beta of a source are read from global memory by its channel number: a staged position IS
 // that number where the plan has n_pub == n_chunks; else a table in LDS gives the chunk (the upper halves of chunkw, whose
 // staging numbers this form has no use for).
-
-// A launch of few rows leaves most CUs idle for some microseconds while the product that follows waits to read its weights:
-// workgroups beyond the rows' read part of them meanwhile, for nothing but the cache.  An XCD's L2 keeps them across the
-// kernels' boundary (28 MB read again by the next kernel: 2.8 us, from behind the L2s 5.4), and workgroup c of the product, on XCD
-// c % 8, finds the first blocks of its features and of its part of K where a workgroup of the same number modulo 8 has read them.
-// How much: see read_ahead_each.  Not in the kernels of packed rows, which mostly go without: the question and its
-// arguments alone cost them 1.3 % (geometric mean over 2300 launches of 1-4096 rows).
-__device__ __forceinline__ void read_ahead(const FusedArgs &a)
-{
-    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-    const uint32_t xcd = blockIdx.x & 7u, first = a.row_groups + ((xcd - (uint32_t)a.row_groups) & 7u); // this XCD's first such workgroup
-    const uint32_t groups = (gridDim.x - first + 7u) >> 3, waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
-    const uint32_t pieces = (uint32_t)a.ahead_each >> 10, of_block = a.ahead_of_block.d; // of 1 KB, per workgroup of the product, per block
-    const uint32_t all = a.ahead_cols.d * a.ahead_splits.d, units = all > xcd ? (all - xcd + 7u) >> 3 : 0u; // this XCD's workgroups of the product
-    // All of this is the wavefront's, stays in scalar registers and is free of divisions: three per load take longer than the
-    // load, in a kernel of seven microseconds (100 x 5120 -> 27648 4 / 4, layer 37.6 us with them, 36.5 without any reading).
-    const uint32_t p = ((blockIdx.x - first) >> 3) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), step = groups * waves;
-    const uint32_t step_units = a.ahead_pieces.divide(step), step_pieces = step - step_units * pieces;
-    uint32_t i = a.ahead_pieces.divide(p), piece = p - i * pieces;
-    while (i < units) {
-        v4u v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t unit = 8u * i + xcd, part = a.ahead_cols.divide(unit), block = a.ahead_of_block.divide(piece);
-            const int64_t at = (int64_t)((unit - part * a.ahead_cols.d) * 8u + block) * a.ahead_block +
-                               (int64_t)(a.ahead_splits.divide(a.ahead_kt * part) * a.ahead_tile + (piece - block * of_block) * 1024u);
-            v[u] = *reinterpret_cast<const v4u *>(a.ahead + (i < units && at + 1024 <= a.ahead_total ? at : 0) + lane * 16u);
-            i += step_units;
-            piece += step_pieces;
-            if (piece >= pieces) piece -= pieces, ++i;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) asm volatile("" : : "v"(v[u]));
-    }
-}
-
 template <typename XT, int BITS, int ITERS, int NT_MAX, bool GAM_REG, int NORM, bool FULL, bool STREAM, bool EMPTY_PASS>
 __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a)
 {
@@ -580,6 +579,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     }
     // TILES6: the row before, packed, between its output groups and its way out
     constexpr bool LAYS_ROW = TILES && BITS == 4;
+    static_assert(!(LAYS_ROW && STREAM), "qllm_fused_tiles_fit has no such call");
     uint32_t *whole_row = reinterpret_cast<uint32_t *>(lds) + a.row_at;
     __shared__ double red_d[2][16];
     __shared__ float red_f[32];
@@ -999,10 +999,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
         // ---- step a4, second half, of the row before: the words its output groups are made of are requested
         //      first and put together further down, after the dense arithmetic of this row
         if constexpr (OUT_IN_PHASE_1) {
-            if (started) {
-                finish_rowsum(prev);
-                lay_row(prev, ltid);
-            }
+            if (started) finish_rowsum(prev);
         } else if (started) {
             out_read_work(o, ltid);
         }
@@ -1398,7 +1395,9 @@ template <typename XT, int BITS, int NORM, bool FULL>
 int32_t dispatch(const FusedArgs &a, const Shape &sh, size_t lds, bool stream_lists, hipStream_t stream)
 {
     // 4 chunks per lane: gamma fits in registers next to y and the prefetched row, except with LayerNorm
-    if (stream_lists) return launch_rows<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL, true>(a, sh, lds, stream);
+    if constexpr (!(TILES && BITS == 4)) { // those rows stay packed, see qllm_fused_tiles_fit
+        if (stream_lists) return launch_rows<XT, BITS, 4, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL, true>(a, sh, lds, stream);
+    }
     if (sh.iters == 1) return launch_rows<XT, BITS, 1, 1024, true, NORM, FULL>(a, sh, lds, stream);
     if (sh.iters == 2) return launch_rows<XT, BITS, 2, 1024, true, NORM, FULL>(a, sh, lds, stream);
     if (sh.iters == 3) return launch_rows<XT, BITS, 3, 1024, NORM != QLLM_NORM_LAYER, NORM, FULL>(a, sh, lds, stream);
