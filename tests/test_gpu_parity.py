@@ -904,19 +904,25 @@ def test_reassembled_linear_w4a8_end_to_end(oracle, b, name, N, C, O, y_dtype):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("N,C,K,O,norm,dtype,every,form,bits", [
-    (517, 4096, 4096, 6144, "rms", "bf16", 40, 1, 4),      # rows past a block of 16, whole K-tiles
-    (1030, 5000, 4999, 5000, "layer", "f32", 25, 1, 4),    # places past K in the last K-tiles, fp32 rows
-    (700, 512, 301, 12288, "none", "bf16", 3, 1, 4),       # more composite groups than plain ones
-    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2, 4),  # lists streamed (packed rows), K split over workgroups
-    (65, 8192, 8192, 20480, "rms", "bf16", 62, 1, 4),      # a row per workgroup, the others read a part of every tile's weights
-    (128, 512, 301, 16500, "none", "bf16", 3, 1, 4),       # ... and all of them, the last tile ragged
-    (40, 512, 301, 16500, "none", "bf16", 3, 1, 8),
-    (128, 5000, 4999, 5000, "layer", "f32", 25, 1, 6)])
-def test_layer_lays_codes_out(b, N, C, K, O, norm, dtype, every, form, bits):
-    """Where the product runs on re-laid operands the fused kernel of the layer call writes the activations so itself, and
-    with few tokens reads weights ahead: bit for bit the result of the two entry points by themselves, packed rows and a
-    launch that lays them out."""
+@pytest.mark.parametrize("N,C,K,O,norm,dtype,every,form,bits,laid", [
+    (517, 4096, 4096, 6144, "rms", "bf16", 40, 1, 4, 1),      # rows past a block of 16, whole K-tiles
+    (1030, 5000, 4999, 5000, "layer", "f32", 25, 1, 4, 1),    # places past K in the last K-tiles, fp32 rows
+    (700, 512, 301, 12288, "none", "bf16", 3, 1, 4, 1),       # more composite groups than plain ones
+    (300, 28032, 28032, 4096, "layer", "bf16", 62, 2, 4, 0),  # lists streamed (packed rows), K split over workgroups
+    (300, 28672, 28672, 4096, "rms", "bf16", 70, 1, 4, 1),    # the whole row just fits in LDS beside the lists
+    (300, 28672, 28672, 4096, "rms", "bf16", 62, 1, 4, 0),    # ... and no more (packed rows)
+    (300, 28032, 28032, 1024, "layer", "bf16", 62, 2, 6, 1),  # bytes are laid out by either form
+    (300, 9216, 9216, 6144, "rms", "f32", 62, 1, 4, 0),       # long fp32 rows (packed)
+    (2060, 13824, 13824, 512, "none", "bf16", 62, 1, 6, 1),   # more than four rows per workgroup: begins with an empty pass
+    (65, 8192, 8192, 20480, "rms", "bf16", 62, 1, 4, 1),      # a row per workgroup, the others read a part of every tile's weights
+    (128, 512, 301, 16500, "none", "bf16", 3, 1, 4, 1),       # ... the last tile ragged
+    (53, 10752, 10752, 3900, "rms", "bf16", 62, 1, 8, 1),     # ... of every part of K
+    (40, 512, 301, 16500, "none", "bf16", 3, 1, 8, 1),
+    (128, 5000, 4999, 5000, "layer", "f32", 25, 1, 6, 1)])
+def test_layer_lays_codes_out(b, N, C, K, O, norm, dtype, every, form, bits, laid):
+    """Where the product runs on re-laid operands the fused kernel of the layer call writes the activations so itself (the workspace's
+    packed rows are then left alone), and with few tokens reads weights ahead: bit for bit the result of the two entry
+    points by themselves, packed rows and a launch that lays them out."""
     import torch
     rng = np.random.default_rng(7)
     row_ptr, src, scale = random_csr_map(rng, C, K, every, longest=3)
@@ -932,11 +938,45 @@ def test_layer_lays_codes_out(b, N, C, K, O, norm, dtype, every, form, bits):
     ws = torch.full((b.qllm_workspace_bytes(N, K, O, bits),), 0xAB, dtype=torch.uint8, device="cuda")
     assert b.qllm_gemm_kernel_choice(dw, bits, N, gws.numel(), True)[0] == (b.GEMM_FP6 if bits == 4 else b.GEMM_BYTES)
     y, want = (torch.full((N, O), float("nan"), dtype=x.dtype, device="cuda") for _ in range(2))
+    facts = b.qllm_probe_layer_launch(dm, x.dtype, N, C, NORM_ID[norm], beta is not None, bits, dw, ws.numel())
+    assert (facts.laid_out, facts.ahead_bytes > 0) == (laid, bool(laid and N <= 128))
     b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, bits, dw, y, ws)
+    packed = ws[:N * b.qllm_packed_row_bytes(K, bits)]
+    assert bool((packed == 0xAB).all()) == bool(laid)
     qa = b.DeviceQAct(N, K, bits)
     b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, bits, qa)
+    assert laid or torch.equal(packed.view(N, -1), qa.codes.view(N, -1))
     b.qllm_int_gemm(qa, dw, want, None, gws)
     assert torch.equal(y, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,C,norm,dtype,bits,empty", [
+    (2052, 4096, "rms", "bf16", 4, (0, 1)), (4100, 5120, "layer", "bf16", 4, (0, 1)), (4100, 6144, "layer", "f32", 6, (0, 1)),
+    (2052, 8192, "layer", "f32", 4, (0, 1)), (2052, 12288, "layer", "f32", 8, (0, 1)), (2052, 7168, "layer", "f32", 4, (0, 0)),
+    (2052, 6144, "layer", "f32", 4, (1, 1)), (2052, 8192, "rms", "bf16", 8, (1, 1))])
+def test_fused_kernels_with_and_without_an_empty_pass(b, N, C, norm, dtype, bits, empty):
+    """Many rows may run a kernel of its own; a row's codes do not depend on it: the same, value by value, as a few rows at a time."""
+    import torch
+    rng = np.random.default_rng(11)
+    row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
+    dm = b.DeviceMap(row_ptr, src, scale, C, b.qllm_plan_map_host(row_ptr, src, scale, C)[0])
+    dw = b.DeviceWeight(b.qllm_pack_codes_host(np.zeros((64, C), np.uint8), bits), np.ones(64, np.float32), np.zeros(64, np.int32),
+                        np.zeros(64, np.int32), C, bits, tiles6=False, tiles8=False)
+    x = torch.randn((N, C), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    gamma, beta = torch.rand(C, device="cuda") + 0.5, (torch.rand(C, device="cuda") if norm == "layer" else None)
+    step = 513 if C < 8192 else 257   # (few rows of the exact fits: at most two per workgroup)
+    got = []
+    for n in (N, step):
+        f = b.qllm_probe_layer_launch(dm, x.dtype, n, C, NORM_ID[norm], beta is not None, bits, dw, 1 << 40)
+        assert f.empty_pass == empty[0 if n == step else 1]
+        rows = []
+        for i in range(0, N, n):
+            qa = b.DeviceQAct(min(n, N - i), C, bits)
+            b.qllm_norm_reassemble_quant(x[i:i + n], NORM_ID[norm], gamma, beta, 1e-5, dm, bits, qa)
+            rows.append((qa.codes.view(qa.N, -1), qa.scale, qa.zero, qa.rowsum))
+        got.append([torch.cat(v) for v in zip(*rows)])
+    assert all(torch.equal(p, q) for p, q in zip(*got))
 
 
 def test_fused_full_down_projection_without_norm(oracle, b):
