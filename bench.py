@@ -426,27 +426,31 @@ def main():
     bev[3].record()
     torch.cuda.synchronize()
     t_fused, t_gemm = bev[0].elapsed_time(bev[1]) * 1e-3 / args.steps, bev[2].elapsed_time(bev[3]) * 1e-3 / args.steps
-    t_pack = 0.0
-    if fp6_path:
-        # the GEMM call is two kernels on this path: the activations re-laid for the FP6 matrix cores, then the
-        # product; the first one alone, back to back in the same way, gives the split
-        tiles = torch.empty(b.qllm_tiles6_bytes(w.N, K), dtype=torch.uint8, device=dev)
-        settle(lambda i: b.qllm_pack_tiles6(qas[i % N_ROTATE].codes, w.N, K, tiles), ms=10.0)
-        bev[0].record()
-        for i in range(args.steps):
-            b.qllm_pack_tiles6(qas[i % N_ROTATE].codes, w.N, K, tiles)
-        bev[1].record()
-        torch.cuda.synchronize()
-        t_pack = bev[0].elapsed_time(bev[1]) * 1e-3 / args.steps
-        del tiles
-    # the roofline below prices the whole GEMM call (on the FP6 path both of its kernels): the sum a kernel trace shows
-    t_gemm_kernel = t_gemm
+    # In the step the fused kernel may lay the codes out for the product (`laid`).  The two entry points by themselves then run
+    # other kernels: the fused one on packed rows, and the GEMM call lays them out first.  What the step runs is timed as its
+    # two halves, back to back in the same way.
+    laid = bool(b.qllm_probe_layer_launch(dmap, x0.dtype, w.N, w.C, norm, beta is not None, w.a_bits, dw, ws.numel()).laid_out)
+    t_fused_packed, t_gemm_call = t_fused, t_gemm
+    if laid:
+        t_half = []
+        for half in (1, 2):
+            def launch_half(i):
+                b.qllm_probe_layer_half(half, xs[i % N_ROTATE], norm, gamma, beta, w.eps, dmap, w.a_bits, dw, ys[i % N_ROTATE], ws)
+
+            settle(launch_half)
+            bev[0].record()
+            for i in range(args.steps):
+                launch_half(i)
+            bev[1].record()
+            torch.cuda.synchronize()
+            t_half.append(bev[0].elapsed_time(bev[1]) * 1e-3 / args.steps)
+        t_fused, t_gemm = t_half
 
     ops = 2.0 * w.N * K * w.O
     x_bytes = w.N * w.C * x0.element_size()
     code_bytes = w.N * K * w.a_bits // 8
     fused_bytes = x_bytes + code_bytes + 12 * w.N            # read X once, write codes + (alpha, beta, rowsum)
-    gemm_tops = ops / t_gemm_kernel / 1e12
+    gemm_tops = ops / t_gemm / 1e12
     fused_gbs = fused_bytes / t_fused / 1e9
 
     # ---- what the machine delivers on the two resources, with none of the path's work in the way
@@ -491,7 +495,7 @@ def main():
     if fp6_path:
         gemm_kernel = "gemm_w4a4_fp6_kernel<bf16>"
     elif bytes_path:
-        gemm_kernel = "gemm_tiles8_kernel<%d,%d,bf16> after tiles8_kernel" % (w.a_bits, w.w_bits)
+        gemm_kernel = "gemm_tiles8_kernel<%d,%d,bf16>" % (w.a_bits, w.w_bits) + ("" if laid else " after tiles8_kernel")
     elif w.N > 128:
         gemm_kernel = ("int_gemm_w4a4_kernel<bf16>" if (w.a_bits, w.w_bits) == (4, 4) else
                        "int_gemm_big_kernel<%d,%d,bf16>" % (w.a_bits, w.w_bits))
@@ -511,14 +515,10 @@ def main():
     elif fp6_path:
         # the operations are those of Eq. (1) on the codes (2 N K O), done by FP6 matrix-core operations: priced
         # against the FP6 peak
-        roofline = {"kernel": gemm_kernel + " after tiles6_kernel", "bound": "mfma", "achieved": gemm_tops,
+        roofline = {"kernel": gemm_kernel + ("" if laid else " after tiles6_kernel"), "bound": "mfma", "achieved": gemm_tops,
                     "peak": FP6_PEAK_TOPS, "unit": "TOP/s", "frac": gemm_tops / FP6_PEAK_TOPS,
-                    "avg_launch_us": t_gemm * 1e6, "single_launch_event_us": spread(gemm_us),
-                    "note": "durations are those of the GEMM call, i.e. of both its kernels (the activation codes re-laid, then "
-                            "the product): in a kernel trace the sum of the two averages; tiles6_kernel_us is the first one "
-                            "alone, launched back to back (launch-bound when it is only a few microseconds long)",
-                    "tiles6_kernel_us": t_pack * 1e6,
-                    "traffic": (traffic.get("gemm_fp6", 0) + traffic.get("tiles6", 0)) or None,
+                    "avg_launch_us": t_gemm * 1e6,
+                    "traffic": (traffic.get("gemm_fp6", 0) + (0 if laid else traffic.get("tiles6", 0))) or None,
                     "frac_of_int8_peak": gemm_tops / INT8_PEAK_TOPS,
                     "probe": {"what": "loop of FP6 matrix-core operations on register operands that hold 4-bit codes, all CUs",
                               "achieved": fp6_probe_tops, "frac_of_probe": gemm_tops / fp6_probe_tops,
@@ -526,11 +526,17 @@ def main():
     else:
         roofline = {"kernel": gemm_kernel, "bound": "mfma", "achieved": gemm_tops,
                     "peak": INT8_PEAK_TOPS, "unit": "TOP/s", "frac": gemm_tops / INT8_PEAK_TOPS,
-                    "avg_launch_us": t_gemm * 1e6, "single_launch_event_us": spread(gemm_us),
-                    "traffic": ((traffic.get("gemm_tiles8", 0) + traffic.get("tiles8", 0)) or None) if bytes_path
+                    "avg_launch_us": t_gemm * 1e6,
+                    "traffic": ((traffic.get("gemm_tiles8", 0) + (0 if laid else traffic.get("tiles8", 0))) or None) if bytes_path
                     else traffic.get("int_gemm"),
                     "probe": {"what": "loop of int8 matrix-core operations on register operands, all CUs",
                               "achieved": mfma_probe_tops, "frac_of_probe": gemm_tops / mfma_probe_tops}}
+    roofline["call"] = {"what": "qllm_int_gemm on packed rows, with the launch that lays them out where there is one",
+                        "achieved": ops / t_gemm_call / 1e12, "avg_launch_us": t_gemm_call * 1e6, "single_launch_event_us": spread(gemm_us)}
+    if laid:
+        roofline["note"] = ("roofline and roofline_fused are of the kernels that the step runs, each back to back by itself: the fused kernel "
+                            "lays the codes out, the product reads them.  Together they may take longer than the step: the product "
+                            "alone has no lighter kernel before it and its clock falls")
     result = {
         "metric": "reassembled W%dA%d linear TOPS at 70B shapes; fused norm+reassembly+quant GB/s" % (w.w_bits, w.a_bits)
                   if args.bits else "reassembled W4A4 linear TOPS at 70B shapes; fused norm+reassembly+quant GB/s",
@@ -556,8 +562,10 @@ def main():
         "roofline": roofline,
         "roofline_fused": {"kernel": "fused_planned_kernel", "bound": "hbm", "achieved": fused_gbs,
                            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": fused_gbs / HBM_PEAK_GBS,
-                           "avg_launch_us": t_fused * 1e6, "single_launch_event_us": spread(fused_us), "algorithmic_bytes": fused_bytes,
-                           "traffic": traffic.get("fused_planned"),
+                           "avg_launch_us": t_fused * 1e6, "algorithmic_bytes": fused_bytes, "lays_codes_out": laid,
+                           "packed_rows": {"what": "qllm_norm_reassemble_quant by itself", "achieved": fused_bytes / t_fused_packed / 1e9,
+                                           "frac": fused_bytes / t_fused_packed / 1e9 / HBM_PEAK_GBS, "avg_launch_us": t_fused_packed * 1e6,
+                                           "single_launch_event_us": spread(fused_us), "traffic": traffic.get("fused_planned")},
                            "probe": {"what": "plain stream, 16 bytes read : 4 written, 1.25 GB per pass",
                                      "achieved": stream_probe_gbs, "frac_of_probe": fused_gbs / stream_probe_gbs}},
         "setup_s": setup_s,

@@ -45,6 +45,16 @@ typedef struct {
 int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta,
                                 int32_t a_bits, const qllm_weight *w, int64_t workspace_bytes, qllm_layer_launch *out);
 
+/*
+ * One half of qllm_reassembled_linear with the same arguments, to be timed by itself: 1 the fused kernel, 2 the product (the
+ * workspace as half 1 left it).  Half 1 then half 2 is the layer call.  Errors: those of qllm_reassembled_linear, SHAPE for any
+ * other half.
+ */
+int32_t qllm_probe_layer_half(int32_t half, const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm,
+                              const float *gamma, const float *beta, float eps, const qllm_map *map, int32_t a_bits,
+                              const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy, void *workspace,
+                              int64_t workspace_bytes, void *hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

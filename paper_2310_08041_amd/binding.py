@@ -97,6 +97,8 @@ _sigs = {
     "qllm_probe_mfma": (_i32, [_i32, _i32, _vp, _vp]),
     "qllm_probe_mfma_fp6": (_i32, [_i32, _i32, _vp, _vp]),
     "qllm_probe_stream": (_i32, [_vp, _vp, _i64, _i32, _vp]),
+    "qllm_probe_layer_half": (_i32, [_i32, _vp, _i32, _i64, _i64, _i64, _i32, _vp, _vp, _f, C.POINTER(_Map), _i32,
+                                     C.POINTER(_Weight), _vp, _i32, _i64, _vp, _i64, _vp]),
     "qllm_probe_layer_launch": (_i32, [C.POINTER(_Map), _i32, _i64, _i64, _i32, _i32, _i32, C.POINTER(_Weight), _i64, C.POINTER(_LayerLaunch)]),
 }
 EXPORTS = tuple(_sigs)
@@ -691,6 +693,19 @@ def qllm_probe_layer_launch(dmap, x_dtype, N, ldx, norm, has_beta, a_bits, weigh
     _chk(_lib.qllm_probe_layer_launch(C.byref(dmap.c), int(x_dtype), int(N), int(ldx), int(norm), int(bool(has_beta)), int(a_bits),
                                       C.byref(weight.c), int(workspace_bytes), C.byref(out)), "qllm_probe_layer_launch")
     return out
+
+
+def qllm_probe_layer_half(half, x, norm, gamma, beta, eps, dmap, a_bits, weight, y, workspace, stream=None):
+    """Half 1 (the fused kernel) or 2 (the product, on what half 1 left in the workspace) of the layer call by itself."""
+    N, Cc = _check_activation_args(x, norm, gamma, beta, dmap)
+    if dmap.C_out != weight.K:
+        _fail(f"the map makes {dmap.C_out} channels, the weights take {weight.K}")
+    _check_output(y, N, weight.O)
+    _check_tensor(workspace, "workspace", _U8_ONLY)
+    _check_on_device(y=y, workspace=workspace, x=x, gamma=gamma, beta=beta)
+    _chk(_lib.qllm_probe_layer_half(int(half), _dp(x), _x_dtype(x), N, Cc, x.stride(0), int(norm), _dp(gamma), _dp(beta),
+                                    float(eps), C.byref(dmap.c), int(a_bits), C.byref(weight.c), _dp(y), _x_dtype(y), y.stride(0),
+                                    _dp(workspace), workspace.numel(), _stream(stream)), "qllm_probe_layer_half")
 
 
 def raw():

@@ -150,6 +150,8 @@ int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C,
 // ever.  ahead: not null where the product's weights may be read into the caches on the side.
 int32_t qllm_fused_run(const qllm_detail::FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,
                        const WeightsAhead *ahead, void *hip_stream);
+// Whether qllm_fused_run lays the codes out where it is asked to.
+bool qllm_fused_lays(const qllm_detail::FusedArgs &a, int32_t x_dtype, int32_t bits, const uint8_t *tiles);
 // As much of the arguments as the choice of a launch depends on, and that choice.
 int32_t qllm_fused_describe(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta, int32_t bits,
                             qllm_detail::FusedArgs *args);

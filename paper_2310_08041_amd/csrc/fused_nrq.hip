@@ -541,12 +541,17 @@ int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C,
     return QLLM_OK;
 }
 
+bool qllm_fused_lays(const FusedArgs &a, int32_t x_dtype, int32_t bits, const uint8_t *tiles)
+{
+    return a.work && tiles && qllm_fused_tiles_fit(a, x_dtype, bits);
+}
+
 namespace {
 
 // What the layer call asks for, put into the arguments where the planned kernel lays the codes out; whether it does.
 bool take_asks(FusedArgs &a, int32_t x_dtype, int32_t bits, uint8_t *tiles, const WeightsAhead *ahead)
 {
-    if (!a.work || !tiles || !qllm_fused_tiles_fit(a, x_dtype, bits)) return false;
+    if (!qllm_fused_lays(a, x_dtype, bits, tiles)) return false;
     a.tiles = tiles;
     a.tiles_kt = bits == 4 ? a.n_groups_pad / 16 : (a.C_out + 63) / 64;
     if (ahead) {

@@ -2225,11 +2225,12 @@ extern "C" int64_t qllm_workspace_bytes(int64_t N, int64_t K, int64_t O, int32_t
     return floor_bytes - up(qllm_gemm_workspace_floor_bytes(N, K, O, a_bits)) + up(qllm_gemm_workspace_bytes(N, K, O, a_bits));
 }
 
-extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx,
-                                           int32_t norm, const float *gamma, const float *beta, float eps,
-                                           const qllm_map *map, int32_t a_bits, const qllm_weight *w, void *y,
-                                           int32_t y_dtype, int64_t ldy, void *workspace, int64_t workspace_bytes,
-                                           void *hip_stream)
+namespace {
+
+// halves: 1 the fused kernel, 2 the product on what it left in the workspace, 3 both
+int32_t layer_call(int halves, const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
+                   const float *beta, float eps, const qllm_map *map, int32_t a_bits, const qllm_weight *w, void *y, int32_t y_dtype,
+                   int64_t ldy, void *workspace, int64_t workspace_bytes, void *hip_stream)
 {
     if (!map || !w) return QLLM_ERR_NULL;
     if (w->K != map->C_out) return QLLM_ERR_SHAPE;
@@ -2258,10 +2259,30 @@ extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64
     rc = check_product(&q, a_bits, N, w, y, y_dtype, ldy, p, left);
     if (rc != QLLM_OK) return rc;
     const LayerAsks ask = layer_asks(N, w, a_bits, p, left);
-    bool laid = false;
-    rc = qllm_fused_run(fused, x_dtype, a_bits, ask.tiles, &laid, ask.ahead.base ? &ask.ahead : nullptr, hip_stream);
-    if (rc != QLLM_OK) return rc;
+    bool laid = qllm_fused_lays(fused, x_dtype, a_bits, ask.tiles);
+    if (halves & 1) rc = qllm_fused_run(fused, x_dtype, a_bits, ask.tiles, &laid, ask.ahead.base ? &ask.ahead : nullptr, hip_stream);
+    if (rc != QLLM_OK || !(halves & 2)) return rc;
     return int_gemm(&q, a_bits, N, w, y, y_dtype, ldy, nullptr, p, left, laid, hip_stream);
+}
+
+} // namespace
+
+extern "C" int32_t qllm_reassembled_linear(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx,
+                                           int32_t norm, const float *gamma, const float *beta, float eps,
+                                           const qllm_map *map, int32_t a_bits, const qllm_weight *w, void *y,
+                                           int32_t y_dtype, int64_t ldy, void *workspace, int64_t workspace_bytes,
+                                           void *hip_stream)
+{
+    return layer_call(3, x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, w, y, y_dtype, ldy, workspace, workspace_bytes, hip_stream);
+}
+
+extern "C" int32_t qllm_probe_layer_half(int32_t half, const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm,
+                                         const float *gamma, const float *beta, float eps, const qllm_map *map, int32_t a_bits,
+                                         const qllm_weight *w, void *y, int32_t y_dtype, int64_t ldy, void *workspace,
+                                         int64_t workspace_bytes, void *hip_stream)
+{
+    if (half != 1 && half != 2) return QLLM_ERR_SHAPE;
+    return layer_call(half, x, x_dtype, N, C, ldx, norm, gamma, beta, eps, map, a_bits, w, y, y_dtype, ldy, workspace, workspace_bytes, hip_stream);
 }
 
 extern "C" int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N, int64_t ldx, int32_t norm, int32_t has_beta,

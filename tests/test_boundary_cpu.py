@@ -195,6 +195,8 @@ def test_layer_entry_point_refuses_what_the_product_refuses_before_launching():
     assert call(100, 4, weight(4, colsum=None)) == -1 and call(100, 4, weight(4), y=None) == -1
     assert call(100, 4, weight(4), ydt=5) == -4 and call(100, 4, weight(4), ldy=4095) == -2
     assert call(100, 4, weight(6)) == -3 and call(1024, 8, weight(6)) == -3                                  # no such pair of widths
+    assert b.raw().qllm_probe_layer_half(3, 0x1000, b.BF16, 100, 64, 64, b.NORM_RMS, 0x2000, None, 1e-5, C.byref(m), 4, C.byref(weight(4)),
+                                         0x9000, b.F32, 4096, 0x40000, 1 << 24, None) == -2
     # what the first half refuses comes first, as ever
     assert b.raw().qllm_reassembled_linear(None, b.BF16, 100, 64, 64, b.NORM_RMS, 0x2000, None, 1e-5, C.byref(m), 4, C.byref(weight(4)),
                                            0x9000, 5, 4096, 0x40000, 1 << 24, None) == -1

@@ -948,6 +948,12 @@ def test_layer_lays_codes_out(b, N, C, K, O, norm, dtype, every, form, bits, lai
     assert laid or torch.equal(packed.view(N, -1), qa.codes.view(N, -1))
     b.qllm_int_gemm(qa, dw, want, None, gws)
     assert torch.equal(y, want)
+    y.fill_(float("nan"))
+    ws.fill_(0xCD)
+    for half in (1, 2):
+        assert half == 1 or not bool((y == y).any())          # half 1 leaves y alone
+        b.qllm_probe_layer_half(half, x, NORM_ID[norm], gamma, beta, 1e-5, dm, bits, dw, y, ws)
+    assert torch.equal(y, want)
 
 
 @pytest.mark.gpu
