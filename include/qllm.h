@@ -159,7 +159,8 @@ int32_t qllm_norm_reassemble_quant(const void *x, int32_t x_dtype, int64_t N, in
  * 64 times the fp32 accumulator is the integer accumulator of Eq. (1), bit for bit.  It is taken when
  * w->tiles6 is set and the workspace holds, behind the qllm_gemm_workspace_floor_bytes(...) bytes rounded up to a
  * multiple of 256, at least qllm_tiles6_bytes(N, w->K) bytes (the activations are re-laid into them first, a few
- * per cent of the GEMM's time; in qllm_reassembled_linear the fused kernel writes them so); otherwise the int8 path runs.  Same results either way.
+ * per cent of the GEMM's time; in qllm_reassembled_linear the fused kernel writes them so where the map's plan and the row fit on
+ * chip together, else packed rows and that launch); otherwise the int8 path runs.  Same results either way.
  *
  * Byte operands.  For the other bit pairs (6/6, 8/8, 8-bit activations on 4-bit weights; Sec. 5, "Quantization
  * settings") and larger batches the int8 matrix cores can be fed straight from one-byte-per-code copies of both operands:

@@ -41,7 +41,7 @@ struct FusedArgs {
     int64_t row_bytes;
     float *alpha;
     int32_t *zero, *rowsum;
-    uint8_t *tiles; // not null: the codes leave in the layout of qllm_pack_tiles6 (4 bits) or qllm_pack_tiles8 instead of packed rows
+    uint8_t *tiles; // not null: the codes leave as the product reads them, TILES6 in the activations' order (4 bits, see tiles6_x) or TILES8
     int32_t tiles_kt; // its K-tiles per row
     int32_t row_at; // 4 bits: where in LDS (dwords) the row is put together before it leaves
     // Workgroups beyond the rows' read weights that the product after this kernel is going to need (see read_ahead)
@@ -144,8 +144,9 @@ struct WeightsAhead {
 int32_t qllm_fused_prepare(const void *x, int32_t x_dtype, int64_t N, int64_t C, int64_t ldx, int32_t norm, const float *gamma,
                            const float *beta, float eps, const qllm_map *map, int32_t bits, const qllm_qact *out,
                            qllm_detail::FusedArgs *args);
-// The launch, with the choice of layout: tiles not null asks for the codes as qllm_pack_tiles6 (4 bits) or
-// qllm_pack_tiles8 lays them out (rows past N in the last block of 16 are left as they are) in place of out->codes;
+// The launch, with the choice of layout: tiles not null asks for the codes as the product reads them, TILES6 in the activations'
+// order (4 bits; not what qllm_pack_tiles6 makes of weights) or TILES8, in place of out->codes (rows past N in the last
+// block of 16 are left as they are: the product of such a row is dropped);
 // *wrote_tiles says whether the kernel that runs does that (the planned one); if not, out->codes holds the packed rows as
 // ever.  ahead: not null where the product's weights may be read into the caches on the side.
 int32_t qllm_fused_run(const qllm_detail::FusedArgs &prepared, int32_t x_dtype, int32_t bits, uint8_t *tiles, bool *wrote_tiles,

@@ -602,8 +602,9 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
     Raw<XT> raw[ITERS];
     // Rows blockIdx, + grid, ...; where 16 rows share lines of the output, each XCD (workgroups go to them in turn) takes
     // whole blocks of 16 of every sweep over the grid, dealt out in turn, so that what is left for the last sweep is
-    // spread over the XCDs as well (a run of neighbours each: 2048 rows on 1280 workgroups leave three XCDs idle in the
-    // second sweep: 2048 x 4096 4-bit RMS 19.9 us, 16.8 so).
+    // spread over the XCDs as well (a run of neighbours each: 2048 rows on 1280 workgroups, when five of 4096 4-bit channels
+    // were resident on a CU, left three XCDs idle in the second sweep, 19.9 us against 16.8; 107 registers now leave four, and
+    // two whole sweeps; begun with an empty pass the kernel takes as long, 0.99-1.00).
     int64_t row = blockIdx.x;
     const uint32_t row_groups = TILES ? (uint32_t)a.row_groups : gridDim.x;
     if (TILES && (row_groups & 7u) == 0) {
@@ -770,7 +771,7 @@ __global__ __launch_bounds__(NT_MAX) void fused_planned_kernel(const FusedArgs a
             if (lane == 0) a.rowsum[r] = s;
         }
     };
-    // A finished row in the layout of the FP6 path (qllm_pack_tiles6): 16 + 8 bytes per 32 codes, from LDS, where its groups
+    // A finished row in the layout of the FP6 path (TILES6 in the activations' order, see tiles6_x): 16 + 8 bytes per 32 codes, from LDS, where its groups
     // were put one by one.  (Each lane its own groups, a dword and a half-word of 6 bytes per group: 79 us at 2048 x 28672, more
     // than the packed rows' 53 and the laying-out pass's 12; L2 takes requests, not bytes.)
     auto lay_row = [&](int64_t r, int ltid) {

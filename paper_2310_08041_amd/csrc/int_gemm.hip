@@ -935,12 +935,12 @@ __device__ __forceinline__ Frag6 read6(const uint8_t *block, int x, int y)
 // reads of a K-tile's first groups in front of the first operation: eight waves' reads keep the LDS busy for some 300 of
 // the K-tile's 1500 clocks before any of them multiplies.)  The large tile reads a token-side block behind every other
 // operation and loads behind every third from the middle on (a load the CU's address unit has not accepted yet holds its
-// wave up).  Measured with the copies of lds_copy.h, kernel alone, us, before : copies : this order: FP6 2048 x 28672 -> 8192
-// 205-213 : 204-208 : 191-195, 4096 x 5120 -> 27648 286 : 283 : 279; bytes, 6-bit 2048 x 28672 -> 8192 317-333 : 308-327 : 298-302,
-// 8-bit 2048 x 5120 -> 13824 133 : 129 : 121-126, small tiles 777 x 5000 -> 4999 36.7 : 35.2 : 34.1, with K split 200 x 13824 ->
-// 5120 25.9 : 23.9 : 22.2.  Where the token-side reads go (every operation, second, third) changes nothing any more: in
-// clocks the large tiles are at 0.78 (FP6) and 0.88 (int8) of the same loop without reads and loads; the clock under this
-// load is 1.95-2.05 GHz (2.45 on operands of zeros).
+// wave up).  With the copies of lds_copy.h, kernel traces on one card, us, before both : now: FP6 2048 x 28672 -> 8192 185.4 : 181.3,
+// 4096 x 5120 -> 27648 283.4 : 278.1, 2048 x 4096 -> 8192 of 12288 39.8 : 39.9; bytes, 6-bit 2048 x 28672 -> 8192 302 : 281, small tiles
+// 777 x 5000 -> 4999 37.4 : 35.0, with K split 200 x 13824 -> 5120 26.7 : 26.2; qllm_int_gemm, small tiles of 300-2048 tokens, 4096-28672
+// channels: bytes 3-16 % faster, FP6 within 2 % either way.  Where the token-side reads go (every operation, second, third)
+// changes nothing any more: in clocks the large tiles are at 0.78 (FP6) and 0.88 (int8) of the same loop without reads and
+// loads; the clock under this load is 1.96-2.05 GHz (2.45 on operands of zeros).
 template <int MI, int NJ>
 struct KTilePlan {
     static constexpr int AHEAD = 2, STEPS = MI * NJ;
