@@ -122,7 +122,9 @@ inline bool begins_with_empty_pass(int rows, int64_t N, int lanes, int cus) { re
 //   10752 -> 3968, 53 tokens 8 / 8       22.8 : 24.2 : 21.3    37.5 : 33.3 : 33.8     (eight parts, 31 columns)
 //   23040 -> 1664, 68 tokens 8 / 8       27.9 : 30.0 : 27.6    42.5 : 44.2 : 42.9
 // Geometric mean over 96 shapes that read (33-128 tokens, 512-28672 channels, 256-27648 features): 1.010 and 1.041 of no reading, 24 MB
-// 0.970 and 1.021; the worst, lists streamed, 23168 -> 2304, 60 tokens 38.6 : 40.9 : 40.1.  With fewer idle CUs than rows the reading
+// 0.970 and 1.021; the worst, lists streamed, 23168 -> 2304, 60 tokens 38.6 : 40.9 : 40.1.  Streamed lists come through
+// the same L2s; where these still hold the weights from the last call their rows wait for nothing gained: 5 % merged, weights of
+// 6-12 MB 0.977 of no reading (41 x 16128 -> 640 8 / 8 32.2 : 34.8), but 1.045 out of cache, where a model's weights are.  With fewer idle CUs than rows the reading
 // takes longer than the rows (160 x 5120 -> 13824 25.4 : 25.9, 200 x 4096 -> 12288 19.2 : 22.5): there is none.
 constexpr int64_t READ_AHEAD_BYTES = 24000000, READ_AHEAD_TRIPS = 4, READ_AHEAD_IN_FLIGHT = 4096;
 inline int64_t read_ahead_each(int64_t block, int64_t tile, int64_t cols, int64_t splits, int64_t waves, bool norm)
