@@ -44,6 +44,10 @@ struct FusedArgs {
     uint8_t *tiles; // not null: the codes leave as the product reads them, TILES6 in the activations' order (4 bits, see tiles6_x) or TILES8
     int32_t tiles_kt; // its K-tiles per row
     int32_t row_at; // 4 bits: where in LDS (dwords) the row is put together before it leaves
+    int32_t row_groups; // workgroups that have rows
+    // calibration variant
+    float *absmax, *y_dump;
+    int32_t n_dump;
     // Workgroups beyond the rows' read weights that the product after this kernel is going to need (see read_ahead)
     const uint8_t *ahead;
     int64_t ahead_total;    // bytes of the weights; 0: none of this
@@ -52,10 +56,6 @@ struct FusedArgs {
     QuotientBy ahead_cols, ahead_splits; // the product's workgroups: 8 blocks each, one after the other, times parts of K
     int32_t ahead_each;     // bytes to read for every workgroup: its first blocks
     QuotientBy ahead_pieces, ahead_of_block; // the same in KB; KB of a block's part of K
-    int32_t row_groups;     // workgroups that have rows
-    // calibration variant
-    float *absmax, *y_dump;
-    int32_t n_dump;
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
