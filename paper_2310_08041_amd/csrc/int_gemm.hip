@@ -1279,6 +1279,168 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
     }
 }
 
+// ---- mid-size batches: one round of workgroups, each with two halves that sum alternate K-tiles.
+// Tiles of 32 MI tokens x 32 NJ features of Y, so that a product too large for the streaming kernel and too small to fill
+// rounds of the tiles above is one workgroup per CU (plan_mid).  Waves 0..3 (2 x 2, 16 MI x 16 NJ each) work on the first K-tile of
+// a step and waves 4..7 on the second; at the end each half finishes half of the tile's tokens and gets the other half's sums of
+// them through LDS.  Against one K-tile per barrier and eight waves over the tile this halves the barriers and takes a third
+// off the operand reads; against K split over workgroups it writes no partial sums and needs no second launch.
+// What bounds it is the way of the operands into LDS: left out of the loop, operations and reads change nothing, loads do
+// (200 x 13824 -> 5120: 26 of 27 us).  A CU's loads return in order and no more than some 64 KB are under way at a time, so
+// that its rate is those over the latency of whatever the slowest comes from (HBM 62, the cache behind the L2s 95, an L2 130 GB/s
+// per CU); a ring deeper than four stages changes nothing, and lines asked for ahead hold up the loads behind them.
+// Operands are read a step ahead of their operations: two sets of registers, a step reads one and multiplies the other.
+struct MidBytes { // TILES8 on both sides, int8 matrix cores
+    typedef v4i Acc;
+    typedef v4i Frag;
+    static constexpr int KT = T8_KT, BLOCK = T8_BLOCK;
+    static constexpr bool FP = false;
+    static __device__ __forceinline__ Frag zero() { return v4i{0, 0, 0, 0}; }
+    static __device__ __forceinline__ const uint8_t *tokens(const GemmArgs &g) { return g.a_tiles8; }
+    static __device__ __forceinline__ const uint8_t *features(const GemmArgs &g) { return g.w_tiles8; }
+    static __device__ __forceinline__ int k_tiles(const GemmArgs &g) { return (g.K + KT - 1) / KT; }
+    static __device__ __forceinline__ Frag token(const uint8_t *block, int lane) { return *reinterpret_cast<const v4i *>(block + 16 * lane); }
+    static __device__ __forceinline__ Frag feature(const uint8_t *block, int lane) { return token(block, lane); }
+    static __device__ __forceinline__ Acc multiply(const Frag &w, const Frag &a, const Acc &c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(w, a, c, 0, 0, 0); }
+};
+
+template <class OP, int MI, int NJ, int STAGES>
+constexpr size_t mid_lds()
+{
+    constexpr int ring = STAGES * 2 * 2 * (MI + NJ) * OP::BLOCK, sums = 8 * ((MI + 1) / 2) * NJ * 1024;
+    return (size_t)(ring > sums ? ring : sums) + EPI_BYTES<32 * MI, 32 * NJ>;
+}
+
+template <class OP, int ABITS, int WBITS, typename YT, int MI, int NJ, int STAGES>
+__global__ __launch_bounds__(LTHREADS, 1) void gemm_mid_kernel(const GemmArgs g)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    typedef typename OP::Acc Acc;
+    constexpr int TM = 32 * MI, TN = 32 * NJ, BLOCKS = 2 * (MI + NJ);
+    constexpr int HALF = BLOCKS * OP::BLOCK, STAGE = 2 * HALF, UNITS = HALF / 1024, NLOAD = (UNITS + 3) / 4;
+    static_assert(HALF % 1024 == 0 && 2 * MI * OP::BLOCK % 1024 == 0, "a load of 1 KB is all token side or all feature side");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    // gridDim.x is a multiple of eight, so that the tiles of the same features run on one XCD; 64-feature tiles go there in
+    // pairs, as the 128-feature columns do whose weights the layer call reads ahead
+    const int x = blockIdx.x, n0 = blockIdx.y * TM, o0 = (NJ == 2 ? 2 * (8 * (x >> 4) + (x & 7)) + (x >> 3 & 1) : x) * TN;
+    if (o0 >= g.O) return;
+    const int all_kt = OP::k_tiles(g), steps = (all_kt + 1) / 2;
+    const int a_blocks = (g.N + 15) / 16, w_blocks = (g.O + 15) / 16;
+
+    // fetch assignment: the four waves of a half bring in its K-tile, load t of wave w its KB NLOAD (w & 3) + t (the last KB
+    // again where the waves have more loads than there are), lane l the l-th 16 bytes of it
+    uint32_t src_off[NLOAD];
+#pragma unroll
+    for (int t = 0; t < NLOAD; ++t) {
+        const int off = min((wave & 3) * NLOAD + t, UNITS - 1) * 1024 + lane * 16, blk = off / OP::BLOCK, within = off % OP::BLOCK;
+        const int rb = blk < 2 * MI ? min(n0 / 16 + blk, a_blocks - 1) : min(o0 / 16 + blk - 2 * MI, w_blocks - 1); // past the edge: the last block
+        src_off[t] = (uint32_t)rb * (uint32_t)all_kt * OP::BLOCK + within;
+    }
+    auto fetch_one = [&](int step, int stage, int t) { // past the last K-tile (of an odd number, or of the ring's end): zeros
+        const int unit = min((wave & 3) * NLOAD + t, UNITS - 1), kt = 2 * step + half;
+        const bool token = unit * 1024 < 2 * MI * OP::BLOCK;
+        const uint32_t bytes = kt < all_kt ? (uint32_t)(token ? a_blocks : w_blocks) * (uint32_t)all_kt * OP::BLOCK : 0u;
+        qllm_detail::copy_1k_to_lds(token ? OP::tokens(g) : OP::features(g), bytes, src_off[t], (uint32_t)kt * OP::BLOCK,
+                                    lds + stage * STAGE + half * HALF + unit * 1024);
+    };
+    constexpr int IN_FLIGHT = (STAGES - 2) * NLOAD; // loads of the steps after the next one
+    constexpr int WAIT_LANDED = IN_FLIGHT | (7 << 4) | (15 << 8);      // s_waitcnt vmcnt(IN_FLIGHT): the next step has landed
+    constexpr int WAIT_LANDED_LGKM0 = IN_FLIGHT | (7 << 4) | (0 << 8); // ... and lgkmcnt(0)
+    static_assert(IN_FLIGHT < 16, "the low four bits of vmcnt");
+
+    Acc acc[MI][NJ];
+    typename OP::Frag ar[2][MI], wr[2][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 2 * MI; ++i) ar[i / MI][i % MI] = OP::zero();
+#pragma unroll
+    for (int j = 0; j < 2 * NJ; ++j) wr[j / NJ][j % NJ] = OP::zero();
+
+    uint8_t *const epi = lds + (mid_lds<OP, MI, NJ, STAGES>() - EPI_BYTES<TM, TN>);
+    store_epilogue<ABITS, WBITS, TM, TN, OP::FP, 8>(g, load_epilogue<TM, TN>(g, n0, o0, tid), epi, tid);
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s)
+#pragma unroll
+        for (int t = 0; t < NLOAD; ++t) fetch_one(s, s, t);
+    __builtin_amdgcn_s_waitcnt(WAIT_LANDED);
+    __syncthreads();
+
+    int stage = 0, fetch_stage = STAGES - 1;
+    // reads this step's operands into set P and multiplies the step's before (the first time zeros) from the other one
+    auto k_step = [&](auto parity, int step) {
+        constexpr int P = decltype(parity)::value;
+        static_assert(NJ + MI <= MI * NJ && 2 * NLOAD <= MI * NJ + 1, "every read and load has its place behind an operation");
+        const uint8_t *const tokens = lds + stage * STAGE + half * HALF + wm * MI * OP::BLOCK;
+        const uint8_t *const features = lds + stage * STAGE + half * HALF + (2 * MI + wn * NJ) * OP::BLOCK;
+#pragma unroll
+        for (int s = 0; s < MI * NJ; ++s) {
+            acc[s / NJ][s % NJ] = OP::multiply(wr[1 - P][s % NJ], ar[1 - P][s / NJ], acc[s / NJ][s % NJ]);
+            if (s < NJ) wr[P][s] = OP::feature(features + s * OP::BLOCK, lane);
+            else if (s < NJ + MI) ar[P][s - NJ] = OP::token(tokens + (s - NJ) * OP::BLOCK, lane);
+            if ((s & 1) == 0 && s / 2 < NLOAD) fetch_one(step + STAGES - 1, fetch_stage, s / 2); // into the stage whose last reader passed the barrier
+            __builtin_amdgcn_sched_barrier(0); // this order is the order issued
+        }
+        // the next step has landed (this wave's share; the barrier adds the others'), own reads done
+        __builtin_amdgcn_s_waitcnt(WAIT_LANDED_LGKM0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        fetch_stage = stage;
+        stage = stage == STAGES - 1 ? 0 : stage + 1;
+    };
+    int step = 0;
+    for (; step + 1 < steps; step += 2) {
+        k_step(std::integral_constant<int, 0>{}, step);
+        k_step(std::integral_constant<int, 1>{}, step + 1);
+    }
+    if (step < steps) k_step(std::integral_constant<int, 0>{}, step);
+    auto last_step = [&](auto parity) {
+        constexpr int P = decltype(parity)::value;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = OP::multiply(wr[P][j], ar[P][i], acc[i][j]);
+    };
+    if (steps & 1) last_step(std::integral_constant<int, 0>{});
+    else last_step(std::integral_constant<int, 1>{});
+    // the loads past the last step went to stages nobody reads; the sums below take their place in LDS
+    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+    __syncthreads();
+
+    constexpr int FIRST = (MI + 1) / 2; // the first half finishes its waves' first FIRST blocks of tokens, the second the others
+    Acc *const sums = reinterpret_cast<Acc *>(lds) + (wave & 3) * FIRST * NJ * 64 + lane;
+    constexpr int OTHER = 4 * FIRST * NJ * 64; // from the sums that the first half leaves to the second's
+    auto leave = [&](auto from, auto to) {
+#pragma unroll
+        for (int i = decltype(from)::value; i < decltype(to)::value; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) sums[half * OTHER + ((i - decltype(from)::value) * NJ + j) * 64] = acc[i][j];
+    };
+    auto finish = [&](auto from, auto to) {
+        constexpr int F = decltype(from)::value, COUNT = decltype(to)::value - F;
+        Acc sum[COUNT][NJ];
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) sum[i][j] = acc[F + i][j] + sums[(1 - half) * OTHER + (i * NJ + j) * 64];
+        const int nl = wm * 16 * MI + 16 * F, ol = wn * 16 * NJ;
+        if (finish_from_lds<YT, TM, TN>(g, sum, epi, n0, o0, nl, ol, lane)) return;
+        finish_wave_tile<ABITS, WBITS, YT, COUNT, NJ>(g, sum, n0 + nl, o0 + ol, lane, g.K);
+    };
+    constexpr std::integral_constant<int, 0> none{};
+    constexpr std::integral_constant<int, FIRST> some{};
+    constexpr std::integral_constant<int, MI> all{};
+    if (half == 0) leave(some, all);
+    else leave(none, some);
+    __syncthreads();
+    if (half == 0) finish(none, some);
+    else finish(some, all);
+}
+
 // Packed rows -> TILES8; one lane per (block, K-tile, lane of the operand read): 16 codes of one row.
 template <int BITS>
 __global__ __launch_bounds__(256) void tiles8_kernel(const uint8_t *codes, int64_t row_bytes, int32_t rows, int32_t K, int32_t n_kt,
@@ -1729,10 +1891,35 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
     return s < 2 ? 1 : (int32_t)s;
 }
 
+// The tile of gemm_mid_kernel that a product on byte operands takes, in units of 32 tokens and 32 features; none: another kernel.
+// Layer call, three sets of weights in turn, us, other kernel : this one:
+//   128 x 64 in place of 128 x 128 tiles with K split (or of half a round of them), where these tiles are one round:
+//     256 x 8192 -> 8192 8/4 38.8 : 29.2, 512 x 4096 -> 4096 8/8 27.5 : 20.8, 200 x 5120 -> 5120 8/8 23.5 : 20.3,
+//     100 x 4096 -> 16384 6/6 29.4 : 23.1, 1000 x 4096 -> 2048 6/6 29.7 : 23.0, 250 x 3000 -> 5000 8/4 21.1 : 16.7
+//   The whole of K is a workgroup's, so that the gain ends with K, the sooner the more parts the other kernel has: two parts
+//     400 x 11008 -> 4096 8/4 40.6 : 38.3, 500 x 14336 -> 4096 67.8 : 69.3; four 100 x 8192 -> 8192 29.3 : 27.8, 160 x 11008 ->
+//     4096 6/6 28.5 : 32.6; six 128 x 5120 -> 5120 6/6 21.8 : 20.7
+//   Up to 128 tokens 6-bit codes with fewer than 184 such tiles stay with the parts of K, for which the layer call reads weights ahead
+//     (100 x 5120 -> 9216 23.4 : 20.9 all the same).
+//   160 x 128, where 128 x 128 tiles are more than one round of workgroups and these are not: 777 x 5000 -> 4999 8/4 31.9 : 24.7 (the
+//     product), 600 x 28672 -> 8192 8/8 216 : 178, 777 x 5120 -> 5120 8/8 43.8 : 36.5, 300 x 4096 -> 12288 8/4 33.3 : 28.6; with no more
+//     128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 : 31.5, 400 x 8192 -> 8192 51 : 53)
+struct MidPlan {
+    int mi, nj;
+};
+MidPlan plan_mid(int64_t N, int64_t K, int64_t O, int a_bits)
+{
+    auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
+    const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80;
+    if (half_tiles >= fewest && half_tiles <= 256 && K <= 12288 && K * t8_splits(N, K, O) <= 36000) return MidPlan{4, 2};
+    if (groups(128, 128) > 256 && groups(160, 128) <= 256) return MidPlan{5, 4};
+    return MidPlan{0, 0};
+}
+
 // 6- or 8-bit activations, more than 32 tokens, byte operands straight into the int8 matrix cores: the
 // activations are re-laid into the workspace, then the product, laid over the chip as on the FP6 path.
 template <int ABITS, int WBITS>
-int32_t launch_t8(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipStream_t stream)
+int32_t launch_t8(const GemmArgs &g, const TilePlan &plan, const MidPlan &mid, int32_t y_dtype, hipStream_t stream)
 {
     if (!g.a_laid) {
         const int32_t st = launch_tiles8(g.a_codes, ABITS, g.N, g.K, const_cast<uint8_t *>(g.a_tiles8), stream);
@@ -1760,6 +1947,17 @@ int32_t launch_t8(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipS
         if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
         return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
     };
+    auto launch_mid = [&](auto mi, auto nj) -> int32_t {
+        constexpr int MI = decltype(mi)::value, NJ = decltype(nj)::value;
+        const unsigned columns = (unsigned)((g.O + 127) / 128 + 7) / 8 * 8;
+        static_assert(NJ == 2 || NJ == 4, "columns of 128 features, or their halves");
+        const dim3 grid(columns * (4 / NJ), (unsigned)((g.N + 32 * MI - 1) / (32 * MI)));
+        constexpr size_t lds = mid_lds<MidBytes, MI, NJ, 4>();
+        if (y_dtype == QLLM_F32) return launch_kernel(gemm_mid_kernel<MidBytes, ABITS, WBITS, float, MI, NJ, 4>, grid, dim3(LTHREADS), lds, g, stream);
+        return launch_kernel(gemm_mid_kernel<MidBytes, ABITS, WBITS, uint16_t, MI, NJ, 4>, grid, dim3(LTHREADS), lds, g, stream);
+    };
+    if (mid.mi == 4) return launch_mid(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+    if (mid.mi == 5) return launch_mid(std::integral_constant<int, 5>{}, std::integral_constant<int, 4>{});
     if (g.splits > 1) return launch_small(g); // K is only split where the small tile is the choice
     if (plan.o_split > 0) { // whole rounds of large tiles, then the other output features with small ones
         GemmArgs first = g, rest = g;
@@ -1891,6 +2089,7 @@ struct Route {
     int32_t kernel;    // QLLM_GEMM_*
     int32_t splits;    // parts of K
     TilePlan tiles;    // not for the streaming kernel
+    MidPlan mid;       // byte operands, K not split
     StreamPlan stream; // the streaming kernel only
 };
 
@@ -1900,7 +2099,7 @@ struct Route {
 Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool tiles6, bool tiles8, int64_t parts8, bool a_laid, bool one_launch)
 {
     const bool both4 = a_bits == 4 && w_bits == 4;
-    Route r{QLLM_GEMM_EXPANDS, 1, TilePlan{true, 0}, plan_stream(N, K, O, a_bits, w_bits, both4 ? tiles6 : tiles8, true)};
+    Route r{QLLM_GEMM_EXPANDS, 1, TilePlan{true, 0}, MidPlan{0, 0}, plan_stream(N, K, O, a_bits, w_bits, both4 ? tiles6 : tiles8, true)};
     if (r.stream.take && !a_laid) {
         r.kernel = QLLM_GEMM_STREAMS;
     } else if (both4) {
@@ -1921,6 +2120,8 @@ Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool t
     } else if (tiles8) {
         r.kernel = QLLM_GEMM_BYTES;
         const int64_t s = t8_splits(N, K, O);
+        r.mid = plan_mid(N, K, O, a_bits);
+        if (r.mid.mi) return r;
         if (s > 1 && parts8 > 1) r.splits = (int32_t)(parts8 < s ? parts8 : s);
         else r.tiles = plan_tiles(N, O, !one_launch);
     } else {
@@ -1951,7 +2152,7 @@ int32_t launch(const GemmArgs &g, const Route &route, int32_t y_dtype, hipStream
         if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_w4a4_kernel<float, 8, 4>, big_grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
         return launch_kernel(int_gemm_w4a4_kernel<uint16_t, 8, 4>, big_grid, dim3(LTHREADS), NBUF * PBUF, g, stream);
     } else {
-        if (route.kernel == QLLM_GEMM_BYTES) return launch_t8<ABITS, WBITS>(g, route.tiles, y_dtype, stream);
+        if (route.kernel == QLLM_GEMM_BYTES) return launch_t8<ABITS, WBITS>(g, route.tiles, route.mid, y_dtype, stream);
         if (small) { // 33..128 tokens
             const dim3 grid((unsigned)((g.O + BN - 1) / BN), (unsigned)((g.N + BM - 1) / BM));
             if (y_dtype == QLLM_F32) return launch_kernel(int_gemm_kernel<ABITS, WBITS, float>, grid, dim3(THREADS), 0, g, stream);

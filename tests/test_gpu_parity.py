@@ -502,6 +502,19 @@ def test_gemm_tiled_kernels(oracle, b, N, K, O, a_bits, w_bits, copies, tile, pa
         check_y(oracle, y, ref, y_dtype)
 
 
+# one round of 128 x 64 or 160 x 128 tiles: K of one K-tile, an even and an odd number of them, partial tiles on both edges
+MID = [(250, 1, 8190, (6, 6), True), (250, 65, 8191, (6, 6), True), (250, 190, 8190, (6, 6), False), (129, 3000, 5121, (6, 6), True),
+       (256, 3000, 8192, (8, 8), False), (250, 4500, 8190, (8, 4), True), (40, 6000, 16320, (8, 8), True)] + [
+       (N, K, O, p, i) for N, K, O, i in [(600, 1, 8190, True), (620, 70, 8191, False), (770, 200, 5000, True)] for p in [(6, 6), (8, 8), (8, 4)]]
+
+
+@pytest.mark.parametrize("N,K,O,bits,inside", MID)
+def test_gemm_mid_size_tiles(oracle, b, N, K, O, bits, inside):
+    """The byte-operand kernel whose halves sum alternate K-tiles, checked as every tiled kernel is: accumulators exact, the two
+    epilogues bit for bit, the result against the oracle."""
+    test_gemm_tiled_kernels(oracle, b, N, K, O, *bits, True, 128, 1, inside)
+
+
 @pytest.mark.parametrize("a_bits,w_bits", [(4, 4), (6, 6), (8, 4)])
 def test_gemm_two_launch_tile_plan(oracle, b, a_bits, w_bits):
     """A shape whose 256 x 256 tiles fill one whole round of the chip and leave a rest that 128 x 128 tiles finish in one
