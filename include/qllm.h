@@ -179,8 +179,8 @@ int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_
  *   QLLM_GEMM_STREAMS   one kernel streams the packed codes of both operands ("Small batches")
  *   QLLM_GEMM_FP6       the FP6 path                QLLM_GEMM_BYTES   byte operands
  *   QLLM_GEMM_EXPANDS   the packed codes are expanded inside a tiled kernel
- * *tile: 256 or 128 (tokens and features of a tile; 128 also for one round of tiles of 128 x 64 or 160 x 128 on byte operands),
- * 256 + 128 (a launch of each), 0 for QLLM_GEMM_STREAMS;
+ * *tile: 256 or 128 (tokens and features of a tile; 128 also for one round of mid-size tiles, 64 or 128
+ * features wide), 256 + 128 (a launch of each), 0 for QLLM_GEMM_STREAMS;
  * *parts: parts of K (1: whole).  Returns the kernel (>= 0) or a QLLM_ERR_* (< 0). */
 #define QLLM_GEMM_STREAMS 0
 #define QLLM_GEMM_FP6 1

@@ -1304,6 +1304,26 @@ struct MidBytes { // TILES8 on both sides, int8 matrix cores
     static __device__ __forceinline__ Acc multiply(const Frag &w, const Frag &a, const Acc &c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(w, a, c, 0, 0, 0); }
 };
 
+struct MidFp6 { // TILES6 on both sides, FP6 matrix cores
+    typedef v4f Acc;
+    typedef Frag6 Frag;
+    static constexpr int KT = T6_KT, BLOCK = T6_BLOCK;
+    static constexpr bool FP = true;
+    static __device__ __forceinline__ Frag zero() { return Frag6{v4i{0, 0, 0, 0}, v2i{0, 0}}; }
+    static __device__ __forceinline__ const uint8_t *tokens(const GemmArgs &g) { return g.a_tiles; }
+    static __device__ __forceinline__ const uint8_t *features(const GemmArgs &g) { return g.w_tiles; }
+    static __device__ __forceinline__ int k_tiles(const GemmArgs &g) { return g.Kpad / KT; }
+    static __device__ __forceinline__ Frag token(const uint8_t *block, int lane)
+    {
+        return read6(block, qllm_detail::tiles6_x(lane & 15, lane >> 4), qllm_detail::tiles6_y(lane & 15, lane >> 4));
+    }
+    static __device__ __forceinline__ Frag feature(const uint8_t *block, int lane) { return read6(block, 16 * lane, T6_X + 8 * lane); }
+    static __device__ __forceinline__ Acc multiply(const Frag &w, const Frag &a, const Acc &c)
+    {
+        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(operand6(w), operand6(a), c, 2, 2, 0, 0, 0, 0);
+    }
+};
+
 template <class OP, int MI, int NJ, int STAGES>
 constexpr size_t mid_lds()
 {
@@ -1373,7 +1393,8 @@ __global__ __launch_bounds__(LTHREADS, 1) void gemm_mid_kernel(const GemmArgs g)
     // reads this step's operands into set P and multiplies the step's before (the first time zeros) from the other one
     auto k_step = [&](auto parity, int step) {
         constexpr int P = decltype(parity)::value;
-        static_assert(NJ + MI <= MI * NJ && 2 * NLOAD <= MI * NJ + 1, "every read and load has its place behind an operation");
+        constexpr int LOAD_STEP = 2 * NLOAD <= MI * NJ + 1 ? 2 : 1;
+        static_assert(NJ + MI <= MI * NJ && NLOAD <= MI * NJ, "every read and load has its place behind an operation");
         const uint8_t *const tokens = lds + stage * STAGE + half * HALF + wm * MI * OP::BLOCK;
         const uint8_t *const features = lds + stage * STAGE + half * HALF + (2 * MI + wn * NJ) * OP::BLOCK;
 #pragma unroll
@@ -1381,7 +1402,7 @@ __global__ __launch_bounds__(LTHREADS, 1) void gemm_mid_kernel(const GemmArgs g)
             acc[s / NJ][s % NJ] = OP::multiply(wr[1 - P][s % NJ], ar[1 - P][s / NJ], acc[s / NJ][s % NJ]);
             if (s < NJ) wr[P][s] = OP::feature(features + s * OP::BLOCK, lane);
             else if (s < NJ + MI) ar[P][s - NJ] = OP::token(tokens + (s - NJ) * OP::BLOCK, lane);
-            if ((s & 1) == 0 && s / 2 < NLOAD) fetch_one(step + STAGES - 1, fetch_stage, s / 2); // into the stage whose last reader passed the barrier
+            if (s % LOAD_STEP == 0 && s / LOAD_STEP < NLOAD) fetch_one(step + STAGES - 1, fetch_stage, s / LOAD_STEP); // into the stage whose last reader passed the barrier
             __builtin_amdgcn_sched_barrier(0); // this order is the order issued
         }
         // the next step has landed (this wave's share; the barrier adds the others'), own reads done
@@ -1818,10 +1839,28 @@ int32_t launch_tiles6(const uint8_t *codes, int64_t row_bytes, int64_t rows, int
     return QLLM_OK;
 }
 
+// The tile of gemm_mid_kernel that a product takes, in units of 32 tokens and 32 features; none: another kernel.
+struct MidPlan {
+    int mi, nj;
+};
+template <class OP, int ABITS, int WBITS, int MI, int NJ, int STAGES>
+int32_t launch_mid(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
+{
+    static_assert(NJ == 2 || NJ == 4, "columns of 128 features, or their halves");
+    const unsigned columns = (unsigned)((g.O + 127) / 128 + 7) / 8 * 8;
+    const dim3 grid(columns * (4 / NJ), (unsigned)((g.N + 32 * MI - 1) / (32 * MI)));
+    constexpr size_t lds = mid_lds<OP, MI, NJ, STAGES>();
+    if (y_dtype == QLLM_F32) return launch_kernel(gemm_mid_kernel<OP, ABITS, WBITS, float, MI, NJ, STAGES>, grid, dim3(LTHREADS), lds, g, stream);
+    return launch_kernel(gemm_mid_kernel<OP, ABITS, WBITS, uint16_t, MI, NJ, STAGES>, grid, dim3(LTHREADS), lds, g, stream);
+}
+
 // 4-bit codes on both sides, more than 32 tokens, on the FP6 matrix cores: the activations are re-laid
 // into g.a_tiles first, unless they are there already.
-int32_t launch_fp6(const GemmArgs &g, const TilePlan &plan, int32_t y_dtype, hipStream_t stream)
+int32_t launch_fp6(const GemmArgs &g, const TilePlan &plan, const MidPlan &mid, int32_t y_dtype, hipStream_t stream)
 {
+    if (mid.mi == 5) return launch_mid<MidFp6, 4, 4, 5, 2, 3>(g, y_dtype, stream); // only where the activations are laid out
+    if (mid.mi == 4 && mid.nj == 2) return launch_mid<MidFp6, 4, 4, 4, 2, 4>(g, y_dtype, stream);
+    if (mid.mi == 4) return launch_mid<MidFp6, 4, 4, 4, 4, 3>(g, y_dtype, stream);
     if (!g.a_laid) {
         const int32_t st = launch_tiles6<true>(g.a_codes, g.a_row_bytes, g.N, g.Kpad, const_cast<uint8_t *>(g.a_tiles), stream);
         if (st != QLLM_OK) return st;
@@ -1891,7 +1930,7 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
     return s < 2 ? 1 : (int32_t)s;
 }
 
-// The tile of gemm_mid_kernel that a product on byte operands takes, in units of 32 tokens and 32 features; none: another kernel.
+// gemm_mid_kernel on byte operands.
 // Layer call, three sets of weights in turn, us, other kernel : this one:
 //   128 x 64 in place of 128 x 128 tiles with K split (or of half a round of them), where these tiles are one round:
 //     256 x 8192 -> 8192 8/4 38.8 : 29.2, 512 x 4096 -> 4096 8/8 27.5 : 20.8, 200 x 5120 -> 5120 8/8 23.5 : 20.3,
@@ -1904,10 +1943,7 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 //   160 x 128, where 128 x 128 tiles are more than one round of workgroups and these are not: 777 x 5000 -> 4999 8/4 31.9 : 24.7 (the
 //     product), 600 x 28672 -> 8192 8/8 216 : 178, 777 x 5120 -> 5120 8/8 43.8 : 36.5, 300 x 4096 -> 12288 8/4 33.3 : 28.6; with no more
 //     128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 : 31.5, 400 x 8192 -> 8192 51 : 53)
-struct MidPlan {
-    int mi, nj;
-};
-MidPlan plan_mid(int64_t N, int64_t K, int64_t O, int a_bits)
+MidPlan plan_mid8(int64_t N, int64_t K, int64_t O, int a_bits)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80;
@@ -1947,17 +1983,8 @@ int32_t launch_t8(const GemmArgs &g, const TilePlan &plan, const MidPlan &mid, i
         if (y_dtype == QLLM_F32) return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, float, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
         return launch_kernel(gemm_tiles8_kernel<ABITS, WBITS, uint16_t, 8, 4, 3>, grid, dim3(LTHREADS), lds, ga, stream);
     };
-    auto launch_mid = [&](auto mi, auto nj) -> int32_t {
-        constexpr int MI = decltype(mi)::value, NJ = decltype(nj)::value;
-        const unsigned columns = (unsigned)((g.O + 127) / 128 + 7) / 8 * 8;
-        static_assert(NJ == 2 || NJ == 4, "columns of 128 features, or their halves");
-        const dim3 grid(columns * (4 / NJ), (unsigned)((g.N + 32 * MI - 1) / (32 * MI)));
-        constexpr size_t lds = mid_lds<MidBytes, MI, NJ, 4>();
-        if (y_dtype == QLLM_F32) return launch_kernel(gemm_mid_kernel<MidBytes, ABITS, WBITS, float, MI, NJ, 4>, grid, dim3(LTHREADS), lds, g, stream);
-        return launch_kernel(gemm_mid_kernel<MidBytes, ABITS, WBITS, uint16_t, MI, NJ, 4>, grid, dim3(LTHREADS), lds, g, stream);
-    };
-    if (mid.mi == 4) return launch_mid(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
-    if (mid.mi == 5) return launch_mid(std::integral_constant<int, 5>{}, std::integral_constant<int, 4>{});
+    if (mid.mi == 4) return launch_mid<MidBytes, ABITS, WBITS, 4, 2, 4>(g, y_dtype, stream);
+    if (mid.mi == 5) return launch_mid<MidBytes, ABITS, WBITS, 5, 4, 4>(g, y_dtype, stream);
     if (g.splits > 1) return launch_small(g); // K is only split where the small tile is the choice
     if (plan.o_split > 0) { // whole rounds of large tiles, then the other output features with small ones
         GemmArgs first = g, rest = g;
@@ -2084,12 +2111,36 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
     return s < 2 ? 1 : (int32_t)s;
 }
 
+// gemm_mid_kernel on the FP6 matrix cores: in the layer call only, where the activations are laid out at no cost (qllm_int_gemm
+// re-lays them in a launch of its own, which is what the streaming kernel and packed rows save).  Layer call, three sets of weights
+// in turn, us, other kernel : this one:
+//   128 x 64 in place of the streaming kernel or of K split, where these tiles are more than half a round:
+//     100 x 4096 -> 12288 22.1 : 17.4, 66 x 5120 -> 9216 23.0 : 18.0, 128 x 6144 -> 16384 32.8 : 25.0, 200 x 5120 -> 5120 24.8 : 18.8,
+//     256 x 8192 -> 8192 30.6 : 25.2, 512 x 4096 -> 4096 23.8 : 18.7, 1000 x 8192 -> 2048 38.2 : 33.0, 512 x 11008 -> 4096 38.1 : 33.3;
+//     128 tiles are about even (100 x 8192 -> 8192 24.0 : 23.5, 66 x 4096 -> 8192 15.1 : 16.2), and so is a long K (160 x 28672 -> 8192
+//     81.8 : 79.7, 256 tokens 88.6 : 95.3; 100 x 11008 -> 12288 44.5 : 44.1).  A short K stays with the streaming kernel: its
+//     4 bits per weight are fewer from memory (250 x 1024 -> 6144 12.9 : 11.5, out of cache 16.6 : 17.8; 140 x 512 -> 8192 10.3 : 10.3 and 14.0 : 15.1;
+//     160 x 2048 -> 8192 15.5 : 13.8 and 19.7 : 19.1)
+//   160 x 64 where 128 x 128 tiles are more than half a round and these are one: 600 x 11008 -> 4096 41.1 : 37.1, 300 x 8192 -> 8192
+//     33.1 : 30.9, 400 x 5120 -> 5120 23.7 : 22.5, 160 x 4096 -> 16384 20.8 : 19.8, 700 x 3000 -> 3000 19.6 : 19.0; 300 x 2048 -> 8192 15.6 : 15.7
+//   128 x 128, as many of them: 400 x 28672 -> 8192 114.5 : 96.7, 1024 x 11008 -> 4096 47.3 : 45.7, 777 tokens 45.0 : 42.9; 400 x 8192
+//     -> 8192 35.0 : 36.1
+MidPlan plan_mid6(int64_t N, int64_t K, int64_t O)
+{
+    auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
+    const int64_t half_tiles = groups(128, 64), tiles = groups(128, 128);
+    if (half_tiles >= 144 && half_tiles <= 256 && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 36000) return MidPlan{4, 2};
+    if (tiles > 128 && groups(160, 64) <= 256 && K >= 3072) return MidPlan{5, 2};
+    if (tiles > 128 && tiles <= 256 && K >= 10240) return MidPlan{4, 4};
+    return MidPlan{0, 0};
+}
+
 // The kernel, tiles and parts of K of a product.
 struct Route {
     int32_t kernel;    // QLLM_GEMM_*
     int32_t splits;    // parts of K
     TilePlan tiles;    // not for the streaming kernel
-    MidPlan mid;       // byte operands, K not split
+    MidPlan mid;       // operands in matrix-core order, K not split
     StreamPlan stream; // the streaming kernel only
 };
 
@@ -2106,7 +2157,9 @@ Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool t
         r.splits = k_splits(N, K, O, 4);
         if (tiles6) {
             r.kernel = QLLM_GEMM_FP6;
-            if (r.splits == 1) r.tiles = plan_tiles(N, O, !one_launch);
+            if (a_laid) r.mid = plan_mid6(N, K, O);
+            if (r.mid.mi) r.splits = 1;
+            else if (r.splits == 1) r.tiles = plan_tiles(N, O, !one_launch);
         } else {
             // 256 x 256 tiles run one workgroup per CU, 128 x 128 tiles two, at about three quarters of the large tile's
             // rate per matrix-core operation: the small tile is taken where it fills the chip's rounds that much
@@ -2120,7 +2173,7 @@ Route plan_route(int64_t N, int64_t K, int64_t O, int a_bits, int w_bits, bool t
     } else if (tiles8) {
         r.kernel = QLLM_GEMM_BYTES;
         const int64_t s = t8_splits(N, K, O);
-        r.mid = plan_mid(N, K, O, a_bits);
+        r.mid = plan_mid8(N, K, O, a_bits);
         if (r.mid.mi) return r;
         if (s > 1 && parts8 > 1) r.splits = (int32_t)(parts8 < s ? parts8 : s);
         else r.tiles = plan_tiles(N, O, !one_launch);
@@ -2137,7 +2190,7 @@ int32_t launch(const GemmArgs &g, const Route &route, int32_t y_dtype, hipStream
     const bool small = route.tiles.small;
     const dim3 big_grid((unsigned)((g.O + LBN - 1) / LBN), (unsigned)((g.N + LBM - 1) / LBM));
     if constexpr (ABITS == 4 && WBITS == 4) {
-        if (route.kernel == QLLM_GEMM_FP6) return launch_fp6(g, route.tiles, y_dtype, stream);
+        if (route.kernel == QLLM_GEMM_FP6) return launch_fp6(g, route.tiles, route.mid, y_dtype, stream);
         if (small) {
             const dim3 grid((unsigned)((g.O + 127) / 128), (unsigned)((g.N + 127) / 128), (unsigned)(g.splits > 1 ? g.splits : 1));
             constexpr size_t lds = (size_t)NBUF * 256 * PROWB;
@@ -2222,6 +2275,12 @@ bool has_room_for_tiles6(int64_t N, const qllm_weight *w, int32_t a_bits, const 
     return a_bits == 4 && w->bits == 4 && w->tiles6 && N > 64 && workspace && 225 * w->K < (1 << 24) &&
            workspace_bytes >= tiles6_at(N, w->K, w->O) + qllm_tiles6_bytes(N, w->K) && qllm_tiles6_bytes(N, w->K) < (1ll << 32) &&
            qllm_tiles6_bytes(w->O, w->K) < (1ll << 32);
+}
+
+// Whether the layer call's product takes packed rows from the fused kernel because the streaming kernel is the cheaper way.
+bool layer_streams(int64_t N, const qllm_weight *w, int32_t a_bits, bool tiles6)
+{
+    return plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take && !(tiles6 && plan_mid6(N, w->K, w->O).mi);
 }
 
 // The byte-operand path's workspace: the activations, then as many parts of a split K as fit behind them.
@@ -2326,9 +2385,9 @@ extern "C" int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits,
     if (workspace_bytes < qllm_gemm_workspace_floor_bytes(N, w->K, w->O, a_bits)) return QLLM_ERR_WORKSPACE;
     const void *some = w; // any address: only whether there is a workspace counts
     const bool tiles8 = has_room_for_tiles8(N, w, a_bits, some, workspace_bytes);
-    const Route r = plan_route(N, w->K, w->O, a_bits, wb, has_room_for_tiles6(N, w, a_bits, some, workspace_bytes), tiles8,
-                               tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
-                               in_layer && tiles8 && !plan_stream(N, w->K, w->O, a_bits, wb, true, false).take, false);
+    const bool tiles6 = has_room_for_tiles6(N, w, a_bits, some, workspace_bytes);
+    const Route r = plan_route(N, w->K, w->O, a_bits, wb, tiles6, tiles8, tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
+                               in_layer && (tiles6 || tiles8) && !layer_streams(N, w, a_bits, tiles6), false);
     *parts = r.splits;
     *tile = r.kernel == QLLM_GEMM_STREAMS ? 0 : r.tiles.o_split > 0 ? 256 + 128 : r.tiles.small ? 128 : 256;
     return r.kernel;
@@ -2402,8 +2461,8 @@ struct LayerAsks {
 LayerAsks layer_asks(int64_t N, const qllm_weight *w, int32_t a_bits, uint8_t *p, int64_t left)
 {
     LayerAsks l{nullptr, {nullptr, 0, 0, 0, 0, 0}};
-    if (plan_stream(N, w->K, w->O, a_bits, w->bits, true, false).take) return l;
     const bool tiles6 = has_room_for_tiles6(N, w, a_bits, p, left);
+    if (layer_streams(N, w, a_bits, tiles6)) return l;
     if (tiles6) l.tiles = p + tiles6_at(N, w->K, w->O);
     else if (has_room_for_tiles8(N, w, a_bits, p, left)) l.tiles = p;
     const int64_t parts8 = l.tiles && !tiles6 ? parts8_that_fit(N, w->K, w->O, left) : 0;

@@ -998,6 +998,34 @@ def test_fused_kernels_with_and_without_an_empty_pass(b, N, C, norm, dtype, bits
     assert all(torch.equal(p, q) for p, q in zip(*got))
 
 
+@pytest.mark.parametrize("N,C,O,alone", [(100, 2304, 9300, 0), (65, 4096, 16381, 0), (130, 2312, 4700, 0), (1000, 2312, 1150, 0), (300, 3072, 5500, 1),
+                                         (160, 3304, 16384, 1), (500, 10240, 8100, 1)])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+def test_layer_mid_size_tiles_fp6(b, N, C, O, alone, y_dtype):
+    """4-bit layers whose product takes one round of 128 x 64, 160 x 64 or 128 x 128 tiles on the FP6 matrix cores, which only the layer
+    call does: bit for bit the two entry points by themselves, whose product streams, splits K or has other tiles (`alone`)."""
+    import torch
+    rng = np.random.default_rng(N + O)
+    row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
+    dm = b.DeviceMap(row_ptr, src, scale, C, b.qllm_plan_map_host(row_ptr, src, scale, C)[0])
+    x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda().bfloat16()
+    gamma = torch.rand(C, device="cuda") + 0.5
+    w = rng.integers(0, 16, (O, C), dtype=np.uint8)
+    dw = b.DeviceWeight(b.qllm_pack_codes_host(w, 4), rng.random(O).astype(np.float32), rng.integers(-2, 16, O).astype(np.int32),
+                        w.astype(np.int64).sum(1).astype(np.int32), C, 4)
+    ws = torch.full((b.qllm_workspace_bytes(N, C, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
+    gws = torch.full((b.qllm_gemm_workspace_bytes(N, C, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
+    assert b.qllm_gemm_kernel_choice(dw, 4, N, gws.numel(), True) == (b.GEMM_FP6, 128, 1)
+    assert b.qllm_gemm_kernel_choice(dw, 4, N, gws.numel())[0] == alone
+    assert b.qllm_probe_layer_launch(dm, x.dtype, N, C, NORM_ID["rms"], False, 4, dw, ws.numel()).laid_out
+    y, want = (torch.full((N, O), float("nan"), dtype=torch.float32 if y_dtype == "f32" else torch.bfloat16, device="cuda") for _ in range(2))
+    b.qllm_reassembled_linear(x, NORM_ID["rms"], gamma, None, 1e-5, dm, 4, dw, y, ws)
+    qa = b.DeviceQAct(N, C, 4)
+    b.qllm_norm_reassemble_quant(x, NORM_ID["rms"], gamma, None, 1e-5, dm, 4, qa)
+    b.qllm_int_gemm(qa, dw, want, None, gws)
+    assert torch.equal(y, want)
+
+
 def test_fused_full_down_projection_without_norm(oracle, b):
     """The down-projection as LLaMA has it: its input comes from the gated activation, not from a norm
     (reassembly is applied before every linear layer but the attention output projection): QLLM_NORM_NONE at the
