@@ -1708,22 +1708,45 @@ __global__ __launch_bounds__(64 * WAVES, (SK_WAVES_PER_SIMD<ABITS, WBITS, NT>)) 
         }
     };
 
-    // Every fetch is unconditional (past the end a wave re-reads its first step, from cache), so that
-    // the number of loads in flight at each wait is known when the code is compiled.
     const int n_steps = g.Kpad / STEP; // rows are padded to a multiple of 256 codes
-    int s = wave;
-    if (s < n_steps) {
-        fetch(w0, a0, s);
-        fetch(w1, a1, s + WAVES < n_steps ? s + WAVES : wave);
-        while (true) { // two steps per turn: the register stages alternate without being indexed
+    if constexpr ((NT == 4 || NT == 6) && ABITS != 6) {
+        // Two steps at a time, each asking for the one after the next; the last two ask for nothing, which is a copy of the step
+        // more in the code.  With one or two tiles of tokens and with 6-bit codes that costs what it gains (product, us, asking for
+        // its first step again : not: 33 x 5120 -> 27648 4 / 4 21.3 : 18.7, 96 x 4096 -> 4096 4 / 4 9.3 : 8.3, 50 x 4096 -> 4096
+        // 8 / 4 9.8 : 8.7, 64 x 28672 -> 8192 4 / 4 44.3 : 44.2; 32 x 8192 -> 8192 6 / 6 15.2 : 15.8, 24 x 5120 -> 13824 4 / 4 10.1 : 10.3), with
+        // eight the registers run out (128 x 8192 -> 8192 18 : 63).
+        const int mine = wave < n_steps ? (n_steps - wave + WAVES - 1) / WAVES : 0; // this wave's steps: wave, wave + WAVES, ..
+        auto step = [&](int k) { return k < mine ? wave + k * WAVES : wave; };
+        if (mine > 0) {
+            fetch(w0, a0, step(0));
+            fetch(w1, a1, step(1));
+            int k = 0;
+            for (; k + 2 < mine; k += 2) {
+                work(w0, a0);
+                fetch(w0, a0, step(k + 2));
+                work(w1, a1);
+                fetch(w1, a1, step(k + 3));
+            }
             work(w0, a0);
-            fetch(w0, a0, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
-            s += WAVES;
-            if (s >= n_steps) break;
-            work(w1, a1);
-            fetch(w1, a1, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
-            s += WAVES;
-            if (s >= n_steps) break;
+            if (k + 1 < mine) work(w1, a1);
+        }
+    } else {
+        // Every fetch is unconditional (past the end a wave re-reads its first step, from cache), so that
+        // the number of loads in flight at each wait is known when the code is compiled.
+        int s = wave;
+        if (s < n_steps) {
+            fetch(w0, a0, s);
+            fetch(w1, a1, s + WAVES < n_steps ? s + WAVES : wave);
+            while (true) { // two steps per turn: the register stages alternate without being indexed
+                work(w0, a0);
+                fetch(w0, a0, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
+                s += WAVES;
+                if (s >= n_steps) break;
+                work(w1, a1);
+                fetch(w1, a1, s + 2 * WAVES < n_steps ? s + 2 * WAVES : wave);
+                s += WAVES;
+                if (s >= n_steps) break;
+            }
         }
     }
 

@@ -570,6 +570,14 @@ def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, N, K, O):
         check_y(oracle, y, ref, y_dtype)
 
 
+@pytest.mark.parametrize("bits,N,K,O", [((4, 4), 50, K, 40) for K in (100, 1300, 2304, 3328, 4100)] + [((4, 4), 90, 2304, 70), ((4, 4), 50, 3328, 16400),
+                                         ((8, 8), 50, 700, 40), ((8, 8), 50, 1700, 40), ((8, 4), 50, 2000, 9000), ((8, 4), 90, 1100, 40), ((6, 6), 50, 3328, 40)])
+def test_gemm_streaming_steps_of_a_wave(oracle, b, bits, N, K, O):
+    """Four and six tiles of tokens per workgroup, whose last two steps ask for nothing: waves with none, one, two, three and four
+    steps, even and odd numbers of them side by side."""
+    test_gemm_streaming_tiles(oracle, b, *bits, N, K, O)
+
+
 @pytest.mark.parametrize("a_bits,w_bits", [(6, 6), (8, 8), (8, 4)])
 @pytest.mark.parametrize("N,C,K,norm,x_dtype", [(700, 8200, 8197, "rms", "bf16"), (513, 8192, 8192, "layer", "f32"), (2050, 8200, 8250, "none", "bf16"),
                                                 (257, 28672, 28600, "rms", "bf16"), (600, 8203, 8200, "rms", "bf16")])
