@@ -1959,19 +1959,20 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 //     256 x 8192 -> 8192 8/4 38.8 : 29.2, 512 x 4096 -> 4096 8/8 27.5 : 20.8, 200 x 5120 -> 5120 8/8 23.5 : 20.3,
 //     100 x 4096 -> 16384 6/6 29.4 : 23.1, 1000 x 4096 -> 2048 6/6 29.7 : 23.0, 250 x 3000 -> 5000 8/4 21.1 : 16.7
 //   The whole of K is a workgroup's, so that the gain ends with K, the sooner the more parts the other kernel has: two parts
-//     400 x 11008 -> 4096 8/4 40.6 : 38.3, 500 x 14336 -> 4096 67.8 : 69.3; four 100 x 8192 -> 8192 29.3 : 27.8, 160 x 11008 ->
-//     4096 6/6 28.5 : 32.6; six 128 x 5120 -> 5120 6/6 21.8 : 20.7
+//     400 x 11008 -> 4096 8/4 40.6 : 38.3, 500 x 14336 -> 4096 67.8 : 69.3; four 100 x 8192 -> 8192 29.3 : 27.8 and
+//     out of cache 48.2 : 55.1, 160 x 11008 -> 4096 6/6 28.5 : 32.6, 200 x 4096 -> 4096 6/6 21.8 : 17.5
 //   Up to 128 tokens 6-bit codes with fewer than 184 such tiles stay with the parts of K, for which the layer call reads weights ahead
 //     (100 x 5120 -> 9216 23.4 : 20.9 all the same).
 //   160 x 128, where 128 x 128 tiles are more than one round of workgroups and these are not: 777 x 5000 -> 4999 8/4 31.9 : 24.7 (the
 //     product), 600 x 28672 -> 8192 8/8 216 : 178, 777 x 5120 -> 5120 8/8 43.8 : 36.5, 300 x 4096 -> 12288 8/4 33.3 : 28.6; with no more
-//     128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 : 31.5, 400 x 8192 -> 8192 51 : 53)
+//     128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 : 31.5, 400 x 8192 -> 8192 51 : 53), and a short K gains
+//     nothing (600 x 2048 -> 8192 8/4 22.9 : 21.2; 640 x 1024 -> 8192 6/6 17.5 : 17.5, out of cache 21.7 : 23.0)
 MidPlan plan_mid8(int64_t N, int64_t K, int64_t O, int a_bits)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80;
-    if (half_tiles >= fewest && half_tiles <= 256 && K <= 12288 && K * t8_splits(N, K, O) <= 36000) return MidPlan{4, 2};
-    if (groups(128, 128) > 256 && groups(160, 128) <= 256) return MidPlan{5, 4};
+    if (half_tiles >= fewest && half_tiles <= 256 && K <= 12288 && K * t8_splits(N, K, O) <= 30000) return MidPlan{4, 2};
+    if (groups(128, 128) > 256 && groups(160, 128) <= 256 && K >= 2048) return MidPlan{5, 4};
     return MidPlan{0, 0};
 }
 
@@ -2152,7 +2153,7 @@ MidPlan plan_mid6(int64_t N, int64_t K, int64_t O)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), tiles = groups(128, 128);
-    if (half_tiles >= 144 && half_tiles <= 256 && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 36000) return MidPlan{4, 2};
+    if (half_tiles >= 144 && half_tiles <= 256 && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 30000) return MidPlan{4, 2};
     if (tiles > 128 && groups(160, 64) <= 256 && K >= 3072) return MidPlan{5, 2};
     if (tiles > 128 && tiles <= 256 && K >= 10240) return MidPlan{4, 4};
     return MidPlan{0, 0};

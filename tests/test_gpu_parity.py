@@ -505,7 +505,7 @@ def test_gemm_tiled_kernels(oracle, b, N, K, O, a_bits, w_bits, copies, tile, pa
 # one round of 128 x 64 or 160 x 128 tiles: K of one K-tile, an even and an odd number of them, partial tiles on both edges
 MID = [(250, 1, 8190, (6, 6), True), (250, 65, 8191, (6, 6), True), (250, 190, 8190, (6, 6), False), (129, 3000, 5121, (6, 6), True),
        (256, 3000, 8192, (8, 8), False), (250, 4500, 8190, (8, 4), True), (40, 6000, 16320, (8, 8), True)] + [
-       (N, K, O, p, i) for N, K, O, i in [(600, 1, 8190, True), (620, 70, 8191, False), (770, 200, 5000, True)] for p in [(6, 6), (8, 8), (8, 4)]]
+       (N, K, O, p, i) for N, K, O, i in [(600, 2049, 8190, True), (620, 2115, 8191, False), (770, 2250, 5000, True)] for p in [(6, 6), (8, 8), (8, 4)]]
 
 
 @pytest.mark.parametrize("N,K,O,bits,inside", MID)
