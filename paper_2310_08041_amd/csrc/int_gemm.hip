@@ -1866,12 +1866,17 @@ int32_t launch_tiles6(const uint8_t *codes, int64_t row_bytes, int64_t rows, int
 struct MidPlan {
     int mi, nj;
 };
+// Whether its launch is one round: columns of 128 features go to the eight XCDs in turn, so that what counts is the XCD with the
+// most of them, 32 workgroups each (2346 x 17792 -> 1280 4 / 4, ten columns, four tiles of 64 features by 15 of tokens on the 32 CUs
+// of an XCD: 145 -> 178 us; 1075 x 896 -> 1536 8 / 4 14.3 -> 18.4).
+int64_t mid_columns(int64_t O) { return ((O + 127) / 128 + 7) / 8 * 8; }
+bool mid_fits(const MidPlan &p, int64_t N, int64_t O) { return mid_columns(O) * (4 / p.nj) * ((N + 32 * p.mi - 1) / (32 * p.mi)) <= 256; }
+
 template <class OP, int ABITS, int WBITS, int MI, int NJ, int STAGES>
 int32_t launch_mid(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 {
     static_assert(NJ == 2 || NJ == 4, "columns of 128 features, or their halves");
-    const unsigned columns = (unsigned)((g.O + 127) / 128 + 7) / 8 * 8;
-    const dim3 grid(columns * (4 / NJ), (unsigned)((g.N + 32 * MI - 1) / (32 * MI)));
+    const dim3 grid((unsigned)mid_columns(g.O) * (4 / NJ), (unsigned)((g.N + 32 * MI - 1) / (32 * MI)));
     constexpr size_t lds = mid_lds<OP, MI, NJ, STAGES>();
     if (y_dtype == QLLM_F32) return launch_kernel(gemm_mid_kernel<OP, ABITS, WBITS, float, MI, NJ, STAGES>, grid, dim3(LTHREADS), lds, g, stream);
     return launch_kernel(gemm_mid_kernel<OP, ABITS, WBITS, uint16_t, MI, NJ, STAGES>, grid, dim3(LTHREADS), lds, g, stream);
@@ -1971,8 +1976,8 @@ MidPlan plan_mid8(int64_t N, int64_t K, int64_t O, int a_bits)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80;
-    if (half_tiles >= fewest && half_tiles <= 256 && K <= 12288 && K * t8_splits(N, K, O) <= 30000) return MidPlan{4, 2};
-    if (groups(128, 128) > 256 && groups(160, 128) <= 256 && K >= 2048) return MidPlan{5, 4};
+    if (half_tiles >= fewest && mid_fits(MidPlan{4, 2}, N, O) && K <= 12288 && K * t8_splits(N, K, O) <= 30000) return MidPlan{4, 2};
+    if (groups(128, 128) > 256 && mid_fits(MidPlan{5, 4}, N, O) && K >= 2048) return MidPlan{5, 4};
     return MidPlan{0, 0};
 }
 
@@ -2153,9 +2158,9 @@ MidPlan plan_mid6(int64_t N, int64_t K, int64_t O)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), tiles = groups(128, 128);
-    if (half_tiles >= 144 && half_tiles <= 256 && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 30000) return MidPlan{4, 2};
-    if (tiles > 128 && groups(160, 64) <= 256 && K >= 3072) return MidPlan{5, 2};
-    if (tiles > 128 && tiles <= 256 && K >= 10240) return MidPlan{4, 4};
+    if (half_tiles >= 144 && mid_fits(MidPlan{4, 2}, N, O) && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 30000) return MidPlan{4, 2};
+    if (tiles > 128 && mid_fits(MidPlan{5, 2}, N, O) && K >= 3072) return MidPlan{5, 2};
+    if (tiles > 128 && mid_fits(MidPlan{4, 4}, N, O) && K >= 10240) return MidPlan{4, 4};
     return MidPlan{0, 0};
 }
 
