@@ -175,12 +175,12 @@ int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, const qllm_
 
 /* Which of those kernels qllm_int_gemm runs for N tokens with this weight and workspace_bytes of workspace (no launch; of w
  * only O, K, bits and whether tiles6 / tiles8 are NULL are read; no acc_dump).  in_layer != 0: inside qllm_reassembled_linear,
- * workspace_bytes being what is left for the product there, with a map whose plan the fused kernel uses.
+ * workspace_bytes being what is left for the product there, where the fused kernel lays the codes out as the product reads them.
  *   QLLM_GEMM_STREAMS   one kernel streams the packed codes of both operands ("Small batches")
  *   QLLM_GEMM_FP6       the FP6 path                QLLM_GEMM_BYTES   byte operands
  *   QLLM_GEMM_EXPANDS   the packed codes are expanded inside a tiled kernel
- * *tile: 256 or 128 (tokens and features of a tile; 128 also for one round of mid-size tiles, 64 or 128
- * features wide), 256 + 128 (a launch of each), 0 for QLLM_GEMM_STREAMS;
+ * *tile: 256 or 128 (tokens and features of a tile), 256 + 128 (a launch of each), 128 also for one round of mid-size
+ * tiles (128 or 160 tokens by 64 or 128 features), 0 for QLLM_GEMM_STREAMS;
  * *parts: parts of K (1: whole).  Returns the kernel (>= 0) or a QLLM_ERR_* (< 0). */
 #define QLLM_GEMM_STREAMS 0
 #define QLLM_GEMM_FP6 1

@@ -46,6 +46,14 @@ int32_t qllm_probe_layer_launch(const qllm_map *map, int32_t x_dtype, int64_t N,
                                 int32_t a_bits, const qllm_weight *w, int64_t workspace_bytes, qllm_layer_launch *out);
 
 /*
+ * The mid-size tiles, *tokens x *features, that qllm_int_gemm, or the product of the layer call, runs one round of; 0 x 0 where it
+ * takes another kernel.  Arguments and errors as of qllm_gemm_kernel_choice, whose *tile does not tell them apart.  Returns QLLM_OK
+ * or a QLLM_ERR_*.
+ */
+int32_t qllm_probe_mid_tile(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
+                            int32_t *tokens, int32_t *features);
+
+/*
  * One half of qllm_reassembled_linear with the same arguments, to be timed by itself: 1 the fused kernel, 2 the product (the
  * workspace as half 1 left it).  Half 1 then half 2 is the layer call.  Errors: those of qllm_reassembled_linear, SHAPE for any
  * other half.

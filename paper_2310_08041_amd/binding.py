@@ -99,6 +99,7 @@ _sigs = {
     "qllm_probe_stream": (_i32, [_vp, _vp, _i64, _i32, _vp]),
     "qllm_probe_layer_half": (_i32, [_i32, _vp, _i32, _i64, _i64, _i64, _i32, _vp, _vp, _f, C.POINTER(_Map), _i32,
                                      C.POINTER(_Weight), _vp, _i32, _i64, _vp, _i64, _vp]),
+    "qllm_probe_mid_tile": (_i32, [C.POINTER(_Weight), _i32, _i64, _i64, _i32, C.POINTER(_i32), C.POINTER(_i32)]),
     "qllm_probe_layer_launch": (_i32, [C.POINTER(_Map), _i32, _i64, _i64, _i32, _i32, _i32, C.POINTER(_Weight), _i64, C.POINTER(_LayerLaunch)]),
 }
 EXPORTS = tuple(_sigs)
@@ -683,6 +684,14 @@ def qllm_probe_mfma_fp6(workgroups, iters, sink, stream=None):
 def qllm_probe_stream(src, dst, workgroups, stream=None):
     _chk(_lib.qllm_probe_stream(_dp(src), _dp(dst), src.numel() * src.element_size(), int(workgroups), _stream(stream)),
          "qllm_probe_stream")
+
+
+def qllm_probe_mid_tile(weight, a_bits, N, workspace_bytes, in_layer=False):
+    """(tokens, features) of the mid-size tiles that qllm_int_gemm, or the layer call's product, runs one round of; (0, 0): another kernel."""
+    tokens, features = _i32(0), _i32(0)
+    _chk(_lib.qllm_probe_mid_tile(C.byref(weight.c), int(a_bits), int(N), int(workspace_bytes), int(in_layer), C.byref(tokens), C.byref(features)),
+         "qllm_probe_mid_tile")
+    return tokens.value, features.value
 
 
 def qllm_probe_layer_launch(dmap, x_dtype, N, ldx, norm, has_beta, a_bits, weight, workspace_bytes):

@@ -2404,10 +2404,11 @@ extern "C" int32_t qllm_int_gemm(const qllm_qact *a, int32_t a_bits, int64_t N, 
     return int_gemm(a, a_bits, N, w, y, y_dtype, ldy, acc_dump, workspace, workspace_bytes, false, hip_stream);
 }
 
-extern "C" int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
-                                           int32_t *tile, int32_t *parts)
+namespace {
+
+// The route of qllm_int_gemm, or of the layer call's product, without a launch.
+int32_t describe_route(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer, Route *r)
 {
-    if (!w || !tile || !parts) return QLLM_ERR_NULL;
     const int32_t wb = w->bits;
     if (!((a_bits == wb && (wb == 4 || wb == 6 || wb == 8)) || (a_bits == 8 && wb == 4))) return QLLM_ERR_BITS;
     if (N <= 0 || N > INT32_MAX || w->O <= 0 || w->O > INT32_MAX || w->K <= 0 || w->K > (1 << 24)) return QLLM_ERR_SHAPE;
@@ -2415,11 +2416,35 @@ extern "C" int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits,
     const void *some = w; // any address: only whether there is a workspace counts
     const bool tiles8 = has_room_for_tiles8(N, w, a_bits, some, workspace_bytes);
     const bool tiles6 = has_room_for_tiles6(N, w, a_bits, some, workspace_bytes);
-    const Route r = plan_route(N, w->K, w->O, a_bits, wb, tiles6, tiles8, tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
-                               in_layer && (tiles6 || tiles8) && !layer_streams(N, w, a_bits, tiles6), false);
+    *r = plan_route(N, w->K, w->O, a_bits, wb, tiles6, tiles8, tiles8 ? parts8_that_fit(N, w->K, w->O, workspace_bytes) : 0,
+                    in_layer && (tiles6 || tiles8) && !layer_streams(N, w, a_bits, tiles6), false);
+    return QLLM_OK;
+}
+
+} // namespace
+
+extern "C" int32_t qllm_gemm_kernel_choice(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
+                                           int32_t *tile, int32_t *parts)
+{
+    if (!w || !tile || !parts) return QLLM_ERR_NULL;
+    Route r;
+    const int32_t rc = describe_route(w, a_bits, N, workspace_bytes, in_layer, &r);
+    if (rc != QLLM_OK) return rc;
     *parts = r.splits;
     *tile = r.kernel == QLLM_GEMM_STREAMS ? 0 : r.tiles.o_split > 0 ? 256 + 128 : r.tiles.small ? 128 : 256;
     return r.kernel;
+}
+
+extern "C" int32_t qllm_probe_mid_tile(const qllm_weight *w, int32_t a_bits, int64_t N, int64_t workspace_bytes, int32_t in_layer,
+                                       int32_t *tokens, int32_t *features)
+{
+    if (!w || !tokens || !features) return QLLM_ERR_NULL;
+    Route r;
+    const int32_t rc = describe_route(w, a_bits, N, workspace_bytes, in_layer, &r);
+    if (rc != QLLM_OK) return rc;
+    *tokens = 32 * r.mid.mi;
+    *features = 32 * r.mid.nj;
+    return QLLM_OK;
 }
 
 extern "C" int64_t qllm_tiles6_bytes(int64_t rows, int64_t K)

@@ -507,6 +507,32 @@ def test_gemm_kernel_choice_of_tiles_and_parts():
             gemm_choice(**args)
 
 
+def mid_tile(N, K, O, a_bits, w_bits, copies=True, in_layer=True, workspace_bytes=1 << 40):
+    w = b._Weight(O, K, w_bits, 0x1000, 0x1000, 0x1000, 0x1000, 0x1000 if copies and (a_bits, w_bits) == (4, 4) else None,
+                  0x1000 if copies and a_bits != 4 else None)
+    return b.qllm_probe_mid_tile(types.SimpleNamespace(c=w), a_bits, N, workspace_bytes, in_layer)
+
+
+def test_mid_size_tiles_are_told_apart():
+    """qllm_gemm_kernel_choice says 128 for every mid-size tile and for the 128 x 128 kernel; the probe says which one runs."""
+    for shape, tile in (((777, 5000, 4999, 8, 4), (160, 128)), ((256, 8192, 8192, 8, 4), (128, 64)), ((200, 5120, 5120, 4, 4), (128, 64)),
+                        ((300, 8192, 8192, 4, 4), (160, 64)), ((400, 28672, 8192, 4, 4), (128, 128)), ((200, 13824, 5120, 6, 6), (0, 0)),
+                        ((2048, 28672, 8192, 6, 6), (0, 0)), ((16, 8192, 8192, 6, 6), (0, 0))):
+        assert mid_tile(*shape) == tile, shape
+        assert not tile[0] or gemm_choice(*shape, in_layer=True)[1:] == (128, 1)
+        # the product by itself re-lays 4-bit activations in a launch of its own and does not take them
+        assert mid_tile(*shape, in_layer=False) == ((0, 0) if shape[3] == 4 else tile), shape
+        if tile[0]:
+            assert mid_tile(*shape, copies=False) == (0, 0)
+    floor = b.qllm_gemm_workspace_floor_bytes(200, 5120, 5120, 4)
+    assert mid_tile(200, 5120, 5120, 4, 4, workspace_bytes=floor) == (0, 0)
+    for bad in (dict(a_bits=5), dict(a_bits=4, w_bits=8), dict(N=0), dict(K=0), dict(O=0), dict(N=200, K=5120, O=5120, a_bits=4, w_bits=4, workspace_bytes=floor - 1)):
+        args = dict(N=64, K=512, O=512, a_bits=6, w_bits=6)
+        args.update(bad)
+        with pytest.raises(b.QllmError):
+            mid_tile(**args)
+
+
 def layer_launch(N, K, O, a_bits, w_bits, dt=b.BF16, norm=b.NORM_RMS, every=100, workspace_bytes=1 << 40, copies=True):
     row_ptr, src, scale = random_csr_map(np.random.default_rng(3), K, K, every, longest=3)
     m = host_map(row_ptr, src, scale, K, b.qllm_plan_map_host(row_ptr, src, scale, K)[0])
