@@ -1959,24 +1959,31 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 }
 
 // gemm_mid_kernel on byte operands.
-// Layer call, three sets of weights in turn, us, other kernel : this one:
+// Layer call, us, other kernel : this one, three sets of weights in turn / weights out of every cache:
 //   128 x 64 in place of 128 x 128 tiles with K split (or of half a round of them), where these tiles are one round:
-//     256 x 8192 -> 8192 8/4 38.8 : 29.2, 512 x 4096 -> 4096 8/8 27.5 : 20.8, 200 x 5120 -> 5120 8/8 23.5 : 20.3,
-//     100 x 4096 -> 16384 6/6 29.4 : 23.1, 1000 x 4096 -> 2048 6/6 29.7 : 23.0, 250 x 3000 -> 5000 8/4 21.1 : 16.7
-//   The whole of K is a workgroup's, so that the gain ends with K, the sooner the more parts the other kernel has: two parts
-//     400 x 11008 -> 4096 8/4 40.6 : 38.3, 500 x 14336 -> 4096 67.8 : 69.3; four 100 x 8192 -> 8192 29.3 : 27.8 and
-//     out of cache 48.2 : 55.1, 160 x 11008 -> 4096 6/6 28.5 : 32.6, 200 x 4096 -> 4096 6/6 21.8 : 17.5
+//     256 x 8192 -> 8192 8/4 36.1 : 30.9 / 42.2 : 40.2, 100 x 4096 -> 16384 6/6 30.4 : 24.3 / 33.8 : 29.2, 553 x 1024 -> 2944 6/6
+//     24.1 : 14.7 / 24.4 : 15.2, 250 x 3000 -> 5000 8/4 21.1 : 16.7
+//   A workgroup loads the whole K of 192 rows where one of the other kernel's loads its part of 256 rows.  From some 640 thousand codes
+//   more on that costs what finish and sums in memory save, first where the weights come from HBM: 822 x 9984 -> 1664 8/8 (two
+//     parts) 54.8 : 44.1 / 54.2 : 47.8, 230 x 5888 -> 5120 8/4 (three) 26.3 : 24.3 / 29.3 : 30.9; 2048 x 7000 -> 512 8/8 (four) 48.6 : 47.3 /
+//     48.4 : 52.1, 362 x 5760 -> 2048 6/6 (five) 26.8 : 26.9 / 27.9 : 32.6.  Sooner up to 128 tokens, for which the layer call reads weights ahead
+//     of parts: 73 x 3584 -> 12160 6/6 21.4 : 18.0 / 24.5 : 22.8, 83 x 4352 -> 9600 8/4 22.2 : 20.4 / 24.3 : 25.9.  Later where the
+//     features are no multiple of four, which the finish takes one by one: 108 x 4800 -> 5534 8/8 28.0 : 20.9 / 30.1 : 25.8, 985 x
+//     5376 -> 975 39.8 : 29.6 / 39.9 : 33.9
 //   Up to 128 tokens 6-bit codes with fewer than 184 such tiles stay with the parts of K, for which the layer call reads weights ahead
 //     (100 x 5120 -> 9216 23.4 : 20.9 all the same).
 //   160 x 128, where 128 x 128 tiles are more than one round of workgroups and these are not: 777 x 5000 -> 4999 8/4 31.9 : 24.7 (the
-//     product), 600 x 28672 -> 8192 8/8 216 : 178, 777 x 5120 -> 5120 8/8 43.8 : 36.5, 300 x 4096 -> 12288 8/4 33.3 : 28.6; with no more
-//     128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 : 31.5, 400 x 8192 -> 8192 51 : 53), and a short K gains
-//     nothing (600 x 2048 -> 8192 8/4 22.9 : 21.2; 640 x 1024 -> 8192 6/6 17.5 : 17.5, out of cache 21.7 : 23.0)
+//     product), 600 x 28672 -> 8192 8/8 207 : 172 / 207 : 173, 777 x 5120 -> 5120 8/8 43.8 : 36.5, 300 x 4096 -> 12288 8/4 34.1 : 29.0 / 36.9 :
+//     35.6; one row of tiles, 129 to 160 tokens, is up to 4 % behind out of cache at a short K (136 x 2432 -> 20480 8/4 25.3 : 22.5 / 28.3 :
+//     29.3; 139 x 2304 -> 27029 31.8 : 24.7 / 33.4 : 31.3).  With no more 128 x 128 tiles than CUs they lose (600 x 5120 -> 5120 8/4 29.5 :
+//     31.5, 400 x 8192 -> 8192 51 : 53), and a short K gains nothing (600 x 2048 -> 8192 8/4 22.9 : 21.2; 640 x 1024 -> 8192 6/6 17.5 :
+//     17.5 / 21.7 : 23.0)
 MidPlan plan_mid8(int64_t N, int64_t K, int64_t O, int a_bits)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
-    const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80;
-    if (half_tiles >= fewest && mid_fits(MidPlan{4, 2}, N, O) && K <= 12288 && K * t8_splits(N, K, O) <= 30000) return MidPlan{4, 2};
+    const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80, parts = t8_splits(N, K, O);
+    const bool gains = parts == 1 || 192 * K - 256 * K / parts <= (O % 4 ? 745000 : N > 128 ? 640000 : 450000);
+    if (half_tiles >= fewest && mid_fits(MidPlan{4, 2}, N, O) && K <= 12288 && gains) return MidPlan{4, 2};
     if (groups(128, 128) > 256 && mid_fits(MidPlan{5, 4}, N, O) && K >= 2048) return MidPlan{5, 4};
     return MidPlan{0, 0};
 }

@@ -533,6 +533,20 @@ def test_mid_size_tiles_are_told_apart():
             mid_tile(**args)
 
 
+@pytest.mark.parametrize("N,K,O,bits,want", [
+    # K in parts by the other kernel, two to five: what the whole K of 192 rows loads beyond a part of 256
+    (822, 9984, 1664, (8, 8), (128, 64)), (512, 11008, 4096, (8, 4), (0, 0)), (230, 5888, 5120, (8, 4), (128, 64)), (224, 7168, 4352, (6, 6), (0, 0)),
+    (375, 6528, 2304, (8, 4), (0, 0)), (1536, 5000, 512, (6, 6), (0, 0)), (2048, 7000, 512, (8, 8), (0, 0)), (362, 5760, 2048, (6, 6), (0, 0)),
+    # up to 128 tokens, whose weights are read ahead of parts
+    (73, 3584, 12160, (6, 6), (128, 64)), (83, 4352, 9600, (8, 4), (0, 0)), (108, 6144, 8192, (8, 4), (0, 0)), (127, 4800, 7748, (8, 8), (0, 0)),
+    # features that the finish of parts takes one by one
+    (108, 4800, 5534, (8, 8), (128, 64)), (985, 5376, 975, (8, 8), (128, 64))])
+def test_mid_size_tiles_where_cold_weights_gain_too(N, K, O, bits, want):
+    """Layers on both sides of the lines, timed with weights in cache and out of every cache: out of cache, where a model's
+    weights are, those beyond the lines took 3 to 17 % longer with mid-size tiles."""
+    assert mid_tile(N, K, O, *bits) == want
+
+
 def layer_launch(N, K, O, a_bits, w_bits, dt=b.BF16, norm=b.NORM_RMS, every=100, workspace_bytes=1 << 40, copies=True):
     row_ptr, src, scale = random_csr_map(np.random.default_rng(3), K, K, every, longest=3)
     m = host_map(row_ptr, src, scale, K, b.qllm_plan_map_host(row_ptr, src, scale, K)[0])
