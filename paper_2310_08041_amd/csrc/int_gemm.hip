@@ -1970,6 +1970,10 @@ int32_t t8_splits(int64_t N, int64_t K, int64_t O)
 //     of parts: 73 x 3584 -> 12160 6/6 21.4 : 18.0 / 24.5 : 22.8, 83 x 4352 -> 9600 8/4 22.2 : 20.4 / 24.3 : 25.9.  Later where the
 //     features are no multiple of four, which the finish takes one by one: 108 x 4800 -> 5534 8/8 28.0 : 20.9 / 30.1 : 25.8, 985 x
 //     5376 -> 975 39.8 : 29.6 / 39.9 : 33.9
+//   Where the other kernel has K whole too, up to 512 channels are mostly start and end and half as many features per workgroup lose out
+//     of cache (487 x 384 -> 2176 8/4 11.6 : 11.4 / 11.7 : 12.6, 235 x 512 -> 3584 6/6 11.6 : 11.3 / 12.5 : 12.9; 240 layers 1.03 / 0.995 of the
+//     other's rate), but for features that are no multiple of four (328 x 384 -> 3985 6/6 13.0 : 12.2 / 13.9 : 13.4); and up to six
+//     columns of 128 features leave two XCDs without work (1987 x 384 -> 640 6/6 13.5 : 13.7 / 13.2 : 13.6)
 //   Up to 128 tokens 6-bit codes with fewer than 184 such tiles stay with the parts of K, for which the layer call reads weights ahead
 //     (100 x 5120 -> 9216 23.4 : 20.9 all the same).
 //   160 x 128, where 128 x 128 tiles are more than one round of workgroups and these are not: 777 x 5000 -> 4999 8/4 31.9 : 24.7 (the
@@ -1982,7 +1986,7 @@ MidPlan plan_mid8(int64_t N, int64_t K, int64_t O, int a_bits)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), fewest = a_bits == 6 && N <= 128 ? 184 : 80, parts = t8_splits(N, K, O);
-    const bool gains = parts == 1 || 192 * K - 256 * K / parts <= (O % 4 ? 745000 : N > 128 ? 640000 : 450000);
+    const bool gains = parts > 1 ? 192 * K - 256 * K / parts <= (O % 4 ? 745000 : N > 128 ? 640000 : 450000) : O > 6 * 128 && (K > 512 || O % 4);
     if (half_tiles >= fewest && mid_fits(MidPlan{4, 2}, N, O) && K <= 12288 && gains) return MidPlan{4, 2};
     if (groups(128, 128) > 256 && mid_fits(MidPlan{5, 4}, N, O) && K >= 2048) return MidPlan{5, 4};
     return MidPlan{0, 0};

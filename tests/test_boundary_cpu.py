@@ -540,7 +540,10 @@ def test_mid_size_tiles_are_told_apart():
     # up to 128 tokens, whose weights are read ahead of parts
     (73, 3584, 12160, (6, 6), (128, 64)), (83, 4352, 9600, (8, 4), (0, 0)), (108, 6144, 8192, (8, 4), (0, 0)), (127, 4800, 7748, (8, 8), (0, 0)),
     # features that the finish of parts takes one by one
-    (108, 4800, 5534, (8, 8), (128, 64)), (985, 5376, 975, (8, 8), (128, 64))])
+    (108, 4800, 5534, (8, 8), (128, 64)), (985, 5376, 975, (8, 8), (128, 64)),
+    # K whole either way: a short one, and few columns of features
+    (235, 512, 3584, (6, 6), (0, 0)), (235, 513, 3584, (6, 6), (128, 64)), (487, 384, 2176, (8, 4), (0, 0)), (328, 384, 3985, (6, 6), (128, 64)),
+    (1931, 640, 640, (8, 4), (0, 0)), (1846, 900, 768, (8, 4), (0, 0)), (1846, 900, 769, (8, 4), (128, 64))])
 def test_mid_size_tiles_where_cold_weights_gain_too(N, K, O, bits, want):
     """Layers on both sides of the lines, timed with weights in cache and out of every cache: out of cache, where a model's
     weights are, those beyond the lines took 3 to 17 % longer with mid-size tiles."""
