@@ -2164,14 +2164,15 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
 //   160 x 64 where 128 x 128 tiles are more than half a round and these are one: 600 x 11008 -> 4096 41.1 : 37.1, 300 x 8192 -> 8192
 //     33.1 : 30.9, 400 x 5120 -> 5120 23.7 : 22.5, 160 x 4096 -> 16384 20.8 : 19.8, 700 x 3000 -> 3000 19.6 : 19.0; 300 x 2048 -> 8192 15.6 : 15.7
 //   128 x 128, as many of them: 400 x 28672 -> 8192 114.5 : 96.7, 1024 x 11008 -> 4096 47.3 : 45.7, 777 tokens 45.0 : 42.9; 400 x 8192
-//     -> 8192 35.0 : 36.1
+//     -> 8192 35.0 : 36.1.  Up to six columns of 128 features leave two XCDs without work: 3917 x 12864 -> 566 91.8 : 103.1, 3111 x 11264
+//     -> 768 68.8 : 73.3 (eight, 3263 x 12416 -> 1024 82.9 : 84.4 / 91.0 : 87.5)
 MidPlan plan_mid6(int64_t N, int64_t K, int64_t O)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), tiles = groups(128, 128);
     if (half_tiles >= 144 && mid_fits(MidPlan{4, 2}, N, O) && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 30000) return MidPlan{4, 2};
     if (tiles > 128 && mid_fits(MidPlan{5, 2}, N, O) && K >= 3072) return MidPlan{5, 2};
-    if (tiles > 128 && mid_fits(MidPlan{4, 4}, N, O) && K >= 10240) return MidPlan{4, 4};
+    if (tiles > 128 && O > 6 * 128 && mid_fits(MidPlan{4, 4}, N, O) && K >= 10240) return MidPlan{4, 4};
     return MidPlan{0, 0};
 }
 
