@@ -2158,7 +2158,10 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
 //     100 x 4096 -> 12288 22.1 : 17.4, 66 x 5120 -> 9216 23.0 : 18.0, 128 x 6144 -> 16384 32.8 : 25.0, 200 x 5120 -> 5120 24.8 : 18.8,
 //     256 x 8192 -> 8192 30.6 : 25.2, 512 x 4096 -> 4096 23.8 : 18.7, 1000 x 8192 -> 2048 38.2 : 33.0, 512 x 11008 -> 4096 38.1 : 33.3;
 //     128 tiles are about even (100 x 8192 -> 8192 24.0 : 23.5, 66 x 4096 -> 8192 15.1 : 16.2), and so is a long K (160 x 28672 -> 8192
-//     81.8 : 79.7, 256 tokens 88.6 : 95.3; 100 x 11008 -> 12288 44.5 : 44.1).  A short K stays with the streaming kernel: its
+//     81.8 : 79.7, 256 tokens 88.6 : 95.3; 128 x 11008 -> 12288 45.5 : 45.5 / 47.0 : 46.8), where the streaming kernel's 4 bits per weight
+//     are the fewer from HBM up to 128 tokens (/: out of every cache; 66 x 7680 -> 9216 24.1 : 23.2 / 27.1 : 29.1, 80 x 8192 -> 10240 26.8 : 24.5 / 29.2 :
+//     30.0; 66 x 5120 -> 9216 22.2 : 18.6 / 26.4 : 23.1); more tokens lose up to 4 % there with three parts of K (1136 x 8448 -> 1024 39.5 : 36.1 /
+//     40.0 : 41.6, 188 x 4096 -> 4864 19.3 : 17.5 / 19.4 : 19.8).  A short K stays with the streaming kernel: its
 //     4 bits per weight are fewer from memory (250 x 1024 -> 6144 12.9 : 11.5, out of cache 16.6 : 17.8; 140 x 512 -> 8192 10.3 : 10.3 and 14.0 : 15.1;
 //     160 x 2048 -> 8192 15.5 : 13.8 and 19.7 : 19.1)
 //   160 x 64 where 128 x 128 tiles are more than half a round and these are one: 600 x 11008 -> 4096 41.1 : 37.1, 300 x 8192 -> 8192
@@ -2170,7 +2173,7 @@ MidPlan plan_mid6(int64_t N, int64_t K, int64_t O)
 {
     auto groups = [&](int64_t tm, int64_t tn) { return ((N + tm - 1) / tm) * ((O + tn - 1) / tn); };
     const int64_t half_tiles = groups(128, 64), tiles = groups(128, 128);
-    if (half_tiles >= 144 && mid_fits(MidPlan{4, 2}, N, O) && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= 30000) return MidPlan{4, 2};
+    if (half_tiles >= 144 && mid_fits(MidPlan{4, 2}, N, O) && K >= (N > 128 ? 2048 : 2304) && K <= 12288 && K * k_splits(N, K, O, 4) <= (N > 128 ? 30000 : 22000)) return MidPlan{4, 2};
     if (tiles > 128 && mid_fits(MidPlan{5, 2}, N, O) && K >= 3072) return MidPlan{5, 2};
     if (tiles > 128 && O > 6 * 128 && mid_fits(MidPlan{4, 4}, N, O) && K >= 10240) return MidPlan{4, 4};
     return MidPlan{0, 0};

@@ -545,7 +545,9 @@ def test_mid_size_tiles_are_told_apart():
     (235, 512, 3584, (6, 6), (0, 0)), (235, 513, 3584, (6, 6), (128, 64)), (487, 384, 2176, (8, 4), (0, 0)), (328, 384, 3985, (6, 6), (128, 64)),
     (1931, 640, 640, (8, 4), (0, 0)), (1846, 900, 768, (8, 4), (0, 0)), (1846, 900, 769, (8, 4), (128, 64)),
     # 4-bit codes, few columns of features
-    (3917, 12864, 566, (4, 4), (0, 0)), (3111, 11264, 768, (4, 4), (0, 0)), (3111, 11264, 769, (4, 4), (128, 128))])
+    (3917, 12864, 566, (4, 4), (0, 0)), (3111, 11264, 768, (4, 4), (0, 0)), (3111, 11264, 769, (4, 4), (128, 128)),
+    # ... and 4 bits per weight in the streaming kernel against 6
+    (66, 7680, 9216, (4, 4), (0, 0)), (80, 8192, 10240, (4, 4), (0, 0)), (66, 5120, 9216, (4, 4), (128, 64)), (100, 8192, 16384, (4, 4), (128, 64))])
 def test_mid_size_tiles_where_cold_weights_gain_too(N, K, O, bits, want):
     """Layers on both sides of the lines, timed with weights in cache and out of every cache: out of cache, where a model's
     weights are, those beyond the lines took 3 to 17 % longer with mid-size tiles, few columns of 4-bit codes in cache."""
