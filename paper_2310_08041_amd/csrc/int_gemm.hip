@@ -1709,12 +1709,16 @@ __global__ __launch_bounds__(64 * WAVES, (SK_WAVES_PER_SIMD<ABITS, WBITS, NT>)) 
     };
 
     const int n_steps = g.Kpad / STEP; // rows are padded to a multiple of 256 codes
-    if constexpr ((NT == 4 || NT == 6) && ABITS != 6) {
-        // Two steps at a time, each asking for the one after the next; the last two ask for nothing, which is a copy of the step
-        // more in the code.  With one or two tiles of tokens and with 6-bit codes that costs what it gains (product, us, asking for
-        // its first step again : not: 33 x 5120 -> 27648 4 / 4 21.3 : 18.7, 96 x 4096 -> 4096 4 / 4 9.3 : 8.3, 50 x 4096 -> 4096
-        // 8 / 4 9.8 : 8.7, 64 x 28672 -> 8192 4 / 4 44.3 : 44.2; 32 x 8192 -> 8192 6 / 6 15.2 : 15.8, 24 x 5120 -> 13824 4 / 4 10.1 : 10.3), with
-        // eight the registers run out (128 x 8192 -> 8192 18 : 63).
+    if constexpr ((NT == 4 || NT == 6) && (ABITS == 4 || (WBITS == 4 && RT == 2))) {
+        // Two steps at a time, each asking for the one after the next.  The last two of an even number ask for nothing, an odd number
+        // still asks for the wave's first step again, once where the other form does so twice.  It is a copy of the step more in the
+        // code, which costs what it gains with one or two tiles of tokens, with 6-bit codes, with 8-bit weights and, under 8-bit
+        // activations, with 64 features; with eight tiles the registers run out (128 x 8192 -> 8192 18 : 63).  us, other form : this one:
+        //   product: 33 x 5120 -> 27648 4 / 4 21.3 : 18.7, 96 x 4096 -> 4096 4 / 4 9.3 : 8.3, 50 x 4096 -> 4096 8 / 4 9.8 : 8.7, 64 x 28672 ->
+        //     8192 4 / 4 44.3 : 44.2; 32 x 8192 -> 8192 6 / 6 15.2 : 15.8, 24 x 5120 -> 13824 4 / 4 10.1 : 10.3
+        //   layer call, weights in cache / out of every cache: 38 x 3712 -> 25472 4 / 4 23.8 : 22.1 / 26.3 : 25.7, 50 x 3200 -> 640 8 / 4 14.2 :
+        //     12.9 / 15.8 : 14.6; 62 x 4544 -> 4583 8 / 8 17.7 : 18.3 / 21.6 : 22.5, 70 x 1536 -> 1408 8 / 8 12.1 : 12.4 / 14.4 : 14.2; 64 features: 59 x 8320 ->
+        //     8320 8 / 4 28.0 : 27.3 / 32.5 : 34.1, 46 x 3840 -> 17152 24.4 : 24.2 / 28.7 : 29.8
         const int mine = wave < n_steps ? (n_steps - wave + WAVES - 1) / WAVES : 0; // this wave's steps: wave, wave + WAVES, ..
         auto step = [&](int k) { return k < mine ? wave + k * WAVES : wave; };
         if (mine > 0) {

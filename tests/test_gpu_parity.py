@@ -573,8 +573,9 @@ def test_gemm_streaming_tiles(oracle, b, a_bits, w_bits, N, K, O):
 @pytest.mark.parametrize("bits,N,K,O", [((4, 4), 50, K, 40) for K in (100, 1300, 2304, 3328, 4100)] + [((4, 4), 90, 2304, 70), ((4, 4), 50, 3328, 16400),
                                          ((8, 8), 50, 700, 40), ((8, 8), 50, 1700, 40), ((8, 4), 50, 2000, 9000), ((8, 4), 90, 1100, 40), ((6, 6), 50, 3328, 40)])
 def test_gemm_streaming_steps_of_a_wave(oracle, b, bits, N, K, O):
-    """Four and six tiles of tokens per workgroup, whose last two steps ask for nothing: waves with none, one, two, three and four
-    steps, even and odd numbers of them side by side."""
+    """Four and six tiles of tokens per workgroup, where 4-bit weights under 4-bit activations, and under 8-bit ones on 32 features,
+    have a tail that asks for no step, or one, beyond the last: waves with none, one, two, three and four steps, even and odd numbers
+    of them side by side, in that form and the other."""
     test_gemm_streaming_tiles(oracle, b, *bits, N, K, O)
 
 
