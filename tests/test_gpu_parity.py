@@ -4,6 +4,8 @@ Bars: packed activation codes, zero-points, row sums and int32 accumulators bit-
 scales bit-exact (same fp32 operations on both sides); dequantised outputs within 1e-3 relative
 (fp32) / 2e-2 (bf16) -- in practice they are bit-exact too, which is reported but not required.
 """
+import types
+
 import numpy as np
 import pytest
 
@@ -503,15 +505,18 @@ def test_gemm_tiled_kernels(oracle, b, N, K, O, a_bits, w_bits, copies, tile, pa
 
 
 # one round of 128 x 64 or 160 x 128 tiles: K of one K-tile, an even and an odd number of them, partial tiles on both edges
-MID = [(250, 1, 8190, (6, 6), True), (250, 65, 8191, (6, 6), True), (250, 190, 8190, (6, 6), False), (129, 3000, 5121, (6, 6), True),
-       (256, 3000, 8192, (8, 8), False), (250, 4500, 8190, (8, 4), True), (40, 6000, 16320, (8, 8), True)] + [
-       (N, K, O, p, i) for N, K, O, i in [(600, 2049, 8190, True), (620, 2115, 8191, False), (770, 2250, 5000, True)] for p in [(6, 6), (8, 8), (8, 4)]]
+MID = [(N, K, O, p, i, (128, 64)) for N, K, O, p, i in [
+           (250, 1, 8190, (6, 6), True), (250, 65, 8191, (6, 6), True), (250, 190, 8190, (6, 6), False), (129, 3000, 5121, (6, 6), True),
+           (256, 3000, 8192, (8, 8), False), (250, 4500, 8190, (8, 4), True), (40, 6000, 16320, (8, 8), True)]] + [
+       (N, K, O, p, i, (160, 128)) for N, K, O, i in [(600, 2049, 8190, True), (620, 2115, 8191, False), (770, 2250, 5000, True)] for p in [(6, 6), (8, 8), (8, 4)]]
 
 
-@pytest.mark.parametrize("N,K,O,bits,inside", MID)
-def test_gemm_mid_size_tiles(oracle, b, N, K, O, bits, inside):
-    """The byte-operand kernel whose halves sum alternate K-tiles, checked as every tiled kernel is: accumulators exact, the two
-    epilogues bit for bit, the result against the oracle."""
+@pytest.mark.parametrize("N,K,O,bits,inside,mid", MID)
+def test_gemm_mid_size_tiles(oracle, b, N, K, O, bits, inside, mid):
+    """The byte-operand kernel whose halves sum alternate K-tiles, seen to be the one that runs, checked as every tiled kernel is:
+    accumulators exact, the two epilogues bit for bit, the result against the oracle."""
+    with_copy = types.SimpleNamespace(c=b._Weight(O, K, bits[1], 16, 16, 16, 16, None, 16))
+    assert b.qllm_probe_mid_tile(with_copy, bits[0], N, b.qllm_gemm_workspace_bytes(N, K, O, bits[0])) == mid
     test_gemm_tiled_kernels(oracle, b, N, K, O, *bits, True, 128, 1, inside)
 
 
@@ -1007,32 +1012,68 @@ def test_fused_kernels_with_and_without_an_empty_pass(b, N, C, norm, dtype, bits
     assert all(torch.equal(p, q) for p, q in zip(*got))
 
 
-@pytest.mark.parametrize("N,C,O,alone", [(100, 2304, 9300, 0), (65, 4096, 16381, 0), (130, 2312, 4700, 0), (1000, 2312, 1150, 0), (300, 3072, 5500, 1),
-                                         (160, 3304, 16384, 1), (500, 10240, 8100, 1)])
-@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
-def test_layer_mid_size_tiles_fp6(b, N, C, O, alone, y_dtype):
-    """4-bit layers whose product takes one round of 128 x 64, 160 x 64 or 128 x 128 tiles on the FP6 matrix cores, which only the layer
-    call does: bit for bit the two entry points by themselves, whose product streams, splits K or has other tiles (`alone`)."""
+def check_layer_on_mid_size_tiles(oracle, b, N, C, O, bits, mid, alone, y_dtype, norm="rms", x_dtype="bf16"):
+    """The layer call, its activations laid out by the fused kernel and its product on one round of mid-size tiles, bit for bit the two
+    entry points by themselves, whose product is `alone` (kernel, mid-size tile), and on sampled tokens against the oracle.
+    Zero-points of the weights: among the codes (the epilogue from LDS in every workgroup), outside them for a few features
+    (the general epilogue in theirs, the other beside it), and outside in every tile."""
     import torch
+    a_bits, w_bits = bits
     rng = np.random.default_rng(N + O)
     row_ptr, src, scale = random_csr_map(rng, C, C, 62, longest=3)
     dm = b.DeviceMap(row_ptr, src, scale, C, b.qllm_plan_map_host(row_ptr, src, scale, C)[0])
-    x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda().bfloat16()
-    gamma = torch.rand(C, device="cuda") + 0.5
-    w = rng.integers(0, 16, (O, C), dtype=np.uint8)
-    dw = b.DeviceWeight(b.qllm_pack_codes_host(w, 4), rng.random(O).astype(np.float32), rng.integers(-2, 16, O).astype(np.int32),
-                        w.astype(np.int64).sum(1).astype(np.int32), C, 4)
-    ws = torch.full((b.qllm_workspace_bytes(N, C, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
-    gws = torch.full((b.qllm_gemm_workspace_bytes(N, C, O, 4),), 0xAB, dtype=torch.uint8, device="cuda")
-    assert b.qllm_gemm_kernel_choice(dw, 4, N, gws.numel(), True) == (b.GEMM_FP6, 128, 1)
-    assert b.qllm_gemm_kernel_choice(dw, 4, N, gws.numel())[0] == alone
-    assert b.qllm_probe_layer_launch(dm, x.dtype, N, C, NORM_ID["rms"], False, 4, dw, ws.numel()).laid_out
-    y, want = (torch.full((N, O), float("nan"), dtype=torch.float32 if y_dtype == "f32" else torch.bfloat16, device="cuda") for _ in range(2))
-    b.qllm_reassembled_linear(x, NORM_ID["rms"], gamma, None, 1e-5, dm, 4, dw, y, ws)
-    qa = b.DeviceQAct(N, C, 4)
-    b.qllm_norm_reassemble_quant(x, NORM_ID["rms"], gamma, None, 1e-5, dm, 4, qa)
-    b.qllm_int_gemm(qa, dw, want, None, gws)
-    assert torch.equal(y, want)
+    x = torch.from_numpy(rng.standard_normal((N, C)).astype(np.float32)).cuda()
+    x = x if x_dtype == "f32" else x.bfloat16()
+    gamma, beta = torch.rand(C, device="cuda") + 0.5, (torch.rand(C, device="cuda") if norm == "layer" else None)
+    w = rng.integers(0, 1 << w_bits, (O, C), dtype=np.uint8)
+    packed, aw, cs = b.qllm_pack_codes_host(w, w_bits), rng.random(O).astype(np.float32), w.astype(np.int64).sum(1).astype(np.int32)
+    ws = torch.full((b.qllm_workspace_bytes(N, C, O, a_bits),), 0xAB, dtype=torch.uint8, device="cuda")
+    gws = torch.full((b.qllm_gemm_workspace_bytes(N, C, O, a_bits),), 0xAB, dtype=torch.uint8, device="cuda")
+    qa = b.DeviceQAct(N, C, a_bits)
+    b.qllm_norm_reassemble_quant(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, qa)
+    rows = np.unique(np.concatenate([rng.choice(N, 12, replace=False), [0, N - 1]]))
+    a, ax, bx, rs = (v[torch.from_numpy(rows).cuda()].cpu().numpy() for v in (qa.codes, qa.scale, qa.zero, qa.rowsum))
+    assert int(qa.zero.min()) >= 0 and int(qa.zero.max()) < 1 << a_bits          # the tokens' leave the epilogue to the weights'
+    acc = (oracle.unpack_codes(a, C, a_bits).astype(np.float64) @ w.astype(np.float64).T).astype(np.int32)   # integers below 2^53: exact
+    among = rng.integers(0, 1 << w_bits, O).astype(np.int32)
+    few, all_tiles = among.copy(), among.copy()
+    few[O // 3:O // 3 + 5] = -2
+    all_tiles[::32] = -1
+    for bw in (among, few, all_tiles):
+        dw = b.DeviceWeight(packed, aw, bw, cs, C, w_bits, tiles8=True if a_bits > 4 else None)
+        kernel = b.GEMM_FP6 if a_bits == 4 else b.GEMM_BYTES
+        assert b.qllm_gemm_kernel_choice(dw, a_bits, N, gws.numel(), True) == (kernel, 128, 1)
+        assert b.qllm_probe_mid_tile(dw, a_bits, N, gws.numel(), True) == mid
+        assert (b.qllm_gemm_kernel_choice(dw, a_bits, N, gws.numel())[0], b.qllm_probe_mid_tile(dw, a_bits, N, gws.numel())) == alone
+        facts = b.qllm_probe_layer_launch(dm, x.dtype, N, C, NORM_ID[norm], beta is not None, a_bits, dw, ws.numel())
+        assert facts.laid_out and (facts.ahead_bytes > 0) == (N <= 128)
+        y, want = (torch.full((N, O), float("nan"), dtype=torch.float32 if y_dtype == "f32" else torch.bfloat16, device="cuda") for _ in range(2))
+        b.qllm_reassembled_linear(x, NORM_ID[norm], gamma, beta, 1e-5, dm, a_bits, dw, y, ws)
+        b.qllm_int_gemm(qa, dw, want, None, gws)
+        assert torch.equal(y, want)
+        check_y(oracle, y[torch.from_numpy(rows).cuda()], oracle.epilogue(acc, C, ax, bx, rs, aw, bw, cs), y_dtype)
+
+
+@pytest.mark.parametrize("N,C,O,alone,mid", [(100, 2304, 9300, 0, (128, 64)), (65, 4096, 16381, 0, (128, 64)), (130, 2312, 4700, 0, (128, 64)),
+                                             (1000, 2312, 1150, 0, (128, 64)), (300, 3072, 5500, 1, (160, 64)), (160, 3304, 16384, 1, (160, 64)),
+                                             (500, 10240, 8100, 1, (128, 128))])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+def test_layer_mid_size_tiles_fp6(oracle, b, N, C, O, alone, mid, y_dtype):
+    """4-bit layers whose product takes one round of 128 x 64, 160 x 64 or 128 x 128 tiles on the FP6 matrix cores, which only the layer
+    call does: by itself the product streams, splits K or has other tiles (`alone`)."""
+    check_layer_on_mid_size_tiles(oracle, b, N, C, O, (4, 4), mid, (alone, (0, 0)), y_dtype)
+
+
+@pytest.mark.parametrize("N,C,O,bits,norm,x_dtype,mid,streams", [
+    (100, 4096, 16384, (6, 6), "rms", "bf16", (128, 64), False), (97, 2312, 11000, (8, 8), "layer", "f32", (128, 64), True),   # weights read ahead
+    (66, 3400, 12001, (8, 4), "rms", "bf16", (128, 64), True), (250, 3000, 8190, (8, 4), "none", "bf16", (128, 64), True),
+    (900, 3080, 1600, (6, 6), "rms", "bf16", (128, 64), False), (777, 5000, 4999, (8, 4), "layer", "f32", (160, 128), False),
+    (600, 2056, 8190, (6, 6), "rms", "bf16", (160, 128), False), (300, 2312, 12288, (8, 8), "none", "f32", (160, 128), False)])
+@pytest.mark.parametrize("y_dtype", ["f32", "bf16"])
+def test_layer_mid_size_tiles_bytes(oracle, b, N, C, O, bits, norm, x_dtype, mid, streams, y_dtype):
+    """The same for byte operands, 128 x 64 and 160 x 128 tiles, odd and even numbers of K-tiles; up to 128 tokens the fused kernel
+    reads the weights of these tiles ahead.  The product by itself has the same tiles, or streams."""
+    check_layer_on_mid_size_tiles(oracle, b, N, C, O, bits, mid, (b.GEMM_STREAMS, (0, 0)) if streams else (b.GEMM_BYTES, mid), y_dtype, norm, x_dtype)
 
 
 def test_fused_full_down_projection_without_norm(oracle, b):
