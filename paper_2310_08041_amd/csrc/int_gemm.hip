@@ -1281,14 +1281,17 @@ __global__ __launch_bounds__(LTHREADS, MI == 8 ? 1 : 2) void gemm_tiles8_kernel(
 
 // ---- mid-size batches: one round of workgroups, each with two halves that sum alternate K-tiles.
 // Tiles of 32 MI tokens x 32 NJ features of Y, so that a product too large for the streaming kernel and too small to fill
-// rounds of the tiles above is one workgroup per CU (plan_mid).  Waves 0..3 (2 x 2, 16 MI x 16 NJ each) work on the first K-tile of
-// a step and waves 4..7 on the second; at the end each half finishes half of the tile's tokens and gets the other half's sums of
-// them through LDS.  Against one K-tile per barrier and eight waves over the tile this halves the barriers and takes a third
-// off the operand reads; against K split over workgroups it writes no partial sums and needs no second launch.
-// What bounds it is the way of the operands into LDS: left out of the loop, operations and reads change nothing, loads do
-// (200 x 13824 -> 5120: 26 of 27 us).  A CU's loads return in order and no more than some 64 KB are under way at a time, so
-// that its rate is those over the latency of whatever the slowest comes from (HBM 62, the cache behind the L2s 95, an L2 130 GB/s
-// per CU); a ring deeper than four stages changes nothing, and lines asked for ahead hold up the loads behind them.
+// rounds of the tiles above is one workgroup per CU (plan_mid6, plan_mid8).  Waves 0..3 (2 x 2, 16 MI x 16 NJ each) work on the
+// first K-tile of a step and waves 4..7 on the second; at the end each half finishes half of the tile's tokens and gets the other
+// half's sums of them through LDS.  Against one K-tile per barrier and eight waves over the tile this halves the barriers and takes
+// a third off the operand reads; against K split over workgroups it writes no partial sums and needs no second launch.
+// What bounds it is the way of the operands into LDS: loads alone take 0.9 to 1.0 of its time.  Copies of it with parts of the loop left out,
+// us: all; without loads; without operand reads; without either; loads alone (/: weights out of every cache, else three sets in turn):
+//   256 x 8192 -> 8192 8/4 22.3; 17.2; 21.5; 13.1; 21.4 / 31.5; 17.9; 31.2; 13.9; 31.2     600 x 28672 -> 8192 8/8 143; 108; 140; 77; 139
+//   200 x 5120 -> 5120 4/4 12.1; 9.9; 11.8; 7.9; 11.6 / 16.2; 10.5; 15.9; 8.5; 15.8        400 x 28672 -> 8192 4/4 75; 46; 72; 33; 72
+// At the first shape that is 74 / 50 GB/s into the LDS of a CU, each line counted for every CU that asks for it (3.2 / 2.2 TB/s of
+// different bytes over the chip).  A ring deeper than four stages changes nothing, and lines asked for ahead hold up the loads
+// behind them.
 // Operands are read a step ahead of their operations: two sets of registers, a step reads one and multiplies the other.
 struct MidBytes { // TILES8 on both sides, int8 matrix cores
     typedef v4i Acc;
@@ -2056,7 +2059,8 @@ int32_t launch_skinny(const GemmArgs &g, int32_t y_dtype, hipStream_t stream)
 // ceil(groups / 256)); what the tiled kernels cost beside it are up to three launches (re-laying, product, finish) and
 // weights of 6 or 8 bits per code.  So it takes products of few workgroups, one or two per CU, whatever the tokens and
 // features are that make them, below a line of cost.  Both sides were timed on 14000 products (33-8192 tokens, K 256-16384,
-// 128-27648 features; weights in cache and not): tiled / stream of the layer call, geometric mean, is 1.23 (4 / 4), 1.11
+// 128-27648 features; weights in cache and not) when the tiled side had no mid-size tiles, which only 4-bit layers ask for first
+// (layer_streams); the others' lines have not been drawn again since: tiled / stream of the layer call, geometric mean, is 1.23 (4 / 4), 1.11
 // (6 / 6), 1.12 (8 / 8) and 1.16 (8 / 4) where the rule streams, the worst 0.84, and 0.72-0.86 where it does not.  Around
 // the lines (us of the layer call, stream : tiled):
 //   4 / 4  two workgroups per CU: 128 tokens, 2048 -> 16384 17.5 : 24.0 (512 workgroups); 256, 1024 -> 12288 17.6 : 14.3
@@ -2169,7 +2173,7 @@ int32_t k_splits(int64_t N, int64_t K, int64_t O, int32_t a_bits)
 //     4 bits per weight are fewer from memory (250 x 1024 -> 6144 12.9 : 11.5, out of cache 16.6 : 17.8; 140 x 512 -> 8192 10.3 : 10.3 and 14.0 : 15.1;
 //     160 x 2048 -> 8192 15.5 : 13.8 and 19.7 : 19.1)
 //   160 x 64 where 128 x 128 tiles are more than half a round and these are one: 600 x 11008 -> 4096 41.1 : 37.1, 300 x 8192 -> 8192
-//     33.1 : 30.9, 400 x 5120 -> 5120 23.7 : 22.5, 160 x 4096 -> 16384 20.8 : 19.8, 700 x 3000 -> 3000 19.6 : 19.0; 300 x 2048 -> 8192 15.6 : 15.7
+//     33.1 : 30.9, 400 x 5120 -> 5120 23.7 : 22.5, 160 x 4096 -> 16384 20.8 : 19.8; 300 x 2048 -> 8192 15.6 : 15.7, 700 x 3000 -> 3000 19.6 : 19.0
 //   128 x 128, as many of them: 400 x 28672 -> 8192 114.5 : 96.7, 1024 x 11008 -> 4096 47.3 : 45.7, 777 tokens 45.0 : 42.9; 400 x 8192
 //     -> 8192 35.0 : 36.1.  Up to six columns of 128 features leave two XCDs without work: 3917 x 12864 -> 566 91.8 : 103.1, 3111 x 11264
 //     -> 768 68.8 : 73.3 (eight, 3263 x 12416 -> 1024 82.9 : 84.4 / 91.0 : 87.5)
